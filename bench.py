@@ -55,9 +55,9 @@ SHORT_STEPS = 100
 # allocations, the runtime, the timing events)
 WORKSPACE_RESERVE = 20 * 2 ** 30
 # algorithmic HBM bytes per grid point of one launch (complex64): a pass
-# reads and writes the field; the adjoint row pass also reads the stored
-# pre-screen field
-PASS_BYTES = {"row_fwd": 16, "col_fwd": 16, "col_adj": 16, "row_adj": 24}
+# reads and writes the field; a forward pass whose pre-screen field is kept
+# writes that too (not counted here), an adjoint pass reads it
+PASS_BYTES = {"row_fwd": 16, "col_fwd": 16, "col_adj": 24, "row_adj": 24}
 
 
 def _desc_list(insts):
@@ -228,17 +228,18 @@ def roofline(head, copy_peak):
     n2, z = float(inst.n) ** 2, inst.n_steps
     ps = head["passes"]
     recomputed = head["fp32"]["recomputed_steps"]
-    launches = {"row_fwd": z + recomputed, "col_fwd": z + recomputed, "col_adj": z,
-                "row_adj": z}
+    # one pass per step, rows and columns in turn
+    launches = {"row_fwd": (z + recomputed) / 2, "col_fwd": (z + recomputed) / 2,
+                "col_adj": z / 2, "row_adj": z / 2}
     total = {k: ps[k] * launches[k] for k in launches}
     dom = max(total, key=total.get)
     bytes_launch = PASS_BYTES[dom] * n2
     achieved = bytes_launch / (ps[dom] * 1e-3) / 1e9
     traffic = traffic_per_launch(dom)
-    names = {"row_fwd": "forward row pass (pending screen fused)",
-             "col_fwd": "forward column pass (FP64 power partials)",
-             "col_adj": "adjoint column pass",
-             "row_adj": "adjoint row pass (adjoint screen and theta partials fused)"}
+    names = {"row_fwd": "forward row pass (factor, screen, next factor; FP64 power partials)",
+             "col_fwd": "forward column pass (factor, screen, next factor; FP64 power partials)",
+             "col_adj": "adjoint column pass (the same in reverse; FP64 theta partials)",
+             "row_adj": "adjoint row pass (the same in reverse; FP64 theta partials)"}
     return {
         "bound": "hbm",
         "kernel": names[dom] + ", 4096^2 complex64",
@@ -620,9 +621,9 @@ def main():
     k = head["fp32"]["stored_segments"]
     rec = head["fp32"]["recomputed_steps"]
     # whole-march algorithmic bytes per grid point and z step (complex64):
-    # forward 32, adjoint 40 (its row pass reads the stored V), and 32 per
-    # recomputed step; recording writes nothing beyond the march's own output
-    design_bytes = 72.0 + 32.0 * rec / inst.n_steps
+    # forward 16, adjoint 24 (it reads the stored V), 16 per recomputed step,
+    # and 8 to write each kept or recomputed V
+    design_bytes = 48.0 + 16.0 * rec / inst.n_steps
     march_gbps = head["fp32"]["value"] * design_bytes / 1e9
     # the same march priced per step as stored (80 B) or recomputed (112 + 8/M B)
     f_rec = rec / inst.n_steps
@@ -655,8 +656,9 @@ def main():
             "bytes_per_gp_step": design_bytes,
             "achieved_GBps": march_gbps,
             "frac": march_gbps / HBM_PEAK_GBS,
-            "note": "whole-march algorithmic bytes (forward 32, adjoint 40, 32 per recomputed "
-                    "step, per grid point and z step) x grid-point.steps/s over the 8 TB/s spec",
+            "note": "whole-march algorithmic bytes (forward 16, adjoint 24, 16 per recomputed "
+                    "step, 8 per kept or recomputed pre-screen field, per grid point and z "
+                    "step) x grid-point.steps/s over the 8 TB/s spec",
             "survey_basis": {
                 "bytes_per_gp_step": survey_bytes,
                 "achieved_GBps": head["fp32"]["value"] * survey_bytes / 1e9,

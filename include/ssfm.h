@@ -136,7 +136,7 @@ int ssfm_checkpoint_plan(const ssfm_instance_desc* desc, int32_t n_inst,
 /* Create a context over a caller-owned device workspace of ws_bytes bytes
  * (256-byte aligned, at least ssfm_workspace_bytes() of the same
  * arguments).  Builds the propagator and twiddle tables (FP64 on the host,
- * rounded once) and the work lists; fields start at zero.  stream:
+ * rounded once); fields start at zero.  stream:
  * hipStream_t or NULL. */
 int ssfm_create(const ssfm_instance_desc* desc, int32_t n_inst,
                 int32_t precision, int64_t max_steps, int32_t ckpt_every,
@@ -477,7 +477,7 @@ int ssfm_select_plan(ssfm_ctx* ctx, int32_t n, int32_t row_variant, int32_t col_
 /* Variants of the adjoint row and column passes for grid size n, chosen
  * apart from the forward ones (their registers and best tiles differ); -1
  * follows the forward variant (the default).  A variant must have the lines
- * per workgroup of the forward variant in use (the work lists are shared),
+ * per workgroup of the forward variant in use (the tuner picks tiles per size),
  * else SSFM_EINVAL; one not built at the context's precision returns
  * SSFM_EUNSUPPORTED.  A later ssfm_select_plan whose lines differ resets the
  * adjoint choice to -1.  Drops the context's captured graphs. */
@@ -493,39 +493,43 @@ int ssfm_select_adjoint_plan(ssfm_ctx* ctx, int32_t n, int32_t row_variant,
  * SSFM_ESTATE unless the context was created with max_steps > 0. */
 int ssfm_time_adjoint_passes(ssfm_ctx* ctx, int32_t reps, double* ms_col, double* ms_row);
 
-/* Time each pass kernel of one step in isolation with HIP events on the
+/* Time each pass kernel of the march in isolation with HIP events on the
  * context's stream: reps launches of the forward row pass and of the
- * forward column pass over all instances.  Writes the mean milliseconds per
- * launch and the bytes each launch moves (algorithmic: read + write of the
- * field).  The passes read the state and write the work buffer only, so the
- * fields and the march position are unchanged. */
+ * forward column pass over all instances, each with the diffraction factor
+ * that ends a step, the screen and the factor that begins the next one (a
+ * step of the march is one such pass, along rows and columns in turn).
+ * Writes the mean milliseconds per launch and the bytes each launch moves
+ * (algorithmic: read + write of the field).  The passes read the state and
+ * write the work buffer only, so the fields and the march position are
+ * unchanged. */
 int ssfm_time_passes(ssfm_ctx* ctx, int32_t reps, double* ms_row,
                      double* ms_col, double* bytes_row, double* bytes_col);
 
-/* Sampled pass timing inside the march itself.  With every > 0, each step
- * s of ssfm_propagate and ssfm_forward_record with s % every == every / 2
- * is launched outside the captured step graphs (which then cover the steps
- * in between) and bracketed by HIP events on the context's stream: one
- * before the row pass, one between the row and the column pass, one after
- * the column pass.  Results are bitwise those of an unsampled march.  0
+/* Sampled pass timing inside the march itself.  With every > 0, the pass
+ * that ends step s of ssfm_propagate and ssfm_forward_record, s % every ==
+ * every / 2, and a neighbouring pass (along the other axis: the next one,
+ * at the end of the march the one before) are launched outside the captured
+ * step graphs (which then cover the passes in between), each with HIP events
+ * on its own dispatch.  Results are bitwise those of an unsampled march.  0
  * (default) turns sampling off.  Changing it drops the captured graphs. */
 int ssfm_set_pass_timing(ssfm_ctx* ctx, int32_t every);
 
-/* Mean milliseconds of the row pass and of the column pass over the samples
- * of the most recent propagate or forward-record call (synchronises the
- * context's stream); *n_samples = 0 and zero times when none were taken. */
+/* Mean milliseconds of the row passes and of the column passes sampled in
+ * the most recent propagate or forward-record call (synchronises the
+ * context's stream); *n_samples: sampled steps, 0 with zero times when none
+ * were taken. */
 int ssfm_pass_times(ssfm_ctx* ctx, double* ms_row, double* ms_col,
                     int32_t* n_samples);
 
 /* Sampled pass timing of the most recent ssfm_backward (with pass timing on,
  * ssfm_set_pass_timing(every > 0), the backward runs without its captured
- * graph; adjoint step s of its first checkpoint segment, the one that runs
- * without a recompute beside it, with s % every == every / 2 is bracketed
- * by HIP events on the context's stream).  Mean milliseconds of the adjoint
- * column pass (reads and writes the cotangent) and of the adjoint row pass
- * (reads the cotangent and the stored pre-screen field, writes the
- * cotangent; the adjoint screen fused); synchronises; *n_samples = 0 and
- * zero times when none were taken. */
+ * graph; the pass of adjoint step s of its first checkpoint segment, the one
+ * that runs without a recompute beside it, with s % every == every / 2, and
+ * the pass after it carry HIP events).  Mean milliseconds of the adjoint
+ * column passes and of the adjoint row passes sampled (each reads the
+ * cotangent and the stored pre-screen field and writes the cotangent);
+ * synchronises; *n_samples: sampled steps, 0 with zero times when none were
+ * taken. */
 int ssfm_adjoint_pass_times(ssfm_ctx* ctx, double* ms_col, double* ms_row,
                             int32_t* n_samples);
 

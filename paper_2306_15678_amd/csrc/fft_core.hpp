@@ -17,9 +17,10 @@
 // The inputs of the first stage and the outputs of the last stage are
 // exactly the thread's own register points, so an FFT needs LDS only
 // between stages, and FFT -> pointwise multiply -> inverse FFT needs no LDS
-// traffic at the junction.  Twiddles come from a table
-// tw[m] = exp(-2 pi i m / N) computed in FP64 on the host and rounded once;
-// each thread loads the ones it needs once and keeps them in registers.
+// traffic at the junction.  Twiddles come from a table in stage order
+// computed in FP64 on the host and rounded once; a thread with few points
+// loads the ones it needs once and keeps them in registers, one with many
+// loads them stage by stage.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -190,6 +191,34 @@ __device__ __forceinline__ void dft16(cx<R>* v) {
 #undef SSFM_SWAP
 }
 
+// 12 = 4 x 3: inner DFT4 over n2 (points n1 + 3 n2), twiddle w12^(n1 k2),
+// outer DFT3 over n1; output index k2 + 4 k1.
+template <int DIR, typename R>
+__device__ __forceinline__ void dft12(cx<R>* v) {
+  constexpr double h = 0.86602540378443864676;  // cos(pi/6)
+  cx<R> t[3][4];
+#pragma unroll
+  for (int n1 = 0; n1 < 3; ++n1) {
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) t[n1][n2] = v[n1 + 3 * n2];
+    dft4_<DIR>(t[n1][0], t[n1][1], t[n1][2], t[n1][3]);
+  }
+  // w12^1, w12^2, w12^3 = dir i; w12^2, w12^4, w12^6 = -1
+  t[1][1] = cmul(t[1][1], cx<R>{R(h), R(DIR * 0.5)});
+  t[1][2] = cmul(t[1][2], cx<R>{R(0.5), R(DIR * h)});
+  t[1][3] = rot_q<DIR>(t[1][3]);
+  t[2][1] = cmul(t[2][1], cx<R>{R(0.5), R(DIR * h)});
+  t[2][2] = cmul(t[2][2], cx<R>{R(-0.5), R(DIR * h)});
+  t[2][3] = cx<R>{-t[2][3].re, -t[2][3].im};
+#pragma unroll
+  for (int k2 = 0; k2 < 4; ++k2) {
+    cx<R> g[3] = {t[0][k2], t[1][k2], t[2][k2]};
+    dft3<DIR>(g);
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) v[k2 + 4 * k1] = g[k1];
+  }
+}
+
 // cos(e pi / 16) and sin(e pi / 16) for integer e (exact table of the
 // first octant, extended by symmetry).
 constexpr double kCos16[9] = {1.0,
@@ -259,6 +288,7 @@ __device__ __forceinline__ void dft(cx<R>* v) {
   else if constexpr (RAD == 3) dft3<DIR>(v);
   else if constexpr (RAD == 4) dft4<DIR>(v);
   else if constexpr (RAD == 8) dft8<DIR>(v);
+  else if constexpr (RAD == 12) dft12<DIR>(v);
   else if constexpr (RAD == 16) dft16<DIR>(v);
   else if constexpr (RAD == 32) dft32<DIR>(v);
   else static_assert(RAD == 2, "unsupported radix");
@@ -276,21 +306,11 @@ constexpr int first_radix() {
 // N points per line, T threads per line, LINES lines per workgroup; column
 // tiles pad their LDS by B slots every A points (see LdsPointMajor).  OPT:
 // bit 0 set loads each stage's twiddles just before that stage (fewer live
-// registers) instead of all of them before the first; bit 1 loads the
-// diffraction factors after the forward FFT instead of with the field (and,
-// in the adjoint row pass, the stored field and the screen phases after
-// the inverse FFT); bits 4-7 set the points per batch of the adjoint
-// screen (0: 4); bits 8-11 give the wavefronts per SIMD the compiler must
-// leave room for in the complex64 kernels (0: no target); bit 12 makes the
-// forward and adjoint row passes persistent and pipelined (complex64 only:
-// each workgroup loads its next row while it transforms the current one);
-// bit 13 recomputes each stage's LDS and twiddle addresses within the stage
-// (fewer registers held through the transform, a few more instructions);
-// bit 14 gives a plain row pass or a pipelined column pass its twiddles
-// from a quarter table in LDS (a pipelined column pass also loads its
-// propagator after the forward transform: its tile leaves no LDS room for
-// the stage tables); bit 15 makes a column pass
-// exchange through half its tile (fft_line_hx), complex64 only.
+// registers) instead of all of them before the first; bits 8-11 give the
+// wavefronts per SIMD the compiler must leave room for in the complex64
+// kernels (0: no target), bits 12-14 the same for the complex128 ones; bit
+// 15 makes a column pass exchange through half its tile (fft_line_hx),
+// complex64 only.
 template <int N_, int T_, int LINES_, class Rad, int PA_ = 32, int PB_ = 0, int OPT_ = 0>
 struct Plan {
   static constexpr int N = N_;
@@ -298,35 +318,44 @@ struct Plan {
   static constexpr int LINES = LINES_;
   static constexpr int E = N_ / T_;
   static constexpr int THREADS = T_ * LINES_;
+  static constexpr int WAVES = (THREADS + 63) / 64;
   static constexpr int PA = PA_;
   static constexpr int PB = PB_;
   static constexpr bool LATE_TW = (OPT_ & 1) != 0;
-  static constexpr bool LATE_PROP = (OPT_ & 2) != 0;
-  static constexpr int ADJ_BATCH = ((OPT_ >> 4) & 15) ? ((OPT_ >> 4) & 15) : 4;
   static constexpr int WAVES_PER_EU = ((OPT_ >> 8) & 15) ? ((OPT_ >> 8) & 15) : 1;
-  static constexpr bool PIPE = (OPT_ & 0x1000) != 0;
-  static constexpr bool LAUNDER = (OPT_ & 0x2000) != 0;
-  static constexpr bool QTW = (OPT_ & 0x4000) != 0;
+  static constexpr int WAVES_PER_EU_F64 = ((OPT_ >> 12) & 7) ? ((OPT_ >> 12) & 7) : 1;
   static constexpr bool HX = (OPT_ & 0x8000) != 0;
   using radices = Rad;
   static_assert(N_ % T_ == 0, "T must divide N");
+  static_assert(THREADS % 64 == 0, "whole wavefronts");
 };
 
 // --------------------------------------------------------- LDS layouts
-// Row lines: line-major with one pad slot per 32 points.
+// Row lines: line-major with 3 pad slots per 32 points (complex64; per 16,
+// complex128), which a bank model (64 banks of 4 bytes, a wavefront's 8- and
+// 16-byte accesses served 32 and 16 lanes at a time) gives 1.0-1.3 cycles
+// per served group over all stages of the radix 4, 8 and 16 plans.
 template <typename R, int N>
 struct LdsLineMajor {
-  static constexpr int LINE = N + N / 32;
-  static constexpr int SIZE_PER_LINE = LINE;
+  static constexpr unsigned A = sizeof(R) == 4 ? 32 : 16;
+  static constexpr int LINE = N + N / int(A) * 3;
   cx<R>* base;
-  __device__ __forceinline__ cx<R> get(int p) const { return base[p + (p >> 5)]; }
-  __device__ __forceinline__ void put(int p, cx<R> v) const { base[p + (p >> 5)] = v; }
+  // unsigned (p >= 0): constant offsets of p that are multiples of A fold
+  // into the instruction's offset
+  __device__ __forceinline__ cx<R>& at(int p) const {
+    return base[unsigned(p) + (unsigned(p) / A) * 3u];
+  }
+  __device__ __forceinline__ cx<R> get(int p) const { return at(p); }
+  __device__ __forceinline__ void put(int p, cx<R> v) const { at(p) = v; }
 };
 
 // Column tiles: point-major, the W columns of a point adjacent, B padding
-// slots after every A points.
-template <typename R, int W, int A, int B>
+// slots after every A points (complex64; half of both for complex128, whose
+// elements span twice the banks).
+template <typename R, int W, int A_, int B_>
 struct LdsPointMajor {
+  static constexpr bool HALF = sizeof(R) == 8 && A_ % 2 == 0 && B_ % 2 == 0;
+  static constexpr int A = HALF ? A_ / 2 : A_, B = HALF ? B_ / 2 : B_;
   static constexpr int size(int n) { return n * W + (n / A) * B; }
   cx<R>* base;  // already offset by the column index
   // unsigned (p >= 0): the division is a shift, and constant offsets of p
@@ -340,15 +369,23 @@ struct LdsPointMajor {
 };
 
 // ------------------------------------------------------------ twiddles
-// A thread's twiddles for every stage are loaded once, before the first
-// stage (one batch of independent loads), and reused conjugated by the
-// inverse transform.  Stage s (span NS > 1, radix R) needs, for each of
-// its E/R butterflies b and r = 1..R-1, tw[r * (j mod NS) * N/(NS R)]
-// with j = t + T b.
+// The twiddles of a radix plan in the order its stages read them: stage of
+// span NS > 1 and radix R has a block of (R - 1) NS entries, entry
+// (r - 1) NS + k = exp(-2 pi i r k / (NS R)) for the butterflies with j mod
+// NS = k.  Blocks follow each other: the block of span NS starts at NS - R0,
+// N - R0 entries together (built on the host in FP64 and rounded once).  The
+// lanes of a wave read consecutive k, so a twiddle costs one coalesced load
+// (hits in L2 and mostly L1) and no index arithmetic; against a quarter table in LDS
+// that saves 10 KB of LDS a workgroup and about 6 instructions a twiddle.
+// Butterflies of one thread share their twiddles when NS divides T.
+template <int N, int T, int NS, int RAD>
+constexpr int stage_tw_sets() {
+  return (T % NS == 0) ? 1 : N / T / RAD;
+}
 template <int N, int T, int... Rs>
 constexpr int twiddle_count() {
   int ns = 1, c = 0;
-  ((c += (ns > 1 ? (N / T / Rs) * (Rs - 1) : 0), ns *= Rs), ...);
+  ((c += (ns > 1 ? ((T % ns == 0) ? 1 : N / T / Rs) * (Rs - 1) : 0), ns *= Rs), ...);
   return c;
 }
 
@@ -360,35 +397,36 @@ struct TwCount<Plan<N, T, L, Radices<Rs...>, A, B, O>> {
   static constexpr int value = (O & 1) ? 0 : twiddle_count<N, T, Rs...>();
 };
 
-template <typename R, int N, int T, int NS, int RAD>
+template <typename R, int N, int T, int NS, int RAD, int R0>
 __device__ __forceinline__ void load_stage_twiddles(cx<R>* w, int t,
                                                     const cx<R>* __restrict__ tw) {
-  constexpr int E = N / T, NB = E / RAD, TWS = N / (NS * RAD);
   if constexpr (NS > 1) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int k = (t + T * b) % NS;
+    for (int b = 0; b < stage_tw_sets<N, T, NS, RAD>(); ++b) {
+      // unsigned (t >= 0): masks; 32-bit offsets from a uniform base
+      const uint32_t k = uint32_t(t + T * b) % uint32_t(NS);
 #pragma unroll
-      for (int r = 1; r < RAD; ++r) w[b * (RAD - 1) + r - 1] = tw[r * k * TWS];
+      for (int r = 1; r < RAD; ++r)
+        w[b * (RAD - 1) + r - 1] = tw[k + uint32_t(NS - R0 + (r - 1) * NS)];
     }
   }
 }
 
-template <typename R, int N, int T, int NS, int R0, int... Rest>
+template <typename R, int N, int T, int NS, int R0, int RA, int... Rest>
 __device__ __forceinline__ void load_twiddles_rec(cx<R>* w, int t,
                                                   const cx<R>* __restrict__ tw) {
-  load_stage_twiddles<R, N, T, NS, R0>(w, t, tw);
+  load_stage_twiddles<R, N, T, NS, RA, R0>(w, t, tw);
   if constexpr (sizeof...(Rest) > 0) {
-    constexpr int used = (NS > 1) ? (N / T / R0) * (R0 - 1) : 0;
-    load_twiddles_rec<R, N, T, NS * R0, Rest...>(w + used, t, tw);
+    constexpr int used = (NS > 1) ? stage_tw_sets<N, T, NS, RA>() * (RA - 1) : 0;
+    load_twiddles_rec<R, N, T, NS * RA, R0, Rest...>(w + used, t, tw);
   }
 }
 
-template <typename R, int N, int T, int... Rs>
+template <typename R, int N, int T, int R0, int... Rs>
 __device__ __forceinline__ void load_twiddles_impl(cx<R>* w, int t,
                                                    const cx<R>* __restrict__ tw,
-                                                   Radices<Rs...>) {
-  load_twiddles_rec<R, N, T, 1, Rs...>(w, t, tw);
+                                                   Radices<R0, Rs...>) {
+  load_twiddles_rec<R, N, T, 1, R0, R0, Rs...>(w, t, tw);
 }
 
 template <typename R, class P>
@@ -400,20 +438,21 @@ __device__ __forceinline__ void load_twiddles(cx<R>* w, int t, const cx<R>* __re
 // w: this stage's twiddles in registers (preloaded), or, with LATE, loaded
 // here from the table before the stage's LDS reads so that their latency
 // overlaps the exchange.
-template <typename R, int N, int T, int RAD, int NS, int DIR, bool FIRST,
-          bool LAST, bool LATE, class Lds, bool LAUNDER = false>
+template <typename R, int N, int T, int RAD, int NS, int R0, int DIR, bool FIRST,
+          bool LAST, bool LATE, class Lds>
 __device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
                                           const cx<R>* wpre, const cx<R>* __restrict__ tw) {
-  // LAUNDER: the thread index made opaque per stage, so the stage's LDS
-  // and twiddle addresses are computed where they are used instead of
-  // held in registers from the kernel's start
-  if constexpr (LAUNDER) asm volatile("" : "+v"(t));
+  // with late twiddles the thread index is made opaque per stage, so the
+  // stage's LDS and twiddle addresses are computed where they are used
+  // instead of held in registers from the kernel's start
+  if constexpr (LATE) asm volatile("" : "+v"(t));
   constexpr int E = N / T;
   constexpr int NB = E / RAD;
   constexpr int STRIDE = N / RAD;
+  constexpr int SETS = stage_tw_sets<N, T, NS, RAD>();
   static_assert(E % RAD == 0, "radix must divide points per thread");
-  cx<R> wl[(LATE && NS > 1) ? NB * (RAD - 1) : 1];
-  if constexpr (LATE && NS > 1) load_stage_twiddles<R, N, T, NS, RAD>(wl, t, tw);
+  cx<R> wl[(LATE && NS > 1) ? SETS * (RAD - 1) : 1];
+  if constexpr (LATE && NS > 1) load_stage_twiddles<R, N, T, NS, RAD, R0>(wl, t, tw);
   const cx<R>* w = LATE ? wl : wpre;
   cx<R> a[NB][RAD];
 #pragma unroll
@@ -432,18 +471,17 @@ __device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
   }
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int j = t + T * b;
-    const int k = j % NS;
+    const unsigned j = unsigned(t + T * b);  // j >= 0: shifts and masks
     if constexpr (NS > 1) {
 #pragma unroll
       for (int r = 1; r < RAD; ++r) {
-        const cx<R> ww = w[b * (RAD - 1) + r - 1];
+        const cx<R> ww = w[(SETS == 1 ? 0 : b * (RAD - 1)) + r - 1];
         a[b][r] = (DIR > 0) ? cmulc(a[b][r], ww) : cmul(a[b][r], ww);
       }
     }
     dft<RAD, DIR>(a[b]);
     if constexpr (!LAST) {
-      const int base = (j / NS) * NS * RAD + k;
+      const int base = int((j / NS) * NS * RAD + j % NS);
 #pragma unroll
       for (int r = 0; r < RAD; ++r) lds.put(base + r * NS, a[b][r]);
     } else {
@@ -456,263 +494,24 @@ __device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
   }
 }
 
-template <typename R, int N, int T, int DIR, int NS, bool FIRST, bool LATE, bool LAUNDER,
-          class Lds, int R0, int... Rest>
+template <typename R, int N, int T, int DIR, int NS, int R0, bool FIRST, bool LATE,
+          class Lds, int RA, int... Rest>
 __device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds,
                                            const cx<R>* w, const cx<R>* __restrict__ tw) {
   constexpr bool LAST = sizeof...(Rest) == 0;
-  fft_stage<R, N, T, R0, NS, DIR, FIRST, LAST, LATE, Lds, LAUNDER>(v, t, lds, w, tw);
+  fft_stage<R, N, T, RA, NS, R0, DIR, FIRST, LAST, LATE>(v, t, lds, w, tw);
   if constexpr (!LAST) {
-    constexpr int used = (!LATE && NS > 1) ? (N / T / R0) * (R0 - 1) : 0;
-    fft_stages<R, N, T, DIR, NS * R0, false, LATE, LAUNDER, Lds, Rest...>(v, t, lds, w + used,
-                                                                         tw);
+    constexpr int used = (!LATE && NS > 1) ? stage_tw_sets<N, T, NS, RA>() * (RA - 1) : 0;
+    fft_stages<R, N, T, DIR, NS * RA, R0, false, LATE, Lds, Rest...>(v, t, lds, w + used, tw);
   }
 }
 
-template <typename R, int N, int T, int DIR, bool LATE, bool LAUNDER, class Lds, int... Rs>
+template <typename R, int N, int T, int DIR, bool LATE, class Lds, int R0, int... Rs>
 __device__ __forceinline__ void fft_line_impl(cx<R>* v, int t, const Lds& lds,
                                               const cx<R>* w, const cx<R>* __restrict__ tw,
-                                              Radices<Rs...>) {
-  fft_stages<R, N, T, DIR, 1, true, LATE, LAUNDER, Lds, Rs...>(v, t, lds, w, tw);
+                                              Radices<R0, Rs...>) {
+  fft_stages<R, N, T, DIR, 1, R0, true, LATE, Lds, R0, Rs...>(v, t, lds, w, tw);
 }
-
-// In-register FFT of one line (DIR = -1 forward, +1 inverse, unscaled),
-// with the thread's twiddles preloaded by load_twiddles<R, P> (w), or, for
-// a late-twiddle plan, read stage by stage from the table tw.  On entry and
-// exit v[e] holds point t + T*e.
-template <typename R, class P, int DIR, class Lds>
-__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
-                                         const cx<R>* __restrict__ tw) {
-  fft_line_impl<R, P::N, P::T, DIR, P::LATE_TW, P::LAUNDER>(v, t, lds, w, tw,
-                                                             typename P::radices{});
-}
-
-// ------------------------------------------- twiddles staged in LDS
-// Persistent kernels copy the twiddles of every stage with span NS > 1 into
-// LDS once, in the order the stage reads them: entry (r - 1) NS + k of the
-// stage's block holds tw[r k N/(NS R)] for butterflies with j mod NS = k.
-// Stage blocks follow each other; the block of span NS starts at NS - R0
-// and they hold N - R0 entries together.  The lanes of a wave read
-// consecutive k (or one broadcast value), so the reads are free of bank
-// conflicts, and the values are those of the table.
-template <int N, int R0, int... Rest>
-constexpr int lds_tw_entries(Radices<R0, Rest...>) {
-  return N - R0;
-}
-
-template <typename R, int N, int NS, int RAD, int... Rest>
-__device__ __forceinline__ cx<R> lds_tw_value(int idx, const cx<R>* __restrict__ tw) {
-  // idx counts from the start of this stage's block
-  if (NS > 1 && idx < (RAD - 1) * NS) {
-    const int r = idx / NS + 1, k = idx - (r - 1) * NS;
-    return tw[r * k * (N / (NS * RAD))];
-  }
-  if constexpr (sizeof...(Rest) > 0) {
-    return lds_tw_value<R, N, NS * RAD, Rest...>(NS > 1 ? idx - (RAD - 1) * NS : idx, tw);
-  } else {
-    return tw[0];
-  }
-}
-
-template <typename R, int N, int THREADS, int... Rs>
-__device__ __forceinline__ void fill_lds_twiddles(cx<R>* twl, int t, const cx<R>* __restrict__ tw,
-                                                  Radices<Rs...> rad) {
-  constexpr int M = lds_tw_entries<N>(rad);
-  for (int i = t; i < M; i += THREADS) twl[i] = lds_tw_value<R, N, 1, Rs...>(i, tw);
-}
-
-template <typename R, int N, int T, int RAD, int NS, int R0, int DIR, bool FIRST, bool LAST,
-          class Lds>
-__device__ __forceinline__ void fft_stage_ltw(cx<R>* v, int t, const Lds& lds,
-                                              const cx<R>* twl) {
-  constexpr int E = N / T;
-  constexpr int NB = E / RAD;
-  constexpr int STRIDE = N / RAD;
-  static_assert(E % RAD == 0, "radix must divide points per thread");
-  const cx<R>* ws = twl + (NS - R0);
-  cx<R> a[NB][RAD];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-#pragma unroll
-    for (int r = 0; r < RAD; ++r) {
-      if constexpr (FIRST) {
-        a[b][r] = v[b + r * NB];
-      } else {
-        a[b][r] = lds.get(t + T * b + r * STRIDE);
-      }
-    }
-  }
-  if constexpr (!FIRST) {
-    __syncthreads();
-  }
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const unsigned j = unsigned(t + T * b);  // j >= 0: shifts and masks
-    const int k = int(j % NS);
-    if constexpr (NS > 1) {
-#pragma unroll
-      for (int r = 1; r < RAD; ++r) {
-        const cx<R> ww = ws[(r - 1) * NS + k];
-        a[b][r] = (DIR > 0) ? cmulc(a[b][r], ww) : cmul(a[b][r], ww);
-      }
-    }
-    dft<RAD, DIR>(a[b]);
-    if constexpr (!LAST) {
-      const int base = int(j / NS) * NS * RAD + k;
-#pragma unroll
-      for (int r = 0; r < RAD; ++r) lds.put(base + r * NS, a[b][r]);
-    } else {
-#pragma unroll
-      for (int r = 0; r < RAD; ++r) v[b + r * NB] = a[b][r];
-    }
-  }
-  if constexpr (!LAST) {
-    __syncthreads();
-  }
-}
-
-template <typename R, int N, int T, int DIR, int NS, int R0, bool FIRST, class Lds, int RA,
-          int... Rest>
-__device__ __forceinline__ void fft_stages_ltw(cx<R>* v, int t, const Lds& lds,
-                                               const cx<R>* twl) {
-  constexpr bool LAST = sizeof...(Rest) == 0;
-  fft_stage_ltw<R, N, T, RA, NS, R0, DIR, FIRST, LAST>(v, t, lds, twl);
-  if constexpr (!LAST) fft_stages_ltw<R, N, T, DIR, NS * RA, R0, false, Lds, Rest...>(v, t, lds, twl);
-}
-
-template <typename R, int N, int T, int DIR, class Lds, int R0, int... Rest>
-__device__ __forceinline__ void fft_line_ltw_impl(cx<R>* v, int t, const Lds& lds,
-                                                  const cx<R>* twl, Radices<R0, Rest...>) {
-  fft_stages_ltw<R, N, T, DIR, 1, R0, true, Lds, R0, Rest...>(v, t, lds, twl);
-}
-
-// fft_line with the twiddles read from the LDS copy made by
-// fill_lds_twiddles; same values and operation order as fft_line.
-template <typename R, class P, int DIR, class Lds>
-__device__ __forceinline__ void fft_line_ltw(cx<R>* v, int t, const Lds& lds, const cx<R>* twl) {
-  fft_line_ltw_impl<R, P::N, P::T, DIR>(v, t, lds, twl, typename P::radices{});
-}
-
-// ----------------------------------- twiddles from a quarter table in LDS
-// tw[m] = exp(-2 pi i m / N) for m < N/4 in LDS; the rest follow from
-// exp(-2 pi i (m + q N/4) / N) = (-i)^q exp(-2 pi i m / N), a swap and sign
-// changes.  For tiles that fill the LDS (N/4 entries instead of N - R0).
-template <typename R, int N>
-__device__ __forceinline__ cx<R> qtw(const cx<R>* twq, int m) {
-  const unsigned u = unsigned(m);  // m >= 0
-  const cx<R> a = twq[u & (N / 4 - 1)];
-  const unsigned q = (u / (N / 4)) & 3;
-  const cx<R> b = (q & 1) ? cx<R>{a.im, -a.re} : a;
-  return (q & 2) ? cx<R>{-b.re, -b.im} : b;
-}
-
-template <typename R, int N, int THREADS>
-__device__ __forceinline__ void fill_qtw(cx<R>* twq, int t, const cx<R>* __restrict__ tw) {
-  for (int i = t; i < N / 4; i += THREADS) twq[i] = tw[i];
-}
-
-// The quarter table (N/4 entries) followed by the second stage's own
-// table (span R0, radix R1: entry (r - 1) R0 + k holds tw[r k N/(R0 R1)]),
-// which that stage reads without the quadrant rotation and by consecutive
-// k across a wave.
-template <int N, int R0, int R1, int... Rest>
-constexpr int qtw_entries(Radices<R0, R1, Rest...>) {
-  return N / 4 + (R1 - 1) * R0;
-}
-
-template <typename R, int N, int THREADS, int R0, int R1, int... Rest>
-__device__ __forceinline__ void fill_qtw_tables(cx<R>* twl, int t, const cx<R>* __restrict__ tw,
-                                                Radices<R0, R1, Rest...>) {
-  fill_qtw<R, N, THREADS>(twl, t, tw);
-  for (int i = t; i < (R1 - 1) * R0; i += THREADS) {
-    const int r = i / R0 + 1, k = i % R0;
-    twl[N / 4 + i] = tw[r * k * (N / (R0 * R1))];
-  }
-}
-
-// A twiddle of stage (span NS, radix RAD) from the tables of fill_qtw_tables.
-template <typename R, int N, int RAD, int NS, int R0>
-__device__ __forceinline__ cx<R> qtw_stage(const cx<R>* twq, int r, int k) {
-  if constexpr (NS == R0)
-    return twq[N / 4 + (r - 1) * NS + k];
-  else
-    return qtw<R, N>(twq, r * k * (N / (NS * RAD)));
-}
-
-template <typename R, int N, int T, int RAD, int NS, int R0, int DIR, bool FIRST, bool LAST,
-          class Lds>
-__device__ __forceinline__ void fft_stage_qtw(cx<R>* v, int t, const Lds& lds,
-                                              const cx<R>* twq) {
-  // the thread index made opaque per stage (addresses computed in the stage)
-  asm volatile("" : "+v"(t));
-  constexpr int E = N / T;
-  constexpr int NB = E / RAD;
-  constexpr int STRIDE = N / RAD;
-  constexpr int TWS = N / (NS * RAD);
-  static_assert(E % RAD == 0, "radix must divide points per thread");
-  cx<R> a[NB][RAD];
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-#pragma unroll
-    for (int r = 0; r < RAD; ++r) {
-      if constexpr (FIRST) {
-        a[b][r] = v[b + r * NB];
-      } else {
-        a[b][r] = lds.get(t + T * b + r * STRIDE);
-      }
-    }
-  }
-  if constexpr (!FIRST) {
-    __syncthreads();
-  }
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const unsigned j = unsigned(t + T * b);  // j >= 0: shifts and masks
-    const int k = int(j % NS);
-    if constexpr (NS > 1) {
-#pragma unroll
-      for (int r = 1; r < RAD; ++r) {
-        const cx<R> ww = qtw_stage<R, N, RAD, NS, R0>(twq, r, k);
-        a[b][r] = (DIR > 0) ? cmulc(a[b][r], ww) : cmul(a[b][r], ww);
-      }
-    }
-    dft<RAD, DIR>(a[b]);
-    if constexpr (!LAST) {
-      const int base = int(j / NS) * NS * RAD + k;
-#pragma unroll
-      for (int r = 0; r < RAD; ++r) lds.put(base + r * NS, a[b][r]);
-    } else {
-#pragma unroll
-      for (int r = 0; r < RAD; ++r) v[b + r * NB] = a[b][r];
-    }
-  }
-  if constexpr (!LAST) {
-    __syncthreads();
-  }
-}
-
-template <typename R, int N, int T, int DIR, int NS, int R0, bool FIRST, class Lds, int RA,
-          int... Rest>
-__device__ __forceinline__ void fft_stages_qtw(cx<R>* v, int t, const Lds& lds,
-                                               const cx<R>* twq) {
-  constexpr bool LAST = sizeof...(Rest) == 0;
-  fft_stage_qtw<R, N, T, RA, NS, R0, DIR, FIRST, LAST>(v, t, lds, twq);
-  if constexpr (!LAST)
-    fft_stages_qtw<R, N, T, DIR, NS * RA, R0, false, Lds, Rest...>(v, t, lds, twq);
-}
-
-template <typename R, int N, int T, int DIR, class Lds, int R0, int... Rs>
-__device__ __forceinline__ void fft_line_qtw_impl(cx<R>* v, int t, const Lds& lds,
-                                                  const cx<R>* twq, Radices<R0, Rs...>) {
-  fft_stages_qtw<R, N, T, DIR, 1, R0, true, Lds, R0, Rs...>(v, t, lds, twq);
-}
-
-// fft_line with the twiddles read from the tables made by fill_qtw_tables.
-template <typename R, class P, int DIR, class Lds>
-__device__ __forceinline__ void fft_line_qtw(cx<R>* v, int t, const Lds& lds, const cx<R>* twq) {
-  fft_line_qtw_impl<R, P::N, P::T, DIR>(v, t, lds, twq, typename P::radices{});
-}
-
 
 // ------------------------------------ exchanges through half an LDS tile
 // A tile that would fill the LDS can exchange through half of it, so that
@@ -724,23 +523,8 @@ __device__ __forceinline__ void fft_line_qtw(cx<R>* v, int t, const Lds& lds, co
 // slots: the lower outputs are written and the lower inputs read, then the
 // upper ones, with a barrier between every write and read (four per
 // exchange, the first guarding the previous exchange's last reads).  The
-// butterflies, twiddles (quarter table) and their order are those of
-// fft_line_qtw.
-template <typename R, int N, int T, int RAD, int NS, int R0, int DIR>
-__device__ __forceinline__ void hx_butterfly(cx<R> (&y)[RAD], int j, const cx<R>* twq) {
-  if constexpr (NS > 1) {
-    // unsigned (j >= 0): butterflies T apart share k when NS divides T,
-    // and the compiler sees it
-    const int k = int(unsigned(j) % unsigned(NS));
-#pragma unroll
-    for (int r = 1; r < RAD; ++r) {
-      const cx<R> ww = qtw_stage<R, N, RAD, NS, R0>(twq, r, k);
-      y[r] = (DIR > 0) ? cmulc(y[r], ww) : cmul(y[r], ww);
-    }
-  }
-  dft<RAD, DIR>(y);
-}
-
+// butterflies, their twiddles (always loaded late) and their order are those
+// of the full exchange.
 template <typename R, int N, int T, int RAD, int NS, int RB, class Lds>
 __device__ __forceinline__ void hx_exchange(cx<R> (&a)[N / T / RAD][RAD],
                                             cx<R> (&nx)[N / T / RB][RB], int t, const Lds& lds) {
@@ -768,49 +552,42 @@ __device__ __forceinline__ void hx_exchange(cx<R> (&a)[N / T / RAD][RAD],
   }
 }
 
-// The last stage hands each butterfly's outputs to sink(b, y) as soon as
-// they are formed: y[r] is point t + T (b + r NB), NB = E / R_last.
-template <typename R, int N, int T, int DIR, int NS, int R0, class Lds, class Sink, int RA,
-          int... Rest>
-__device__ __forceinline__ void hx_stages(cx<R> (&a)[N / T / RA][RA], int t, const Lds& lds,
-                                          const cx<R>* twq, Sink&& sink) {
+template <typename R, int N, int T, int DIR, int NS, int R0, class Lds, int RA, int... Rest>
+__device__ __forceinline__ void hx_stages(cx<R>* v, cx<R> (&a)[N / T / RA][RA], int t,
+                                          const Lds& lds, const cx<R>* __restrict__ tw) {
   constexpr int NB = N / T / RA;
+  constexpr int SETS = stage_tw_sets<N, T, NS, RA>();
   // the thread index made opaque per stage (addresses computed in the stage)
   asm volatile("" : "+v"(t));
+  if constexpr (NS > 1) {
+    cx<R> w[SETS * (RA - 1)];
+    load_stage_twiddles<R, N, T, NS, RA, R0>(w, t, tw);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int r = 1; r < RA; ++r) {
+        const cx<R> ww = w[(SETS == 1 ? 0 : b * (RA - 1)) + r - 1];
+        a[b][r] = (DIR > 0) ? cmulc(a[b][r], ww) : cmul(a[b][r], ww);
+      }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) dft<RA, DIR>(a[b]);
   if constexpr (sizeof...(Rest) == 0) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      hx_butterfly<R, N, T, RA, NS, R0, DIR>(a[b], t + T * b, twq);
-      sink(b, a[b]);
-    }
-  } else {
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int b = 0; b < NB; ++b) hx_butterfly<R, N, T, RA, NS, R0, DIR>(a[b], t + T * b, twq);
+      for (int r = 0; r < RA; ++r) v[b + r * NB] = a[b][r];
+  } else {
     constexpr int RB = first_radix<Rest...>();
     cx<R> nx[N / T / RB][RB];
     hx_exchange<R, N, T, RA, NS, RB>(a, nx, t, lds);
-    hx_stages<R, N, T, DIR, NS * RA, R0, Lds, Sink, Rest...>(nx, t, lds, twq,
-                                                             static_cast<Sink&&>(sink));
+    hx_stages<R, N, T, DIR, NS * RA, R0, Lds, Rest...>(v, nx, t, lds, tw);
   }
 }
 
-template <int... Rs>
-constexpr int last_radix() {
-  int r = 0;
-  ((r = Rs), ...);
-  return r;
-}
-
-template <class P>
-struct LastRadix;
-template <int N, int T, int L, int... Rs, int A, int B, int O>
-struct LastRadix<Plan<N, T, L, Radices<Rs...>, A, B, O>> {
-  static constexpr int value = last_radix<Rs...>();
-};
-
-template <typename R, int N, int T, int DIR, class Lds, class Sink, int R0, int... Rest>
+template <typename R, int N, int T, int DIR, class Lds, int R0, int... Rest>
 __device__ __forceinline__ void fft_line_hx_impl(cx<R>* v, int t, const Lds& lds,
-                                                 const cx<R>* twq, Sink&& sink,
+                                                 const cx<R>* __restrict__ tw,
                                                  Radices<R0, Rest...>) {
   constexpr int NB = N / T / R0;
   cx<R> a[NB][R0];
@@ -819,30 +596,30 @@ __device__ __forceinline__ void fft_line_hx_impl(cx<R>* v, int t, const Lds& lds
 #pragma unroll
     for (int r = 0; r < R0; ++r) a[b][r] = v[b + r * NB];
   }
-  hx_stages<R, N, T, DIR, 1, R0, Lds, Sink, R0, Rest...>(a, t, lds, twq,
-                                                        static_cast<Sink&&>(sink));
+  hx_stages<R, N, T, DIR, 1, R0, Lds, R0, Rest...>(v, a, t, lds, tw);
 }
 
-// fft_line with half-tile exchanges and the twiddles of fill_qtw_tables
-// (lds spans N/2 points of each line); the outputs go to sink(b, y)
-// butterfly by butterfly of the last stage (y[r]: point t + T (b + r NB)).
-template <typename R, class P, int DIR, class Lds, class Sink>
-__device__ __forceinline__ void fft_line_hx(cx<R>* v, int t, const Lds& lds, const cx<R>* twq,
-                                            Sink&& sink) {
-  fft_line_hx_impl<R, P::N, P::T, DIR>(v, t, lds, twq, static_cast<Sink&&>(sink),
-                                       typename P::radices{});
-}
-
-// the same with the outputs in place (v[e] = point t + T e)
+// In-register FFT of one line (DIR = -1 forward, +1 inverse, unscaled),
+// with the thread's twiddles preloaded by load_twiddles<R, P> (w), or, for
+// a late-twiddle or half-exchange plan, read stage by stage from the plan's
+// stage-ordered table tw.  On entry and exit v[e] holds point t + T*e.  A
+// full exchange leaves the LDS free (its last barrier follows the last
+// reads); a half exchange opens with the barrier that guards the last reads.
 template <typename R, class P, int DIR, class Lds>
-__device__ __forceinline__ void fft_line_hx(cx<R>* v, int t, const Lds& lds, const cx<R>* twq) {
-  [&]<int... Rs>(Radices<Rs...>) {
-    constexpr int NB = P::E / last_radix<Rs...>();
-    fft_line_hx<R, P, DIR>(v, t, lds, twq, [&](int b, const auto& y) {
-#pragma unroll
-      for (int r = 0; r < last_radix<Rs...>(); ++r) v[b + r * NB] = y[r];
-    });
-  }(typename P::radices{});
+__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
+                                         const cx<R>* __restrict__ tw) {
+  if constexpr (P::HX)
+    fft_line_hx_impl<R, P::N, P::T, DIR>(v, t, lds, tw, typename P::radices{});
+  else
+    fft_line_impl<R, P::N, P::T, DIR, P::LATE_TW>(v, t, lds, w, tw, typename P::radices{});
+}
+
+// Host side: the radix list of a plan.
+template <int... Rs>
+inline void radix_list(Radices<Rs...>, int* out) {
+  int i = 0;
+  ((out[i++] = Rs), ...);
+  out[i] = 0;
 }
 
 }  // namespace ssfm

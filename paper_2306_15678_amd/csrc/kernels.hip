@@ -28,12 +28,27 @@ int plan_count(bool column, int n) {
   return c;
 }
 
+int plan_default(bool column, int n, bool fp64) {
+  struct Default {
+    int n, row, col, row_f64, col_f64;
+  };
+  static constexpr Default kDefaults[] = {{128, 0, 1, 0, 1},  {256, 0, 1, 3, 5},
+                                          {512, 0, 3, 0, 3},  {768, 3, 2, 0, 2},
+                                          {1024, 0, 0, 7, 0}, {2048, 3, 4, 1, 7},
+                                          {4096, 3, 5, 3, 2}};
+  for (const Default& d : kDefaults)
+    if (d.n == n) return column ? (fp64 ? d.col_f64 : d.col) : (fp64 ? d.row_f64 : d.row);
+  return 0;
+}
+
 // false when the plan is not built at this precision (its tile does not
-// fit a workgroup's LDS, or a pipelined plan at complex128)
+// fit a workgroup's LDS, or a half-exchange plan at complex128)
 template <class P, bool COLUMN>
 static bool fill_info(bool fp64, PlanInfo* o) {
   o->threads = P::THREADS;
   o->lines = P::LINES;
+  o->waves = P::WAVES;
+  radix_list(typename P::radices{}, o->radices);
   o->t = P::T;
   o->lds = fp64 ? plan_lds_bytes<double, P>(COLUMN) : plan_lds_bytes<float, P>(COLUMN);
   return fp64 ? plan_fits<double, P>(COLUMN) : plan_fits<float, P>(COLUMN);
@@ -52,15 +67,15 @@ bool plan_info(bool column, int n, int v, bool fp64, PlanInfo* o) {
 }
 
 template <typename R>
-hipError_t launch_pass(int kind, int n, int variant, int n_blocks, const PassArgs<R>& a,
-                       hipStream_t s, const LaunchEv* ev) {
-  if (n_blocks <= 0) return hipSuccess;
-  if (is_col_kind(kind)) return launch_col<R>(kind, n, variant, n_blocks, a, s, ev);
-  return launch_row<R>(kind, n, variant, n_blocks, a, s, ev);
+hipError_t launch_pass(int kind, int n, int variant, const PassArgs<R>& a, hipStream_t s,
+                       const LaunchEv* ev) {
+  if (a.n_tiles <= 0) return hipSuccess;
+  if (is_col_kind(kind)) return launch_col<R>(kind, n, variant, a, s, ev);
+  return launch_row<R>(kind, n, variant, a, s, ev);
 }
-template hipError_t launch_pass<float>(int, int, int, int, const PassArgs<float>&, hipStream_t,
+template hipError_t launch_pass<float>(int, int, int, const PassArgs<float>&, hipStream_t,
                                        const LaunchEv*);
-template hipError_t launch_pass<double>(int, int, int, int, const PassArgs<double>&, hipStream_t,
+template hipError_t launch_pass<double>(int, int, int, const PassArgs<double>&, hipStream_t,
                                         const LaunchEv*);
 
 // ----------------------------------------------------- pointwise kernels
@@ -436,23 +451,23 @@ hipError_t launch_copy(const void* src, void* dst, int64_t n_elem, hipStream_t s
 template hipError_t launch_copy<float>(const void*, void*, int64_t, hipStream_t);
 template hipError_t launch_copy<double>(const void*, void*, int64_t, hipStream_t);
 
-// One thread per (beam, step): fixed-order sum / max over the beam's
-// column work items.
-// One workgroup per (beam, step): thread t sums the beam's work items
-// t, t + 256, ... in order, then a fixed tree across the workgroup, so the
-// result depends only on the beam's own item count (a beam in a batch sums
+// One workgroup per (beam, step): thread t sums the beam's partials t,
+// t + 256, ... in order, then a fixed tree across the workgroup, so the
+// result depends only on the beam's own partials (a beam in a batch sums
 // exactly as it does alone).
 __global__ void __launch_bounds__(256)
-k_diag_finalize(const double* __restrict__ part, int n_work, const int32_t* __restrict__ wbegin,
+k_diag_finalize(const double* __restrict__ part, int64_t stride,
+                const int32_t* __restrict__ begin_even, const int32_t* __restrict__ begin_odd,
                 double* __restrict__ diag, int64_t ring0, int64_t cap) {
   __shared__ double red[8];
   const int b = blockIdx.x;
   const int step = blockIdx.y;
-  const double* p = part + int64_t(step) * n_work * 2;
+  const int32_t* begin = ((ring0 + step) & 1) ? begin_odd : begin_even;
+  const double* p = part + int64_t(step) * stride * 2;
   double s[1] = {0.0}, m[1] = {0.0};
-  for (int w = wbegin[b] + int(threadIdx.x); w < wbegin[b + 1]; w += 256) {
-    s[0] += p[2 * w];
-    m[0] = fmax(m[0], p[2 * w + 1]);
+  for (int w = begin[b] + int(threadIdx.x); w < begin[b + 1]; w += 256) {
+    s[0] += p[2 * int64_t(w)];
+    m[0] = fmax(m[0], p[2 * int64_t(w) + 1]);
   }
   block_reduce<1, 256, false>(s, red);
   block_reduce<1, 256, true>(m, red + 4);
@@ -463,38 +478,43 @@ k_diag_finalize(const double* __restrict__ part, int n_work, const int32_t* __re
   }
 }
 
-hipError_t launch_diag_finalize(const double* part, int n_work, const int32_t* wbegin,
-                                int n_beams, int steps, double* diag, int64_t ring0,
-                                int64_t cap, double, hipStream_t s) {
+hipError_t launch_diag_finalize(const double* part, int64_t stride, const int32_t* begin_even,
+                                const int32_t* begin_odd, int n_beams, int steps,
+                                double* diag, int64_t ring0, int64_t cap, hipStream_t s) {
   if (steps <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_diag_finalize, dim3(n_beams, steps), dim3(256), 0, s, part, n_work,
-                     wbegin, diag, ring0, cap);
+  hipLaunchKernelGGL(k_diag_finalize, dim3(n_beams, steps), dim3(256), 0, s, part, stride,
+                     begin_even, begin_odd, diag, ring0, cap);
   return hipGetLastError();
 }
 
-// Per beam (one workgroup each), the column sums of its rows of a
-// [rows][width] array, width <= 8: strided partial sums then a fixed tree.
+// Per beam (one workgroup each), the sums of its 8 theta accumulators over
+// the row and column passes: strided partial sums then a fixed tree.
 __global__ void __launch_bounds__(256)
-k_reduce_rows(const double* __restrict__ part, int width, const int32_t* __restrict__ begin,
-              double* __restrict__ out) {
+k_reduce_theta(const double* __restrict__ rows, const int32_t* __restrict__ row_begin,
+               const double* __restrict__ cols, const int32_t* __restrict__ col_begin,
+               double* __restrict__ out) {
   __shared__ double red[4 * 8];
   const int b = blockIdx.x;
   double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int r = begin[b] + int(threadIdx.x); r < begin[b + 1]; r += 256) {
+  for (int r = row_begin[b] + int(threadIdx.x); r < row_begin[b + 1]; r += 256) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      if (k < width) s[k] += part[int64_t(r) * width + k];
+    for (int k = 0; k < 8; ++k) s[k] += rows[int64_t(r) * 8 + k];
+  }
+  for (int r = col_begin[b] + int(threadIdx.x); r < col_begin[b + 1]; r += 256) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s[k] += cols[int64_t(r) * 8 + k];
   }
   block_reduce<8, 256, false>(s, red);
   if (threadIdx.x == 0) {
-    for (int k = 0; k < width; ++k) out[int64_t(b) * width + k] = s[k];
+    for (int k = 0; k < 8; ++k) out[int64_t(b) * 8 + k] = s[k];
   }
 }
 
-hipError_t launch_reduce_rows(const double* part, int width, const int32_t* begin,
-                              int n_beams, double* out, hipStream_t s) {
-  if (width < 1 || width > 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_reduce_rows, dim3(n_beams), dim3(256), 0, s, part, width, begin, out);
+hipError_t launch_reduce_theta(const double* rows, const int32_t* row_begin, const double* cols,
+                               const int32_t* col_begin, int n_beams, double* out,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_theta, dim3(n_beams), dim3(256), 0, s, rows, row_begin, cols,
+                     col_begin, out);
   return hipGetLastError();
 }
 

@@ -13,16 +13,18 @@ namespace ssfm {
 template <typename R>
 struct cx;
 
-// Pass kinds.  A forward step is ROW_FWD (pending screen applied on load,
-// then row diffraction) followed by COL_FWD (column diffraction, FP64 power
-// partials, store of the pre-screen field).  An adjoint step is COL_ADJ
-// followed by ROW_ADJ (adjoint screen of the previous step fused into the
-// epilogue).  ROW_INV / COL_INV are plain inverse DFTs for screen synthesis.
-// ROW_FD / COL_FD are the finite-difference reference scheme's passes: COL_FD
-// applies the inverse of 1 - (i dz/4k0) Lap_h between a forward and an
-// inverse column DFT (Lap_h diagonal in the 2-D DFT basis), ROW_FD inverts
-// the row DFT, forms the next right-hand side pointwise (or finishes the
-// step) and transforms the rows again.
+// Pass kinds.  The diffraction factor is a product of a row and a column
+// factor, which commute, so the march takes them in alternating order: an
+// even step diffracts along the rows first, an odd one along the columns.
+// The second factor of a step, its screen and the first factor of the next
+// step then act along one axis, and one ROW_FWD or COL_FWD pass does all
+// three on lines it reads and writes once.  ROW_ADJ / COL_ADJ are the same
+// for the adjoint.  ROW_INV / COL_INV are plain inverse DFTs for screen
+// synthesis.  ROW_FD / COL_FD are the finite-difference reference scheme's
+// passes: COL_FD applies the inverse of 1 - (i dz/4k0) Lap_h between a
+// forward and an inverse column DFT (Lap_h diagonal in the 2-D DFT basis),
+// ROW_FD inverts the row DFT, forms the next right-hand side pointwise (or
+// finishes the step) and transforms the rows again.
 enum PassKind {
   ROW_FWD = 0, ROW_ADJ = 1, ROW_INV = 2, COL_FWD = 3, COL_ADJ = 4, COL_INV = 5,
   ROW_FD = 6, COL_FD = 7
@@ -31,6 +33,13 @@ constexpr bool is_col_kind(int k) {
   return k == COL_FWD || k == COL_ADJ || k == COL_INV || k == COL_FD;
 }
 
+// Parts of a march pass (ROW_FWD, COL_FWD, ROW_ADJ, COL_ADJ), in the order
+// they act: the diffraction factor of the step that ends, the screen (its
+// adjoint), the factor of the step that begins.  PASS_RAW: the power
+// partials are those of |V|^2 without the screen's A^2; PASS_PLANE: some
+// beam of the launch has a turbulence plane at this step (else none is
+// looked for).
+enum : int32_t { PASS_OP1 = 1, PASS_SCREEN = 2, PASS_OP2 = 4, PASS_RAW = 8, PASS_PLANE = 16 };
 // ROW_FD flags: the input is row-transformed (else it is U itself), the pass
 // finishes the step (U+ = 2 Ubar - U into the state, power partials), the
 // finished step is the last one of the launch sequence (no next RHS).
@@ -41,43 +50,54 @@ struct LaunchEv {
   hipEvent_t start, stop;
 };
 
+// One launch covers the beams of one grid size, which are consecutive in
+// the beam table and in every field buffer: tile t of the launch holds
+// lines (t mod per) LINES .. of beam beam0 + t / per, per = n / LINES.
 template <typename R>
 struct PassArgs {
   const void* src;            // cx<R> field buffer read
   void* dst;                  // cx<R> field buffer written
-  const void* aux;            // ROW_ADJ: pre-screen field s_n (cx<R>)
+  const void* aux;            // *_ADJ: pre-screen field V of the screen (cx<R>)
+  void* rec;                  // *_FWD: pre-screen field V written here too (or null)
   void* state;                // ROW_FD: U of the step (read; U+ written when finishing)
-  const WorkItem* work;       // one entry per workgroup
   const InstDev* inst;        // beam table
   const void* tables;         // cx<R> twiddle and propagator tables
   const R* screens;           // turbulence planes (read)
   R* planes_out;              // COL_INV: screen planes (write)
   const int64_t* screen_steps;  // per-beam sorted step lists
-  double* part;               // COL_FWD: [n_work][2] (sum x A^2, max x A^2)
-                              // ROW_ADJ: [n_work][8] theta accumulators
-  int64_t step;               // step whose screen is pending (-1: none)
-  int32_t pair;               // COL_INV: screen pair index
-  int32_t flags;              // COL_FWD: bit 0 = power partials without the screen's A^2;
-                              // ROW_FD: FD_* bits
-  int32_t n_work;             // entries of the work list (persistent passes; set at launch)
-  int32_t precise;            // library sine/cosine in the screens: the pipelined row
-                              // passes (which carry none) are replaced by k_row
+  double* part;               // *_FWD, ROW_FD: per wavefront {sum x A^2, max x A^2};
+                              // *_ADJ: per wavefront 8 theta accumulators
+  int64_t step;               // step whose screen the pass applies
+  int64_t off0;               // element offset of the launch's first beam in a field buffer
+  int64_t prop0;              // element offset of its propagator (filter, solve) table
+  int64_t tw;                 // element offset of the plan's stage-ordered twiddles
+  int32_t prop_stride;        // elements from one beam's table to the next one's
+  int32_t beam0;              // beam table index of the first beam
+  int32_t part0;              // partials of the beams before it
+  int32_t n_tiles;            // tiles of the launch
+  int32_t pair;               // *_INV: screen pair index
+  int32_t flags;              // march passes: PASS_*; ROW_FD: FD_*
+  int32_t precise;            // library sine and cosine in the screens (FP32)
 };
 
 struct PlanInfo {
   int threads;   // workgroup size
   int lines;     // lines per workgroup
+  int waves;     // wavefronts per workgroup (each writes its own partials)
   int t;         // threads per line
   size_t lds;    // static LDS bytes
+  int radices[8];  // radix plan in stage order, ended by 0
 };
 
-// Number of variants and their shape for (kind is column?, n, precision).
+// Number of variants, the default one, and their shape for (kind is column?,
+// n, precision).
+int plan_default(bool column, int n, bool fp64);
 int plan_count(bool column, int n);
 bool plan_info(bool column, int n, int variant, bool fp64, PlanInfo* out);
 
 template <typename R>
-hipError_t launch_pass(int kind, int n, int variant, int n_blocks,
-                       const PassArgs<R>& a, hipStream_t s, const LaunchEv* ev = nullptr);
+hipError_t launch_pass(int kind, int n, int variant, const PassArgs<R>& a, hipStream_t s,
+                       const LaunchEv* ev = nullptr);
 
 // Pointwise helpers -------------------------------------------------------
 
@@ -112,18 +132,19 @@ hipError_t launch_seed(int mode, const void* state, const InstDev* inst, int b,
 template <typename R>
 hipError_t launch_copy(const void* src, void* dst, int64_t n_elem, hipStream_t s);
 
-// Reduce per-workgroup diag partials of `steps` consecutive steps:
-// part[step][n_work][2] -> diag[b][(ring0 + step) % cap][2].
-hipError_t launch_diag_finalize(const double* part, int n_work,
-                                const int32_t* beam_work_begin, int n_beams,
-                                int steps, double* diag, int64_t ring0,
-                                int64_t cap, double power_scale_unused,
-                                hipStream_t s);
+// Reduce the diag partials of `steps` consecutive steps, stride entries
+// each: part[step][stride][2] -> diag[b][(ring0 + step) % cap][2].  Beam b's
+// partials of a step are entries [begin[b], begin[b + 1]); begin is
+// begin_even for even steps (ring0 + step) and begin_odd for odd ones.
+hipError_t launch_diag_finalize(const double* part, int64_t stride, const int32_t* begin_even,
+                                const int32_t* begin_odd, int n_beams, int steps,
+                                double* diag, int64_t ring0, int64_t cap, hipStream_t s);
 
-// Fixed-order sum of rows of a [n_rows][width] FP64 array per beam range.
-hipError_t launch_reduce_rows(const double* part, int width,
-                              const int32_t* beam_begin, int n_beams,
-                              double* out, hipStream_t s);
+// Per beam the fixed-order sum of its entries of two [entries][8] FP64
+// arrays (row-pass and column-pass accumulators).
+hipError_t launch_reduce_theta(const double* rows, const int32_t* row_begin, const double* cols,
+                               const int32_t* col_begin, int n_beams, double* out,
+                               hipStream_t s);
 
 // Sum of squares of a float64 array divided by scale^2 (one value).
 hipError_t launch_sumsq(const double* x, int64_t n, double inv_scale,

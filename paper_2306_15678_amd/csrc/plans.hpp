@@ -23,89 +23,119 @@
 
 namespace ssfm {
 
-#define SSFM_ROW_PLANS(X)              \
-  X(128, 0, 8, 32, 0, 16, 8)              \
-  X(128, 1, 16, 16, 0, 8, 4, 4)           \
-  X(256, 0, 16, 16, 0, 16, 16)            \
-  X(256, 1, 32, 8, 0, 8, 8, 4)            \
-  X(512, 0, 64, 4, 0, 8, 8, 8)            \
-  X(512, 1, 32, 8, 0, 16, 16, 2)          \
-  X(512, 2, 64, 1, 0, 8, 8, 8)            \
-  X(768, 0, 32, 8, 0, 8, 8, 4, 3)         \
-  X(768, 1, 64, 4, 0, 4, 4, 4, 4, 3)      \
-  X(1024, 0, 64, 4, 0, 16, 8, 8)          \
-  X(1024, 1, 128, 2, 0, 8, 8, 4, 4)       \
-  X(1024, 2, 256, 1, 0, 4, 4, 4, 4, 4)    \
-  X(1024, 3, 64, 2, 0, 16, 8, 8)          \
-  X(1024, 4, 64, 1, 0, 16, 8, 8)          \
-  X(1024, 5, 128, 1, 0, 8, 8, 4, 4)       \
-  X(1024, 6, 32, 2, 0, 32, 32)            \
-  X(2048, 0, 128, 2, 0, 16, 16, 8)        \
-  X(2048, 1, 256, 1, 0, 8, 8, 8, 4)       \
-  X(2048, 2, 256, 1, 0x1000, 8, 8, 8, 4)  \
-  X(4096, 0, 256, 1, 0, 16, 16, 16)       \
-  X(4096, 1, 512, 1, 0, 8, 8, 8, 8)       \
-  X(4096, 2, 256, 1, 0x201, 16, 16, 16)   \
-  X(4096, 3, 256, 1, 0x203, 16, 16, 16)   \
-  X(4096, 4, 256, 1, 0x323, 16, 16, 16)   \
-  X(4096, 5, 256, 1, 0x303, 16, 16, 16)   \
-  X(4096, 6, 512, 1, 0x1000, 8, 8, 8, 8)  \
-  X(4096, 7, 512, 1, 0x1010, 8, 8, 8, 8)  \
-  X(4096, 8, 256, 1, 0x4303, 16, 16, 16)
+#define SSFM_ROW_PLANS(X) \
+  X(128, 0, 32, 2, 0x0, 4, 4, 4, 2) \
+  X(128, 1, 16, 4, 0x0, 8, 4, 4) \
+  X(128, 2, 16, 8, 0x0, 8, 4, 4) \
+  X(128, 3, 32, 4, 0x0, 4, 4, 4, 2) \
+  X(256, 0, 64, 1, 0x0, 4, 4, 4, 4) \
+  X(256, 1, 32, 2, 0x0, 8, 8, 4) \
+  X(256, 2, 32, 4, 0x0, 8, 8, 4) \
+  X(256, 3, 16, 4, 0x1, 16, 16) \
+  X(256, 4, 64, 2, 0x0, 4, 4, 4, 4) \
+  X(512, 0, 64, 1, 0x0, 8, 8, 8) \
+  X(512, 1, 128, 1, 0x0, 4, 4, 4, 4, 2) \
+  X(512, 2, 64, 2, 0x0, 8, 8, 8) \
+  X(512, 3, 32, 4, 0x1, 16, 16, 2) \
+  X(768, 0, 64, 1, 0x0, 4, 4, 4, 4, 3) \
+  X(768, 1, 64, 2, 0x0, 4, 4, 4, 4, 3) \
+  X(768, 2, 32, 4, 0x1, 8, 8, 4, 3) \
+  X(768, 3, 64, 1, 0x0, 12, 4, 4, 4) \
+  X(768, 4, 32, 2, 0x1, 12, 8, 8) \
+  X(768, 5, 64, 1, 0x1, 12, 4, 4, 4) \
+  X(1024, 0, 128, 1, 0x0, 8, 8, 4, 4) \
+  X(1024, 1, 256, 1, 0x0, 4, 4, 4, 4, 4) \
+  X(1024, 2, 64, 1, 0x0, 16, 8, 8) \
+  X(1024, 3, 64, 1, 0x1, 16, 8, 8) \
+  X(1024, 4, 64, 1, 0x1, 16, 16, 4) \
+  X(1024, 5, 32, 2, 0x1, 32, 32) \
+  X(1024, 6, 128, 2, 0x0, 8, 8, 4, 4) \
+  X(1024, 7, 128, 1, 0x1, 8, 8, 4, 4) \
+  X(2048, 0, 256, 1, 0x0, 8, 8, 8, 4) \
+  X(2048, 1, 256, 1, 0x1, 8, 8, 8, 4) \
+  X(2048, 2, 128, 1, 0x1, 16, 16, 8) \
+  X(2048, 3, 128, 1, 0x401, 16, 16, 8) \
+  X(2048, 4, 128, 2, 0x1, 16, 16, 8) \
+  X(4096, 0, 256, 1, 0x401, 16, 16, 16) \
+  X(4096, 1, 256, 1, 0x1, 16, 16, 16) \
+  X(4096, 2, 256, 1, 0x301, 16, 16, 16) \
+  X(4096, 3, 256, 1, 0x421, 16, 16, 16) \
+  X(4096, 4, 512, 1, 0x0, 8, 8, 8, 8) \
+  X(4096, 5, 512, 1, 0x1, 8, 8, 8, 8) \
+  X(4096, 6, 512, 1, 0x401, 8, 8, 8, 8) \
+  X(4096, 7, 512, 1, 0x601, 8, 8, 8, 8) \
+  X(4096, 8, 512, 1, 0x421, 8, 8, 8, 8) \
+  X(4096, 9, 256, 1, 0x321, 16, 16, 16)
 
-#define SSFM_COL_PLANS(X)              \
-  X(128, 0, 8, 32, 1, 0, 0, 16, 8) \
-  X(128, 1, 16, 16, 2, 4, 0, 8, 4, 4) \
-  X(256, 0, 16, 16, 2, 2, 0, 16, 16) \
-  X(256, 1, 32, 8, 4, 4, 0, 8, 8, 4) \
-  X(512, 0, 64, 4, 8, 4, 0, 8, 8, 8) \
-  X(512, 1, 32, 8, 4, 2, 0, 16, 16, 2) \
-  X(768, 0, 32, 8, 4, 4, 0, 8, 8, 4, 3) \
-  X(768, 1, 64, 4, 8, 4, 0, 4, 4, 4, 4, 3) \
-  X(1024, 0, 64, 4, 8, 2, 0, 16, 8, 8) \
-  X(1024, 1, 128, 2, 16, 2, 0, 8, 8, 4, 4) \
-  X(1024, 2, 128, 4, 8, 4, 0, 8, 8, 4, 4) \
-  X(1024, 3, 256, 2, 16, 6, 0, 4, 4, 4, 4, 4) \
-  X(1024, 4, 64, 8, 4, 2, 0, 16, 8, 8) \
-  X(1024, 5, 32, 8, 4, 1, 0, 32, 32) \
-  X(1024, 6, 64, 16, 4, 4, 0x2403, 16, 8, 8) \
-  X(2048, 0, 128, 2, 16, 2, 0, 16, 16, 8) \
-  X(2048, 1, 256, 2, 16, 2, 0, 8, 8, 8, 4) \
-  X(2048, 2, 256, 2, 16, 2, 0x1000, 8, 8, 8, 4) \
-  X(2048, 3, 128, 8, 4, 2, 0x7403, 16, 16, 8) \
-  X(4096, 0, 256, 2, 16, 2, 0, 16, 16, 16) \
-  X(4096, 1, 512, 2, 16, 2, 0, 8, 8, 8, 8) \
-  X(4096, 2, 256, 2, 16, 2, 0x203, 16, 16, 16) \
-  X(4096, 3, 256, 4, 16, 2, 0x403, 16, 16, 16) \
-  X(4096, 4, 128, 2, 16, 2, 0x203, 16, 16, 16) \
-  X(4096, 5, 128, 4, 16, 2, 0x203, 16, 16, 16) \
-  X(4096, 6, 512, 2, 16, 2, 0x1000, 8, 8, 8, 8) \
-  X(4096, 7, 256, 2, 16, 2, 0x1000, 16, 16, 16) \
-  X(4096, 8, 256, 4, 16, 2, 0x7403, 16, 16, 16) \
-  X(4096, 9, 256, 4, 8, 2, 0x7403, 16, 16, 16) \
-  X(4096, 10, 128, 4, 16, 2, 0x8400, 16, 16, 16)
+#define SSFM_COL_PLANS(X) \
+  X(128, 0, 32, 4, 8, 4, 0x0, 4, 4, 4, 2) \
+  X(128, 1, 32, 2, 16, 6, 0x0, 4, 4, 4, 2) \
+  X(128, 2, 16, 4, 8, 4, 0x0, 8, 4, 4) \
+  X(128, 3, 16, 8, 4, 4, 0x0, 8, 4, 4) \
+  X(128, 4, 32, 8, 4, 4, 0x0, 4, 4, 4, 2) \
+  X(256, 0, 64, 4, 8, 4, 0x0, 4, 4, 4, 4) \
+  X(256, 1, 64, 2, 16, 6, 0x0, 4, 4, 4, 4) \
+  X(256, 2, 32, 4, 8, 4, 0x0, 8, 8, 4) \
+  X(256, 3, 32, 8, 4, 4, 0x0, 8, 8, 4) \
+  X(256, 4, 32, 2, 16, 2, 0x0, 8, 8, 4) \
+  X(256, 5, 16, 8, 4, 2, 0x1, 16, 16) \
+  X(512, 0, 64, 4, 8, 4, 0x0, 8, 8, 8) \
+  X(512, 1, 64, 2, 16, 2, 0x0, 8, 8, 8) \
+  X(512, 2, 64, 8, 4, 4, 0x0, 8, 8, 8) \
+  X(512, 3, 128, 2, 16, 6, 0x0, 4, 4, 4, 4, 2) \
+  X(512, 4, 128, 4, 8, 4, 0x0, 4, 4, 4, 4, 2) \
+  X(512, 5, 64, 1, 32, 3, 0x0, 8, 8, 8) \
+  X(768, 0, 64, 4, 8, 4, 0x0, 4, 4, 4, 4, 3) \
+  X(768, 1, 64, 2, 16, 6, 0x0, 4, 4, 4, 4, 3) \
+  X(768, 2, 64, 4, 32, 4, 0x0, 12, 4, 4, 4) \
+  X(768, 3, 64, 2, 32, 1, 0x0, 12, 4, 4, 4) \
+  X(768, 4, 32, 8, 8, 8, 0x1, 12, 8, 8) \
+  X(768, 5, 32, 4, 32, 4, 0x1, 12, 8, 8) \
+  X(768, 6, 32, 8, 4, 4, 0x1, 8, 8, 4, 3) \
+  X(1024, 0, 128, 4, 8, 4, 0x0, 8, 8, 4, 4) \
+  X(1024, 1, 128, 2, 16, 2, 0x0, 8, 8, 4, 4) \
+  X(1024, 2, 256, 2, 16, 6, 0x0, 4, 4, 4, 4, 4) \
+  X(1024, 3, 256, 4, 8, 4, 0x0, 4, 4, 4, 4, 4) \
+  X(1024, 4, 64, 4, 8, 2, 0x0, 16, 8, 8) \
+  X(1024, 5, 64, 4, 8, 2, 0x1, 16, 8, 8) \
+  X(1024, 6, 64, 8, 4, 2, 0x1, 16, 8, 8) \
+  X(1024, 7, 64, 4, 8, 2, 0x1, 16, 16, 4) \
+  X(1024, 8, 128, 8, 4, 4, 0x1, 8, 8, 4, 4) \
+  X(1024, 9, 64, 2, 16, 2, 0x1, 16, 8, 8) \
+  X(2048, 0, 256, 2, 16, 2, 0x0, 8, 8, 8, 4) \
+  X(2048, 1, 256, 4, 8, 4, 0x0, 8, 8, 8, 4) \
+  X(2048, 2, 256, 2, 16, 2, 0x1, 8, 8, 8, 4) \
+  X(2048, 3, 128, 4, 8, 2, 0x1, 16, 16, 8) \
+  X(2048, 4, 128, 4, 8, 2, 0x401, 16, 16, 8) \
+  X(2048, 5, 128, 8, 4, 2, 0x401, 16, 16, 8) \
+  X(2048, 6, 256, 4, 8, 4, 0x401, 8, 8, 8, 4) \
+  X(2048, 7, 128, 2, 16, 2, 0x401, 16, 16, 8) \
+  X(4096, 0, 128, 4, 16, 2, 0x8400, 16, 16, 16) \
+  X(4096, 1, 128, 4, 16, 2, 0x8200, 16, 16, 16) \
+  X(4096, 2, 256, 2, 16, 2, 0x401, 16, 16, 16) \
+  X(4096, 3, 256, 2, 16, 2, 0x301, 16, 16, 16) \
+  X(4096, 4, 256, 2, 16, 2, 0x1, 16, 16, 16) \
+  X(4096, 5, 256, 4, 8, 2, 0x401, 16, 16, 16) \
+  X(4096, 6, 512, 2, 16, 2, 0x0, 8, 8, 8, 8) \
+  X(4096, 7, 512, 2, 16, 2, 0x401, 8, 8, 8, 8) \
+  X(4096, 8, 128, 4, 8, 2, 0x8400, 16, 16, 16) \
+  X(4096, 9, 128, 2, 16, 2, 0x8400, 16, 16, 16) \
+  X(4096, 10, 256, 4, 8, 4, 0x8400, 8, 8, 8, 8) \
+  X(4096, 11, 256, 4, 8, 2, 0x421, 16, 16, 16)
 
-// LDS of a pass workgroup (line tiles, plus the FP64 reduction scratch)
-// against the 160 KiB a gfx950 workgroup may allocate.
+// LDS of a pass workgroup against the 160 KiB a gfx950 workgroup may
+// allocate; half-exchange plans are built for complex64 columns only.
 constexpr size_t kMaxLdsBytes = 160 * 1024;
-// (pipelined plans also hold the twiddles of every stage, N - R0 entries,
-// or a quarter table of N / 4 and the second stage's (R1 - 1) R0 entries)
 template <typename R, class P>
 constexpr size_t plan_lds_bytes(bool column) {
   const size_t tile =
       column ? size_t(LdsPointMajor<R, P::LINES, P::PA, P::PB>::size(P::HX ? P::N / 2 : P::N))
              : size_t(P::LINES) * LdsLineMajor<R, P::N>::LINE;
-  const size_t tw = (P::HX || P::QTW) ? size_t(qtw_entries<P::N>(typename P::radices{}))
-                    : !P::PIPE         ? 0
-                                       : size_t(lds_tw_entries<P::N>(typename P::radices{}));
-  return (tile + tw) * sizeof(cx<R>) + sizeof(double) * 8 * ((P::THREADS + 63) / 64);
+  return tile * sizeof(cx<R>);
 }
-// Pipelined (persistent) plans are built for complex64 only, rows with one
-// row per workgroup; half-exchange plans for complex64 columns only.
 template <typename R, class P>
 constexpr bool plan_fits(bool column) {
   return plan_lds_bytes<R, P>(column) <= kMaxLdsBytes &&
-         !(P::PIPE && (sizeof(R) != 4 || (!column && P::LINES != 1))) &&
          !(P::HX && (sizeof(R) != 4 || !column));
 }
 

@@ -318,15 +318,14 @@ __device__ __forceinline__ void screen_amp2_n(const ScreenConst<R>& s, const R* 
   }
 }
 
-// u <- u E(|u|^2) exp(i phi_t) at C points.
-template <typename R, int C>
+// u <- u E(|u|^2) exp(i phi_t) at C points; x: |u|^2 and a: A at them.
+template <typename R, int C, bool PRECISE>
 __device__ __forceinline__ void screen_apply_n(const ScreenConst<R>& s, cx<R>* u,
-                                               const R* phi_t) {
-  R x[C], log_a[C], phi[C];
+                                               const R* phi_t, R* x, R* a) {
+  R log_a[C], phi[C];
 #pragma unroll
   for (int e = 0; e < C; ++e) x[e] = u[e].re * u[e].re + u[e].im * u[e].im;
   screen_eval_n<R, C>(s, x, log_a, phi);
-  R a[C];
   if (s.terms & (T_MPA | T_ANSATZ)) {
 #pragma unroll
     for (int e = 0; e < C; ++e)
@@ -336,13 +335,8 @@ __device__ __forceinline__ void screen_apply_n(const ScreenConst<R>& s, cx<R>* u
     for (int e = 0; e < C; ++e) a[e] = R(1);
   }
   R sn[C], cs[C];
-  if (s.terms & T_PRECISE) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) sin_cos(phi[e] + phi_t[e], &sn[e], &cs[e], true);
-  } else {
-#pragma unroll
-    for (int e = 0; e < C; ++e) sin_cos(phi[e] + phi_t[e], &sn[e], &cs[e], false);
-  }
+  for (int e = 0; e < C; ++e) sin_cos(phi[e] + phi_t[e], &sn[e], &cs[e], PRECISE);
 #pragma unroll
   for (int e = 0; e < C; ++e)
     u[e] = {a[e] * (u[e].re * cs[e] - u[e].im * sn[e]),
@@ -351,21 +345,19 @@ __device__ __forceinline__ void screen_apply_n(const ScreenConst<R>& s, cx<R>* u
 
 // Adjoint of the screen at C points (see screen_adjoint): lam holds the
 // cotangents of the screened values and is overwritten with those of V;
-// the ansatz gradient terms are added to gth[8] point by point in order.
+// the ansatz gradient terms over -cK are added to gth[8] point by point in
+// order.
 // has_plane: a turbulence plane phi_t is applied at this step.
-// SERIAL: a scheduling barrier after each point's gradient terms, so the
-// FP64 products of later points are not computed ahead and held.
-template <typename R, int C, bool SERIAL = false>
+template <typename R, int C, bool PRECISE>
 __device__ __forceinline__ void screen_adjoint_n(const ScreenConst<R>& s, const cx<R>* v,
                                                  cx<R>* lam, const R* phi_t, bool has_plane,
                                                  double* gth) {
   const unsigned tm = s.terms;
-  const bool precise = (tm & T_PRECISE) != 0;
   if (has_plane) {  // lam <- conj(T) lam
 #pragma unroll
     for (int e = 0; e < C; ++e) {
       R sn, cs;
-      sin_cos(phi_t[e], &sn, &cs, precise);
+      sin_cos(phi_t[e], &sn, &cs, PRECISE);
       lam[e] = {lam[e].re * cs + lam[e].im * sn, lam[e].im * cs - lam[e].re * sn};
     }
   }
@@ -426,13 +418,8 @@ __device__ __forceinline__ void screen_adjoint_n(const ScreenConst<R>& s, const 
     }
   }
   R sn[C], cs[C];
-  if (precise) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) sin_cos(phi[e], &sn[e], &cs[e], true);
-  } else {
-#pragma unroll
-    for (int e = 0; e < C; ++e) sin_cos(phi[e], &sn[e], &cs[e], false);
-  }
+  for (int e = 0; e < C; ++e) sin_cos(phi[e], &sn[e], &cs[e], PRECISE);
 #pragma unroll
   for (int e = 0; e < C; ++e) {
     const R a = (log_a[e] == R(0)) ? R(1) : fast_exp2(log_a[e] * R(1.44269504088896340736));
@@ -452,12 +439,11 @@ __device__ __forceinline__ void screen_adjoint_n(const ScreenConst<R>& s, const 
       const R q_im = lam[e].re * w.im - lam[e].im * w.re;
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        gth[p] += -double(s.cK) * double(q_im) * double(bx[p]);
-        gth[4 + p] += -double(s.cK) * double(q_re) * double(bx[p]);
+        gth[p] += double(q_im) * double(bx[p]);
+        gth[4 + p] += double(q_re) * double(bx[p]);
       }
     }
     lam[e] = t1 + t2;
-    if constexpr (SERIAL) __builtin_amdgcn_sched_barrier(0);
   }
 }
 

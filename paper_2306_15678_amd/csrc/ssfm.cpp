@@ -2,19 +2,23 @@
 //
 // The host side turns beam descriptions into device tables (twiddles and
 // diffraction factors computed in FP64 and rounded once, per-beam screen
-// constants), builds the per-pass work lists, and drives the march:
+// constants) and drives the march:
 //
-//   forward step n   ROW_FWD (pending screen n-1 applied on load) -> COL_FWD
-//   adjoint step n   COL_ADJ -> ROW_ADJ (adjoint of screen n-1 fused)
+//   forward  one pass per step: the diffraction factor that ends step n, its
+//            screen, the factor that begins step n+1, along one axis; the
+//            axis alternates from step to step (see pass_kernels.hpp)
+//   adjoint  the same passes in reverse
 //
-// All beams of a context march in lock-step; beams of equal grid size share
-// one launch per pass, so a batch of uneven beams costs one launch per
-// distinct size per pass (captured once into a HIP graph and replayed).
+// All beams of a context march in lock-step; beams of equal grid size are
+// neighbours in every table and buffer and share one launch per pass, so a
+// batch of uneven beams costs one launch per distinct size per pass
+// (captured once into a HIP graph and replayed).
 #include "../../include/ssfm.h"
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -91,15 +95,14 @@ int validate_desc(const ssfm_instance_desc* d, int32_t n_inst, int32_t precision
 
 // Device-side layout of everything a context keeps in the workspace.
 struct Layout {
-  size_t inst, steps, work, wbegin_row, wbegin_col, tables;
-  size_t S, Wk, Lam, ckpt, stack, screens, stage, diag_part, diag, theta_acc,
-      theta_out, seed_loss, seed_theta, scal, sumsq_part, lens_inst, half_inst, back_inst,
-      fd_inst, subh, subh_beams;
+  size_t inst, steps, begins, tables;
+  size_t S, Wk, Lam, ckpt, stack, screens, stage, diag_part, diag, theta_rows, theta_cols,
+      theta_out, seed_loss, seed_theta, scal, sumsq_part, subh, subh_beams;
   size_t total;
   int64_t field_elems;  // sum n^2
   int64_t table_elems;
-  int64_t n_work_rows, n_work_cols;  // launch entries (with padding)
-  int64_t n_widx_rows, n_widx_cols;  // real work items
+  int64_t part_stride;  // power partials of one step (room for any variant, either axis)
+  int64_t theta_row_parts, theta_col_parts;  // theta accumulators of the adjoint passes
   int64_t n_ckpt, n_stack, diag_cap, screen_elems, n_steps_total;
   // regions of n_stack segment slots: recompute banks (0, 1 or 2) and
   // segments kept whole by the forward record
@@ -107,16 +110,26 @@ struct Layout {
   int max_n;
 };
 
+// The passes a beam size runs through: variants of the forward and adjoint
+// row and column pass.
+enum PassSlot { P_ROW = 0, P_COL = 1, P_ROW_ADJ = 2, P_COL_ADJ = 3, P_SLOTS = 4 };
+// Tables of n entries each beam keeps: propagator, lens filter, half steps
+// forward and back, finite-difference solve.
+enum BeamTable { T_PROP = 0, T_LENS = 1, T_HALF = 2, T_BACK = 3, T_FD = 4, T_COUNT = 5 };
+
+// Beams of one grid size: consecutive in the beam table and every buffer.
 struct Group {
   int n;
-  int row_var = 0, col_var = 0;
-  // variants of the adjoint passes (-1: the forward ones); same lines per
-  // workgroup as the forward variant, so the work lists are shared
-  int row_adj_var = -1, col_adj_var = -1;
-  std::vector<int> beams;
-  // launch order (XCD-aware), offsets into the work array
-  int64_t row_work_off = 0, col_work_off = 0;
-  int row_blocks = 0, col_blocks = 0;
+  int beam0 = 0, count = 0;
+  // variants of the adjoint passes may be -1: the forward ones
+  int var[P_SLOTS] = {0, 0, -1, -1};
+  int64_t tw = 0;     // element offset of P_SLOTS stage-ordered twiddle tables, n entries each
+  int64_t prop = 0;   // element offset of beam0's tables (T_COUNT n entries per beam)
+  int32_t part0[P_SLOTS] = {0, 0, 0, 0};  // first partial of beam0 in each pass
+  int lines[P_SLOTS] = {0, 0, 0, 0};      // lines per workgroup of each pass
+  int variant(int slot) const {
+    return (slot >= P_ROW_ADJ && var[slot] < 0) ? var[slot - P_ROW_ADJ] : var[slot];
+  }
 };
 
 }  // namespace
@@ -124,20 +137,20 @@ struct Group {
 struct ssfm_ctx {
   int precision = SSFM_FP32;
   size_t el = 8;  // bytes per complex element
+  // beams in the order of the groups (equal sizes together); slot[i] is the
+  // position of the caller's instance i, caller[b] the instance at position b
   std::vector<ssfm_instance_desc> desc;
+  std::vector<int32_t> slot, caller;
   std::vector<InstDev> inst;
   std::vector<int64_t> screen_steps;
-  std::vector<int64_t> lens_off;  // element offset of each beam's lens filter table
   // Strang splitting: the state holds V = L(dz/2) U and every step applies
-  // its own screen on load; half_off / back_off: tables of L(+-dz/2)
+  // its own screen on load
   bool strang = false;
-  std::vector<int64_t> half_off, back_off;
   // finite-difference reference scheme (Crank-Nicolson, fixed-point
-  // iterations per step); fd_off: each beam's table of
-  // d[m] = (dz / (k0 dx^2)) sin^2(pi m / n)
+  // iterations per step)
   bool fd = false;
   int fd_iters = 4;
-  std::vector<int64_t> fd_off;
+  bool precise = false;  // library sine and cosine in the FP32 screens
   std::vector<SubBeam> sub_beams;  // host copy of the last uploaded subharmonic list
   struct Spectrum {
     int kind = SSFM_SPECTRUM_KOLMOGOROV;
@@ -146,8 +159,7 @@ struct ssfm_ctx {
   };
   std::vector<Spectrum> spectrum;  // per beam, for gen_screens
   std::vector<Group> groups;
-  std::vector<WorkItem> work;  // all launch entries, group by group
-  std::vector<int32_t> wbegin_row, wbegin_col;
+  std::vector<int32_t> begins;  // P_SLOTS lists of n_inst + 1 first partials per beam
   Layout L{};
   char* ws = nullptr;
   hipStream_t stream = nullptr;
@@ -167,21 +179,27 @@ struct ssfm_ctx {
   std::vector<char> seeded_beam;  // per beam: cotangent set since the record
   bool use_graphs = true;
   std::map<std::tuple<int, int64_t, int64_t, int64_t, int64_t>, hipGraphExec_t> graphs;
-  // Sampled pass timing (0: off): with timing_every = m, step s of a
-  // forward march with s % m == m / 2 runs outside the step graphs, each of
-  // its pass kernels launched with start/stop events on its own dispatch;
-  // samples holds those of the most recent forward march.  ev[2 * (p * G +
-  // g) + {0, 1}]: start/stop of pass p (0 row, 1 column) for size group g.
+  // step_base of every beam when the graphs were captured (they hold which
+  // of their passes meet a turbulence screen)
+  std::vector<int64_t> graph_bases;
+  // Sampled pass timing (0: off): with timing_every = m, the pass that ends
+  // step s of a forward march, s % m == m / 2, runs outside the step
+  // graphs, launched with start/stop events on its own dispatch, and so
+  // does a neighbouring pass (along the other axis); samples holds those of
+  // the most recent forward march.  ev[2 g + {0, 1}]: start/stop for size
+  // group g.
   struct PassSample {
     std::vector<hipEvent_t> ev;
+    bool col = false;
   };
   int32_t timing_every = 0;
   std::vector<PassSample> samples, free_samples;
+  int32_t n_samples = 0;
   // samples of the most recent backward: adjoint steps s of its first
   // segment (which runs alone, not beside a recompute) with
-  // s % timing_every == timing_every / 2; pass 0 the column pass, 1 the row
-  // pass
+  // s % timing_every == timing_every / 2, and the pass after each
   std::vector<PassSample> adj_samples;
+  int32_t n_adj_samples = 0;
   // second stream (default priority) and events for the overlapped backward
   hipStream_t aux = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -244,129 +262,92 @@ double band_q2(double length, double kappa_h) {
   return q * q * (1.0 + 0x1p-40);
 }
 
-// Groups by grid size in first-appearance order.
+// Beams in group order: by grid size in first-appearance order, beams of
+// one size in the caller's order.  order[b]: the caller's index of beam b.
+std::vector<int32_t> group_order(const ssfm_instance_desc* d, int n_inst) {
+  std::vector<int32_t> order;
+  std::vector<int> sizes;
+  for (int i = 0; i < n_inst; ++i)
+    if (std::find(sizes.begin(), sizes.end(), d[i].n) == sizes.end()) sizes.push_back(d[i].n);
+  for (int n : sizes)
+    for (int i = 0; i < n_inst; ++i)
+      if (d[i].n == n) order.push_back(i);
+  return order;
+}
+
+// Groups of beams of one grid size (d in group order).
 std::vector<Group> make_groups(const ssfm_instance_desc* d, int n_inst) {
   std::vector<Group> g;
   for (int i = 0; i < n_inst; ++i) {
-    auto it = std::find_if(g.begin(), g.end(), [&](const Group& x) { return x.n == d[i].n; });
-    if (it == g.end()) {
+    if (g.empty() || g.back().n != d[i].n) {
       Group ng;
       ng.n = d[i].n;
-      ng.beams.push_back(i);
+      ng.beam0 = i;
       g.push_back(ng);
-    } else {
-      it->beams.push_back(i);
     }
+    ++g.back().count;
   }
   return g;
 }
 
-// XCD-aware launch order: workgroups are dispatched round-robin over the 8
-// XCDs (blockIdx mod 8), so entry b runs on XCD b % 8.  Giving each XCD a
-// contiguous run of work items keeps neighbouring lines (which share cache
-// lines in the column pass) in one XCD's L2.
-std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& items) {
-  const size_t n = items.size();
-  const size_t m = (n + 7) / 8 * 8;
-  const size_t chunk = m / 8;
-  std::vector<WorkItem> out(m, WorkItem{-1, 0, -1, 0});
-  for (size_t b = 0; b < m; ++b) {
-    const size_t x = b % 8, q = b / 8;
-    const size_t t = x * chunk + q;
-    if (t < n) out[b] = items[t];
-  }
-  return out;
-}
+using VariantMap = std::map<int, std::array<int, P_SLOTS>>;  // n -> variants
 
-// Builds groups, work lists and the layout.  Pure host computation.
-using VariantMap = std::map<int, std::pair<int, int>>;  // n -> (row, column)
-
-// Largest number of work items any variant gives a beam of size n.
-int64_t max_items(bool column, int n, bool fp64) {
+// Most partials any variant gives a beam of size n (one per wavefront).
+int64_t max_parts(bool column, int n, bool fp64) {
   int64_t m = 0;
   for (int v = 0; v < plan_count(column, n); ++v) {
     PlanInfo pi;
-    if (plan_info(column, n, v, fp64, &pi)) m = std::max<int64_t>(m, n / pi.lines);
+    if (plan_info(column, n, v, fp64, &pi)) m = std::max<int64_t>(m, int64_t(n / pi.lines) * pi.waves);
   }
   return m;
 }
 
+// Builds groups, partial offsets and the layout (d in group order).  Pure
+// host computation.
 int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t max_steps,
                 int32_t ckpt_every, int32_t stored_segments, const VariantMap* variants,
-                std::vector<Group>* groups_out,
-                std::vector<WorkItem>* work_out, std::vector<int32_t>* wb_row,
-                std::vector<int32_t>* wb_col, Layout* L) {
-  const size_t el = precision == SSFM_FP64 ? 16 : 8;
+                std::vector<Group>* groups_out, std::vector<int32_t>* begins_out, Layout* L) {
+  const bool fp64 = precision == SSFM_FP64;
+  const size_t el = fp64 ? 16 : 8;
   const size_t rel = el / 2;
   std::vector<Group> groups = make_groups(d, n_inst);
-  if (variants) {
-    for (auto& g : groups) {
+  std::vector<int32_t> begins(size_t(P_SLOTS) * (n_inst + 1), 0);
+  int64_t fill[P_SLOTS] = {0, 0, 0, 0};
+  int64_t toff = 0, nr_max = 0, nc_max = 0;
+  for (auto& g : groups) {
+    g.var[P_ROW] = plan_default(false, g.n, fp64);
+    g.var[P_COL] = plan_default(true, g.n, fp64);
+    if (variants) {
       auto it = variants->find(g.n);
-      if (it != variants->end()) {
-        g.row_var = it->second.first;
-        g.col_var = it->second.second;
+      if (it != variants->end()) std::copy(it->second.begin(), it->second.end(), g.var);
+    }
+    for (int s = 0; s < P_SLOTS; ++s) {
+      PlanInfo pi;
+      if (!plan_info(s & 1, g.n, g.variant(s), fp64, &pi))
+        return fail(SSFM_EUNSUPPORTED, "no kernel plan for n=%d", g.n);
+      g.lines[s] = pi.lines;
+      g.part0[s] = int32_t(fill[s]);
+      for (int b = g.beam0; b < g.beam0 + g.count; ++b) {
+        begins[size_t(s) * (n_inst + 1) + b] = int32_t(fill[s]);
+        fill[s] += int64_t(g.n / pi.lines) * pi.waves;
       }
     }
+    g.tw = toff;
+    toff += int64_t(P_SLOTS) * g.n;
+    g.prop = toff;
+    toff += int64_t(g.count) * T_COUNT * g.n;
+    // partial-sum arrays are sized for the variant with the most of them
+    nr_max += g.count * max_parts(false, g.n, fp64);
+    nc_max += g.count * max_parts(true, g.n, fp64);
   }
-  // beam-contiguous work indices
-  std::vector<int32_t> row_first(n_inst + 1), col_first(n_inst + 1);
-  int64_t nr = 0, nc = 0;
-  std::vector<PlanInfo> rinfo(n_inst), cinfo(n_inst);
-  for (auto& g : groups) {
-    PlanInfo ri, ci;
-    if (!plan_info(false, g.n, g.row_var, precision == SSFM_FP64, &ri) ||
-        !plan_info(true, g.n, g.col_var, precision == SSFM_FP64, &ci))
-      return fail(SSFM_EUNSUPPORTED, "no kernel plan for n=%d", g.n);
-    for (int b : g.beams) {
-      rinfo[b] = ri;
-      cinfo[b] = ci;
-    }
-  }
-  for (int b = 0; b < n_inst; ++b) {
-    row_first[b] = int32_t(nr);
-    col_first[b] = int32_t(nc);
-    nr += d[b].n / rinfo[b].lines;
-    nc += d[b].n / cinfo[b].lines;
-  }
-  row_first[n_inst] = int32_t(nr);
-  col_first[n_inst] = int32_t(nc);
-  std::vector<WorkItem> work;
-  for (auto& g : groups) {
-    std::vector<WorkItem> rows, cols;
-    for (int b : g.beams) {
-      const int rl = rinfo[b].lines, cl = cinfo[b].lines;
-      for (int k = 0; k < d[b].n / rl; ++k)
-        rows.push_back(WorkItem{b, k * rl, row_first[b] + k, 0});
-      for (int k = 0; k < d[b].n / cl; ++k)
-        cols.push_back(WorkItem{b, k * cl, col_first[b] + k, 0});
-    }
-    auto ro = xcd_order(rows), co = xcd_order(cols);
-    g.row_work_off = int64_t(work.size());
-    g.row_blocks = int(ro.size());
-    work.insert(work.end(), ro.begin(), ro.end());
-    g.col_work_off = int64_t(work.size());
-    g.col_blocks = int(co.size());
-    work.insert(work.end(), co.begin(), co.end());
-  }
-  // partial-sum arrays are sized for the variant with the most work items
-  int64_t nr_max = 0, nc_max = 0;
-  for (int b = 0; b < n_inst; ++b) {
-    nr_max += max_items(false, d[b].n, precision == SSFM_FP64);
-    nc_max += max_items(true, d[b].n, precision == SSFM_FP64);
-  }
+  for (int s = 0; s < P_SLOTS; ++s)
+    begins[size_t(s) * (n_inst + 1) + n_inst] = int32_t(fill[s]);
   Layout l{};
-  int64_t fe = 0, te = 0, se = 0, nsteps = 0, subh_doubles = 0;
+  int64_t fe = 0, se = 0, nsteps = 0, subh_doubles = 0;
   int max_n = 0;
-  std::vector<int> tw_done;
   for (int b = 0; b < n_inst; ++b) {
     fe += int64_t(d[b].n) * d[b].n;
     max_n = std::max(max_n, d[b].n);
-    if (std::find(tw_done.begin(), tw_done.end(), d[b].n) == tw_done.end()) {
-      tw_done.push_back(d[b].n);
-      te += d[b].n;
-    }
-    // propagator, lens filter, +/- half-step propagators, finite-difference table
-    te += 5 * int64_t(d[b].n);
     if (d[b].terms & SSFM_TURB) {
       se += int64_t(d[b].n_screens) * d[b].n * d[b].n;
       nsteps += d[b].n_screens;
@@ -374,14 +355,13 @@ int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t 
     }
   }
   l.field_elems = fe;
-  l.table_elems = te;
+  l.table_elems = toff;
   l.screen_elems = se;
   l.n_steps_total = nsteps;
   l.max_n = max_n;
-  l.n_work_rows = nr;
-  l.n_work_cols = nc;
-  l.n_widx_rows = nr;
-  l.n_widx_cols = nc;
+  l.part_stride = std::max(nr_max, nc_max);
+  l.theta_row_parts = nr_max;
+  l.theta_col_parts = nc_max;
   if (max_steps > 0) {
     const int64_t m = std::max<int64_t>(1, ckpt_every);
     const int64_t seg = std::min<int64_t>(m, max_steps);
@@ -404,11 +384,8 @@ int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t 
   };
   l.inst = take(sizeof(InstDev) * n_inst);
   l.steps = take(sizeof(int64_t) * std::max<int64_t>(nsteps, 1));
-  // room for the work list of any variant choice (with XCD padding)
-  l.work = take(sizeof(WorkItem) * size_t(nr_max + nc_max + 16 * groups.size()));
-  l.wbegin_row = take(sizeof(int32_t) * (n_inst + 1));
-  l.wbegin_col = take(sizeof(int32_t) * (n_inst + 1));
-  l.tables = take(el * te);
+  l.begins = take(sizeof(int32_t) * P_SLOTS * (n_inst + 1));
+  l.tables = take(el * toff);
   l.S = take(el * fe);
   l.Wk = take(el * fe);
   // (with more than one segment the recompute of the next segment runs
@@ -419,11 +396,11 @@ int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t 
   l.stack = take(el * fe * l.n_stack * (l.n_banks + l.n_kept));
   l.screens = take(rel * se);
   l.stage = take(16 * size_t(max_n) * max_n);
-  // power partials of column work items (split-step) or row work items
-  // (finite differences)
-  l.diag_part = take(sizeof(double) * 2 * kDiagChunk * std::max(nr_max, nc_max));
+  // power partials of the pass that ends a step
+  l.diag_part = take(sizeof(double) * 2 * kDiagChunk * l.part_stride);
   l.diag = take(sizeof(double) * 2 * l.diag_cap * n_inst);
-  l.theta_acc = take(sizeof(double) * 8 * nr_max);
+  l.theta_rows = take(sizeof(double) * 8 * nr_max);
+  l.theta_cols = take(sizeof(double) * 8 * nc_max);
   l.theta_out = take(sizeof(double) * 8 * n_inst);
   l.seed_loss = take(sizeof(double) * max_n);
   l.seed_theta = take(sizeof(double) * 8 * max_n * n_inst);
@@ -431,29 +408,33 @@ int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t 
   // 256 partials of a sum of squares, moment or hot-area count, then 256 x 5
   // measure-vector partials
   l.sumsq_part = take(sizeof(double) * 256 * 6);
-  l.lens_inst = take(sizeof(InstDev) * n_inst);
-  l.half_inst = take(sizeof(InstDev) * n_inst);
-  l.back_inst = take(sizeof(InstDev) * n_inst);
-  l.fd_inst = take(sizeof(InstDev) * n_inst);
   // subharmonic tables and coefficients of every turbulent beam, its beam list
   l.subh = take(sizeof(double) * size_t(subh_doubles));
   l.subh_beams = take(sizeof(SubBeam) * n_inst);
   l.total = off;
   if (groups_out) *groups_out = groups;
-  if (work_out) *work_out = work;
-  if (wb_row) *wb_row = row_first;
-  if (wb_col) *wb_col = col_first;
+  if (begins_out) *begins_out = begins;
   *L = l;
   return SSFM_OK;
 }
 
-// exp(-2 pi i m / n) in FP64, rounded to the working precision.
-void twiddles(int n, std::vector<double>* out) {
-  out->resize(2 * size_t(n));
-  for (int m = 0; m < n; ++m) {
-    const double a = 2.0 * M_PI * double(m) / double(n);
-    (*out)[2 * m] = std::cos(a);
-    (*out)[2 * m + 1] = -std::sin(a);
+// Twiddles of a radix plan in the order its stages read them (see
+// fft_core.hpp): exp(-2 pi i r k / (NS R)) in FP64, rounded to the working
+// precision; n entries, the last R0 unused.
+void stage_twiddles(int n, const int* radices, std::vector<double>* out) {
+  out->assign(2 * size_t(n), 0.0);
+  const int r0 = radices[0];
+  int ns = r0;
+  for (int i = 1; radices[i] != 0; ++i) {
+    const int rad = radices[i], step = n / (ns * rad);
+    for (int r = 1; r < rad; ++r)
+      for (int k = 0; k < ns; ++k) {
+        const double a = 2.0 * M_PI * double(int64_t(r) * k * step) / double(n);
+        const size_t at = size_t(ns - r0) + size_t(r - 1) * ns + k;
+        (*out)[2 * at] = std::cos(a);
+        (*out)[2 * at + 1] = -std::sin(a);
+      }
+    ns *= rad;
   }
 }
 
@@ -485,10 +466,12 @@ int check_ctx(ssfm_ctx* c) {
   return SSFM_OK;
 }
 
-int check_inst(ssfm_ctx* c, int32_t i) {
+// Maps the caller's instance to its position among the beams.
+int check_inst(ssfm_ctx* c, int32_t& i) {
   if (int r = check_ctx(c)) return r;
   if (i < 0 || i >= int32_t(c->desc.size()))
     return fail(SSFM_EINVAL, "instance %d out of range [0, %zu)", i, c->desc.size());
+  i = c->slot[i];
   return SSFM_OK;
 }
 
@@ -519,9 +502,21 @@ PassArgs<R> base_args(ssfm_ctx* c) {
   a.screens = c->at<R>(c->L.screens);
   a.screen_steps = c->at<int64_t>(c->L.steps);
   a.step = -1;
-  for (const auto& in : c->inst)
-    if (in.terms & (1u << 8)) a.precise = 1;
+  a.precise = c->precise ? 1 : 0;
   return a;
+}
+
+// Whether a beam of the group has a turbulence screen after context step
+// `step`, so that the passes of the other steps do not look for one.
+bool group_has_plane(const ssfm_ctx* c, const Group& g, int64_t step) {
+  if (step < 0) return false;
+  for (int b = g.beam0; b < g.beam0 + g.count; ++b) {
+    const InstDev& in = c->inst[b];
+    if (!(in.terms & SSFM_TURB) || in.n_screens <= 0) continue;
+    const auto first = c->screen_steps.begin() + in.steps_off;
+    if (std::binary_search(first, first + in.n_screens, step - in.step_base)) return true;
+  }
+  return false;
 }
 
 // One pass over every beam: one launch per grid-size group.  On the main
@@ -534,8 +529,12 @@ PassArgs<R> base_args(ssfm_ctx* c) {
 // auxiliary stream instead.
 template <typename R>
 int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, hipStream_t st = nullptr,
-             const hipEvent_t* ev = nullptr) {
+             int table = T_PROP, const hipEvent_t* ev = nullptr) {
   const bool col = is_col_kind(kind);
+  const bool adj = kind == ROW_ADJ || kind == COL_ADJ;
+  const int slot = (adj ? P_ROW_ADJ : P_ROW) + (col ? 1 : 0);
+  const int32_t flags = a.flags;
+  const bool screen = (adj || kind == ROW_FWD || kind == COL_FWD) && (flags & PASS_SCREEN);
   if (!st) st = c->stream;
   const size_t ng = c->groups.size();
   const bool fork = st != c->aux && ng > 1 && c->gstream.size() + 1 >= ng;
@@ -545,13 +544,17 @@ int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, hipStream_t st = nullptr,
   }
   for (size_t gi = 0; gi < ng; ++gi) {
     const Group& g = c->groups[gi];
-    a.work = c->at<WorkItem>(c->L.work) + (col ? g.col_work_off : g.row_work_off);
-    const int nb = col ? g.col_blocks : g.row_blocks;
-    const int v = col ? ((kind == COL_ADJ && g.col_adj_var >= 0) ? g.col_adj_var : g.col_var)
-                      : ((kind == ROW_ADJ && g.row_adj_var >= 0) ? g.row_adj_var : g.row_var);
+    a.off0 = c->inst[g.beam0].off;
+    a.prop0 = g.prop + int64_t(table) * g.n;
+    a.prop_stride = T_COUNT * g.n;
+    a.tw = g.tw + int64_t(slot) * g.n;
+    a.beam0 = g.beam0;
+    a.part0 = g.part0[slot];
+    a.n_tiles = g.count * (g.n / g.lines[slot]);
+    a.flags = flags | ((screen && group_has_plane(c, g, a.step)) ? PASS_PLANE : 0);
     hipStream_t sg = (fork && gi > 0) ? c->gstream[gi - 1] : st;
     const LaunchEv le = ev ? LaunchEv{ev[2 * gi], ev[2 * gi + 1]} : LaunchEv{nullptr, nullptr};
-    HIP_TRY(launch_pass<R>(kind, g.n, v, nb, a, sg, ev ? &le : nullptr));
+    HIP_TRY(launch_pass<R>(kind, g.n, g.variant(slot), a, sg, ev ? &le : nullptr));
   }
   if (fork) {
     for (size_t g = 1; g < ng; ++g) {
@@ -562,11 +565,10 @@ int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, hipStream_t st = nullptr,
   return SSFM_OK;
 }
 
-// One forward step: src (s_n) -> work -> dst (s_{n+1}), on stream st.
-// A timing sample (a start/stop pair per pass and size group) from the
-// pool; false if none could be made.
+// A timing sample (a start/stop pair per size group) from the pool; false
+// if none could be made.
 bool take_sample(ssfm_ctx* c, ssfm_ctx::PassSample* ps) {
-  const size_t need = 4 * c->groups.size();
+  const size_t need = 2 * c->groups.size();
   if (!c->free_samples.empty()) {
     *ps = std::move(c->free_samples.back());
     c->free_samples.pop_back();
@@ -590,94 +592,89 @@ void clear_graphs(ssfm_ctx* c) {
   c->graphs.clear();
 }
 
-// Whether steps into fresh slots of the stored trajectory go through the
-// work buffer (see fwd_step): for beams whose field spans at least 64 MiB
-// (4096^2 complex64 and up), where it measures faster; the 1024^2 march
-// measures faster with the column pass in place on the slot.
-bool fresh_via_work(const ssfm_ctx* c) {
-  return int64_t(c->L.max_n) * c->L.max_n * int64_t(c->el) >= (int64_t(64) << 20);
-}
+// Axis along which context step `step` diffracts first (false: rows) and
+// second.  Tied to the step index, so a march cut anywhere, a recomputed
+// segment and the adjoint all see the same fields.
+bool first_axis_col(int64_t step) { return (step & 1) != 0; }
+bool second_axis_col(int64_t step) { return (step & 1) == 0; }
 
-template <typename R>
-int fwd_step(ssfm_ctx* c, const void* src, void* dst, int64_t pending_step, double* part,
-             void* work = nullptr, hipStream_t st = nullptr,
-             const ssfm_ctx::PassSample* ts = nullptr) {
-  // both passes transform whole lines, each read and written by one
-  // workgroup, so the row pass can write straight into dst and the column
-  // pass finish there in place.  For large beams a step into a fresh slot
-  // of the stored trajectory goes through a work buffer instead (row pass
-  // into it, column pass out of it): the column pass then reads a buffer
-  // every step uses and only its stores touch the new slot, which measures
-  // faster than column reads and writes on the freshly written slot there.
-  if (!work) work = dst;
-  if (!st) st = c->stream;
-  PassArgs<R> a = base_args<R>(c);
-  a.src = src;
-  a.dst = work;
-  a.step = pending_step;
-  const size_t ng = c->groups.size();
-  if (int r = run_pass<R>(c, ROW_FWD, a, st, ts ? ts->ev.data() : nullptr)) return r;
-  PassArgs<R> b = base_args<R>(c);
-  b.src = work;
-  b.dst = dst;
-  b.part = part;
-  b.flags = c->strang ? 1 : 0;  // Strang: |U|^2 = |V|^2 summed as it is
-  return run_pass<R>(c, COL_FWD, b, st, ts ? ts->ev.data() + 2 * ng : nullptr);
-}
+// Where a march of n steps reads and writes: V_0 comes from src, the
+// half-diffracted field lives in cur (whole lines per workgroup: in place),
+// V_n goes to dst, and rec(i) (0 <= i < n), where it gives a buffer, gets
+// V_i.
+struct MarchBuffers {
+  const void* src;
+  void *cur, *dst;
+};
 
-// One adjoint step: Lam -> Wk (columns) -> Lam (rows + adjoint screen with
-// the pre-screen field `sv` of the screen applied after step pending_step).
-// ts: timing events around the two passes (sampled steps only).
-template <typename R>
-int adj_step(ssfm_ctx* c, const void* sv, int64_t pending_step,
-             const ssfm_ctx::PassSample* ts = nullptr) {
-  const size_t ng = c->groups.size();
-  // both passes in place on the cotangent (whole lines per workgroup)
-  PassArgs<R> a = base_args<R>(c);
-  a.src = c->field(c->L.Lam);
-  a.dst = c->field(c->L.Lam);
-  if (int r = run_pass<R>(c, COL_ADJ, a, nullptr, ts ? ts->ev.data() : nullptr)) return r;
-  PassArgs<R> b = base_args<R>(c);
-  b.src = c->field(c->L.Lam);
-  b.dst = c->field(c->L.Lam);
-  b.aux = sv;
-  b.step = pending_step;
-  b.part = c->at<double>(c->L.theta_acc);
-  return run_pass<R>(c, ROW_ADJ, b, nullptr, ts ? ts->ev.data() + 2 * ng : nullptr);
-}
-
-template <typename R>
-int diag_flush(ssfm_ctx* c, int steps, int64_t first_step) {
-  HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), int(c->L.n_widx_cols),
-                               c->at<int32_t>(c->L.wbegin_col), int(c->desc.size()), steps,
-                               c->at<double>(c->L.diag), first_step, c->L.diag_cap, 0.0,
-                               c->stream));
-  return SSFM_OK;
-}
-
-// Enqueue steps i0 <= i < i1 of a plain forward march from step0 (step
-// step0 + i; pending0: the state holds V with the screen of step0 - 1 still
-// to apply).  ts: timing events around the passes (single steps only).
-template <typename R>
-int enqueue_propagate(ssfm_ctx* c, int64_t step0, bool pending0, int64_t i0, int64_t i1,
-                      const ssfm_ctx::PassSample* ts) {
+// The passes that end steps i0 <= i < i1 of a march of n steps from step0
+// (for i0 = 0 also the pass that opens it).  pend(i): step whose screen acts
+// before step i diffracts (-1: none).  part: whether to reduce the power and
+// peak of each step.  open, end: timing events of the opening and of the
+// (single) ending pass.
+template <typename R, typename Pend, typename Rec>
+int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
+                  const MarchBuffers& m, Pend pend, Rec rec, bool part, hipStream_t st,
+                  const ssfm_ctx::PassSample* open, const ssfm_ctx::PassSample* end) {
+  const int32_t raw = c->strang ? PASS_RAW : 0;  // Strang: |U|^2 = |V|^2 summed as it is
+  if (i0 == 0) {
+    PassArgs<R> a = base_args<R>(c);
+    a.src = m.src;
+    a.dst = m.cur;
+    a.rec = rec(0);
+    a.step = pend(0);
+    a.flags = PASS_OP2 | (a.step >= 0 ? PASS_SCREEN : 0);
+    const bool col = first_axis_col(step0);
+    if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, st, T_PROP,
+                            open ? open->ev.data() : nullptr))
+      return r;
+  }
   int64_t chunk_start = step0 + i0;
   for (int64_t i = i0; i < i1; ++i) {
-    const int64_t step = step0 + i;
     const int slot = int((i - i0) % kDiagChunk);
-    double* part = c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.n_widx_cols;
-    // Lie: the screen of the previous step, pending in the state; Strang:
-    // the state is V = L(dz/2) U and this step's own screen acts first
-    const int64_t pend = c->strang ? step : ((i == 0 && !pending0) ? -1 : step - 1);
-    if (int r = fwd_step<R>(c, c->field(c->L.S), c->field(c->L.S), pend, part, nullptr, nullptr,
-                            ts))
+    const bool last = i == n - 1;
+    PassArgs<R> a = base_args<R>(c);
+    a.src = m.cur;
+    a.dst = last ? m.dst : m.cur;
+    if (part) a.part = c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.part_stride;
+    a.flags = PASS_OP1 | raw;
+    if (!last) {
+      a.rec = rec(i + 1);
+      a.step = pend(i + 1);
+      a.flags |= PASS_SCREEN | PASS_OP2;
+    }
+    const bool col = second_axis_col(step0 + i);
+    if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, st, T_PROP,
+                            end ? end->ev.data() : nullptr))
       return r;
-    if (slot == kDiagChunk - 1 || i == i1 - 1) {
-      if (int r = diag_flush<R>(c, slot + 1, chunk_start)) return r;
-      chunk_start = step + 1;
+    if (part && (slot == kDiagChunk - 1 || i == i1 - 1)) {
+      const int32_t* begins = c->at<int32_t>(c->L.begins);
+      const size_t nb = c->desc.size() + 1;
+      HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), c->L.part_stride,
+                                   begins + P_COL * nb, begins + P_ROW * nb,
+                                   int(c->desc.size()), slot + 1, c->at<double>(c->L.diag),
+                                   chunk_start, c->L.diag_cap, c->stream));
+      chunk_start = step0 + i + 1;
     }
   }
   return SSFM_OK;
+}
+
+// Steps i0 <= i < i1 of an n-step plain forward march from step0 (pending0:
+// the state holds V with the screen of step0 - 1 still to apply), in place
+// on the state.  Lie: the screen of the previous step acts before step i;
+// Strang: the state is V = L(dz/2) U and the step's own screen does.
+template <typename R>
+int enqueue_propagate(ssfm_ctx* c, int64_t n, int64_t step0, bool pending0, int64_t i0,
+                      int64_t i1, const ssfm_ctx::PassSample* open,
+                      const ssfm_ctx::PassSample* end) {
+  void* S = c->field(c->L.S);
+  auto pend = [&](int64_t i) {
+    return c->strang ? step0 + i : (i == 0 && !pending0) ? -1 : step0 + i - 1;
+  };
+  return enqueue_march<R>(
+      c, n, step0, i0, i1, MarchBuffers{S, S, S}, pend,
+      [](int64_t) -> void* { return nullptr; }, true, c->stream, open, end);
 }
 
 // Steps i0 <= i < i1 of a finite-difference march from step step0 + i0, on
@@ -689,14 +686,12 @@ int enqueue_propagate(ssfm_ctx* c, int64_t step0, bool pending0, int64_t i0, int
 template <typename R>
 int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1) {
   PassArgs<R> a = base_args<R>(c);
-  a.inst = c->at<InstDev>(c->L.fd_inst);
   a.state = c->field(c->L.S);
   a.src = c->field(c->L.S);
   a.dst = c->field(c->L.Wk);
   a.flags = 0;
   if (int r = run_pass<R>(c, ROW_FD, a)) return r;
   PassArgs<R> col = base_args<R>(c);
-  col.inst = a.inst;
   col.src = c->field(c->L.Wk);
   col.dst = c->field(c->L.Wk);
   a.src = c->field(c->L.Wk);
@@ -704,18 +699,18 @@ int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1) {
   for (int64_t i = i0; i < i1; ++i) {
     const int slot = int((i - i0) % kDiagChunk);
     for (int k = 1; k <= c->fd_iters; ++k) {
-      if (int r = run_pass<R>(c, COL_FD, col)) return r;
+      if (int r = run_pass<R>(c, COL_FD, col, nullptr, T_FD)) return r;
       const bool fin = (k == c->fd_iters);
       a.flags = FD_SPECTRAL | (fin ? FD_FINISH : 0) | ((fin && i == i1 - 1) ? FD_LAST : 0);
-      a.part = fin ? c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.n_widx_rows
+      a.part = fin ? c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.part_stride
                    : nullptr;
       if (int r = run_pass<R>(c, ROW_FD, a)) return r;
     }
     if (slot == kDiagChunk - 1 || i == i1 - 1) {
-      HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), int(c->L.n_widx_rows),
-                                   c->at<int32_t>(c->L.wbegin_row), int(c->desc.size()),
-                                   slot + 1, c->at<double>(c->L.diag), chunk_start,
-                                   c->L.diag_cap, 0.0, c->stream));
+      const int32_t* rows = c->at<int32_t>(c->L.begins) + P_ROW * (c->desc.size() + 1);
+      HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), c->L.part_stride, rows, rows,
+                                   int(c->desc.size()), slot + 1, c->at<double>(c->L.diag),
+                                   chunk_start, c->L.diag_cap, c->stream));
       chunk_start = step0 + i + 1;
     }
   }
@@ -726,6 +721,15 @@ int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1) {
 template <typename F>
 int maybe_graph(ssfm_ctx* c, int kind, int64_t a, int64_t b, int64_t i0, int64_t i1, F body) {
   if (!c->use_graphs) return body();
+  // captured passes hold whether a turbulence screen acts on them, which
+  // depends on the step at which each beam's field was set
+  std::vector<int64_t> bases;
+  for (const InstDev& in : c->inst) bases.push_back(in.step_base);
+  if (bases != c->graph_bases) {
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    clear_graphs(c);
+    c->graph_bases = bases;
+  }
   auto key = std::make_tuple(kind, a, b, i0, i1);
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
@@ -767,31 +771,48 @@ int maybe_graph(ssfm_ctx* c, int kind, int64_t a, int64_t b, int64_t i0, int64_t
   return SSFM_OK;
 }
 
-// Steps [0, n) of a forward march from step0 through seg(i0, i1, ts): in
-// captured graphs keyed by (kind, key, n, i0, i1) between the sampled steps,
-// each sampled step launched directly between its timing events.
+// Steps [0, n) of a forward march from step0 through seg(i0, i1, open, end):
+// in captured graphs keyed by (kind, key, n, i0, i1) between the sampled
+// passes, each of those launched directly with its timing events: the pass
+// that ends a sampled step and a neighbour along the other axis (the next
+// pass, else the one before).
 template <typename Seg>
 int run_forward(ssfm_ctx* c, int kind, int64_t key, int64_t n, int64_t step0, Seg seg) {
-  for (auto& e : c->samples) c->free_samples.push_back(e);
+  for (auto& e : c->samples) c->free_samples.push_back(std::move(e));
   c->samples.clear();
+  c->n_samples = 0;
   int64_t i = 0;
   auto graph_to = [&](int64_t k) -> int {
     if (k <= i) return SSFM_OK;
     const int64_t i0 = i;
-    return maybe_graph(c, kind, key, n, i0, k, [&] { return seg(i0, k, nullptr); });
+    i = k;
+    return maybe_graph(c, kind, key, n, i0, k, [&] { return seg(i0, k, nullptr, nullptr); });
+  };
+  auto timed = [&](int64_t k, bool with_open) -> int {
+    ssfm_ctx::PassSample open, end;
+    const bool have_open = with_open && take_sample(c, &open);
+    const bool have_end = take_sample(c, &end);
+    open.col = first_axis_col(step0 + k);
+    end.col = second_axis_col(step0 + k);
+    int r = seg(k, k + 1, have_open ? &open : nullptr, have_end ? &end : nullptr);
+    if (have_open) c->samples.push_back(std::move(open));
+    if (have_end) c->samples.push_back(std::move(end));
+    i = k + 1;
+    return r;
   };
   const int64_t m = c->timing_every;
   if (m > 0) {
     int64_t first = (m / 2 - step0 % m) % m;  // first i with (step0 + i) % m == m / 2
     if (first < 0) first += m;
     for (int64_t k = first; k < n; k += m) {
-      if (int r = graph_to(k)) return r;
-      ssfm_ctx::PassSample ps;
-      const bool have = take_sample(c, &ps);
-      int r = seg(k, k + 1, have ? &ps : nullptr);
-      if (have) c->samples.push_back(std::move(ps));
-      if (r) return r;
-      i = k + 1;
+      const bool pair_before = k + 1 == n && k - 1 >= i;
+      if (int r = graph_to(pair_before ? k - 1 : k)) return r;
+      if (pair_before)
+        if (int r = timed(k - 1, false)) return r;
+      if (int r = timed(k, n == 1)) return r;
+      ++c->n_samples;
+      if (m > 1 && k + 1 < n)
+        if (int r = timed(k + 1, false)) return r;
     }
   }
   return graph_to(n);
@@ -815,8 +836,9 @@ int do_propagate(ssfm_ctx* c, int64_t n) {
     return SSFM_OK;
   }
   int r = run_forward(c, 0, step0 * 2 + (pend ? 1 : 0), n, step0,
-                      [&](int64_t i0, int64_t i1, const ssfm_ctx::PassSample* ts) {
-                        return enqueue_propagate<R>(c, step0, pend, i0, i1, ts);
+                      [&](int64_t i0, int64_t i1, const ssfm_ctx::PassSample* open,
+                          const ssfm_ctx::PassSample* end) {
+                        return enqueue_propagate<R>(c, n, step0, pend, i0, i1, open, end);
                       });
   if (r) return r;
   c->step += n;
@@ -834,22 +856,22 @@ template <typename R>
 int half_steps(ssfm_ctx* c, bool forward) {
   HIP_TRY(launch_copy<R>(c->field(c->L.S), c->field(c->L.Wk), c->L.field_elems, c->stream));
   PassArgs<R> a = base_args<R>(c);
-  a.inst = c->at<InstDev>(forward ? c->L.half_inst : c->L.back_inst);
   a.src = c->field(c->L.Wk);
   a.dst = c->field(c->L.Wk);
-  if (int r = run_pass<R>(c, ROW_FWD, a)) return r;
-  return run_pass<R>(c, COL_FWD, a);
+  a.flags = PASS_OP2;
+  if (int r = run_pass<R>(c, ROW_FWD, a, nullptr, forward ? T_HALF : T_BACK)) return r;
+  return run_pass<R>(c, COL_FWD, a, nullptr, forward ? T_HALF : T_BACK);
 }
 
 // Lam <- L(+-dz/2) Lam in place (the half-step tables, no screen).
 template <typename R>
 int half_step_lam(ssfm_ctx* c, bool forward) {
   PassArgs<R> a = base_args<R>(c);
-  a.inst = c->at<InstDev>(forward ? c->L.half_inst : c->L.back_inst);
   a.src = c->field(c->L.Lam);
   a.dst = c->field(c->L.Lam);
-  if (int r = run_pass<R>(c, ROW_FWD, a)) return r;
-  return run_pass<R>(c, COL_FWD, a);
+  a.flags = PASS_OP2;
+  if (int r = run_pass<R>(c, ROW_FWD, a, nullptr, forward ? T_HALF : T_BACK)) return r;
+  return run_pass<R>(c, COL_FWD, a, nullptr, forward ? T_HALF : T_BACK);
 }
 
 // Apply the pending screen in place (state becomes U_n).
@@ -907,40 +929,25 @@ Segments rec_segments(const ssfm_ctx* c, int64_t n) {
   return g;
 }
 
-// Location of s_i during a record of n steps (i in [0, n]).
-void* rec_slot(ssfm_ctx* c, const Segments& g, int64_t i, int64_t n) {
-  if (i == n) return c->field(c->L.S);
+// Where a record of n steps keeps s_i = V_i (0 <= i < n; null: not kept).
+void* rec_slot(ssfm_ctx* c, const Segments& g, int64_t i) {
   if (i % g.M == 0) return c->field(c->L.ckpt, i / g.M);
   const int64_t k = i / g.M;
   if (!g.recomputed(k)) return c->field(c->L.stack, g.region(k) * c->L.n_stack + i % g.M - 1);
-  return c->field(c->L.S);
+  return nullptr;
 }
 
-// Steps i0 <= i < i1 of an n-step record from step0 (the first range also
-// copies s_0 into checkpoint 0).  ts: timing events (single steps only).
+// Steps i0 <= i < i1 of an n-step record from step0, in place on the state;
+// the passes write the fields that are kept as they come by.
 template <typename R>
 int enqueue_record(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
-                   const ssfm_ctx::PassSample* ts) {
-  if (i0 == 0)
-    HIP_TRY(launch_copy<R>(c->field(c->L.S), c->field(c->L.ckpt, 0), c->L.field_elems,
-                           c->stream));
-  int64_t chunk_start = step0 + i0;
+                   const ssfm_ctx::PassSample* open, const ssfm_ctx::PassSample* end) {
   const Segments g = rec_segments(c, n);
-  for (int64_t i = i0; i < i1; ++i) {
-    const int slot = int((i - i0) % kDiagChunk);
-    double* part = c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.n_widx_cols;
-    const int64_t pend = rec_pending(c, step0, step0 + i);
-    // a step whose state is kept goes through the work buffer for large
-    // beams (see fwd_step); the others run in place
-    void* dsl = rec_slot(c, g, i + 1, n);
-    void* wk = (fresh_via_work(c) && dsl != c->field(c->L.S)) ? c->field(c->L.Wk) : nullptr;
-    if (int r = fwd_step<R>(c, rec_slot(c, g, i, n), dsl, pend, part, wk, nullptr, ts)) return r;
-    if (slot == kDiagChunk - 1 || i == i1 - 1) {
-      if (int r = diag_flush<R>(c, slot + 1, chunk_start)) return r;
-      chunk_start = step0 + i + 1;
-    }
-  }
-  return SSFM_OK;
+  void* S = c->field(c->L.S);
+  return enqueue_march<R>(
+      c, n, step0, i0, i1, MarchBuffers{S, S, S},
+      [&](int64_t i) { return rec_pending(c, step0, step0 + i); },
+      [&](int64_t i) { return rec_slot(c, g, i); }, true, c->stream, open, end);
 }
 
 template <typename R>
@@ -951,8 +958,9 @@ int do_record(ssfm_ctx* c, int64_t n) {
   if (int r = flush_pending<R>(c)) return r;
   const int64_t step0 = c->step;
   int r = run_forward(c, 1, step0, n, step0,
-                      [&](int64_t i0, int64_t i1, const ssfm_ctx::PassSample* ts) {
-                        return enqueue_record<R>(c, n, step0, i0, i1, ts);
+                      [&](int64_t i0, int64_t i1, const ssfm_ctx::PassSample* open,
+                          const ssfm_ctx::PassSample* end) {
+                        return enqueue_record<R>(c, n, step0, i0, i1, open, end);
                       });
   if (r) return r;
   c->step += n;
@@ -984,20 +992,52 @@ int enqueue_backward(ssfm_ctx* c) {
     if (i == 0) return c->field(c->L.ckpt, k);
     return slot(k, i - 1);
   };
+  // s_{kM+1} .. of segment k from its checkpoint: the work buffer, which
+  // nothing else uses during the backward sweep, holds the half-diffracted
+  // field
   auto recompute = [&](int64_t k, hipStream_t st) -> int {
     const int64_t s0 = k * M;
     const int64_t len = std::min<int64_t>(M, n - s0);
-    for (int64_t i = 0; i + 1 < len; ++i) {
-      const int64_t g = s0 + i;
-      const int64_t pend = rec_pending(c, step0, step0 + g);
-      // large beams through the work buffer, which nothing else uses during
-      // the backward sweep (the adjoint steps run in place on the cotangent)
-      void* wk = fresh_via_work(c) ? c->field(c->L.Wk) : nullptr;
-      if (int r = fwd_step<R>(c, sv(k, i), slot(k, i), pend, nullptr, wk, st)) return r;
-    }
-    return SSFM_OK;
+    if (len < 2) return SSFM_OK;
+    return enqueue_march<R>(
+        c, len - 1, step0 + s0, 0, len - 1,
+        MarchBuffers{sv(k, 0), c->field(c->L.Wk), slot(k, len - 2)},
+        [&](int64_t i) { return rec_pending(c, step0, step0 + s0 + i); },
+        [&](int64_t i) { return i > 0 ? slot(k, i - 1) : nullptr; }, false, st, nullptr,
+        nullptr);
   };
-  HIP_TRY(launch_fill_f64(c->at<double>(c->L.theta_acc), 8 * c->L.n_widx_rows, 0.0, c->stream));
+  // the pass along one axis that ends adjoint step s + 1 and begins step s
+  // (of the march's n; s = n opens the sweep), in place on the cotangent:
+  // the adjoints of step s's first factor, of the screen before it (with
+  // the stored V_s), and of the factor that precedes the screen
+  auto adj_pass = [&](int64_t s, const void* v_s, const ssfm_ctx::PassSample* ts) -> int {
+    PassArgs<R> a = base_args<R>(c);
+    a.src = c->field(c->L.Lam);
+    a.dst = c->field(c->L.Lam);
+    const bool col = (s == n) ? second_axis_col(step0 + n - 1) : first_axis_col(step0 + s);
+    a.part = c->at<double>(col ? c->L.theta_cols : c->L.theta_rows);
+    if (s < n) {
+      a.flags = PASS_OP1;
+      a.aux = v_s;
+      a.step = rec_pending(c, step0, step0 + s);
+      if (a.step >= 0) a.flags |= PASS_SCREEN;
+    }
+    if (s > 0) a.flags |= PASS_OP2;
+    return run_pass<R>(c, col ? COL_ADJ : ROW_ADJ, a, nullptr, T_PROP,
+                       ts ? ts->ev.data() : nullptr);
+  };
+  auto timed_adj_pass = [&](int64_t s, const void* v_s) -> int {
+    ssfm_ctx::PassSample ps;
+    const bool have = take_sample(c, &ps);
+    ps.col = (s == n) ? second_axis_col(step0 + n - 1) : first_axis_col(step0 + s);
+    const int r = adj_pass(s, v_s, have ? &ps : nullptr);
+    if (have) c->adj_samples.push_back(std::move(ps));
+    return r;
+  };
+  HIP_TRY(launch_fill_f64(c->at<double>(c->L.theta_rows), 8 * c->L.theta_row_parts, 0.0,
+                          c->stream));
+  HIP_TRY(launch_fill_f64(c->at<double>(c->L.theta_cols), 8 * c->L.theta_col_parts, 0.0,
+                          c->stream));
   // Strang: the seed is the cotangent of U_N = L(-dz/2) V_N, so the march's
   // adjoint starts from L(dz/2) of it (the adjoint of the read-out)
   if (c->strang)
@@ -1005,6 +1045,9 @@ int enqueue_backward(ssfm_ctx* c) {
   if (g.recomputed(n_seg - 1)) {
     if (int r = recompute(n_seg - 1, c->stream)) return r;
   }
+  const int64_t every = c->timing_every;
+  if (int r = (every > 0 && n == 1) ? timed_adj_pass(n, nullptr) : adj_pass(n, nullptr, nullptr))
+    return r;
   for (int64_t k = n_seg - 1; k >= 0; --k) {
     const bool rec_prev = k >= 1 && g.recomputed(k - 1);
     const bool overlap = rec_prev && c->overlap_recompute;
@@ -1016,14 +1059,15 @@ int enqueue_backward(ssfm_ctx* c) {
     }
     const int64_t s0 = k * M;
     const int64_t len = std::min<int64_t>(M, n - s0);
-    const int64_t every = c->timing_every;
     for (int64_t i = len - 1; i >= 0; --i) {
-      const int64_t g = s0 + i;
-      const int64_t pend = rec_pending(c, step0, step0 + g);
-      ssfm_ctx::PassSample ps;
-      const bool sample = every > 0 && k == 0 && g % every == every / 2 && take_sample(c, &ps);
-      if (int r = adj_step<R>(c, sv(k, i), pend, sample ? &ps : nullptr)) return r;
-      if (sample) c->adj_samples.push_back(std::move(ps));
+      const int64_t s = s0 + i;
+      // sampled steps of the first segment, and the pass after each (along
+      // the other axis)
+      const bool sampled = every > 0 && k == 0 && s % every == every / 2;
+      const bool after = every > 0 && k == 0 && i < len - 1 && (s + 1) % every == every / 2;
+      if (sampled) ++c->n_adj_samples;
+      if (int r = (sampled || after) ? timed_adj_pass(s, sv(k, i)) : adj_pass(s, sv(k, i), nullptr))
+        return r;
     }
     if (overlap) {
       HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_join, 0));
@@ -1034,8 +1078,11 @@ int enqueue_backward(ssfm_ctx* c) {
   // Strang: V_0 = L(dz/2) U_0, so dL/dU_0 = L(-dz/2) dL/dV_0
   if (c->strang)
     if (int r = half_step_lam<R>(c, false)) return r;
-  HIP_TRY(launch_reduce_rows(c->at<double>(c->L.theta_acc), 8, c->at<int32_t>(c->L.wbegin_row),
-                             int(c->desc.size()), c->at<double>(c->L.theta_out), c->stream));
+  const int32_t* begins = c->at<int32_t>(c->L.begins);
+  const size_t nb = c->desc.size() + 1;
+  HIP_TRY(launch_reduce_theta(c->at<double>(c->L.theta_rows), begins + P_ROW_ADJ * nb,
+                              c->at<double>(c->L.theta_cols), begins + P_COL_ADJ * nb,
+                              int(c->desc.size()), c->at<double>(c->L.theta_out), c->stream));
   return SSFM_OK;
 }
 
@@ -1045,6 +1092,7 @@ int do_backward(ssfm_ctx* c) {
   if (!c->seeded) return fail(SSFM_ESTATE, "backward needs a cotangent (set_cotangent/fluence_loss)");
   for (auto& e : c->adj_samples) c->free_samples.push_back(std::move(e));
   c->adj_samples.clear();
+  c->n_adj_samples = 0;
   // a beam without a cotangent contributes nothing to the loss: its
   // cotangent and its seed-step theta partials are zero (else the adjoint
   // would march whatever an earlier backward left there)
@@ -1188,116 +1236,99 @@ int do_gen_screens(ssfm_ctx* c) {
   return SSFM_OK;
 }
 
-// Upload host tables, beam constants and work lists.
+// Upload the twiddle tables of every group's plans and the first partials
+// of every beam (they follow the variants in use); *blob holds the host copy
+// until the caller synchronises.
+template <typename R>
+int upload_variants(ssfm_ctx* c, std::vector<std::vector<unsigned char>>* blobs) {
+  const bool fp64 = c->precision == SSFM_FP64;
+  std::vector<double> tmp;
+  for (const Group& g : c->groups) {
+    std::vector<unsigned char> blob;
+    for (int s = 0; s < P_SLOTS; ++s) {
+      PlanInfo pi;
+      if (!plan_info(s & 1, g.n, g.variant(s), fp64, &pi))
+        return fail(SSFM_EUNSUPPORTED, "no kernel plan for n=%d", g.n);
+      stage_twiddles(g.n, pi.radices, &tmp);
+      append_table<R>(&blob, tmp);
+    }
+    blobs->push_back(std::move(blob));
+    HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + g.tw * c->el, blobs->back().data(),
+                           blobs->back().size(), hipMemcpyHostToDevice, c->stream));
+  }
+  HIP_TRY(hipMemcpyAsync(c->ws + c->L.begins, c->begins.data(),
+                         sizeof(int32_t) * c->begins.size(), hipMemcpyHostToDevice, c->stream));
+  return SSFM_OK;
+}
+
+// Upload host tables and beam constants.
 template <typename R>
 int upload_plan(ssfm_ctx* c) {
   const int n_inst = int(c->desc.size());
-  // tables: twiddles per distinct n, then one propagator per beam
-  std::vector<unsigned char> blob;
-  std::map<int, int64_t> tw_off;
   std::vector<double> tmp;
   c->inst.assign(n_inst, InstDev{});
-  c->lens_off.assign(n_inst, 0);
-  c->half_off.assign(n_inst, 0);
-  c->back_off.assign(n_inst, 0);
-  c->fd_off.assign(n_inst, 0);
   if (c->spectrum.size() != size_t(n_inst)) c->spectrum.assign(n_inst, ssfm_ctx::Spectrum{});
   c->screen_steps.clear();
   int64_t foff = 0, soff = 0;
-  for (int b = 0; b < n_inst; ++b) {
-    const ssfm_instance_desc& d = c->desc[b];
-    InstDev& in = c->inst[b];
-    if (!tw_off.count(d.n)) {
-      tw_off[d.n] = int64_t(blob.size() / c->el);
-      twiddles(d.n, &tmp);
+  std::vector<std::vector<unsigned char>> blobs;
+  blobs.reserve(2 * c->groups.size());
+  if (int r = upload_variants<R>(c, &blobs)) return r;
+  for (const Group& g : c->groups) {
+    // the group's beams: T_COUNT tables each
+    std::vector<unsigned char> blob;
+    for (int b = g.beam0; b < g.beam0 + g.count; ++b) {
+      const ssfm_instance_desc& d = c->desc[b];
+      InstDev& in = c->inst[b];
+      in.n = d.n;
+      in.K = (d.mpa_order >= 2) ? d.mpa_order : 2;
+      in.terms = d.terms;
+      in.n_screens = (d.terms & SSFM_TURB) ? d.n_screens : 0;
+      in.off = foff;
+      foff += int64_t(d.n) * d.n;
+      in.screen_off = soff;
+      soff += int64_t(in.n_screens) * d.n * d.n;
+      propagator(d, &tmp);
       append_table<R>(&blob, tmp);
-    }
-    in.n = d.n;
-    in.K = (d.mpa_order >= 2) ? d.mpa_order : 2;
-    in.terms = d.terms;
-    in.n_screens = (d.terms & SSFM_TURB) ? d.n_screens : 0;
-    in.off = foff;
-    foff += int64_t(d.n) * d.n;
-    in.screen_off = soff;
-    soff += int64_t(in.n_screens) * d.n * d.n;
-    in.tw_off = tw_off[d.n];
-    in.prop_off = int64_t(blob.size() / c->el);
-    propagator(d, &tmp);
-    append_table<R>(&blob, tmp);
-    c->lens_off[b] = int64_t(blob.size() / c->el);
-    tmp.assign(2 * size_t(d.n), 0.0);
-    for (int m = 0; m < d.n; ++m) tmp[2 * m] = 1.0 / d.n;  // identity filter until set
-    append_table<R>(&blob, tmp);
-    for (int sgn = 1; sgn >= -1; sgn -= 2) {
-      ssfm_instance_desc h = d;
-      h.dz = sgn * 0.5 * d.dz;
-      (sgn > 0 ? c->half_off : c->back_off)[b] = int64_t(blob.size() / c->el);
-      propagator(h, &tmp);
+      tmp.assign(2 * size_t(d.n), 0.0);
+      for (int m = 0; m < d.n; ++m) tmp[2 * m] = 1.0 / d.n;  // identity filter until set
       append_table<R>(&blob, tmp);
-    }
-    {
+      for (int sgn = 1; sgn >= -1; sgn -= 2) {
+        ssfm_instance_desc h = d;
+        h.dz = sgn * 0.5 * d.dz;
+        propagator(h, &tmp);
+        append_table<R>(&blob, tmp);
+      }
       // 1 - (i dz/4k0) Lap_h has eigenvalue 1 + i (d[mx] + d[my]) on the DFT
       // mode (mx, my) of the periodic 5-point Laplacian
       const double k0 = 2.0 * M_PI / d.wavelength;
       const double dx = d.length / d.n;
       const double coef = d.dz / (k0 * dx * dx);
-      c->fd_off[b] = int64_t(blob.size() / c->el);
       tmp.assign(2 * size_t(d.n), 0.0);
       for (int m = 0; m < d.n; ++m) {
         const double sn = std::sin(M_PI * m / d.n);
         tmp[2 * m] = coef * sn * sn;
       }
       append_table<R>(&blob, tmp);
+      in.steps_off = int64_t(c->screen_steps.size());
+      for (int64_t s : screen_step_list(d)) c->screen_steps.push_back(s);
+      in.cK = k0 * d.n2 * d.i_ref * d.dz;
+      in.cM = (d.terms & SSFM_MPA) ? (in.K - 1) * d.beta_k * std::pow(d.i_ref, in.K - 1) * d.dz : 0.0;
+      in.inv2k1 = 1.0 / (2.0 * (in.K - 1));
+      in.cK_f = float(in.cK);
+      in.cM_f = float(in.cM);
+      in.inv2k1_f = float(in.inv2k1);
+      for (int p = 0; p < 8; ++p) in.theta[p] = in.theta_f[p] = 0.0;
     }
-    in.steps_off = int64_t(c->screen_steps.size());
-    for (int64_t s : screen_step_list(d)) c->screen_steps.push_back(s);
-    const double k0 = 2.0 * M_PI / d.wavelength;
-    in.cK = k0 * d.n2 * d.i_ref * d.dz;
-    in.cM = (d.terms & SSFM_MPA) ? (in.K - 1) * d.beta_k * std::pow(d.i_ref, in.K - 1) * d.dz : 0.0;
-    in.inv2k1 = 1.0 / (2.0 * (in.K - 1));
-    for (int p = 0; p < 8; ++p) in.theta[p] = 0.0;
+    blobs.push_back(std::move(blob));
+    HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + g.prop * c->el, blobs.back().data(),
+                           blobs.back().size(), hipMemcpyHostToDevice, c->stream));
   }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables, blob.data(), blob.size(), hipMemcpyHostToDevice,
-                         c->stream));
   HIP_TRY(hipMemcpyAsync(c->ws + c->L.inst, c->inst.data(), sizeof(InstDev) * n_inst,
-                         hipMemcpyHostToDevice, c->stream));
-  // the lens filter runs the pass kernels on a copy of the beam table whose
-  // propagator is the filter and whose screen is off
-  std::vector<InstDev> lens_inst = c->inst;
-  for (int b = 0; b < n_inst; ++b) {
-    lens_inst[b].prop_off = c->lens_off[b];
-    lens_inst[b].terms = 0;
-    lens_inst[b].n_screens = 0;
-  }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.lens_inst, lens_inst.data(), sizeof(InstDev) * n_inst,
-                         hipMemcpyHostToDevice, c->stream));
-  std::vector<InstDev> half_inst = lens_inst, back_inst = lens_inst;
-  for (int b = 0; b < n_inst; ++b) {
-    half_inst[b].prop_off = c->half_off[b];
-    back_inst[b].prop_off = c->back_off[b];
-  }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.half_inst, half_inst.data(), sizeof(InstDev) * n_inst,
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.back_inst, back_inst.data(), sizeof(InstDev) * n_inst,
-                         hipMemcpyHostToDevice, c->stream));
-  // finite differences: the beam's own screen constants, the solve table
-  std::vector<InstDev> fd_inst = c->inst;
-  for (int b = 0; b < n_inst; ++b) {
-    fd_inst[b].prop_off = c->fd_off[b];
-    fd_inst[b].n_screens = 0;
-  }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.fd_inst, fd_inst.data(), sizeof(InstDev) * n_inst,
                          hipMemcpyHostToDevice, c->stream));
   if (!c->screen_steps.empty())
     HIP_TRY(hipMemcpyAsync(c->ws + c->L.steps, c->screen_steps.data(),
                            sizeof(int64_t) * c->screen_steps.size(), hipMemcpyHostToDevice,
                            c->stream));
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.work, c->work.data(), sizeof(WorkItem) * c->work.size(),
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.wbegin_row, c->wbegin_row.data(),
-                         sizeof(int32_t) * c->wbegin_row.size(), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.wbegin_col, c->wbegin_col.data(),
-                         sizeof(int32_t) * c->wbegin_col.size(), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipMemsetAsync(c->field(c->L.S), 0, c->el * c->L.field_elems, c->stream));
   HIP_TRY(hipMemsetAsync(c->ws + c->L.diag, 0, sizeof(double) * 2 * c->L.diag_cap * n_inst,
                          c->stream));
@@ -1305,6 +1336,11 @@ int upload_plan(ssfm_ctx* c) {
   return SSFM_OK;
 }
 
+const Group& group_of(const ssfm_ctx* c, int b) {
+  for (const Group& g : c->groups)
+    if (b >= g.beam0 && b < g.beam0 + g.count) return g;
+  return c->groups.front();
+}
 
 // The lens filter exp(-l_dif k^2) of beam b (1/n per pass) into its filter
 // table; *blob holds the host copy until the caller synchronises.
@@ -1319,8 +1355,10 @@ int upload_lens_filter(ssfm_ctx* c, int b, double l_dif, std::vector<unsigned ch
     tab[2 * m] = std::exp(-l_dif * k * k) / d.n;
   }
   append_table<R>(blob, tab);
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + c->lens_off[b] * c->el, blob->data(),
-                         blob->size(), hipMemcpyHostToDevice, c->stream));
+  const Group& g = group_of(c, b);
+  const int64_t off = g.prop + (int64_t(b - g.beam0) * T_COUNT + T_LENS) * g.n;
+  HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + off * c->el, blob->data(), blob->size(),
+                         hipMemcpyHostToDevice, c->stream));
   return SSFM_OK;
 }
 
@@ -1329,12 +1367,11 @@ int upload_lens_filter(ssfm_ctx* c, int b, double l_dif, std::vector<unsigned ch
 template <typename R>
 int lens_filter_passes(ssfm_ctx* c) {
   PassArgs<R> a = base_args<R>(c);
-  a.inst = c->at<InstDev>(c->L.lens_inst);
   a.src = c->field(c->L.Wk);
   a.dst = c->field(c->L.Wk);
-  if (int r = run_pass<R>(c, ROW_FWD, a)) return r;
-  a.part = nullptr;
-  return run_pass<R>(c, COL_FWD, a);
+  a.flags = PASS_OP2;
+  if (int r = run_pass<R>(c, ROW_FWD, a, nullptr, T_LENS)) return r;
+  return run_pass<R>(c, COL_FWD, a, nullptr, T_LENS);
 }
 
 LensDev lens_dev(const ssfm_instance_desc& d, const ssfm_lens& l) {
@@ -1486,6 +1523,35 @@ int plan_lines(bool column, int n, int v) {
   return pi.lines;
 }
 
+// Switch size n to other variants: the partials' offsets and the twiddle
+// tables follow; the layout's arrays hold any variant, so their offsets
+// stay.
+int apply_variants(ssfm_ctx* c, int n, const std::array<int, P_SLOTS>& var) {
+  VariantMap vm;
+  for (auto& g : c->groups) {
+    std::array<int, P_SLOTS> v;
+    std::copy(g.var, g.var + P_SLOTS, v.begin());
+    vm[g.n] = (g.n == n) ? var : v;
+  }
+  Layout L2;
+  std::vector<Group> groups;
+  std::vector<int32_t> begins;
+  if (int r = plan_layout(c->desc.data(), int(c->desc.size()), c->precision, c->max_steps,
+                          c->ckpt_every, c->stored_segments, &vm, &groups, &begins, &L2))
+    return r;
+  if (L2.total != c->L.total) return fail(SSFM_EUNSUPPORTED, "variant changes the workspace layout");
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  c->groups = groups;
+  c->begins = begins;
+  c->L = L2;
+  clear_graphs(c);
+  std::vector<std::vector<unsigned char>> blobs;
+  blobs.reserve(groups.size());
+  if (int r = SSFM_DISPATCH(c, upload_variants, c, &blobs)) return r;
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  return SSFM_OK;
+}
+
 // Adjoint-pass variants of size n (-1: follow the forward variants).
 int do_select_adjoint(ssfm_ctx* c, int32_t n, int32_t rv, int32_t cv) {
   const bool fp64 = c->precision == SSFM_FP64;
@@ -1501,23 +1567,19 @@ int do_select_adjoint(ssfm_ctx* c, int32_t n, int32_t rv, int32_t cv) {
   if (rv >= 0) {
     if (!plan_info(false, n, rv, fp64, &pi))
       return fail(SSFM_EUNSUPPORTED, "row variant %d of n=%d is not built at this precision", rv, n);
-    if (pi.lines != plan_lines(false, n, grp->row_var))
+    if (pi.lines != grp->lines[P_ROW])
       return fail(SSFM_EINVAL, "row variant %d has %d lines per workgroup, the forward one %d", rv,
-                  pi.lines, plan_lines(false, n, grp->row_var));
+                  pi.lines, grp->lines[P_ROW]);
   }
   if (cv >= 0) {
     if (!plan_info(true, n, cv, fp64, &pi))
       return fail(SSFM_EUNSUPPORTED, "column variant %d of n=%d is not built at this precision",
                   cv, n);
-    if (pi.lines != plan_lines(true, n, grp->col_var))
+    if (pi.lines != grp->lines[P_COL])
       return fail(SSFM_EINVAL, "column variant %d has %d columns per workgroup, the forward one %d",
-                  cv, pi.lines, plan_lines(true, n, grp->col_var));
+                  cv, pi.lines, grp->lines[P_COL]);
   }
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  grp->row_adj_var = rv;
-  grp->col_adj_var = cv;
-  clear_graphs(c);
-  return SSFM_OK;
+  return apply_variants(c, n, {grp->var[P_ROW], grp->var[P_COL], rv, cv});
 }
 
 int do_select(ssfm_ctx* c, int32_t n, int32_t rv, int32_t cv) {
@@ -1525,52 +1587,16 @@ int do_select(ssfm_ctx* c, int32_t n, int32_t rv, int32_t cv) {
   if (rc == 0) return fail(SSFM_EUNSUPPORTED, "grid size %d not supported", n);
   if (rv < 0 || rv >= rc || cv < 0 || cv >= cc)
     return fail(SSFM_EINVAL, "variant (%d, %d) out of range [0, %d) x [0, %d)", rv, cv, rc, cc);
-  bool found = false;
-  VariantMap vm;
-  for (auto& g : c->groups) {
-    vm[g.n] = {g.row_var, g.col_var};
-    if (g.n == n) found = true;
-  }
-  if (!found) return fail(SSFM_EINVAL, "no instance with n=%d in this context", n);
-  vm[n] = {rv, cv};
-  // rebuild work lists; the layout's partial arrays are already sized for
-  // the variant with the most work items, so offsets stay valid
-  Layout L2;
-  std::vector<Group> groups;
-  std::vector<WorkItem> work;
-  std::vector<int32_t> wr, wc;
-  if (int r = plan_layout(c->desc.data(), int(c->desc.size()), c->precision, c->max_steps,
-                          c->ckpt_every, c->stored_segments, &vm, &groups, &work, &wr, &wc, &L2))
-    return r;
-  if (L2.total != c->L.total) return fail(SSFM_EUNSUPPORTED, "variant changes the workspace layout");
-  // keep each size's adjoint variants while their lines per workgroup still
-  // match the forward ones
-  for (auto& g : groups) {
-    for (const auto& o : c->groups) {
-      if (o.n != g.n) continue;
-      g.row_adj_var = o.row_adj_var;
-      g.col_adj_var = o.col_adj_var;
-    }
-    if (g.row_adj_var >= 0 && plan_lines(false, g.n, g.row_adj_var) != plan_lines(false, g.n, g.row_var))
-      g.row_adj_var = -1;
-    if (g.col_adj_var >= 0 && plan_lines(true, g.n, g.col_adj_var) != plan_lines(true, g.n, g.col_var))
-      g.col_adj_var = -1;
-  }
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  c->groups = groups;
-  c->work = work;
-  c->wbegin_row = wr;
-  c->wbegin_col = wc;
-  c->L = L2;
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.work, c->work.data(), sizeof(WorkItem) * c->work.size(),
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.wbegin_row, c->wbegin_row.data(),
-                         sizeof(int32_t) * c->wbegin_row.size(), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.wbegin_col, c->wbegin_col.data(),
-                         sizeof(int32_t) * c->wbegin_col.size(), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  clear_graphs(c);
-  return SSFM_OK;
+  const Group* grp = nullptr;
+  for (auto& g : c->groups)
+    if (g.n == n) grp = &g;
+  if (!grp) return fail(SSFM_EINVAL, "no instance with n=%d in this context", n);
+  // keep the adjoint variants while their lines per workgroup still match
+  // the forward ones
+  int ra = grp->var[P_ROW_ADJ], ca = grp->var[P_COL_ADJ];
+  if (ra >= 0 && plan_lines(false, n, ra) != plan_lines(false, n, rv)) ra = -1;
+  if (ca >= 0 && plan_lines(true, n, ca) != plan_lines(true, n, cv)) ca = -1;
+  return apply_variants(c, n, {rv, cv, ra, ca});
 }
 
 }  // namespace
@@ -1604,8 +1630,8 @@ int ssfm_workspace_bytes(const ssfm_instance_desc* desc, int32_t n_inst, int32_t
   if (max_steps < 0 || ckpt_every < 1 || stored_segments < 0)
     return fail(SSFM_EINVAL, "need max_steps >= 0, ckpt_every >= 1, stored_segments >= 0");
   Layout L;
-  if (int r = plan_layout(desc, n_inst, precision, max_steps, ckpt_every, stored_segments,
-                          nullptr, nullptr, nullptr, nullptr, nullptr, &L))
+  if (int r = plan_layout(desc, n_inst, precision, max_steps, ckpt_every, stored_segments, nullptr,
+                          nullptr, nullptr, &L))
     return r;
   *bytes = L.total;
   return SSFM_OK;
@@ -1621,7 +1647,7 @@ int ssfm_checkpoint_plan(const ssfm_instance_desc* desc, int32_t n_inst, int32_t
   Layout L;
   auto bytes_of = [&](int64_t m, int64_t k, size_t* out) {
     int r = plan_layout(desc, n_inst, precision, n_steps, int32_t(m), int32_t(k), nullptr,
-                        nullptr, nullptr, nullptr, nullptr, &L);
+                        nullptr, nullptr, &L);
     *out = L.total;
     return r;
   };
@@ -1704,15 +1730,19 @@ int ssfm_create(const ssfm_instance_desc* desc, int32_t n_inst, int32_t precisio
   std::unique_ptr<ssfm_ctx> c(new ssfm_ctx);
   c->precision = precision;
   c->el = precision == SSFM_FP64 ? 16 : 8;
-  c->desc.assign(desc, desc + n_inst);
+  c->caller = group_order(desc, n_inst);
+  c->slot.assign(n_inst, 0);
+  for (int b = 0; b < n_inst; ++b) {
+    c->slot[c->caller[b]] = b;
+    c->desc.push_back(desc[c->caller[b]]);
+  }
   c->seeded_beam.assign(n_inst, 0);
   c->max_steps = max_steps;
   c->ckpt_every = ckpt_every;
   c->stored_segments = stored_segments;
   c->stream = static_cast<hipStream_t>(stream);
-  if (int r = plan_layout(desc, n_inst, precision, max_steps, ckpt_every, stored_segments,
-                          nullptr, &c->groups,
-                          &c->work, &c->wbegin_row, &c->wbegin_col, &c->L))
+  if (int r = plan_layout(c->desc.data(), n_inst, precision, max_steps, ckpt_every,
+                          stored_segments, nullptr, &c->groups, &c->begins, &c->L))
     return r;
   if (!workspace) return fail(SSFM_EWORKSPACE, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign)
@@ -1756,6 +1786,7 @@ int ssfm_set_theta(ssfm_ctx* c, int32_t inst, const double* theta) {
   for (int p = 0; p < 8; ++p) {
     if (!std::isfinite(theta[p])) return fail(SSFM_EINVAL, "theta[%d] not finite", p);
     c->inst[inst].theta[p] = theta[p];
+    c->inst[inst].theta_f[p] = float(theta[p]);
   }
   // a recorded march (its stored fields, the screen its adjoint applies)
   // belongs to the old parameters
@@ -1831,7 +1862,7 @@ int ssfm_set_splitting(ssfm_ctx* c, int32_t scheme) {
       if ((d.terms & SSFM_ANSATZ) || ((d.terms & SSFM_TURB) && d.n_screens > 0))
         return fail(SSFM_EUNSUPPORTED,
                     "the finite-difference scheme covers the Kerr, plasma and multiphoton "
-                    "terms only (instance %zu has the ansatz or turbulence screens)", b);
+                    "terms only (instance %d has the ansatz or turbulence screens)", c->caller[b]);
     }
   }
   HIP_TRY(hipStreamSynchronize(c->stream));
@@ -2053,6 +2084,7 @@ int ssfm_set_recompute_overlap(ssfm_ctx* c, int32_t enable) {
 
 int ssfm_set_precise_math(ssfm_ctx* c, int32_t enable) {
   if (int r = check_ctx(c)) return r;
+  c->precise = enable != 0;
   for (auto& in : c->inst) {
     if (enable) in.terms |= (1u << 8);
     else in.terms &= ~(1u << 8);
@@ -2106,18 +2138,19 @@ int ssfm_time_adjoint_passes(ssfm_ctx* c, int32_t reps, double* ms_col, double* 
   for (auto& x : ev.e) HIP_TRY(hipEventCreate(&x));
   // column pass: cotangent -> work buffer; row pass: work buffer in place,
   // the state standing in for the stored pre-screen field, at a step with
-  // no turbulence screen (its ansatz partials go to the accumulators every
+  // no turbulence screen (the ansatz partials go to the accumulators every
   // backward clears first).  Fields, cotangent and gradients are unchanged.
   auto body = [&]<typename R>(R*) -> int {
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.Lam);
     a.dst = c->field(c->L.Wk);
-    PassArgs<R> b = base_args<R>(c);
+    a.aux = c->field(c->L.S);
+    a.step = int64_t(1) << 60;
+    a.flags = PASS_OP1 | PASS_SCREEN | PASS_OP2;
+    PassArgs<R> b = a;
+    a.part = c->at<double>(c->L.theta_cols);
     b.src = c->field(c->L.Wk);
-    b.dst = c->field(c->L.Wk);
-    b.aux = c->field(c->L.S);
-    b.step = int64_t(1) << 60;
-    b.part = c->at<double>(c->L.theta_acc);
+    b.part = c->at<double>(c->L.theta_rows);
     HIP_TRY(hipEventRecord(ev.e[0], c->stream));
     for (int i = 0; i < reps; ++i)
       if (int q = run_pass<R>(c, COL_ADJ, a)) return q;
@@ -2157,11 +2190,11 @@ int ssfm_time_passes(ssfm_ctx* c, int32_t reps, double* ms_row, double* ms_col,
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.S);
     a.dst = c->field(c->L.Wk);
-    a.step = c->pending ? c->step - 1 : -1;
-    PassArgs<R> b = base_args<R>(c);
+    a.step = int64_t(1) << 60;  // a step with no turbulence screen
+    a.flags = PASS_OP1 | PASS_SCREEN | PASS_OP2;
+    a.part = c->at<double>(c->L.diag_part);
+    PassArgs<R> b = a;
     b.src = c->field(c->L.Wk);
-    b.dst = c->field(c->L.Wk);
-    b.part = c->at<double>(c->L.diag_part);
     HIP_TRY(hipEventRecord(e0, c->stream));
     for (int i = 0; i < reps; ++i)
       if (int q = run_pass<R>(c, ROW_FWD, a)) return q;
@@ -2399,54 +2432,53 @@ int ssfm_set_pass_timing(ssfm_ctx* c, int32_t every) {
   if (every == c->timing_every) return SSFM_OK;
   HIP_TRY(hipStreamSynchronize(c->stream));
   clear_graphs(c);  // the step graphs are cut at the sampled steps
-  for (auto& e : c->samples) c->free_samples.push_back(e);
+  for (auto& e : c->samples) c->free_samples.push_back(std::move(e));
   c->samples.clear();
+  c->n_samples = 0;
   c->timing_every = every;
   return SSFM_OK;
 }
 
 namespace {
-// Mean span of pass 0 and pass 1 over samples: for each sample the earliest
-// start to the latest stop over its size groups (group 0 launches first;
-// the others run concurrently).
-int mean_spans(ssfm_ctx* c, const std::vector<ssfm_ctx::PassSample>& samples, double* t0,
-               double* t1, int32_t* count) {
+// Mean span of the sampled row passes and column passes: for each sample the
+// earliest start to the latest stop over its size groups (group 0 launches
+// first; the others run concurrently).
+int mean_spans(ssfm_ctx* c, const std::vector<ssfm_ctx::PassSample>& samples, double* row,
+               double* col) {
   double acc[2] = {0.0, 0.0};
-  int32_t n = 0;
+  int n[2] = {0, 0};
   if (!samples.empty()) {
     HIP_TRY(hipStreamSynchronize(c->stream));
     const size_t ng = c->groups.size();
     for (const auto& e : samples) {
-      for (int p = 0; p < 2; ++p) {
-        const hipEvent_t ref = e.ev[2 * (p * ng)];
-        double lo = 0.0, hi = 0.0;
-        for (size_t g = 0; g < ng; ++g) {
-          float a = 0.f, b = 0.f;
-          HIP_TRY(hipEventElapsedTime(&a, ref, e.ev[2 * (p * ng + g)]));
-          HIP_TRY(hipEventElapsedTime(&b, ref, e.ev[2 * (p * ng + g) + 1]));
-          lo = std::min(lo, double(a));
-          hi = std::max(hi, double(b));
-        }
-        acc[p] += hi - lo;
+      double lo = 0.0, hi = 0.0;
+      for (size_t g = 0; g < ng; ++g) {
+        float a = 0.f, b = 0.f;
+        HIP_TRY(hipEventElapsedTime(&a, e.ev[0], e.ev[2 * g]));
+        HIP_TRY(hipEventElapsedTime(&b, e.ev[0], e.ev[2 * g + 1]));
+        lo = std::min(lo, double(a));
+        hi = std::max(hi, double(b));
       }
-      ++n;
+      acc[e.col] += hi - lo;
+      ++n[e.col];
     }
   }
-  if (t0) *t0 = n ? acc[0] / n : 0.0;
-  if (t1) *t1 = n ? acc[1] / n : 0.0;
-  if (count) *count = n;
+  if (row) *row = n[0] ? acc[0] / n[0] : 0.0;
+  if (col) *col = n[1] ? acc[1] / n[1] : 0.0;
   return SSFM_OK;
 }
 }  // namespace
 
 int ssfm_pass_times(ssfm_ctx* c, double* ms_row, double* ms_col, int32_t* n_samples) {
   if (int r = check_ctx(c)) return r;
-  return mean_spans(c, c->samples, ms_row, ms_col, n_samples);
+  if (n_samples) *n_samples = c->n_samples;
+  return mean_spans(c, c->samples, ms_row, ms_col);
 }
 
 int ssfm_adjoint_pass_times(ssfm_ctx* c, double* ms_col, double* ms_row, int32_t* n_samples) {
   if (int r = check_ctx(c)) return r;
-  return mean_spans(c, c->adj_samples, ms_col, ms_row, n_samples);
+  if (n_samples) *n_samples = c->n_adj_samples;
+  return mean_spans(c, c->adj_samples, ms_row, ms_col);
 }
 
 int ssfm_synchronize(ssfm_ctx* c) {

@@ -8,9 +8,9 @@ On the 1024 x 1024 multifilamentation beam it selects each forward row-pass
 variant in turn (column variant 0), then each column-pass variant (row
 variant 0), and runs a recorded forward march of ``--steps`` steps with
 graphs off, so that a counter profiler sees one plain dispatch per pass.
-Each recorded march starts with one copy of the whole field into the first
-checkpoint slot: a plain copy kernel of known size (n^2 complex elements
-read and written) against which byte counters can be scaled.
+Each recorded march is preceded by a block mean of an n x n float64 array
+with blocks of one: a plain copy of known size (8 n^2 bytes read and
+written) against which byte counters can be scaled.
 
 Variants appear in index order: the k-th distinct forward row-pass kernel
 name in dispatch order is row variant k, likewise for columns.  Last comes
@@ -31,7 +31,7 @@ import sys
 # The sources the row and column pass kernels are compiled from.
 PASS_SOURCES = ("fft_core.hpp", "plans.hpp", "screen.hpp", "internal.hpp", "kernels.hpp",
                 "pass_kernels.hpp", "pass_row_f32.hip", "pass_row_f64.hip",
-                "pass_col_f32.hip", "pass_col_f64.hip", "pass_col_hx.hpp",
+                "pass_col_f32.hip", "pass_col_f64.hip",
                 "pass_col_hx_f32.hip")
 
 
@@ -50,27 +50,17 @@ def kernel_source_hash() -> str:
     return h.hexdigest()
 
 
-# pass kinds by kernel: (kernel template name, kind number) -> key
-KIND_KEYS = {("k_row", 0): "row_fwd", ("k_col", 3): "col_fwd", ("k_col", 4): "col_adj",
-             ("k_row", 1): "row_adj"}
-
-
 def kernel_kind(name: str):
-    """'row_fwd' / 'col_fwd' / 'col_adj' / 'row_adj' for a pass kernel's
-    name (its last template argument is the pass kind), 'copy' for the
-    calibration copy, None otherwise."""
+    """'row_fwd' / 'col_fwd' / 'col_adj' / 'row_adj' for a march pass
+    kernel's name (its last three template arguments: column pass, adjoint,
+    library sine), 'copy' for the calibration copy, None otherwise."""
     base = name.split("<")[0].split("::")[-1].strip()
-    if base == "k_copy":
+    if base == "k_block_mean":
         return "copy"
-    if base in ("k_row_pipe", "k_col_pipe"):  # persistent forms of the same passes
-        base = base[:-len("_pipe")]
-    if base == "k_col_hx":  # column passes exchanging through half the tile
-        base = "k_col"
-    if base in ("k_row", "k_col"):
-        tail = name.rsplit(",", 1)[-1]
-        digits = "".join(ch for ch in tail if ch.isdigit())
-        if digits:
-            return KIND_KEYS.get((base, int(digits)))
+    if base == "k_march":
+        args = name.split("(")[0].rstrip("> ").split(",")
+        col, adj = (a.strip() in ("true", "1") for a in args[-3:-1])
+        return ("col" if col else "row") + ("_adj" if adj else "_fwd")
     return None
 
 
@@ -124,9 +114,8 @@ def run_march(args) -> int:
     """The large-aperture 4096^2 beam with all its screen terms and
     turbulence: a recorded forward march of --steps steps, the fluence
     loss and the adjoint, graphs off, with the given tile variants, so that
-    a counter profiler sees one plain dispatch per pass of every kind.  The
-    record starts with one copy of the field (n^2 complex64 read and
-    written), the calibration kernel."""
+    a counter profiler sees one plain dispatch per pass of every kind,
+    after the calibration copy (8 n^2 bytes read and written)."""
     import torch
 
     import workloads as W
@@ -141,6 +130,7 @@ def run_march(args) -> int:
     p.set_theta(0, inst.theta)
     u0 = torch.from_numpy(W.initial_field(inst)).cuda()
     tgt = torch.from_numpy(W.synthetic_target(inst, 5)).cuda()
+    p.block_mean(tgt, 1)
     p.set_field(0, u0)
     p.forward_record(args.steps)
     p.fluence_loss(0, tgt)
@@ -177,6 +167,8 @@ def main(argv=None) -> int:
         return run_march(args)
     import dataclasses
 
+    import torch
+
     import workloads as W
     from .march import Propagator, desc_of, plan_variants
 
@@ -191,11 +183,13 @@ def main(argv=None) -> int:
                    ckpt_every=args.steps)
     p.use_graphs(False)
     u0 = W.initial_field(inst)
+    calibration = torch.zeros((n, n), dtype=torch.float64, device="cuda")
     n_row, n_col = plan_variants(n, args.precision)
     order = []
     for kind, count in (("row", n_row), ("col", n_col)):
         for v in range(count):
             p.select_plan(n, v if kind == "row" else 0, v if kind == "col" else 0)
+            p.block_mean(calibration, 1)
             p.set_field(0, u0)
             p.forward_record(args.steps)
             p.synchronize()
@@ -214,7 +208,7 @@ def main(argv=None) -> int:
     p.close()
     info = {"grid": n, "precision": args.precision, "steps": args.steps,
             "n_row": n_row, "n_col": n_col, "order": order, "fd_iters": FD_ITERS,
-            "copy_bytes": n * n * (8 if args.precision == 32 else 16),
+            "copy_bytes": 8 * n * n,
             "source_hash": kernel_source_hash()}
     if args.out:
         with open(args.out, "w") as f:
