@@ -25,13 +25,45 @@
 
 #include <hip/hip_runtime.h>
 
-#include <utility>
-
 namespace ssfm {
 
 template <typename R>
 struct cx {
   R re, im;
+};
+
+// A stretch of memory read and written through a buffer descriptor: element
+// i + c, i per thread, c the same for all.  A thread's elements lie at
+// compile-time distances; the instruction takes those as a scalar offset, so
+// they cost no vector instruction (flat addresses took one or two an access,
+// 8 to 10 % of a pass).
+template <typename T>
+struct Buf {
+  typedef uint32_t U2 __attribute__((ext_vector_type(2)));
+  typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+  static constexpr int S = int(sizeof(T));
+  static_assert(S == 4 || S == 8 || S == 16, "dword, two or four dwords");
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit Buf(const T* p)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, -1, 0x00020000)) {}
+  __device__ __forceinline__ T get(uint32_t i, uint32_t c) const {
+    const uint32_t v = i * uint32_t(S), k = c * uint32_t(S);
+    if constexpr (S == 4)
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, int(v), int(k), 0));
+    else if constexpr (S == 8)
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, int(v), int(k), 0));
+    else
+      return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, int(v), int(k), 0));
+  }
+  __device__ __forceinline__ void put(uint32_t i, uint32_t c, T x) const {
+    const uint32_t v = i * uint32_t(S), k = c * uint32_t(S);
+    if constexpr (S == 4)
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, int(v), int(k), 0);
+    else if constexpr (S == 8)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, x), r, int(v), int(k), 0);
+    else
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, x), r, int(v), int(k), 0);
+  }
 };
 
 template <typename R>
@@ -42,22 +74,22 @@ template <typename R>
 __device__ __forceinline__ cx<R> operator-(cx<R> a, cx<R> b) {
   return {a.re - b.re, a.im - b.im};
 }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// Products with the fused operation spelled out: the compiler is left no
+// choice of which product to round, so every kernel forms the same bits.
 template <typename R>
 __device__ __forceinline__ cx<R> cmul(cx<R> a, cx<R> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fma_(a.re, b.re, -(a.im * b.im)), fma_(a.re, b.im, a.im * b.re)};
 }
 // a * conj(b)
 template <typename R>
 __device__ __forceinline__ cx<R> cmulc(cx<R> a, cx<R> b) {
-  return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
+  return {fma_(a.re, b.re, a.im * b.im), fma_(a.im, b.re, -(a.re * b.im))};
 }
 template <typename R>
 __device__ __forceinline__ cx<R> conjg(cx<R> a) {
   return {a.re, -a.im};
-}
-template <typename R>
-__device__ __forceinline__ cx<R> scale(cx<R> a, R s) {
-  return {a.re * s, a.im * s};
 }
 // multiply by (dir * i): dir = -1 gives -i, dir = +1 gives +i
 template <int DIR, typename R>
@@ -68,66 +100,86 @@ __device__ __forceinline__ cx<R> rot_q(cx<R> a) {
     return {-a.im, a.re};
   }
 }
-// multiply by exp(dir i pi/4) = (1 + dir i)/sqrt(2)
-template <int DIR, typename R>
-__device__ __forceinline__ cx<R> rot_8(cx<R> a) {
-  const R h = R(0.70710678118654752440);
-  if constexpr (DIR < 0) {
-    return {(a.re + a.im) * h, (a.im - a.re) * h};
-  } else {
-    return {(a.re - a.im) * h, (a.im + a.re) * h};
-  }
+// a + s b
+template <typename R>
+__device__ __forceinline__ cx<R> axpy(cx<R> a, R s, cx<R> b) {
+  return {fma_(s, b.re, a.re), fma_(s, b.im, a.im)};
 }
-// multiply by exp(dir 3 i pi/4) = (-1 + dir i)/sqrt(2)
+// a + b w (DIR < 0) or a + b conj(w): 4 fused operations
 template <int DIR, typename R>
-__device__ __forceinline__ cx<R> rot_38(cx<R> a) {
-  const R h = R(0.70710678118654752440);
-  if constexpr (DIR < 0) {
-    return {(a.im - a.re) * h, -(a.re + a.im) * h};
-  } else {
-    return {-(a.re + a.im) * h, (a.re - a.im) * h};
-  }
+__device__ __forceinline__ cx<R> cfma(cx<R> a, cx<R> b, cx<R> w) {
+  if constexpr (DIR < 0)
+    return {fma_(-b.im, w.im, fma_(b.re, w.re, a.re)), fma_(b.re, w.im, fma_(b.im, w.re, a.im))};
+  else
+    return {fma_(b.im, w.im, fma_(b.re, w.re, a.re)), fma_(-b.re, w.im, fma_(b.im, w.re, a.im))};
 }
-// multiply by exp(dir 2 pi i e / 16) for e = 1, 3, 9
-template <int DIR, int EXP, typename R>
-__device__ __forceinline__ cx<R> rot_16(cx<R> a) {
-  constexpr double c1 = 0.92387953251128675613;  // cos(pi/8)
-  constexpr double s1 = 0.38268343236508977173;  // sin(pi/8)
-  double cr, ci;
-  if constexpr (EXP == 1) {
-    cr = c1;
-    ci = DIR * s1;
-  } else if constexpr (EXP == 3) {
-    cr = s1;
-    ci = DIR * c1;
-  } else {  // EXP == 9
-    cr = -c1;
-    ci = -DIR * s1;
-  }
-  return cmul(a, cx<R>{R(cr), R(ci)});
+// b w or b conj(w)
+template <int DIR, typename R>
+__device__ __forceinline__ cx<R> twist(cx<R> b, cx<R> w) {
+  return (DIR > 0) ? cmulc(b, w) : cmul(b, w);
+}
+// 2 a - b
+template <typename R>
+__device__ __forceinline__ cx<R> other(cx<R> a, cx<R> b) {
+  return {fma_(R(2), a.re, -b.re), fma_(R(2), a.im, -b.im)};
+}
+// sqrt(2) a exp(dir i pi/4) and sqrt(2) a exp(3 dir i pi/4): the scale
+// 1/sqrt(2) is left to the fused operations that add the result
+template <int DIR, typename R>
+__device__ __forceinline__ cx<R> rot_8s(cx<R> a) {
+  if constexpr (DIR < 0)
+    return {a.re + a.im, a.im - a.re};
+  else
+    return {a.re - a.im, a.im + a.re};
+}
+template <int DIR, typename R>
+__device__ __forceinline__ cx<R> rot_38s(cx<R> a) {
+  if constexpr (DIR < 0)
+    return {a.im - a.re, -(a.re + a.im)};
+  else
+    return {-(a.re + a.im), a.re - a.im};
 }
 
 // ---------------------------------------------------------------- DFTs
-// In-place DFT of R points in natural order: y_k = sum_n x_n w^(nk),
-// w = exp(dir 2 pi i / R).
+// In-place DFT of RAD points in natural order: y_k = sum_n x_n w^(nk),
+// w = exp(dir 2 pi i / RAD).  The TW forms take x_n w_n instead of x_n, with
+// the stage twiddles tw[n - 1] = w_n (n > 0; conjugated for DIR > 0).
+//
+// Operation counts decide the large grids (their passes keep the vector
+// units 85-90 % busy), so everything is arranged for fused multiply-adds:
+// a twiddled butterfly a + w b, a - w b is formed as t = a + w b (4 fused
+// operations) and 2 a - t (2), instead of 4 for the product and 4 for the
+// sums; a rotation by a constant leaves its scale to the fused operations
+// that add it.  Per radix-16 stage 188 operations instead of 220, radix 8
+// 72 instead of 84, radix 4 24 instead of 28, with no more roundings on the
+// way to any output.
 
-template <int DIR, typename R>
-__device__ __forceinline__ void dft2(cx<R>* v) {
-  cx<R> a = v[0];
-  v[0] = a + v[1];
-  v[1] = a - v[1];
+// s a, rounded by itself
+template <typename R>
+__device__ __forceinline__ cx<R> scaled(cx<R> a, R s) {
+#pragma clang fp contract(off)
+  return {a.re * s, a.im * s};
 }
-
-template <int DIR, typename R>
-__device__ __forceinline__ void dft3(cx<R>* v) {
-  const R h = R(0.86602540378443864676);  // sqrt(3)/2
-  cx<R> t = v[1] + v[2];
-  cx<R> u = v[1] - v[2];
-  cx<R> m = {v[0].re - R(0.5) * t.re, v[0].im - R(0.5) * t.im};
-  cx<R> w = scale(rot_q<DIR>(u), h);
-  v[0] = v[0] + t;
-  v[1] = m + w;
-  v[2] = m - w;
+// Half of a radix-4 butterfly's rest: from t0, t1 = x0 +- x2 and s u, s w
+// with u = x1 + x3, w = rot(x1 - x3) over the scale s.  complex128 rounds
+// the products by themselves: the march against its oracle is closer so
+// (100 steps of a 256^2 gradient: 4.8e-13, fused 5.7e-13).
+template <typename R>
+__device__ __forceinline__ void dft4_tail(cx<R> t0, cx<R> t1, cx<R> u, cx<R> w, R s, cx<R>& a0,
+                                          cx<R>& a1, cx<R>& a2, cx<R>& a3) {
+  if constexpr (sizeof(R) == 8) {
+    u = scaled(u, s);
+    w = scaled(w, s);
+    a0 = t0 + u;
+    a2 = t0 - u;
+    a1 = t1 + w;
+    a3 = t1 - w;
+  } else {
+    a0 = axpy(t0, s, u);
+    a2 = axpy(t0, -s, u);
+    a1 = axpy(t1, s, w);
+    a3 = axpy(t1, -s, w);
+  }
 }
 
 template <int DIR, typename R>
@@ -141,67 +193,138 @@ __device__ __forceinline__ void dft4_(cx<R>& a0, cx<R>& a1, cx<R>& a2,
   a3 = t1 - t3;
 }
 
+// radix 4 of x0, a1 w1, a2 w2, a3 w3 (x0 twiddled by the caller)
 template <int DIR, typename R>
-__device__ __forceinline__ void dft4(cx<R>* v) {
-  dft4_<DIR>(v[0], v[1], v[2], v[3]);
+__device__ __forceinline__ void dft4_tw_(cx<R>& a0, cx<R>& a1, cx<R>& a2, cx<R>& a3, cx<R> w1,
+                                         cx<R> w2, cx<R> w3) {
+  const cx<R> t0 = cfma<DIR>(a0, a2, w2), t1 = other(a0, t0);
+  const cx<R> x1 = twist<DIR>(a1, w1);
+  const cx<R> t2 = cfma<DIR>(x1, a3, w3), t3 = rot_q<DIR>(other(x1, t2));
+  a0 = t0 + t2;
+  a2 = t0 - t2;
+  a1 = t1 + t3;
+  a3 = t1 - t3;
+}
+
+template <int DIR, bool TW, typename R>
+__device__ __forceinline__ void dft2(cx<R>* v, const cx<R>* w) {
+  if constexpr (TW) {
+    const cx<R> t = cfma<DIR>(v[0], v[1], w[0]);
+    v[1] = other(v[0], t);
+    v[0] = t;
+  } else {
+    const cx<R> a = v[0];
+    v[0] = a + v[1];
+    v[1] = a - v[1];
+  }
 }
 
 template <int DIR, typename R>
-__device__ __forceinline__ void dft8(cx<R>* v) {
-  cx<R> b0 = v[0] + v[4], c0 = v[0] - v[4];
-  cx<R> b1 = v[1] + v[5], c1 = v[1] - v[5];
-  cx<R> b2 = v[2] + v[6], c2 = v[2] - v[6];
-  cx<R> b3 = v[3] + v[7], c3 = v[3] - v[7];
-  c1 = rot_8<DIR>(c1);
-  c2 = rot_q<DIR>(c2);
-  c3 = rot_38<DIR>(c3);
-  dft4_<DIR>(b0, b1, b2, b3);  // even outputs
-  dft4_<DIR>(c0, c1, c2, c3);  // odd outputs
-  v[0] = b0; v[2] = b1; v[4] = b2; v[6] = b3;
-  v[1] = c0; v[3] = c1; v[5] = c2; v[7] = c3;
+__device__ __forceinline__ void dft3(cx<R>* v) {
+  const R h = R(0.86602540378443864676);  // sqrt(3)/2
+  const cx<R> t = v[1] + v[2];
+  const cx<R> u = rot_q<DIR>(v[1] - v[2]);
+  const cx<R> m = axpy(v[0], R(-0.5), t);
+  v[0] = v[0] + t;
+  v[1] = axpy(m, h, u);
+  v[2] = axpy(m, -h, u);
+}
+
+template <int DIR, bool TW, typename R>
+__device__ __forceinline__ void dft4(cx<R>* v, const cx<R>* w) {
+  if constexpr (TW)
+    dft4_tw_<DIR>(v[0], v[1], v[2], v[3], w[0], w[1], w[2]);
+  else
+    dft4_<DIR>(v[0], v[1], v[2], v[3]);
+}
+
+template <int DIR, bool TW, typename R>
+__device__ __forceinline__ void dft8(cx<R>* v, const cx<R>* w) {
+  const R h = R(0.70710678118654752440);
+  cx<R> b[4], c[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (TW) {
+      const cx<R> x = (i == 0) ? v[0] : twist<DIR>(v[i], w[i == 0 ? 0 : i - 1]);
+      b[i] = cfma<DIR>(x, v[i + 4], w[i + 3]);
+      c[i] = other(x, b[i]);
+    } else {
+      b[i] = v[i] + v[i + 4];
+      c[i] = v[i] - v[i + 4];
+    }
+  }
+  dft4_<DIR>(b[0], b[1], b[2], b[3]);  // even outputs
+  // odd outputs: radix 4 of c0, c1 w8, c2 w8^2, c3 w8^3
+  const cx<R> c2 = rot_q<DIR>(c[2]);
+  const cx<R> p = rot_8s<DIR>(c[1]), q = rot_38s<DIR>(c[3]);
+  dft4_tail(c[0] + c2, c[0] - c2, p + q, rot_q<DIR>(p - q), h, v[1], v[3], v[5], v[7]);
+  v[0] = b[0];
+  v[2] = b[1];
+  v[4] = b[2];
+  v[6] = b[3];
 }
 
 // 16 = 4 x 4: inner DFT4 over n2 (stride 4), twiddle w16^(n1 k2), outer
 // DFT4 over n1; output index k2 + 4 k1.
-template <int DIR, typename R>
-__device__ __forceinline__ void dft16(cx<R>* v) {
-  dft4_<DIR>(v[0], v[4], v[8], v[12]);
-  dft4_<DIR>(v[1], v[5], v[9], v[13]);
-  dft4_<DIR>(v[2], v[6], v[10], v[14]);
-  dft4_<DIR>(v[3], v[7], v[11], v[15]);
-  // v[n1 + 4 k2] *= w16^(n1 k2)
-  v[5] = rot_16<DIR, 1>(v[5]);
-  v[9] = rot_8<DIR>(v[9]);
-  v[13] = rot_16<DIR, 3>(v[13]);
-  v[6] = rot_8<DIR>(v[6]);
-  v[10] = rot_q<DIR>(v[10]);
-  v[14] = rot_38<DIR>(v[14]);
-  v[7] = rot_16<DIR, 3>(v[7]);
-  v[11] = rot_38<DIR>(v[11]);
-  v[15] = rot_16<DIR, 9>(v[15]);
+template <int DIR, bool TW, typename R>
+__device__ __forceinline__ void dft16(cx<R>* v, const cx<R>* w) {
+  const R h = R(0.70710678118654752440);
+  const R c1 = R(0.92387953251128675613);              // cos(pi/8)
+  const R tau = R(DIR * 0.41421356237309504880);       // dir tan(pi/8)
+  const R tq = R(0.41421356237309504880), d = R(DIR);
+#pragma unroll
+  for (int n1 = 0; n1 < 4; ++n1) {
+    if constexpr (TW) {
+      if (n1 > 0) v[n1] = twist<DIR>(v[n1], w[n1 > 0 ? n1 - 1 : 0]);
+      dft4_tw_<DIR>(v[n1], v[n1 + 4], v[n1 + 8], v[n1 + 12], w[n1 + 3], w[n1 + 7], w[n1 + 11]);
+    } else {
+      dft4_<DIR>(v[n1], v[n1 + 4], v[n1 + 8], v[n1 + 12]);
+    }
+  }
+  // v[n1 + 4 k2]; over the scale c1: a w16 and a w16^3 (2 operations each)
+  auto w16 = [&](cx<R> a) { return cx<R>{fma_(-tau, a.im, a.re), fma_(tau, a.re, a.im)}; };
+  auto w16_3 = [&](cx<R> a) { return cx<R>{fma_(tq, a.re, -d * a.im), fma_(tq, a.im, d * a.re)}; };
+  cx<R> y[16];
   dft4_<DIR>(v[0], v[1], v[2], v[3]);
-  dft4_<DIR>(v[4], v[5], v[6], v[7]);
-  dft4_<DIR>(v[8], v[9], v[10], v[11]);
-  dft4_<DIR>(v[12], v[13], v[14], v[15]);
-  // now v[4 k2 + k1] holds y[k2 + 4 k1]: transpose the 4x4 index
-  cx<R> t;
-#define SSFM_SWAP(a, b) t = v[a]; v[a] = v[b]; v[b] = t;
-  SSFM_SWAP(1, 4) SSFM_SWAP(2, 8) SSFM_SWAP(3, 12)
-  SSFM_SWAP(6, 9) SSFM_SWAP(7, 13) SSFM_SWAP(11, 14)
-#undef SSFM_SWAP
+#pragma unroll
+  for (int k1 = 0; k1 < 4; ++k1) y[4 * k1] = v[k1];
+  {  // k2 = 1: w16^(0, 1, 2, 3)
+    const cx<R> p = rot_8s<DIR>(v[6]);
+    const cx<R> t0 = axpy(v[4], h, p), t1 = axpy(v[4], -h, p);
+    const cx<R> b = w16(v[5]), e = w16_3(v[7]);
+    dft4_tail(t0, t1, b + e, rot_q<DIR>(b - e), c1, y[1], y[5], y[9], y[13]);
+  }
+  {  // k2 = 2: w16^(0, 2, 4, 6)
+    const cx<R> r = rot_q<DIR>(v[10]);
+    const cx<R> p = rot_8s<DIR>(v[9]), q = rot_38s<DIR>(v[11]);
+    dft4_tail(v[8] + r, v[8] - r, p + q, rot_q<DIR>(p - q), h, y[2], y[6], y[10], y[14]);
+  }
+  {  // k2 = 3: w16^(0, 3, 6, 9), w16^9 = -w16
+    const cx<R> q = rot_38s<DIR>(v[14]);
+    const cx<R> t0 = axpy(v[12], h, q), t1 = axpy(v[12], -h, q);
+    const cx<R> b = w16_3(v[13]), e = w16(v[15]);
+    dft4_tail(t0, t1, b - e, rot_q<DIR>(b + e), c1, y[3], y[7], y[11], y[15]);
+  }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = y[k];
 }
 
 // 12 = 4 x 3: inner DFT4 over n2 (points n1 + 3 n2), twiddle w12^(n1 k2),
 // outer DFT3 over n1; output index k2 + 4 k1.
-template <int DIR, typename R>
-__device__ __forceinline__ void dft12(cx<R>* v) {
+template <int DIR, bool TW, typename R>
+__device__ __forceinline__ void dft12(cx<R>* v, const cx<R>* w) {
   constexpr double h = 0.86602540378443864676;  // cos(pi/6)
   cx<R> t[3][4];
 #pragma unroll
   for (int n1 = 0; n1 < 3; ++n1) {
 #pragma unroll
     for (int n2 = 0; n2 < 4; ++n2) t[n1][n2] = v[n1 + 3 * n2];
-    dft4_<DIR>(t[n1][0], t[n1][1], t[n1][2], t[n1][3]);
+    if constexpr (TW) {
+      if (n1 > 0) t[n1][0] = twist<DIR>(t[n1][0], w[n1 > 0 ? n1 - 1 : 0]);
+      dft4_tw_<DIR>(t[n1][0], t[n1][1], t[n1][2], t[n1][3], w[n1 + 2], w[n1 + 5], w[n1 + 8]);
+    } else {
+      dft4_<DIR>(t[n1][0], t[n1][1], t[n1][2], t[n1][3]);
+    }
   }
   // w12^1, w12^2, w12^3 = dir i; w12^2, w12^4, w12^6 = -1
   t[1][1] = cmul(t[1][1], cx<R>{R(h), R(DIR * 0.5)});
@@ -219,78 +342,21 @@ __device__ __forceinline__ void dft12(cx<R>* v) {
   }
 }
 
-// cos(e pi / 16) and sin(e pi / 16) for integer e (exact table of the
-// first octant, extended by symmetry).
-constexpr double kCos16[9] = {1.0,
-                              0.98078528040323044913,
-                              0.92387953251128675613,
-                              0.83146961230254523708,
-                              0.70710678118654752440,
-                              0.55557023301960222474,
-                              0.38268343236508977173,
-                              0.19509032201612826785,
-                              0.0};
-constexpr double cos16(int e) {
-  e = ((e % 32) + 32) % 32;
-  if (e <= 8) return kCos16[e];
-  if (e <= 16) return -kCos16[16 - e];
-  if (e <= 24) return -kCos16[e - 16];
-  return kCos16[32 - e];
-}
-constexpr double sin16(int e) { return cos16(8 - e); }
-
-// multiply by exp(dir 2 pi i e / 32)
-template <int DIR, int EXP, typename R>
-__device__ __forceinline__ cx<R> rot_32(cx<R> a) {
-  constexpr int e = ((EXP % 32) + 32) % 32;
-  if constexpr (e == 0) return a;
-  else if constexpr (e == 8) return rot_q<DIR>(a);
-  else if constexpr (e == 16) return cx<R>{-a.re, -a.im};
-  else if constexpr (e == 24) return rot_q<-DIR>(a);
-  else if constexpr (e == 4) return rot_8<DIR>(a);
-  else if constexpr (e == 12) return rot_38<DIR>(a);
-  else return cmul(a, cx<R>{R(cos16(e)), R(DIR * sin16(e))});
-}
-
-// 32 = 4 x 8: inner DFT8 over n2 (points n1 + 4 n2), twiddle w32^(n1 k2),
-// outer DFT4 over n1; output index k2 + 8 k1.
-template <int DIR, int N1, int K2, typename R>
-__device__ __forceinline__ void dft32_tw(cx<R>* v) {
-  v[N1 + 4 * K2] = rot_32<DIR, N1 * K2>(v[N1 + 4 * K2]);
-}
-
-template <int DIR, typename R>
-__device__ __forceinline__ void dft32(cx<R>* v) {
-  cx<R> t[32];
-#pragma unroll
-  for (int n1 = 0; n1 < 4; ++n1) {
-    cx<R> g[8];
-#pragma unroll
-    for (int n2 = 0; n2 < 8; ++n2) g[n2] = v[n1 + 4 * n2];
-    dft8<DIR>(g);
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) t[n1 + 4 * k2] = g[k2];
+// radix RAD with (TW) or without stage twiddles
+template <int RAD, int DIR, bool TW, typename R>
+__device__ __forceinline__ void dft(cx<R>* v, const cx<R>* w) {
+  if constexpr (RAD == 2) dft2<DIR, TW>(v, w);
+  else if constexpr (RAD == 3) {
+    if constexpr (TW) {
+      v[1] = twist<DIR>(v[1], w[0]);
+      v[2] = twist<DIR>(v[2], w[1]);
+    }
+    dft3<DIR>(v);
   }
-  [&]<int... I>(std::integer_sequence<int, I...>) {
-    ((dft32_tw<DIR, I / 8, I % 8>(t)), ...);
-  }(std::make_integer_sequence<int, 32>{});
-#pragma unroll
-  for (int k2 = 0; k2 < 8; ++k2) {
-    dft4_<DIR>(t[4 * k2], t[4 * k2 + 1], t[4 * k2 + 2], t[4 * k2 + 3]);
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) v[k2 + 8 * k1] = t[4 * k2 + k1];
-  }
-}
-
-template <int RAD, int DIR, typename R>
-__device__ __forceinline__ void dft(cx<R>* v) {
-  if constexpr (RAD == 2) dft2<DIR>(v);
-  else if constexpr (RAD == 3) dft3<DIR>(v);
-  else if constexpr (RAD == 4) dft4<DIR>(v);
-  else if constexpr (RAD == 8) dft8<DIR>(v);
-  else if constexpr (RAD == 12) dft12<DIR>(v);
-  else if constexpr (RAD == 16) dft16<DIR>(v);
-  else if constexpr (RAD == 32) dft32<DIR>(v);
+  else if constexpr (RAD == 4) dft4<DIR, TW>(v, w);
+  else if constexpr (RAD == 8) dft8<DIR, TW>(v, w);
+  else if constexpr (RAD == 12) dft12<DIR, TW>(v, w);
+  else if constexpr (RAD == 16) dft16<DIR, TW>(v, w);
   else static_assert(RAD == 2, "unsupported radix");
 }
 
@@ -335,18 +401,19 @@ struct Plan {
 // complex128), which a bank model (64 banks of 4 bytes, a wavefront's 8- and
 // 16-byte accesses served 32 and 16 lanes at a time) gives 1.0-1.3 cycles
 // per served group over all stages of the radix 4, 8 and 16 plans.
+//
+// Both layouts map point p to slot idx(p), a sum of floors of p by powers of
+// two: for points p, q without a common bit idx(p + q) = idx(p) + idx(q).
+// The stages use that: a thread's slots are one computed index plus
+// compile-time offsets, which fold into the LDS instructions (one by one
+// the indices took a quarter to a third of the column passes' instructions).
 template <typename R, int N>
 struct LdsLineMajor {
-  static constexpr unsigned A = sizeof(R) == 4 ? 32 : 16;
-  static constexpr int LINE = N + N / int(A) * 3;
+  static constexpr int A = sizeof(R) == 4 ? 32 : 16;
+  static constexpr int LINE = N + N / A * 3;
+  static constexpr __device__ __host__ unsigned idx(unsigned p) { return p + p / A * 3u; }
   cx<R>* base;
-  // unsigned (p >= 0): constant offsets of p that are multiples of A fold
-  // into the instruction's offset
-  __device__ __forceinline__ cx<R>& at(int p) const {
-    return base[unsigned(p) + (unsigned(p) / A) * 3u];
-  }
-  __device__ __forceinline__ cx<R> get(int p) const { return at(p); }
-  __device__ __forceinline__ void put(int p, cx<R> v) const { at(p) = v; }
+  __device__ __forceinline__ cx<R>& slot(unsigned i) const { return base[i]; }
 };
 
 // Column tiles: point-major, the W columns of a point adjacent, B padding
@@ -357,15 +424,28 @@ struct LdsPointMajor {
   static constexpr bool HALF = sizeof(R) == 8 && A_ % 2 == 0 && B_ % 2 == 0;
   static constexpr int A = HALF ? A_ / 2 : A_, B = HALF ? B_ / 2 : B_;
   static constexpr int size(int n) { return n * W + (n / A) * B; }
-  cx<R>* base;  // already offset by the column index
-  // unsigned (p >= 0): the division is a shift, and constant offsets of p
-  // that are multiples of A fold into the instruction's offset
-  __device__ __forceinline__ int idx(int p) const {
-    const unsigned u = unsigned(p);
-    return int(u * W + (u / A) * B);
+  static constexpr __device__ __host__ unsigned idx(unsigned p) {
+    return p * unsigned(W) + p / unsigned(A) * unsigned(B);
   }
-  __device__ __forceinline__ cx<R> get(int p) const { return base[idx(p)]; }
-  __device__ __forceinline__ void put(int p, cx<R> v) const { base[idx(p)] = v; }
+  cx<R>* base;  // already offset by the column index
+  __device__ __forceinline__ cx<R>& slot(unsigned i) const { return base[i]; }
+};
+
+// First output point of butterfly j (span NS, radix RAD); output r is r NS
+// further.  Slot of that output: with NS and NS RAD powers of two the bits
+// of r NS are free in the first point, so the slots differ by constants.
+constexpr bool pow2(int x) { return (x & (x - 1)) == 0; }
+template <class Lds, int RAD, int NS>
+struct OutSlots {
+  unsigned first, at;
+  __device__ __forceinline__ explicit OutSlots(unsigned j)
+      : first((j / NS) * (NS * RAD) + j % NS), at(Lds::idx(first)) {}
+  __device__ __forceinline__ unsigned operator()(unsigned r) const {
+    if constexpr (pow2(NS) && pow2(RAD))
+      return at + Lds::idx(r * NS);
+    else
+      return Lds::idx(first + r * NS);
+  }
 };
 
 // ------------------------------------------------------------ twiddles
@@ -389,6 +469,17 @@ constexpr int twiddle_count() {
   return c;
 }
 
+// registers for the twiddles of the stage that follows (1 if there are none
+// to request)
+template <int N, int T, bool LATE, int NS>
+constexpr int next_tw_regs() {
+  return 1;
+}
+template <int N, int T, bool LATE, int NS, int RAD, int... Rest>
+constexpr int next_tw_regs() {
+  return LATE ? stage_tw_sets<N, T, NS, RAD>() * (RAD - 1) : 1;
+}
+
 template <class P>
 struct TwCount;
 template <int N, int T, int L, int... Rs, int A, int B, int O>
@@ -399,22 +490,22 @@ struct TwCount<Plan<N, T, L, Radices<Rs...>, A, B, O>> {
 
 template <typename R, int N, int T, int NS, int RAD, int R0>
 __device__ __forceinline__ void load_stage_twiddles(cx<R>* w, int t,
-                                                    const cx<R>* __restrict__ tw) {
+                                                    const Buf<cx<R>>& tw) {
   if constexpr (NS > 1) {
 #pragma unroll
     for (int b = 0; b < stage_tw_sets<N, T, NS, RAD>(); ++b) {
-      // unsigned (t >= 0): masks; 32-bit offsets from a uniform base
+      // unsigned (t >= 0): masks
       const uint32_t k = uint32_t(t + T * b) % uint32_t(NS);
 #pragma unroll
       for (int r = 1; r < RAD; ++r)
-        w[b * (RAD - 1) + r - 1] = tw[k + uint32_t(NS - R0 + (r - 1) * NS)];
+        w[b * (RAD - 1) + r - 1] = tw.get(k, uint32_t(NS - R0 + (r - 1) * NS));
     }
   }
 }
 
 template <typename R, int N, int T, int NS, int R0, int RA, int... Rest>
 __device__ __forceinline__ void load_twiddles_rec(cx<R>* w, int t,
-                                                  const cx<R>* __restrict__ tw) {
+                                                  const Buf<cx<R>>& tw) {
   load_stage_twiddles<R, N, T, NS, RA, R0>(w, t, tw);
   if constexpr (sizeof...(Rest) > 0) {
     constexpr int used = (NS > 1) ? stage_tw_sets<N, T, NS, RA>() * (RA - 1) : 0;
@@ -424,37 +515,47 @@ __device__ __forceinline__ void load_twiddles_rec(cx<R>* w, int t,
 
 template <typename R, int N, int T, int R0, int... Rs>
 __device__ __forceinline__ void load_twiddles_impl(cx<R>* w, int t,
-                                                   const cx<R>* __restrict__ tw,
+                                                   const Buf<cx<R>>& tw,
                                                    Radices<R0, Rs...>) {
   load_twiddles_rec<R, N, T, 1, R0, R0, Rs...>(w, t, tw);
 }
 
 template <typename R, class P>
-__device__ __forceinline__ void load_twiddles(cx<R>* w, int t, const cx<R>* __restrict__ tw) {
+__device__ __forceinline__ void load_twiddles(cx<R>* w, int t, const Buf<cx<R>>& tw) {
   if constexpr (!P::LATE_TW) load_twiddles_impl<R, P::N, P::T>(w, t, tw, typename P::radices{});
 }
 
-// ---------------------------------------------------------- one stage
-// w: this stage's twiddles in registers (preloaded), or, with LATE, loaded
-// here from the table before the stage's LDS reads so that their latency
-// overlaps the exchange.
-template <typename R, int N, int T, int RAD, int NS, int R0, int DIR, bool FIRST,
-          bool LAST, bool LATE, class Lds>
-__device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
-                                          const cx<R>* wpre, const cx<R>* __restrict__ tw) {
+// ------------------------------------------------------------- stages
+// w: the twiddles of the stage at hand, from registers (preloaded) or, with
+// LATE, requested one stage ahead, so that their latency passes behind a
+// whole butterfly and exchange (requested where they are used, the waits for
+// them were a fifth of a 4096-point pass).  tail() is called where the last
+// stage would request the next one's: it requests what follows the
+// transform.
+template <typename R, int N, int T, int DIR, int NS, int R0, bool LATE, class Lds, class Tail,
+          int RAD, int... Rest>
+__device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
+                                           const Buf<cx<R>>& tw, Tail&& tail) {
   // with late twiddles the thread index is made opaque per stage, so the
   // stage's LDS and twiddle addresses are computed where they are used
   // instead of held in registers from the kernel's start
   if constexpr (LATE) asm volatile("" : "+v"(t));
+  constexpr bool FIRST = NS == 1, LAST = sizeof...(Rest) == 0;
   constexpr int E = N / T;
   constexpr int NB = E / RAD;
   constexpr int STRIDE = N / RAD;
   constexpr int SETS = stage_tw_sets<N, T, NS, RAD>();
   static_assert(E % RAD == 0, "radix must divide points per thread");
-  cx<R> wl[(LATE && NS > 1) ? SETS * (RAD - 1) : 1];
-  if constexpr (LATE && NS > 1) load_stage_twiddles<R, N, T, NS, RAD, R0>(wl, t, tw);
-  const cx<R>* w = LATE ? wl : wpre;
+  static_assert(pow2(T), "the input slots of a thread differ by constants");
+  cx<R> wn[next_tw_regs<N, T, LATE, NS * RAD, Rest...>()];
+  if constexpr (LATE) {
+    if constexpr (LAST)
+      tail();
+    else
+      load_stage_twiddles<R, N, T, NS * RAD, first_radix<Rest...>(), R0>(wn, t, tw);
+  }
   cx<R> a[NB][RAD];
+  const unsigned in0 = Lds::idx(unsigned(t));
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
 #pragma unroll
@@ -462,7 +563,7 @@ __device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
       if constexpr (FIRST) {
         a[b][r] = v[b + r * NB];
       } else {
-        a[b][r] = lds.get(t + T * b + r * STRIDE);
+        a[b][r] = lds.slot(in0 + Lds::idx(T * b + r * STRIDE));
       }
     }
   }
@@ -471,19 +572,11 @@ __device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
   }
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const unsigned j = unsigned(t + T * b);  // j >= 0: shifts and masks
-    if constexpr (NS > 1) {
-#pragma unroll
-      for (int r = 1; r < RAD; ++r) {
-        const cx<R> ww = w[(SETS == 1 ? 0 : b * (RAD - 1)) + r - 1];
-        a[b][r] = (DIR > 0) ? cmulc(a[b][r], ww) : cmul(a[b][r], ww);
-      }
-    }
-    dft<RAD, DIR>(a[b]);
+    dft<RAD, DIR, (NS > 1)>(a[b], w + (SETS == 1 ? 0 : b * (RAD - 1)));
     if constexpr (!LAST) {
-      const int base = int((j / NS) * NS * RAD + j % NS);
+      const OutSlots<Lds, RAD, NS> out(unsigned(t + T * b));  // >= 0: shifts and masks
 #pragma unroll
-      for (int r = 0; r < RAD; ++r) lds.put(base + r * NS, a[b][r]);
+      for (int r = 0; r < RAD; ++r) lds.slot(out(r)) = a[b][r];
     } else {
 #pragma unroll
       for (int r = 0; r < RAD; ++r) v[b + r * NB] = a[b][r];
@@ -491,26 +584,10 @@ __device__ __forceinline__ void fft_stage(cx<R>* v, int t, const Lds& lds,
   }
   if constexpr (!LAST) {
     __syncthreads();
+    constexpr int used = NS > 1 ? SETS * (RAD - 1) : 0;
+    fft_stages<R, N, T, DIR, NS * RAD, R0, LATE, Lds, Tail, Rest...>(
+        v, t, lds, LATE ? wn : w + used, tw, static_cast<Tail&&>(tail));
   }
-}
-
-template <typename R, int N, int T, int DIR, int NS, int R0, bool FIRST, bool LATE,
-          class Lds, int RA, int... Rest>
-__device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds,
-                                           const cx<R>* w, const cx<R>* __restrict__ tw) {
-  constexpr bool LAST = sizeof...(Rest) == 0;
-  fft_stage<R, N, T, RA, NS, R0, DIR, FIRST, LAST, LATE>(v, t, lds, w, tw);
-  if constexpr (!LAST) {
-    constexpr int used = (!LATE && NS > 1) ? stage_tw_sets<N, T, NS, RA>() * (RA - 1) : 0;
-    fft_stages<R, N, T, DIR, NS * RA, R0, false, LATE, Lds, Rest...>(v, t, lds, w + used, tw);
-  }
-}
-
-template <typename R, int N, int T, int DIR, bool LATE, class Lds, int R0, int... Rs>
-__device__ __forceinline__ void fft_line_impl(cx<R>* v, int t, const Lds& lds,
-                                              const cx<R>* w, const cx<R>* __restrict__ tw,
-                                              Radices<R0, Rs...>) {
-  fft_stages<R, N, T, DIR, 1, R0, true, LATE, Lds, R0, Rs...>(v, t, lds, w, tw);
 }
 
 // ------------------------------------ exchanges through half an LDS tile
@@ -537,42 +614,52 @@ __device__ __forceinline__ void hx_exchange(cx<R> (&a)[N / T / RAD][RAD],
     __syncthreads();
 #pragma unroll
     for (int b = h * NB / 2; b < (h + 1) * NB / 2; ++b) {
-      const unsigned j = unsigned(t + T * b);
-      const int base = int((j / NS) * NS * RAD + j % NS) - h * H;
+      // butterfly t + T (b - h NB / 2) of the half's own N/2 points
+      const OutSlots<Lds, RAD, NS> out(unsigned(t + T * (b - h * NB / 2)));
 #pragma unroll
-      for (int r = 0; r < RAD; ++r) lds.put(base + r * NS, a[b][r]);
+      for (int r = 0; r < RAD; ++r) lds.slot(out(r)) = a[b][r];
     }
     __syncthreads();
+    const unsigned in0 = Lds::idx(unsigned(t));
 #pragma unroll
     for (int b = 0; b < NB2; ++b) {
 #pragma unroll
       for (int r = h * RB / 2; r < (h + 1) * RB / 2; ++r)
-        nx[b][r] = lds.get(t + T * b + r * (N / RB) - h * H);
+        nx[b][r] = lds.slot(in0 + Lds::idx(T * b + r * (N / RB) - h * H));
     }
   }
 }
 
-template <typename R, int N, int T, int DIR, int NS, int R0, class Lds, int RA, int... Rest>
+template <typename R, int N, int T, int DIR, int NS, int R0, class Lds, class Tail, int RA,
+          int... Rest>
 __device__ __forceinline__ void hx_stages(cx<R>* v, cx<R> (&a)[N / T / RA][RA], int t,
-                                          const Lds& lds, const cx<R>* __restrict__ tw) {
+                                          const Lds& lds, const Buf<cx<R>>& tw,
+                                          Tail&& tail) {
+  constexpr bool LAST = sizeof...(Rest) == 0;
   constexpr int NB = N / T / RA;
   constexpr int SETS = stage_tw_sets<N, T, NS, RA>();
   // the thread index made opaque per stage (addresses computed in the stage)
   asm volatile("" : "+v"(t));
-  if constexpr (NS > 1) {
-    cx<R> w[SETS * (RA - 1)];
-    load_stage_twiddles<R, N, T, NS, RA, R0>(w, t, tw);
+  // one butterfly at a time, each with its own twiddles: all of a thread's
+  // points are live here, and twiddles of two butterflies beside them would
+  // not fit the registers of two workgroups per compute unit
+  cx<R> w[NS > 1 ? RA - 1 : 1];
 #pragma unroll
-    for (int b = 0; b < NB; ++b)
+  for (int b = 0; b < NB; ++b) {
+    if constexpr (NS > 1) {
+      if (b < SETS) {
+        const uint32_t k = uint32_t(t + T * b) % uint32_t(NS);
 #pragma unroll
-      for (int r = 1; r < RA; ++r) {
-        const cx<R> ww = w[(SETS == 1 ? 0 : b * (RA - 1)) + r - 1];
-        a[b][r] = (DIR > 0) ? cmulc(a[b][r], ww) : cmul(a[b][r], ww);
+        for (int r = 1; r < RA; ++r) w[r - 1] = tw.get(k, uint32_t(NS - R0 + (r - 1) * NS));
       }
-  }
+    }
+    dft<RA, DIR, (NS > 1)>(a[b], w);
 #pragma unroll
-  for (int b = 0; b < NB; ++b) dft<RA, DIR>(a[b]);
-  if constexpr (sizeof...(Rest) == 0) {
+    for (int r = 0; r < RA; ++r) asm volatile("" : "+v"(a[b][r].re), "+v"(a[b][r].im));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (LAST) tail();
+  if constexpr (LAST) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -581,37 +668,47 @@ __device__ __forceinline__ void hx_stages(cx<R>* v, cx<R> (&a)[N / T / RA][RA], 
     constexpr int RB = first_radix<Rest...>();
     cx<R> nx[N / T / RB][RB];
     hx_exchange<R, N, T, RA, NS, RB>(a, nx, t, lds);
-    hx_stages<R, N, T, DIR, NS * RA, R0, Lds, Rest...>(v, nx, t, lds, tw);
+    hx_stages<R, N, T, DIR, NS * RA, R0, Lds, Tail, Rest...>(v, nx, t, lds, tw,
+                                                             static_cast<Tail&&>(tail));
   }
 }
 
-template <typename R, int N, int T, int DIR, class Lds, int R0, int... Rest>
-__device__ __forceinline__ void fft_line_hx_impl(cx<R>* v, int t, const Lds& lds,
-                                                 const cx<R>* __restrict__ tw,
-                                                 Radices<R0, Rest...>) {
-  constexpr int NB = N / T / R0;
-  cx<R> a[NB][R0];
+template <typename R, class P, int DIR, class Lds, class Tail, int R0, int... Rest>
+__device__ __forceinline__ void fft_line_impl(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
+                                              const Buf<cx<R>>& tw, Tail&& tail,
+                                              Radices<R0, Rest...>) {
+  if constexpr (P::HX) {
+    constexpr int NB = P::E / R0;
+    cx<R> a[NB][R0];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
+    for (int b = 0; b < NB; ++b) {
 #pragma unroll
-    for (int r = 0; r < R0; ++r) a[b][r] = v[b + r * NB];
+      for (int r = 0; r < R0; ++r) a[b][r] = v[b + r * NB];
+    }
+    hx_stages<R, P::N, P::T, DIR, 1, R0, Lds, Tail, R0, Rest...>(v, a, t, lds, tw,
+                                                                 static_cast<Tail&&>(tail));
+  } else {
+    fft_stages<R, P::N, P::T, DIR, 1, R0, P::LATE_TW, Lds, Tail, R0, Rest...>(
+        v, t, lds, w, tw, static_cast<Tail&&>(tail));
   }
-  hx_stages<R, N, T, DIR, 1, R0, Lds, R0, Rest...>(v, a, t, lds, tw);
 }
 
 // In-register FFT of one line (DIR = -1 forward, +1 inverse, unscaled),
 // with the thread's twiddles preloaded by load_twiddles<R, P> (w), or, for
 // a late-twiddle or half-exchange plan, read stage by stage from the plan's
-// stage-ordered table tw.  On entry and exit v[e] holds point t + T*e.  A
-// full exchange leaves the LDS free (its last barrier follows the last
-// reads); a half exchange opens with the barrier that guards the last reads.
+// stage-ordered table tw, tail() called with the last stage.  On entry and
+// exit v[e] holds point t + T*e.  A full exchange leaves the LDS free (its
+// last barrier follows the last reads); a half exchange opens with the
+// barrier that guards the last reads.
+template <typename R, class P, int DIR, class Lds, class Tail>
+__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
+                                         const Buf<cx<R>>& tw, Tail&& tail) {
+  fft_line_impl<R, P, DIR>(v, t, lds, w, tw, static_cast<Tail&&>(tail), typename P::radices{});
+}
 template <typename R, class P, int DIR, class Lds>
 __device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
-                                         const cx<R>* __restrict__ tw) {
-  if constexpr (P::HX)
-    fft_line_hx_impl<R, P::N, P::T, DIR>(v, t, lds, tw, typename P::radices{});
-  else
-    fft_line_impl<R, P::N, P::T, DIR, P::LATE_TW>(v, t, lds, w, tw, typename P::radices{});
+                                         const Buf<cx<R>>& tw) {
+  fft_line<R, P, DIR>(v, t, lds, w, tw, [] {});
 }
 
 // Host side: the radix list of a plan.

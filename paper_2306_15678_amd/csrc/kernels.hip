@@ -32,10 +32,10 @@ int plan_default(bool column, int n, bool fp64) {
   struct Default {
     int n, row, col, row_f64, col_f64;
   };
-  static constexpr Default kDefaults[] = {{128, 0, 1, 0, 1},  {256, 0, 1, 3, 5},
-                                          {512, 0, 3, 0, 3},  {768, 3, 2, 0, 2},
-                                          {1024, 0, 0, 7, 0}, {2048, 3, 4, 1, 7},
-                                          {4096, 3, 5, 3, 2}};
+  static constexpr Default kDefaults[] = {{128, 0, 0, 0, 0},  {256, 0, 0, 1, 3},
+                                          {512, 0, 0, 0, 0},  {768, 0, 0, 0, 0},
+                                          {1024, 0, 1, 2, 5}, {2048, 0, 0, 1, 3},
+                                          {4096, 3, 0, 3, 1}};
   for (const Default& d : kDefaults)
     if (d.n == n) return column ? (fp64 ? d.col_f64 : d.col) : (fp64 ? d.row_f64 : d.row);
   return 0;

@@ -45,12 +45,14 @@ __device__ __forceinline__ ScreenConst<R> screen_const(const InstDev& in) {
     s.cK = in.cK_f;
     s.cM = in.cM_f;
     s.inv2k1 = in.inv2k1_f;
+    s.x_weak = in.x_weak_f;
 #pragma unroll
     for (int p = 0; p < 8; ++p) s.th[p] = in.theta_f[p];
   } else {
     s.cK = in.cK;
     s.cM = in.cM;
     s.inv2k1 = in.inv2k1;
+    s.x_weak = in.x_weak;
 #pragma unroll
     for (int p = 0; p < 8; ++p) s.th[p] = in.theta[p];
   }
@@ -280,21 +282,21 @@ __global__ void __launch_bounds__(P::THREADS)
   const TL tl;
   if (tl.tile >= a.n_tiles) return;
   const int64_t base = tl.base(a.off0);
-  const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
+  const Buf<cx<R>> src(static_cast<const cx<R>*>(a.src) + base);
   cx<R> v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = src[tl.toff + STRIDE * uint32_t(e)];
+  for (int e = 0; e < E; ++e) v[e] = src.get(tl.toff, STRIDE * uint32_t(e));
   const cx<R>* tables = static_cast<const cx<R>*>(a.tables);
-  const cx<R>* __restrict__ tw = tables + a.tw;
-  const cx<R>* __restrict__ prop = tables + a.prop0 + int64_t(tl.beam) * a.prop_stride;
+  const Buf<cx<R>> tw(tables + a.tw);
+  const Buf<cx<R>> prop(tables + a.prop0 + int64_t(tl.beam) * a.prop_stride);
   // plans with few points a thread keep twiddles and propagator in
   // registers for both factors; the others read them as they go
   constexpr bool LATE = P::LATE_TW || P::HX;
   cx<R> wt[LATE ? 1 : tw_regs<P>()];
-  cx<R> pr[LATE ? 1 : E];
+  cx<R> pr[P::HX ? 1 : E];
   if constexpr (!LATE) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) pr[e] = prop[uint32_t(tl.t + T * e)];
+    for (int e = 0; e < E; ++e) pr[e] = prop.get(uint32_t(tl.t), uint32_t(T * e));
     load_twiddles<R, P>(wt, tl.t, tw);
   }
   const auto lds = LD::make(lds_mem, tl.line);
@@ -312,9 +314,9 @@ __global__ void __launch_bounds__(P::THREADS)
       asm volatile("" : "+v"(to));
       if constexpr (!ADJ) {
         if (a.rec != nullptr) {
-          cx<R>* __restrict__ rec = static_cast<cx<R>*>(a.rec) + base;
+          const Buf<cx<R>> rec(static_cast<const cx<R>*>(a.rec) + base);
 #pragma unroll
-          for (int e = 0; e < E; ++e) rec[to + STRIDE * uint32_t(e)] = v[e];
+          for (int e = 0; e < E; ++e) rec.put(to, STRIDE * uint32_t(e), v[e]);
         }
         if ((flags & PASS_SCREEN) || a.part != nullptr) {
           const InstDev in = load_uniform(ip);
@@ -323,7 +325,8 @@ __global__ void __launch_bounds__(P::THREADS)
                                ? find_plane(a.screens, a.screen_steps, in, a.step)
                                : nullptr;
           if (plane) plane += tl.in_beam();
-          constexpr int SB = (E % 4 == 0) ? 4 : E;
+          constexpr int SB = 4;  // points per batch
+          static_assert(E % SB == 0, "whole batches");
           double s = 0.0, m = 0.0;
 #pragma unroll
           for (int c = 0; c < E; c += SB) {
@@ -371,7 +374,7 @@ __global__ void __launch_bounds__(P::THREADS)
                                ? find_plane(a.screens, a.screen_steps, in, a.step)
                                : nullptr;
           if (plane) plane += tl.in_beam();
-          const cx<R>* __restrict__ svp = static_cast<const cx<R>*>(a.aux) + base;
+          const Buf<cx<R>> svp(static_cast<const cx<R>*>(a.aux) + base);
           constexpr int AC = 2;  // points per batch
           static_assert(E % AC == 0, "whole batches");
           // each batch's stored field and phases are requested one batch
@@ -380,7 +383,7 @@ __global__ void __launch_bounds__(P::THREADS)
           R ph[2][AC];
           auto load_inputs = [&](int c, int k) {
 #pragma unroll
-            for (int e = 0; e < AC; ++e) sv[k][e] = svp[to + STRIDE * uint32_t(c + e)];
+            for (int e = 0; e < AC; ++e) sv[k][e] = svp.get(to, STRIDE * uint32_t(c + e));
 #pragma unroll
             for (int e = 0; e < AC; ++e) ph[k][e] = R(0);
             if (plane) {
@@ -411,23 +414,41 @@ __global__ void __launch_bounds__(P::THREADS)
       }
       if (!(flags & PASS_OP2)) break;
     }
-    fft_line<R, P, -1>(v, tl.t, lds, wt, tw);
-    int tp = tl.t;
-    asm volatile("" : "+v"(tp));
+    fft_line<R, P, -1>(v, tl.t, lds, wt, tw, [&] {
+      if constexpr (LATE && !P::HX) {
+        int tp = tl.t;
+        asm volatile("" : "+v"(tp));
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const cx<R> q = LATE ? prop[uint32_t(tp + T * e)] : pr[LATE ? 0 : e];
-      v[e] = ADJ ? cmulc(v[e], q) : cmul(v[e], q);
+        for (int e = 0; e < E; ++e) pr[e] = prop.get(uint32_t(tp), uint32_t(T * e));
+      }
+    });
+    if constexpr (P::HX) {
+      // the points fill the registers: the propagator comes in batches
+      constexpr int PB = 4;
+      int tp = tl.t;
+      asm volatile("" : "+v"(tp));
+#pragma unroll
+      for (int c = 0; c < E; c += PB) {
+        cx<R> q[PB];
+#pragma unroll
+        for (int e = 0; e < PB; ++e) q[e] = prop.get(uint32_t(tp), uint32_t(T * (c + e)));
+#pragma unroll
+        for (int e = 0; e < PB; ++e) v[c + e] = ADJ ? cmulc(v[c + e], q[e]) : cmul(v[c + e], q[e]);
+        if (c % (4 * PB) == 3 * PB) __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = ADJ ? cmulc(v[e], pr[e]) : cmul(v[e], pr[e]);
     }
     fft_line<R, P, +1>(v, tl.t, lds, wt, tw);
     if (second) break;
     second = true;
   }
-  cx<R>* __restrict__ dst = static_cast<cx<R>*>(a.dst) + base;
+  const Buf<cx<R>> dst(static_cast<const cx<R>*>(a.dst) + base);
   uint32_t to = tl.toff;
   asm volatile("" : "+v"(to));
 #pragma unroll
-  for (int e = 0; e < E; ++e) dst[to + STRIDE * uint32_t(e)] = v[e];
+  for (int e = 0; e < E; ++e) dst.put(to, STRIDE * uint32_t(e), v[e]);
 }
 
 // ------------------------------------------------ screen synthesis pass
@@ -443,7 +464,7 @@ __global__ void __launch_bounds__(P::THREADS) k_inverse(PassArgs<R> a) {
   if (2 * a.pair >= in.n_screens || !(in.terms & T_TURB)) return;
   const int64_t base = tl.base(a.off0);
   const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
-  const cx<R>* __restrict__ tw = static_cast<const cx<R>*>(a.tables) + a.tw;
+  const Buf<cx<R>> tw(static_cast<const cx<R>*>(a.tables) + a.tw);
   cx<R> v[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = src[tl.toff + TL::STRIDE * uint32_t(e)];
@@ -480,7 +501,7 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_row(PassArgs<R> a) {
   const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
   cx<R>* __restrict__ st = static_cast<cx<R>*>(a.state) + base;
   cx<R>* __restrict__ dst = static_cast<cx<R>*>(a.dst) + base;
-  const cx<R>* __restrict__ tw = static_cast<const cx<R>*>(a.tables) + a.tw;
+  const Buf<cx<R>> tw(static_cast<const cx<R>*>(a.tables) + a.tw);
   // v is Ubar row-transformed (the column pass applied the solve and both
   // 1/N), or U itself when the step starts
   cx<R> v[E], un[E];
@@ -549,7 +570,7 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_col(PassArgs<R> a) {
   const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
   cx<R>* __restrict__ dst = static_cast<cx<R>*>(a.dst) + base;
   const cx<R>* tables = static_cast<const cx<R>*>(a.tables);
-  const cx<R>* __restrict__ tw = tables + a.tw;
+  const Buf<cx<R>> tw(tables + a.tw);
   const cx<R>* __restrict__ prop = tables + a.prop0 + int64_t(tl.beam) * a.prop_stride;
   cx<R> v[E];
 #pragma unroll

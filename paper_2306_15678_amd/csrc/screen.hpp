@@ -35,6 +35,7 @@ enum : unsigned {
 template <typename R>
 struct ScreenConst {
   R cK, cM, inv2k1;  // inv2k1 = 1 / (2 (K - 1))
+  R x_weak;          // up to here x^(K-1) and cM x^(K-1) vanish beside 1
   R th[8];
   int K;
   unsigned terms;
@@ -219,6 +220,22 @@ __device__ __forceinline__ cx<R> screen_adjoint(const ScreenConst<R>& s,
 }
 
 // ------------------------------------------------------------------------
+// Below x_weak, 1 + x^(K-1) and 1 + cM x^(K-1) round to 1: the plasma phase
+// and the absorption are exactly 0 in the working precision.  A wavefront
+// whose points all lie there skips those terms (the result is the same bit
+// for bit); that is most of every beam outside its filaments, and the
+// skipped logarithm, reciprocal and exponential run at a quarter of the
+// vector rate (complex128: library calls).  The sum of the intensities
+// decides, which a NaN fails.
+template <typename R, int C>
+__device__ __forceinline__ bool strong_n(const ScreenConst<R>& s, const R* x) {
+  if (!(s.terms & (T_MPA | T_PLASMA))) return false;
+  R t = x[0];
+#pragma unroll
+  for (int e = 1; e < C; ++e) t += x[e];
+  return __any(!(t <= s.x_weak));
+}
+
 // Batched forms over C points of one thread.  The term tests are uniform
 // over a launch; here they sit outside the point loops, so a thread takes
 // each branch once per batch instead of once per point.  Per point the
@@ -248,30 +265,32 @@ __device__ __forceinline__ void ipow_n(const R* x, int m, R* out) {
   }
 }
 
-// ln A and Phi (without turbulence) at C points.
+// ln A and Phi (without turbulence) at C points; strong: strong_n of them.
 template <typename R, int C>
-__device__ __forceinline__ void screen_eval_n(const ScreenConst<R>& s, const R* x, R* log_a,
-                                              R* phi) {
+__device__ __forceinline__ void screen_eval_n(const ScreenConst<R>& s, const R* x, bool strong,
+                                              R* log_a, R* phi) {
   const unsigned tm = s.terms;
 #pragma unroll
   for (int e = 0; e < C; ++e) {
     log_a[e] = R(0);
     phi[e] = R(0);
   }
-  R xk1[C];
-  if (tm & (T_MPA | T_PLASMA)) ipow_n<R, C>(x, s.K - 1, xk1);
   if (tm & T_KERR) {
 #pragma unroll
     for (int e = 0; e < C; ++e) phi[e] += s.cK * x[e];
   }
-  if (tm & T_PLASMA) {
+  if (strong) {
+    R xk1[C];
+    ipow_n<R, C>(x, s.K - 1, xk1);
+    if (tm & T_PLASMA) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) phi[e] -= s.cK * x[e] * (R(1) - rcp(R(1) + xk1[e]));
-  }
-  if (tm & T_MPA) {
+      for (int e = 0; e < C; ++e) phi[e] -= s.cK * x[e] * (R(1) - rcp(R(1) + xk1[e]));
+    }
+    if (tm & T_MPA) {
 #pragma unroll
-    for (int e = 0; e < C; ++e)
-      log_a[e] -= fast_log2(R(1) + s.cM * xk1[e]) * (R(0.69314718055994530942) * s.inv2k1);
+      for (int e = 0; e < C; ++e)
+        log_a[e] -= fast_log2(R(1) + s.cM * xk1[e]) * (R(0.69314718055994530942) * s.inv2k1);
+    }
   }
   if (tm & T_ANSATZ) {
 #pragma unroll
@@ -293,7 +312,8 @@ __device__ __forceinline__ void screen_amp2_n(const ScreenConst<R>& s, const R* 
   R l2[C];
 #pragma unroll
   for (int e = 0; e < C; ++e) l2[e] = R(0);
-  if (tm & T_MPA) {
+  const bool absorb = (tm & T_MPA) && strong_n<R, C>(s, x);
+  if (absorb) {
     R xk1[C];
     ipow_n<R, C>(x, s.K - 1, xk1);
 #pragma unroll
@@ -309,7 +329,7 @@ __device__ __forceinline__ void screen_amp2_n(const ScreenConst<R>& s, const R* 
       l2[e] -= R(2) * s.cK * im * R(1.44269504088896340736);
     }
   }
-  if (tm & (T_MPA | T_ANSATZ)) {
+  if (absorb || (tm & T_ANSATZ)) {
 #pragma unroll
     for (int e = 0; e < C; ++e) out[e] = (l2[e] == R(0)) ? R(1) : fast_exp2(l2[e]);
   } else {
@@ -325,8 +345,9 @@ __device__ __forceinline__ void screen_apply_n(const ScreenConst<R>& s, cx<R>* u
   R log_a[C], phi[C];
 #pragma unroll
   for (int e = 0; e < C; ++e) x[e] = u[e].re * u[e].re + u[e].im * u[e].im;
-  screen_eval_n<R, C>(s, x, log_a, phi);
-  if (s.terms & (T_MPA | T_ANSATZ)) {
+  const bool strong = strong_n<R, C>(s, x);
+  screen_eval_n<R, C>(s, x, strong, log_a, phi);
+  if ((strong && (s.terms & T_MPA)) || (s.terms & T_ANSATZ)) {
 #pragma unroll
     for (int e = 0; e < C; ++e)
       a[e] = (log_a[e] == R(0)) ? R(1) : fast_exp2(log_a[e] * R(1.44269504088896340736));
@@ -367,12 +388,6 @@ __device__ __forceinline__ void screen_adjoint_n(const ScreenConst<R>& s, const 
     x[e] = v[e].re * v[e].re + v[e].im * v[e].im;
     log_a[e] = phi[e] = dla[e] = dphi[e] = R(0);
   }
-  R xk1[C], xk2[C];
-  if (tm & (T_MPA | T_PLASMA)) {
-    ipow_n<R, C>(x, s.K - 2, xk2);
-#pragma unroll
-    for (int e = 0; e < C; ++e) xk1[e] = xk2[e] * x[e];
-  }
   if (tm & T_KERR) {
 #pragma unroll
     for (int e = 0; e < C; ++e) {
@@ -380,21 +395,32 @@ __device__ __forceinline__ void screen_adjoint_n(const ScreenConst<R>& s, const 
       dphi[e] += s.cK;
     }
   }
-  if (tm & T_PLASMA) {
+  const bool strong = strong_n<R, C>(s, x);
+  if (tm & (T_MPA | T_PLASMA)) {
+    R xk2[C];
+    ipow_n<R, C>(x, s.K - 2, xk2);
+    if (strong) {
+      if (tm & T_PLASMA) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) {
-      const R id = rcp(R(1) + xk1[e]);
-      const R sat = R(1) - id;
-      phi[e] -= s.cK * x[e] * sat;
-      dphi[e] -= s.cK * sat * (R(s.K) * id + sat);
-    }
-  }
-  if (tm & T_MPA) {
+        for (int e = 0; e < C; ++e) {
+          const R id = rcp(R(1) + xk2[e] * x[e]);
+          const R sat = R(1) - id;
+          phi[e] -= s.cK * x[e] * sat;
+          dphi[e] -= s.cK * sat * (R(s.K) * id + sat);
+        }
+      }
+      if (tm & T_MPA) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) {
-      const R q = R(1) + s.cM * xk1[e];
-      log_a[e] -= fast_log2(q) * (R(0.69314718055994530942) * s.inv2k1);
-      dla[e] -= s.cM * xk2[e] * R(0.5) * rcp(q);
+        for (int e = 0; e < C; ++e) {
+          const R q = R(1) + s.cM * (xk2[e] * x[e]);
+          log_a[e] -= fast_log2(q) * (R(0.69314718055994530942) * s.inv2k1);
+          dla[e] -= s.cM * xk2[e] * R(0.5) * rcp(q);
+        }
+      }
+    } else if (tm & T_MPA) {
+      // q = 1: no absorption, but its derivative is not yet lost
+#pragma unroll
+      for (int e = 0; e < C; ++e) dla[e] -= s.cM * xk2[e] * R(0.5);
     }
   }
   const bool ansatz = (tm & T_ANSATZ) != 0;
@@ -422,7 +448,9 @@ __device__ __forceinline__ void screen_adjoint_n(const ScreenConst<R>& s, const 
   for (int e = 0; e < C; ++e) sin_cos(phi[e], &sn[e], &cs[e], PRECISE);
 #pragma unroll
   for (int e = 0; e < C; ++e) {
-    const R a = (log_a[e] == R(0)) ? R(1) : fast_exp2(log_a[e] * R(1.44269504088896340736));
+    const R a = (!(strong || ansatz) || log_a[e] == R(0))
+                    ? R(1)
+                    : fast_exp2(log_a[e] * R(1.44269504088896340736));
     const cx<R> ee = {a * cs[e], a * sn[e]};
     // 1 + x conj(g), g = dla + i dphi
     const cx<R> one_xg = {R(1) + x[e] * dla[e], -x[e] * dphi[e]};
