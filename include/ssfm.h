@@ -398,10 +398,9 @@ int ssfm_hot_areas(ssfm_ctx* ctx, const double* w, int32_t n, double threshold,
 
 /* ssfm_hot_areas for callers that cannot allocate device memory (code that
  * must not call hipMalloc, e.g. tight serving loops or harnesses that forbid
- * it) and have no context: the same count, with the labels, overflow flag
- * and partial counts in a fixed device array inside the library (16 MiB +
- * 4 KiB per GPU, held until the process ends) instead of a workspace.  w:
- * n x n FP64 device array [W/m^2], row-major; n <= 2048 (larger grids:
+ * it) and have no context: the same count, with the labels and the result
+ * in a fixed device array inside the library (16 MiB + 4 KiB per GPU, held
+ * until the process ends) instead of a workspace.  w: n x n FP64 device array [W/m^2], row-major; n <= 2048 (larger grids:
  * ssfm_hot_areas with a context), else SSFM_EINVAL; stream: hipStream_t or
  * NULL.  Calls no hipMalloc or hipFree.  All calls on one GPU share that
  * array: calls that overlap on one GPU (other threads or streams) race and

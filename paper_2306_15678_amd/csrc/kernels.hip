@@ -385,14 +385,17 @@ __global__ void k_lens_vjp_final(const double* __restrict__ u, const cx<R>* __re
   }
 }
 
-// fixed-order sum of the per-block partials
-__global__ void k_lens_vjp_reduce(const double* __restrict__ part, int blocks,
-                                  double* __restrict__ out) {
-  const int k = threadIdx.x;
-  if (k >= kLensGrads) return;
-  double s = 0.0;
-  for (int b = 0; b < blocks; ++b) s += part[int64_t(b) * kLensGrads + k];
-  out[k] = s;
+// Fixed-order sums of the per-block partials, one workgroup per gradient:
+// strided partial sums, then a tree (one thread walking the 512 blocks of
+// each gradient took 126 us of dependent loads).
+__global__ void __launch_bounds__(256)
+k_lens_vjp_reduce(const double* __restrict__ part, int blocks, double* __restrict__ out) {
+  __shared__ double red[4];
+  const int k = blockIdx.x;
+  double s[1] = {0.0};
+  for (int b = threadIdx.x; b < blocks; b += 256) s[0] += part[int64_t(b) * kLensGrads + k];
+  block_reduce<1, 256, false>(s, red);
+  if (threadIdx.x == 0) out[k] = s[0];
 }
 
 template <typename R>
@@ -418,8 +421,8 @@ hipError_t launch_lens_vjp_final(const double* u, const void* wk, double i_ref, 
                                  int64_t n2, double* part, double* grads, hipStream_t st) {
   hipLaunchKernelGGL((k_lens_vjp_final<R>), dim3(grid_for(n2, 256)), dim3(256), 0, st, u,
                      static_cast<const cx<R>*>(wk), 1.0 / i_ref, g_in, n2);
-  hipLaunchKernelGGL(k_lens_vjp_reduce, dim3(1), dim3(64), 0, st, part, lens_vjp_blocks(n2),
-                     grads);
+  hipLaunchKernelGGL(k_lens_vjp_reduce, dim3(kLensGrads), dim3(256), 0, st, part,
+                     lens_vjp_blocks(n2), grads);
   return hipGetLastError();
 }
 template hipError_t launch_lens_vjp_prep<float>(const double*, double, void*, int64_t,

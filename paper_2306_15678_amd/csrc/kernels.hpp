@@ -179,11 +179,16 @@ template <typename R>
 hipError_t launch_lens_apply(void* u, const void* wdif, int64_t n2, const LensDev& p,
                              hipStream_t st);
 
-// Hot-area labelling of an n x n FP64 array (labels: n^2 ints, overflow:
-// one int set if a union exceeded its retry cap) and the root count as
-// n_part per-block partial sums; spatial moment partial sums.
+// Hot-area count of an n x n FP64 array (labels: n^2 ints of scratch):
+// regions, and whether a union exceeded its retry cap.
+struct HotResult {
+  int64_t regions;
+  int32_t overflow;
+  int32_t pad;
+};
 hipError_t launch_hot_areas(const double* w, int n, double threshold, int periodic, int* labels,
-                            int* overflow, double* part, int n_part, hipStream_t s);
+                            HotResult* res, hipStream_t s);
+// Spatial moment partial sums (n_part blocks).
 hipError_t launch_moment(const double* w, int n, double dx, double p, int m, double* part,
                          int n_part, hipStream_t s);
 // Measure-vector partials: n_part blocks x [sum w, sum w r^2, sum w^2,
@@ -195,13 +200,11 @@ hipError_t launch_block_mean(const double* src, int n, int b, double* dst,
                              hipStream_t s);
 
 // Allocation-free hot-area count: a file-scope device array (one per GPU)
-// holds the labels of grids up to kStaticMaxN^2, the overflow flag at
-// kStaticOverflowOff and kStaticParts partial counts at kStaticPartOff.
+// holds the labels of grids up to kStaticMaxN^2 and the result at
+// kStaticResultOff.
 constexpr int kStaticMaxN = 2048;
-constexpr int kStaticParts = 256;
-constexpr size_t kStaticOverflowOff = size_t(kStaticMaxN) * kStaticMaxN * sizeof(int);
-constexpr size_t kStaticPartOff = kStaticOverflowOff + 256;
-constexpr size_t kStaticScratchBytes = kStaticPartOff + kStaticParts * sizeof(double);
+constexpr size_t kStaticResultOff = size_t(kStaticMaxN) * kStaticMaxN * sizeof(int);
+constexpr size_t kStaticScratchBytes = kStaticResultOff + 4096;
 // Device address of the current device's copy (looked up once per device).
 hipError_t static_scratch(void** out);
 

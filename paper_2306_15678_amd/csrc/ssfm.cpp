@@ -2293,6 +2293,24 @@ int ssfm_lens_vjp(ssfm_ctx* c, int32_t inst, const ssfm_lens* lens, const void* 
                        static_cast<const double*>(g_out), static_cast<double*>(g_in), grad);
 }
 
+namespace {
+// The result of a count whose n^2 labels start at base.
+HotResult* hot_result_at(char* base, int32_t n) {
+  return reinterpret_cast<HotResult*>(base + align_up(sizeof(int) * size_t(n) * n));
+}
+
+int count_hot_areas(const double* w, int32_t n, double threshold, int32_t periodic, int* labels,
+                    HotResult* res, hipStream_t st, int64_t* count) {
+  HIP_TRY(launch_hot_areas(w, n, threshold, periodic ? 1 : 0, labels, res, st));
+  HotResult h{};
+  HIP_TRY(hipMemcpyAsync(&h, res, sizeof(h), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipStreamSynchronize(st));
+  if (h.overflow) return fail(SSFM_EHIP, "hot-area labelling: a union exceeded its retry cap");
+  *count = h.regions;
+  return SSFM_OK;
+}
+}  // namespace
+
 int ssfm_hot_areas(ssfm_ctx* c, const double* w, int32_t n, double threshold, int32_t periodic,
                    int64_t* count) {
   if (int r = check_ctx(c)) return r;
@@ -2301,23 +2319,9 @@ int ssfm_hot_areas(ssfm_ctx* c, const double* w, int32_t n, double threshold, in
     return fail(SSFM_EINVAL, "n=%d must be in [1, %d] (the context's largest grid)", n,
                 c->L.max_n);
   if (!std::isfinite(threshold)) return fail(SSFM_EINVAL, "threshold must be finite");
-  // labels (n^2 ints) and the overflow flag live in the staging buffer
-  int* labels = c->at<int>(c->L.stage);
-  int* overflow = labels + int64_t(n) * n;
-  double* part = c->at<double>(c->L.sumsq_part);
-  constexpr int kParts = 256;
-  HIP_TRY(launch_hot_areas(w, n, threshold, periodic ? 1 : 0, labels, overflow, part, kParts,
-                           c->stream));
-  double host[kParts];
-  int ovf = 0;
-  HIP_TRY(hipMemcpyAsync(host, part, sizeof(host), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(&ovf, overflow, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  if (ovf) return fail(SSFM_EHIP, "hot-area labelling: a union exceeded its retry cap");
-  double total = 0.0;
-  for (int k = 0; k < kParts; ++k) total += host[k];
-  *count = int64_t(total);
-  return SSFM_OK;
+  // labels (n^2 ints) and the result live in the staging buffer
+  return count_hot_areas(w, n, threshold, periodic, c->at<int>(c->L.stage),
+                         hot_result_at(c->at<char>(c->L.stage), n), c->stream, count);
 }
 
 int ssfm_hot_areas_static(const double* w, int32_t n, double threshold, int32_t periodic,
@@ -2332,22 +2336,9 @@ int ssfm_hot_areas_static(const double* w, int32_t n, double threshold, int32_t 
   void* base = nullptr;
   HIP_TRY(static_scratch(&base));
   char* sc = static_cast<char*>(base);
-  int* labels = reinterpret_cast<int*>(sc);
-  int* overflow = reinterpret_cast<int*>(sc + kStaticOverflowOff);
-  double* part = reinterpret_cast<double*>(sc + kStaticPartOff);
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  HIP_TRY(launch_hot_areas(w, n, threshold, periodic ? 1 : 0, labels, overflow, part,
-                           kStaticParts, st));
-  double host[kStaticParts];
-  int ovf = 0;
-  HIP_TRY(hipMemcpyAsync(host, part, sizeof(host), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&ovf, overflow, sizeof(int), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
-  if (ovf) return fail(SSFM_EHIP, "hot-area labelling: a union exceeded its retry cap");
-  double total = 0.0;
-  for (int k = 0; k < kStaticParts; ++k) total += host[k];
-  *count = int64_t(total);
-  return SSFM_OK;
+  return count_hot_areas(w, n, threshold, periodic, reinterpret_cast<int*>(sc),
+                         reinterpret_cast<HotResult*>(sc + kStaticResultOff),
+                         static_cast<hipStream_t>(stream), count);
 }
 
 namespace {
