@@ -454,16 +454,16 @@ hipError_t launch_copy(const void* src, void* dst, int64_t n_elem, hipStream_t s
 template hipError_t launch_copy<float>(const void*, void*, int64_t, hipStream_t);
 template hipError_t launch_copy<double>(const void*, void*, int64_t, hipStream_t);
 
-// One workgroup per (beam, step): thread t sums the beam's partials t,
+// One workgroup per (beam from b0, step): thread t sums the beam's partials t,
 // t + 256, ... in order, then a fixed tree across the workgroup, so the
 // result depends only on the beam's own partials (a beam in a batch sums
 // exactly as it does alone).
 __global__ void __launch_bounds__(256)
 k_diag_finalize(const double* __restrict__ part, int64_t stride,
                 const int32_t* __restrict__ begin_even, const int32_t* __restrict__ begin_odd,
-                double* __restrict__ diag, int64_t ring0, int64_t cap) {
+                int b0, double* __restrict__ diag, int64_t ring0, int64_t cap) {
   __shared__ double red[8];
-  const int b = blockIdx.x;
+  const int b = b0 + int(blockIdx.x);
   const int step = blockIdx.y;
   const int32_t* begin = ((ring0 + step) & 1) ? begin_odd : begin_even;
   const double* p = part + int64_t(step) * stride * 2;
@@ -482,11 +482,11 @@ k_diag_finalize(const double* __restrict__ part, int64_t stride,
 }
 
 hipError_t launch_diag_finalize(const double* part, int64_t stride, const int32_t* begin_even,
-                                const int32_t* begin_odd, int n_beams, int steps,
+                                const int32_t* begin_odd, int b0, int n_beams, int steps,
                                 double* diag, int64_t ring0, int64_t cap, hipStream_t s) {
   if (steps <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_diag_finalize, dim3(n_beams, steps), dim3(256), 0, s, part, stride,
-                     begin_even, begin_odd, diag, ring0, cap);
+                     begin_even, begin_odd, b0, diag, ring0, cap);
   return hipGetLastError();
 }
 

@@ -132,12 +132,13 @@ hipError_t launch_seed(int mode, const void* state, const InstDev* inst, int b,
 template <typename R>
 hipError_t launch_copy(const void* src, void* dst, int64_t n_elem, hipStream_t s);
 
-// Reduce the diag partials of `steps` consecutive steps, stride entries
-// each: part[step][stride][2] -> diag[b][(ring0 + step) % cap][2].  Beam b's
-// partials of a step are entries [begin[b], begin[b + 1]); begin is
-// begin_even for even steps (ring0 + step) and begin_odd for odd ones.
+// For beams [b0, b0 + n_beams): reduce the diag partials of `steps`
+// consecutive steps, stride entries each: part[step][stride][2] ->
+// diag[b][(ring0 + step) % cap][2].  Beam b's partials of a step are entries
+// [begin[b], begin[b + 1]); begin is begin_even for even steps (ring0 +
+// step) and begin_odd for odd ones.
 hipError_t launch_diag_finalize(const double* part, int64_t stride, const int32_t* begin_even,
-                                const int32_t* begin_odd, int n_beams, int steps,
+                                const int32_t* begin_odd, int b0, int n_beams, int steps,
                                 double* diag, int64_t ring0, int64_t cap, hipStream_t s);
 
 // Per beam the fixed-order sum of its entries of two [entries][8] FP64

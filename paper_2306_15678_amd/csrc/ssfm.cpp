@@ -519,30 +519,52 @@ bool group_has_plane(const ssfm_ctx* c, const Group& g, int64_t step) {
   return false;
 }
 
-// One pass over every beam: one launch per grid-size group.  On the main
-// chain (the context's stream, the primary stream of a graph capture) the
-// groups run concurrently (group g > 0 on its own stream, forked from and
-// joined back to st), so their ramps and tails overlap.  On the auxiliary
-// chain (the checkpoint recompute, itself a fork of the main chain) they
-// run in sequence on that stream: a stream capture must join every fork
-// to its primary stream, and a fork of a fork would be joined to the
-// auxiliary stream instead.
+// The size groups [g0, g1) and the stream that their passes go to.
+struct Chain {
+  size_t g0, g1;
+  hipStream_t st;
+};
+
+Chain whole(ssfm_ctx* c, hipStream_t st = nullptr) {
+  return {0, c->groups.size(), st ? st : c->stream};
+}
+
+// Runs body(chain) for chains that cover every size group.  Beams never
+// wait for one another, so each group marches on its own stream (group 0 on
+// the context's), forked and joined once around the whole run of passes: a
+// group of few small beams fills a fraction of the chip, and joining the
+// groups after every pass kept each step as long as its slowest launch plus
+// two event hops (11 beams of 256^2 to
+// 1024^2, 24 steps: 2060 us; as chains 1650).
+// split = false, or a context without the streams: one chain of all groups.
+template <typename F>
+int each_chain(ssfm_ctx* c, bool split, F body) {
+  const size_t ng = c->groups.size();
+  if (!split || ng < 2 || c->gstream.size() + 1 < ng) return body(whole(c));
+  HIP_TRY(hipEventRecord(c->gfork, c->stream));
+  for (size_t g = 1; g < ng; ++g) HIP_TRY(hipStreamWaitEvent(c->gstream[g - 1], c->gfork, 0));
+  int r = SSFM_OK;
+  for (size_t g = 0; g < ng && r == SSFM_OK; ++g)
+    r = body(Chain{g, g + 1, g > 0 ? c->gstream[g - 1] : c->stream});
+  // joined on every path: the streams carry no work past the call
+  for (size_t g = 1; g < ng; ++g) {
+    HIP_TRY(hipEventRecord(c->gjoin[g - 1], c->gstream[g - 1]));
+    HIP_TRY(hipStreamWaitEvent(c->stream, c->gjoin[g - 1], 0));
+  }
+  return r;
+}
+
+// One pass over the beams of a chain: one launch per grid-size group, in
+// sequence.
 template <typename R>
-int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, hipStream_t st = nullptr,
-             int table = T_PROP, const hipEvent_t* ev = nullptr) {
+int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, const Chain& ch, int table = T_PROP,
+             const hipEvent_t* ev = nullptr) {
   const bool col = is_col_kind(kind);
   const bool adj = kind == ROW_ADJ || kind == COL_ADJ;
   const int slot = (adj ? P_ROW_ADJ : P_ROW) + (col ? 1 : 0);
   const int32_t flags = a.flags;
   const bool screen = (adj || kind == ROW_FWD || kind == COL_FWD) && (flags & PASS_SCREEN);
-  if (!st) st = c->stream;
-  const size_t ng = c->groups.size();
-  const bool fork = st != c->aux && ng > 1 && c->gstream.size() + 1 >= ng;
-  if (fork) {
-    HIP_TRY(hipEventRecord(c->gfork, st));
-    for (size_t g = 1; g < ng; ++g) HIP_TRY(hipStreamWaitEvent(c->gstream[g - 1], c->gfork, 0));
-  }
-  for (size_t gi = 0; gi < ng; ++gi) {
+  for (size_t gi = ch.g0; gi < ch.g1; ++gi) {
     const Group& g = c->groups[gi];
     a.off0 = c->inst[g.beam0].off;
     a.prop0 = g.prop + int64_t(table) * g.n;
@@ -552,16 +574,21 @@ int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, hipStream_t st = nullptr,
     a.part0 = g.part0[slot];
     a.n_tiles = g.count * (g.n / g.lines[slot]);
     a.flags = flags | ((screen && group_has_plane(c, g, a.step)) ? PASS_PLANE : 0);
-    hipStream_t sg = (fork && gi > 0) ? c->gstream[gi - 1] : st;
     const LaunchEv le = ev ? LaunchEv{ev[2 * gi], ev[2 * gi + 1]} : LaunchEv{nullptr, nullptr};
-    HIP_TRY(launch_pass<R>(kind, g.n, g.variant(slot), a, sg, ev ? &le : nullptr));
+    HIP_TRY(launch_pass<R>(kind, g.n, g.variant(slot), a, ch.st, ev ? &le : nullptr));
   }
-  if (fork) {
-    for (size_t g = 1; g < ng; ++g) {
-      HIP_TRY(hipEventRecord(c->gjoin[g - 1], c->gstream[g - 1]));
-      HIP_TRY(hipStreamWaitEvent(st, c->gjoin[g - 1], 0));
-    }
-  }
+  return SSFM_OK;
+}
+
+// Power and peak of `steps` steps from context step `step0`, for the beams of
+// a chain.
+int finalize_diag(ssfm_ctx* c, const int32_t* begin_even, const int32_t* begin_odd, int steps,
+                  int64_t step0, const Chain& ch) {
+  const int b0 = c->groups[ch.g0].beam0;
+  const Group& last = c->groups[ch.g1 - 1];
+  HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), c->L.part_stride, begin_even,
+                               begin_odd, b0, last.beam0 + last.count - b0, steps,
+                               c->at<double>(c->L.diag), step0, c->L.diag_cap, ch.st));
   return SSFM_OK;
 }
 
@@ -614,7 +641,7 @@ struct MarchBuffers {
 // (single) ending pass.
 template <typename R, typename Pend, typename Rec>
 int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
-                  const MarchBuffers& m, Pend pend, Rec rec, bool part, hipStream_t st,
+                  const MarchBuffers& m, Pend pend, Rec rec, bool part, const Chain& ch,
                   const ssfm_ctx::PassSample* open, const ssfm_ctx::PassSample* end) {
   const int32_t raw = c->strang ? PASS_RAW : 0;  // Strang: |U|^2 = |V|^2 summed as it is
   if (i0 == 0) {
@@ -625,7 +652,7 @@ int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
     a.step = pend(0);
     a.flags = PASS_OP2 | (a.step >= 0 ? PASS_SCREEN : 0);
     const bool col = first_axis_col(step0);
-    if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, st, T_PROP,
+    if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, ch, T_PROP,
                             open ? open->ev.data() : nullptr))
       return r;
   }
@@ -644,16 +671,15 @@ int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
       a.flags |= PASS_SCREEN | PASS_OP2;
     }
     const bool col = second_axis_col(step0 + i);
-    if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, st, T_PROP,
+    if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, ch, T_PROP,
                             end ? end->ev.data() : nullptr))
       return r;
     if (part && (slot == kDiagChunk - 1 || i == i1 - 1)) {
       const int32_t* begins = c->at<int32_t>(c->L.begins);
       const size_t nb = c->desc.size() + 1;
-      HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), c->L.part_stride,
-                                   begins + P_COL * nb, begins + P_ROW * nb,
-                                   int(c->desc.size()), slot + 1, c->at<double>(c->L.diag),
-                                   chunk_start, c->L.diag_cap, c->stream));
+      if (int r = finalize_diag(c, begins + P_COL * nb, begins + P_ROW * nb, slot + 1, chunk_start,
+                                ch))
+        return r;
       chunk_start = step0 + i + 1;
     }
   }
@@ -668,13 +694,15 @@ template <typename R>
 int enqueue_propagate(ssfm_ctx* c, int64_t n, int64_t step0, bool pending0, int64_t i0,
                       int64_t i1, const ssfm_ctx::PassSample* open,
                       const ssfm_ctx::PassSample* end) {
-  void* S = c->field(c->L.S);
-  auto pend = [&](int64_t i) {
-    return c->strang ? step0 + i : (i == 0 && !pending0) ? -1 : step0 + i - 1;
-  };
-  return enqueue_march<R>(
-      c, n, step0, i0, i1, MarchBuffers{S, S, S}, pend,
-      [](int64_t) -> void* { return nullptr; }, true, c->stream, open, end);
+  return each_chain(c, true, [&](const Chain& ch) {
+    void* S = c->field(c->L.S);
+    auto pend = [&](int64_t i) {
+      return c->strang ? step0 + i : (i == 0 && !pending0) ? -1 : step0 + i - 1;
+    };
+    return enqueue_march<R>(
+        c, n, step0, i0, i1, MarchBuffers{S, S, S}, pend,
+        [](int64_t) -> void* { return nullptr; }, true, ch, open, end);
+  });
 }
 
 // Steps i0 <= i < i1 of a finite-difference march from step step0 + i0, on
@@ -684,13 +712,13 @@ int enqueue_propagate(ssfm_ctx* c, int64_t n, int64_t step0, bool pending0, int6
 // side); the last row pass of a step writes U+ = 2 Ubar - U and its power
 // partials and, unless the range ends, starts the next step.
 template <typename R>
-int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1) {
+int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1, const Chain& ch) {
   PassArgs<R> a = base_args<R>(c);
   a.state = c->field(c->L.S);
   a.src = c->field(c->L.S);
   a.dst = c->field(c->L.Wk);
   a.flags = 0;
-  if (int r = run_pass<R>(c, ROW_FD, a)) return r;
+  if (int r = run_pass<R>(c, ROW_FD, a, ch)) return r;
   PassArgs<R> col = base_args<R>(c);
   col.src = c->field(c->L.Wk);
   col.dst = c->field(c->L.Wk);
@@ -699,18 +727,16 @@ int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1) {
   for (int64_t i = i0; i < i1; ++i) {
     const int slot = int((i - i0) % kDiagChunk);
     for (int k = 1; k <= c->fd_iters; ++k) {
-      if (int r = run_pass<R>(c, COL_FD, col, nullptr, T_FD)) return r;
+      if (int r = run_pass<R>(c, COL_FD, col, ch, T_FD)) return r;
       const bool fin = (k == c->fd_iters);
       a.flags = FD_SPECTRAL | (fin ? FD_FINISH : 0) | ((fin && i == i1 - 1) ? FD_LAST : 0);
       a.part = fin ? c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.part_stride
                    : nullptr;
-      if (int r = run_pass<R>(c, ROW_FD, a)) return r;
+      if (int r = run_pass<R>(c, ROW_FD, a, ch)) return r;
     }
     if (slot == kDiagChunk - 1 || i == i1 - 1) {
       const int32_t* rows = c->at<int32_t>(c->L.begins) + P_ROW * (c->desc.size() + 1);
-      HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), c->L.part_stride, rows, rows,
-                                   int(c->desc.size()), slot + 1, c->at<double>(c->L.diag),
-                                   chunk_start, c->L.diag_cap, c->stream));
+      if (int r = finalize_diag(c, rows, rows, slot + 1, chunk_start, ch)) return r;
       chunk_start = step0 + i + 1;
     }
   }
@@ -825,7 +851,10 @@ int do_propagate(ssfm_ctx* c, int64_t n) {
   if (c->fd) {
     // one graph per (start step, length): the diagnostics ring slots depend
     // on the absolute step
-    int r = maybe_graph(c, 3, step0, n, 0, n, [&] { return enqueue_fd<R>(c, step0, 0, n); });
+    int r = maybe_graph(c, 3, step0, n, 0, n, [&] {
+      return each_chain(c, true,
+                        [&](const Chain& ch) { return enqueue_fd<R>(c, step0, 0, n, ch); });
+    });
     if (r) return r;
     c->step += n;
     c->pending = false;
@@ -859,19 +888,22 @@ int half_steps(ssfm_ctx* c, bool forward) {
   a.src = c->field(c->L.Wk);
   a.dst = c->field(c->L.Wk);
   a.flags = PASS_OP2;
-  if (int r = run_pass<R>(c, ROW_FWD, a, nullptr, forward ? T_HALF : T_BACK)) return r;
-  return run_pass<R>(c, COL_FWD, a, nullptr, forward ? T_HALF : T_BACK);
+  return each_chain(c, true, [&](const Chain& ch) {
+    if (int r = run_pass<R>(c, ROW_FWD, a, ch, forward ? T_HALF : T_BACK)) return r;
+    return run_pass<R>(c, COL_FWD, a, ch, forward ? T_HALF : T_BACK);
+  });
 }
 
-// Lam <- L(+-dz/2) Lam in place (the half-step tables, no screen).
+// Lam <- L(+-dz/2) Lam in place (the half-step tables, no screen), for the
+// beams of a chain.
 template <typename R>
-int half_step_lam(ssfm_ctx* c, bool forward) {
+int half_step_lam(ssfm_ctx* c, bool forward, const Chain& ch) {
   PassArgs<R> a = base_args<R>(c);
   a.src = c->field(c->L.Lam);
   a.dst = c->field(c->L.Lam);
   a.flags = PASS_OP2;
-  if (int r = run_pass<R>(c, ROW_FWD, a, nullptr, forward ? T_HALF : T_BACK)) return r;
-  return run_pass<R>(c, COL_FWD, a, nullptr, forward ? T_HALF : T_BACK);
+  if (int r = run_pass<R>(c, ROW_FWD, a, ch, forward ? T_HALF : T_BACK)) return r;
+  return run_pass<R>(c, COL_FWD, a, ch, forward ? T_HALF : T_BACK);
 }
 
 // Apply the pending screen in place (state becomes U_n).
@@ -944,10 +976,12 @@ int enqueue_record(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1
                    const ssfm_ctx::PassSample* open, const ssfm_ctx::PassSample* end) {
   const Segments g = rec_segments(c, n);
   void* S = c->field(c->L.S);
-  return enqueue_march<R>(
-      c, n, step0, i0, i1, MarchBuffers{S, S, S},
-      [&](int64_t i) { return rec_pending(c, step0, step0 + i); },
-      [&](int64_t i) { return rec_slot(c, g, i); }, true, c->stream, open, end);
+  return each_chain(c, true, [&](const Chain& ch) {
+    return enqueue_march<R>(
+        c, n, step0, i0, i1, MarchBuffers{S, S, S},
+        [&](int64_t i) { return rec_pending(c, step0, step0 + i); },
+        [&](int64_t i) { return rec_slot(c, g, i); }, true, ch, open, end);
+  });
 }
 
 template <typename R>
@@ -978,7 +1012,11 @@ int do_record(ssfm_ctx* c, int64_t n) {
 // (into the other bank, through the work buffer): segment k-1 after the
 // adjoint of segment k on the same stream, or (overlap_recompute) on the
 // auxiliary stream while the adjoint of segment k runs on the main stream,
-// the two chains joining before the adjoint of segment k-1.
+// the two joining before the adjoint of segment k-1.  The size groups sweep
+// independently: through the whole backward, or with the overlap through
+// the adjoint of each segment (the recompute takes them in sequence on its
+// stream: a stream capture must join every fork to its primary stream, and a
+// fork of a fork would be joined to the auxiliary one instead).
 template <typename R>
 int enqueue_backward(ssfm_ctx* c) {
   const int64_t n = c->rec_steps, step0 = c->rec_step0;
@@ -995,7 +1033,7 @@ int enqueue_backward(ssfm_ctx* c) {
   // s_{kM+1} .. of segment k from its checkpoint: the work buffer, which
   // nothing else uses during the backward sweep, holds the half-diffracted
   // field
-  auto recompute = [&](int64_t k, hipStream_t st) -> int {
+  auto recompute = [&](int64_t k, const Chain& ch) -> int {
     const int64_t s0 = k * M;
     const int64_t len = std::min<int64_t>(M, n - s0);
     if (len < 2) return SSFM_OK;
@@ -1003,14 +1041,15 @@ int enqueue_backward(ssfm_ctx* c) {
         c, len - 1, step0 + s0, 0, len - 1,
         MarchBuffers{sv(k, 0), c->field(c->L.Wk), slot(k, len - 2)},
         [&](int64_t i) { return rec_pending(c, step0, step0 + s0 + i); },
-        [&](int64_t i) { return i > 0 ? slot(k, i - 1) : nullptr; }, false, st, nullptr,
+        [&](int64_t i) { return i > 0 ? slot(k, i - 1) : nullptr; }, false, ch, nullptr,
         nullptr);
   };
   // the pass along one axis that ends adjoint step s + 1 and begins step s
   // (of the march's n; s = n opens the sweep), in place on the cotangent:
   // the adjoints of step s's first factor, of the screen before it (with
   // the stored V_s), and of the factor that precedes the screen
-  auto adj_pass = [&](int64_t s, const void* v_s, const ssfm_ctx::PassSample* ts) -> int {
+  auto adj_pass = [&](int64_t s, const void* v_s, const Chain& ch,
+                      const ssfm_ctx::PassSample* ts) -> int {
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.Lam);
     a.dst = c->field(c->L.Lam);
@@ -1023,40 +1062,39 @@ int enqueue_backward(ssfm_ctx* c) {
       if (a.step >= 0) a.flags |= PASS_SCREEN;
     }
     if (s > 0) a.flags |= PASS_OP2;
-    return run_pass<R>(c, col ? COL_ADJ : ROW_ADJ, a, nullptr, T_PROP,
+    return run_pass<R>(c, col ? COL_ADJ : ROW_ADJ, a, ch, T_PROP,
                        ts ? ts->ev.data() : nullptr);
   };
-  auto timed_adj_pass = [&](int64_t s, const void* v_s) -> int {
-    ssfm_ctx::PassSample ps;
-    const bool have = take_sample(c, &ps);
-    ps.col = (s == n) ? second_axis_col(step0 + n - 1) : first_axis_col(step0 + s);
-    const int r = adj_pass(s, v_s, have ? &ps : nullptr);
-    if (have) c->adj_samples.push_back(std::move(ps));
-    return r;
+  // a sampled pass: one sample of every group's events
+  std::map<int64_t, size_t> sample_of;
+  auto timed_adj_pass = [&](int64_t s, const void* v_s, const Chain& ch) -> int {
+    auto it = sample_of.find(s);
+    if (it == sample_of.end() && ch.g0 == 0) {
+      ssfm_ctx::PassSample ps;
+      if (take_sample(c, &ps)) {
+        ps.col = (s == n) ? second_axis_col(step0 + n - 1) : first_axis_col(step0 + s);
+        it = sample_of.emplace(s, c->adj_samples.size()).first;
+        c->adj_samples.push_back(std::move(ps));
+      }
+    }
+    return adj_pass(s, v_s, ch, it == sample_of.end() ? nullptr : &c->adj_samples[it->second]);
   };
   HIP_TRY(launch_fill_f64(c->at<double>(c->L.theta_rows), 8 * c->L.theta_row_parts, 0.0,
                           c->stream));
   HIP_TRY(launch_fill_f64(c->at<double>(c->L.theta_cols), 8 * c->L.theta_col_parts, 0.0,
                           c->stream));
+  const int64_t every = c->timing_every;
   // Strang: the seed is the cotangent of U_N = L(-dz/2) V_N, so the march's
   // adjoint starts from L(dz/2) of it (the adjoint of the read-out)
-  if (c->strang)
-    if (int r = half_step_lam<R>(c, true)) return r;
-  if (g.recomputed(n_seg - 1)) {
-    if (int r = recompute(n_seg - 1, c->stream)) return r;
-  }
-  const int64_t every = c->timing_every;
-  if (int r = (every > 0 && n == 1) ? timed_adj_pass(n, nullptr) : adj_pass(n, nullptr, nullptr))
-    return r;
-  for (int64_t k = n_seg - 1; k >= 0; --k) {
-    const bool rec_prev = k >= 1 && g.recomputed(k - 1);
-    const bool overlap = rec_prev && c->overlap_recompute;
-    if (overlap) {
-      HIP_TRY(hipEventRecord(c->ev_fork, c->stream));
-      HIP_TRY(hipStreamWaitEvent(c->aux, c->ev_fork, 0));
-      if (int r = recompute(k - 1, c->aux)) return r;
-      HIP_TRY(hipEventRecord(c->ev_join, c->aux));
-    }
+  auto open = [&](const Chain& ch) -> int {
+    if (c->strang)
+      if (int r = half_step_lam<R>(c, true, ch)) return r;
+    if (g.recomputed(n_seg - 1))
+      if (int r = recompute(n_seg - 1, ch)) return r;
+    return (every > 0 && n == 1) ? timed_adj_pass(n, nullptr, ch)
+                                 : adj_pass(n, nullptr, ch, nullptr);
+  };
+  auto segment = [&](int64_t k, const Chain& ch) -> int {
     const int64_t s0 = k * M;
     const int64_t len = std::min<int64_t>(M, n - s0);
     for (int64_t i = len - 1; i >= 0; --i) {
@@ -1065,19 +1103,44 @@ int enqueue_backward(ssfm_ctx* c) {
       // the other axis)
       const bool sampled = every > 0 && k == 0 && s % every == every / 2;
       const bool after = every > 0 && k == 0 && i < len - 1 && (s + 1) % every == every / 2;
-      if (sampled) ++c->n_adj_samples;
-      if (int r = (sampled || after) ? timed_adj_pass(s, sv(k, i)) : adj_pass(s, sv(k, i), nullptr))
+      if (sampled && ch.g0 == 0) ++c->n_adj_samples;
+      if (int r = (sampled || after) ? timed_adj_pass(s, sv(k, i), ch)
+                                     : adj_pass(s, sv(k, i), ch, nullptr))
         return r;
     }
-    if (overlap) {
-      HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_join, 0));
-    } else if (rec_prev) {
-      if (int r = recompute(k - 1, c->stream)) return r;
-    }
-  }
+    return SSFM_OK;
+  };
   // Strang: V_0 = L(dz/2) U_0, so dL/dU_0 = L(-dz/2) dL/dV_0
-  if (c->strang)
-    if (int r = half_step_lam<R>(c, false)) return r;
+  auto close = [&](const Chain& ch) -> int {
+    return c->strang ? half_step_lam<R>(c, false, ch) : SSFM_OK;
+  };
+  const bool overlap = c->overlap_recompute && g.first_kept > 0 && n_seg > 1;
+  if (!overlap) {
+    const int r = each_chain(c, true, [&](const Chain& ch) -> int {
+      if (int q = open(ch)) return q;
+      for (int64_t k = n_seg - 1; k >= 0; --k) {
+        if (int q = segment(k, ch)) return q;
+        if (k >= 1 && g.recomputed(k - 1))
+          if (int q = recompute(k - 1, ch)) return q;
+      }
+      return close(ch);
+    });
+    if (r) return r;
+  } else {
+    if (int r = each_chain(c, true, open)) return r;
+    for (int64_t k = n_seg - 1; k >= 0; --k) {
+      const bool rec_prev = k >= 1 && g.recomputed(k - 1);
+      if (rec_prev) {
+        HIP_TRY(hipEventRecord(c->ev_fork, c->stream));
+        HIP_TRY(hipStreamWaitEvent(c->aux, c->ev_fork, 0));
+        if (int r = recompute(k - 1, whole(c, c->aux))) return r;
+        HIP_TRY(hipEventRecord(c->ev_join, c->aux));
+      }
+      if (int r = each_chain(c, true, [&](const Chain& ch) { return segment(k, ch); })) return r;
+      if (rec_prev) HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_join, 0));
+    }
+    if (int r = each_chain(c, true, close)) return r;
+  }
   const int32_t* begins = c->at<int32_t>(c->L.begins);
   const size_t nb = c->desc.size() + 1;
   HIP_TRY(launch_reduce_theta(c->at<double>(c->L.theta_rows), begins + P_ROW_ADJ * nb,
@@ -1221,12 +1284,12 @@ int do_gen_screens(ssfm_ctx* c) {
     a.src = c->field(c->L.Wk);
     a.dst = c->field(c->L.Wk);
     a.pair = p;
-    if (int r = run_pass<R>(c, ROW_INV, a)) return r;
+    if (int r = run_pass<R>(c, ROW_INV, a, whole(c))) return r;
     PassArgs<R> b = base_args<R>(c);
     b.src = c->field(c->L.Wk);
     b.planes_out = c->at<R>(c->L.screens);
     b.pair = p;
-    if (int r = run_pass<R>(c, COL_INV, b)) return r;
+    if (int r = run_pass<R>(c, COL_INV, b, whole(c))) return r;
     if (n_sub > 0)
       HIP_TRY(launch_subharmonic_apply<R>(c->at<SubBeam>(c->L.subh_beams), n_sub,
                                           c->at<InstDev>(c->L.inst), p, max_n2,
@@ -1367,16 +1430,19 @@ int upload_lens_filter(ssfm_ctx* c, int b, double l_dif, std::vector<unsigned ch
   return SSFM_OK;
 }
 
-// Wk <- the lens filter applied to Wk (row and column passes with the filter
-// tables in place of the propagators, no screen).
+// Beam b of Wk (and its group's others) <- the lens filter applied to it (row
+// and column passes with the filter tables in place of the propagators, no
+// screen).
 template <typename R>
-int lens_filter_passes(ssfm_ctx* c) {
+int lens_filter_passes(ssfm_ctx* c, int b) {
   PassArgs<R> a = base_args<R>(c);
   a.src = c->field(c->L.Wk);
   a.dst = c->field(c->L.Wk);
   a.flags = PASS_OP2;
-  if (int r = run_pass<R>(c, ROW_FWD, a, nullptr, T_LENS)) return r;
-  return run_pass<R>(c, COL_FWD, a, nullptr, T_LENS);
+  const size_t gi = size_t(&group_of(c, b) - c->groups.data());
+  const Chain ch{gi, gi + 1, c->stream};
+  if (int r = run_pass<R>(c, ROW_FWD, a, ch, T_LENS)) return r;
+  return run_pass<R>(c, COL_FWD, a, ch, T_LENS);
 }
 
 LensDev lens_dev(const ssfm_instance_desc& d, const ssfm_lens& l) {
@@ -1409,9 +1475,9 @@ int do_lens_vjp(ssfm_ctx* c, int b, const ssfm_lens& l, const double* u, const d
   std::vector<unsigned char> blob;
   if (int r = upload_lens_filter<R>(c, b, l.l_dif, &blob)) return r;
   HIP_TRY(launch_lens_vjp_prep<R>(u, d.i_ref, wk, n2, c->stream));
-  if (int r = lens_filter_passes<R>(c)) return r;
+  if (int r = lens_filter_passes<R>(c, b)) return r;
   HIP_TRY(launch_lens_vjp_point<R>(u, g_out, wk, g_in, n2, lens_dev(d, l), part, c->stream));
-  if (int r = lens_filter_passes<R>(c)) return r;
+  if (int r = lens_filter_passes<R>(c, b)) return r;
   HIP_TRY(launch_lens_vjp_final<R>(u, wk, d.i_ref, g_in, n2, part, sums, c->stream));
   double all[kLensGrads];
   HIP_TRY(hipMemcpyAsync(all, sums, sizeof(all), hipMemcpyDeviceToHost, c->stream));
@@ -1436,7 +1502,7 @@ int do_apply_lens(ssfm_ctx* c, int b, const ssfm_lens& l) {
   std::vector<unsigned char> blob;
   if (int r = upload_lens_filter<R>(c, b, l.l_dif, &blob)) return r;
   HIP_TRY(launch_lens_prep<R>(c->field(c->L.S), c->field(c->L.Wk), c->L.field_elems, c->stream));
-  if (int r = lens_filter_passes<R>(c)) return r;
+  if (int r = lens_filter_passes<R>(c, b)) return r;
   const LensDev p = lens_dev(d, l);
   const int64_t off = c->inst[b].off;
   HIP_TRY(launch_lens_apply<R>(static_cast<char*>(c->field(c->L.S)) + off * c->el,
@@ -2158,10 +2224,10 @@ int ssfm_time_adjoint_passes(ssfm_ctx* c, int32_t reps, double* ms_col, double* 
     b.part = c->at<double>(c->L.theta_rows);
     HIP_TRY(hipEventRecord(ev.e[0], c->stream));
     for (int i = 0; i < reps; ++i)
-      if (int q = run_pass<R>(c, COL_ADJ, a)) return q;
+      if (int q = run_pass<R>(c, COL_ADJ, a, whole(c))) return q;
     HIP_TRY(hipEventRecord(ev.e[1], c->stream));
     for (int i = 0; i < reps; ++i)
-      if (int q = run_pass<R>(c, ROW_ADJ, b)) return q;
+      if (int q = run_pass<R>(c, ROW_ADJ, b, whole(c))) return q;
     HIP_TRY(hipEventRecord(ev.e[2], c->stream));
     return SSFM_OK;
   };
@@ -2202,10 +2268,10 @@ int ssfm_time_passes(ssfm_ctx* c, int32_t reps, double* ms_row, double* ms_col,
     b.src = c->field(c->L.Wk);
     HIP_TRY(hipEventRecord(e0, c->stream));
     for (int i = 0; i < reps; ++i)
-      if (int q = run_pass<R>(c, ROW_FWD, a)) return q;
+      if (int q = run_pass<R>(c, ROW_FWD, a, whole(c))) return q;
     HIP_TRY(hipEventRecord(e1, c->stream));
     for (int i = 0; i < reps; ++i)
-      if (int q = run_pass<R>(c, COL_FWD, b)) return q;
+      if (int q = run_pass<R>(c, COL_FWD, b, whole(c))) return q;
     HIP_TRY(hipEventRecord(e2, c->stream));
     return SSFM_OK;
   };
