@@ -1,6 +1,6 @@
 // kernels.hip -- plan tables, pass dispatch and the pointwise kernels of
 // the march (field load/store with the pending screen, loss and cotangent
-// seed, FP64 reductions, Philox turbulence noise, block means).  The row and
+// seed, FP64 reductions, subharmonic coefficients, block means).  The row and
 // column pass kernels live in pass_kernels.hpp and are compiled per
 // precision in pass_{row,col}_{f32,f64}.hip.
 #include <hip/hip_runtime.h>
@@ -10,7 +10,7 @@
 #include "kernels.hpp"
 #include "pass_kernels.hpp"
 #include "lens_vjp.hpp"
-#include "subharmonics.hpp"
+#include "noise.hpp"
 
 namespace ssfm {
 
@@ -549,78 +549,9 @@ hipError_t launch_sumsq(const double* x, int64_t n, double inv_scale, double* pa
   return hipGetLastError();
 }
 
-// ------------------------------------------------ turbulence white noise
-// Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64-bit
-// multiplies, key advanced by the Weyl constants between rounds.
-__device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
-  const uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
-  const uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    if (r > 0) {
-      k0 += W0;
-      k1 += W1;
-    }
-    const uint64_t p0 = uint64_t(M0) * c[0];
-    const uint64_t p1 = uint64_t(M1) * c[2];
-    const uint32_t hi0 = uint32_t(p0 >> 32), lo0 = uint32_t(p0);
-    const uint32_t hi1 = uint32_t(p1 >> 32), lo1 = uint32_t(p1);
-    const uint32_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
-    c[0] = n0;
-    c[1] = lo1;
-    c[2] = n2;
-    c[3] = lo0;
-  }
-}
-
-// Spectrum sample c * sqrt(Phi(f)) df at FFT index (row, col) of beam b:
-// Phi(f) df^2 = amp0^2 * m^(-11/3) with m = |(signed col, signed row)|.
-template <typename R>
-__global__ void k_noise(const InstDev* inst, int b, int pair, uint32_t k0, uint32_t k1,
-                        double amp0, int kind, double band_q2, cx<R>* __restrict__ dst) {
-  const InstDev& in = inst[b];
-  const int n = in.n;
-  const int64_t n2 = int64_t(n) * n;
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n2;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const int row = int(i / n), col = int(i - int64_t(row) * n);
-    uint32_t c[4] = {uint32_t(col), uint32_t(row), uint32_t(pair), 0u};
-    philox4x32_10(c, k0, k1);
-    const double u1 = (double(c[0]) + 0.5) * 2.3283064365386962890625e-10;
-    const double u2 = (double(c[1]) + 0.5) * 2.3283064365386962890625e-10;
-    const double rr = sqrt(-2.0 * log(u1));
-    double sn, cs;
-    sincospi(2.0 * u2, &sn, &cs);
-    const int mx = (col <= n / 2) ? col : col - n;
-    const int my = (row <= n / 2) ? row : row - n;
-    // |m|^2 is an exact integer (at most n^2 / 2)
-    const double m2 = double(int64_t(mx) * mx + int64_t(my) * my);
-    double a;
-    if (kind == 1) {
-      // Eq. (10) band on the integer mode indices: 0 < |m|^2 <= q2
-      a = (m2 > 0.0 && m2 <= band_q2) ? amp0 : 0.0;
-    } else {
-      a = (m2 > 0.0) ? amp0 * pow(m2, -11.0 / 12.0) : 0.0;
-    }
-    dst[in.off + i] = {R(a * rr * cs), R(a * rr * sn)};
-  }
-}
-
-template <typename R>
-hipError_t launch_noise(const InstDev* inst, int b, int n, int pair, uint64_t seed,
-                        double amp0, int kind, double band_q2, void* dst, hipStream_t s) {
-  hipLaunchKernelGGL((k_noise<R>), dim3(grid_for(int64_t(n) * n, 256)), dim3(256), 0, s,
-                     inst, b, pair, uint32_t(seed & 0xffffffffu), uint32_t(seed >> 32), amp0,
-                     kind, band_q2, static_cast<cx<R>*>(dst));
-  return hipGetLastError();
-}
-template hipError_t launch_noise<float>(const InstDev*, int, int, int, uint64_t, double, int,
-                                        double, void*, hipStream_t);
-template hipError_t launch_noise<double>(const InstDev*, int, int, int, uint64_t, double, int,
-                                         double, void*, hipStream_t);
-
-// Subharmonic part of the screens, for all beams at once.  Coefficients
-// (grid: pairs x beams, one workgroup each): thread t < 8 levels draws mode t
+// Subharmonic part of the screens: coefficients and tables of all beams
+// (grid: x over pairs, then table blocks; y over beams).
+// Coefficients (one workgroup per pair): thread t < 8 levels draws mode t
 // (level p = t / 8 + 1, cell q = the t % 8-th of the 3 x 3 cells around f = 0
 // without the centre, (mx, my) = (q % 3 - 1, q / 3 - 1), spacing df =
 // 1 / (3^p L)) from Philox counter (q, p, pair, 1) and stores w = c
@@ -628,14 +559,31 @@ template hipError_t launch_noise<double>(const InstDev*, int, int, int, uint64_t
 // the w (the mean of exp(2 pi i m df x) over the cell-centred grid x_j =
 // (j + 1/2 - n/2) L/n is g_p = sin(pi/3^p) / (n sin(pi/(3^p n))) for |m| = 1,
 // 1 for m = 0), each mode's share by its own thread, summed in fixed order.
-// Tables (grid: blocks x beams): e_p[j] = exp(2 pi i (j + 1/2 - n/2) /
-// (3^p n)), the same for rows and columns of the square grid.  Apply (grid:
-// blocks x beams, one launch per pair): every point adds Re / Im of
-// sum w e_p[col]^mx e_p[row]^my - mean to its two planes, in FP64.
-__global__ void __launch_bounds__(256) k_subharm_coef(const SubBeam* __restrict__ beams,
-                                                     double* __restrict__ region) {
+// Tables: e_p[j] = exp(2 pi i (j + 1/2 - n/2) / (3^p n)), the same for rows
+// and columns of the square grid.  The column pass of the synthesis adds
+// Re / Im of sum w e_p[col]^mx e_p[row]^my - mean to the pair's planes.
+__global__ void __launch_bounds__(256) k_subharm_setup(const SubBeam* __restrict__ beams,
+                                                      int max_pairs,
+                                                      double* __restrict__ region) {
   __shared__ double sre[8 * kMaxSubharmonicLevels], sim[8 * kMaxSubharmonicLevels];
   const SubBeam sb = beams[blockIdx.y];
+  if (sb.sp.levels == 0) return;
+  if (int(blockIdx.x) >= max_pairs) {
+    const int n = sb.n;
+    const int64_t total = int64_t(sb.sp.levels) * n;
+    double* tab = region + sb.tab_off;
+    for (int64_t k = (blockIdx.x - max_pairs) * int64_t(blockDim.x) + threadIdx.x; k < total;
+         k += int64_t(gridDim.x - max_pairs) * blockDim.x) {
+      const int p = int(k / n), j = int(k - int64_t(p) * n);
+      double pow3 = 3.0;
+      for (int i = 0; i < p; ++i) pow3 *= 3.0;
+      double sn, cs;
+      sincospi(2.0 * (double(j) + 0.5 - 0.5 * n) / (pow3 * n), &sn, &cs);
+      tab[2 * k] = cs;
+      tab[2 * k + 1] = sn;
+    }
+    return;
+  }
   const int pair = blockIdx.x;
   if (pair >= sb.pairs) return;
   const SubharmonicSpec& sp = sb.sp;
@@ -647,12 +595,8 @@ __global__ void __launch_bounds__(256) k_subharm_coef(const SubBeam* __restrict_
     const int p = t / 8 + 1, j = t % 8, q = (j < 4) ? j : j + 1;
     const int mx = q % 3 - 1, my = q / 3 - 1;
     uint32_t c[4] = {uint32_t(q), uint32_t(p), uint32_t(pair), 1u};
-    philox4x32_10(c, sb.k0, sb.k1);
-    const double u1 = (double(c[0]) + 0.5) * 2.3283064365386962890625e-10;
-    const double u2 = (double(c[1]) + 0.5) * 2.3283064365386962890625e-10;
-    const double rr = sqrt(-2.0 * log(u1));
-    double sn, cs;
-    sincospi(2.0 * u2, &sn, &cs);
+    double g_re, g_im;
+    gaussian_pair(c, sb.k0, sb.k1, &g_re, &g_im);
     double pow3 = 1.0;
     for (int i = 0; i < p; ++i) pow3 *= 3.0;
     const double df = 1.0 / (pow3 * sp.length);
@@ -666,7 +610,7 @@ __global__ void __launch_bounds__(256) k_subharm_coef(const SubBeam* __restrict_
       const double fx = double(mx) * df, fy = double(my) * df;
       a = sqrt(0.023 * pow(sp.r0, -5.0 / 3.0) * pow(hypot(fx, fy), -11.0 / 3.0)) * df;
     }
-    const double wr = rr * cs * a, wi = rr * sn * a;
+    const double wr = g_re * a, wi = g_im * a;
     blk[2 * t] = wr;
     blk[2 * t + 1] = wi;
     const double g = sinpi(1.0 / pow3) / (double(n) * sinpi(1.0 / (pow3 * n)));
@@ -686,94 +630,13 @@ __global__ void __launch_bounds__(256) k_subharm_coef(const SubBeam* __restrict_
   }
 }
 
-__global__ void __launch_bounds__(256) k_subharm_table(const SubBeam* __restrict__ beams,
-                                                      double* __restrict__ region) {
-  const SubBeam sb = beams[blockIdx.y];
-  const int n = sb.n;
-  const int64_t total = int64_t(sb.sp.levels) * n;
-  double* tab = region + sb.tab_off;
-  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < total;
-       k += int64_t(gridDim.x) * blockDim.x) {
-    const int p = int(k / n), j = int(k - int64_t(p) * n);
-    double pow3 = 3.0;
-    for (int i = 0; i < p; ++i) pow3 *= 3.0;
-    double sn, cs;
-    sincospi(2.0 * (double(j) + 0.5 - 0.5 * n) / (pow3 * n), &sn, &cs);
-    tab[2 * k] = cs;
-    tab[2 * k + 1] = sn;
-  }
-}
-
-template <typename R>
-__global__ void __launch_bounds__(256) k_subharm_apply(const SubBeam* __restrict__ beams,
-                                                      const InstDev* __restrict__ inst, int pair,
-                                                      const double* __restrict__ region,
-                                                      R* __restrict__ planes) {
-  __shared__ double w[kSubPair];
-  const SubBeam sb = beams[blockIdx.y];
-  if (pair >= sb.pairs) return;
-  const InstDev& in = inst[sb.inst];
-  const int n = sb.n;
-  const int levels = sb.sp.levels;
-  const double* blk = region + sb.coef_off + int64_t(kSubPair) * pair;
-  for (int k = threadIdx.x; k < 16 * levels; k += blockDim.x) w[k] = blk[k];
-  if (threadIdx.x < 2) w[128 + threadIdx.x] = blk[128 + threadIdx.x];
-  __syncthreads();
-  const double mre = w[128], mim = w[129];
-  const double* __restrict__ tab = region + sb.tab_off;
-  const int64_t n2 = int64_t(n) * n;
-  R* pre = planes + in.screen_off + int64_t(2 * pair) * n2;
-  R* pim = pre + n2;
-  const bool has_im = 2 * pair + 1 < in.n_screens;
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n2;
-       i += int64_t(gridDim.x) * blockDim.x) {
-    const int row = int(i / n), col = int(i - int64_t(row) * n);
-    double sre = 0.0, sim = 0.0;
-    for (int p = 0; p < levels; ++p) {
-      const double xr = tab[2 * (p * n + col)], xi = tab[2 * (p * n + col) + 1];
-      const double yr = tab[2 * (p * n + row)], yi = tab[2 * (p * n + row) + 1];
-      // e^{i a} for the x-exponents (-1, 0, 1) and y-exponents, combined per
-      // cell; cells in the order q = 0..8 without q = 4
-      const double exr[3] = {xr, 1.0, xr}, exi[3] = {-xi, 0.0, xi};
-      const double eyr[3] = {yr, 1.0, yr}, eyi[3] = {-yi, 0.0, yi};
-      const double* wp = w + 16 * p;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int q = (j < 4) ? j : j + 1, ix = q % 3, iy = q / 3;
-        const double er = exr[ix] * eyr[iy] - exi[ix] * eyi[iy];
-        const double ei = exr[ix] * eyi[iy] + exi[ix] * eyr[iy];
-        const double wr = wp[2 * j], wi = wp[2 * j + 1];
-        sre += wr * er - wi * ei;
-        sim += wr * ei + wi * er;
-      }
-    }
-    pre[i] = R(double(pre[i]) + (sre - mre));
-    if (has_im) pim[i] = R(double(pim[i]) + (sim - mim));
-  }
-}
-
 hipError_t launch_subharmonic_setup(const SubBeam* beams, int n_beams, int max_pairs,
                                     int64_t max_table, double* region, hipStream_t s) {
   if (n_beams <= 0 || max_pairs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_subharm_coef, dim3(max_pairs, n_beams), dim3(256), 0, s, beams, region);
-  hipLaunchKernelGGL(k_subharm_table, dim3(grid_for(max_table, 256), n_beams), dim3(256), 0, s,
-                     beams, region);
+  hipLaunchKernelGGL(k_subharm_setup, dim3(max_pairs + grid_for(max_table, 256), n_beams),
+                     dim3(256), 0, s, beams, max_pairs, region);
   return hipGetLastError();
 }
-
-template <typename R>
-hipError_t launch_subharmonic_apply(const SubBeam* beams, int n_beams, const InstDev* inst,
-                                    int pair, int64_t max_n2, const double* region, void* planes,
-                                    hipStream_t s) {
-  if (n_beams <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_subharm_apply<R>), dim3(std::min(grid_for(max_n2, 256), 4096), n_beams),
-                     dim3(256), 0, s, beams, inst, pair, region, static_cast<R*>(planes));
-  return hipGetLastError();
-}
-template hipError_t launch_subharmonic_apply<float>(const SubBeam*, int, const InstDev*, int,
-                                                    int64_t, const double*, void*, hipStream_t);
-template hipError_t launch_subharmonic_apply<double>(const SubBeam*, int, const InstDev*, int,
-                                                     int64_t, const double*, void*, hipStream_t);
 
 template <typename R>
 __global__ void k_plane_f64(const R* __restrict__ p, int64_t n, double* __restrict__ d) {

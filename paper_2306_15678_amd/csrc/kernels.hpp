@@ -57,9 +57,11 @@ template <typename R>
 struct PassArgs {
   const void* src;            // cx<R> field buffer read
   void* dst;                  // cx<R> field buffer written
-  const void* aux;            // *_ADJ: pre-screen field V of the screen (cx<R>)
+  const void* aux;            // *_ADJ: pre-screen field V of the screen (cx<R>);
+                              // *_INV: the screens' spectra (SubBeam per beam)
   void* rec;                  // *_FWD: pre-screen field V written here too (or null)
-  void* state;                // ROW_FD: U of the step (read; U+ written when finishing)
+  void* state;                // ROW_FD: U of the step (read; U+ written when finishing);
+                              // COL_INV: the subharmonic region (read)
   const InstDev* inst;        // beam table
   const void* tables;         // cx<R> twiddle and propagator tables
   const R* screens;           // turbulence planes (read)
@@ -150,13 +152,6 @@ hipError_t launch_reduce_theta(const double* rows, const int32_t* row_begin, con
 // Sum of squares of a float64 array divided by scale^2 (one value).
 hipError_t launch_sumsq(const double* x, int64_t n, double inv_scale,
                         double* partial, double* out, hipStream_t s);
-
-// White noise shaped by the screen spectrum: kind 0 Kolmogorov (amp0 (m^2)^(-11/12)),
-// kind 1 step (amp0 where 0 < mx^2 + my^2 <= band_q2, integer mode indices).
-template <typename R>
-hipError_t launch_noise(const InstDev* inst, int b, int n, int pair,
-                        uint64_t seed, double amp0, int kind, double band_q2,
-                        void* dst, hipStream_t s);
 
 template <typename R>
 hipError_t launch_screen_to_f64(const R* plane, int64_t n_elem, double* dst,

@@ -33,6 +33,7 @@
 
 #include "fft_core.hpp"
 #include "kernels.hpp"
+#include "noise.hpp"
 #include "plans.hpp"
 #include "screen.hpp"
 
@@ -452,9 +453,16 @@ __global__ void __launch_bounds__(P::THREADS)
 }
 
 // ------------------------------------------------ screen synthesis pass
+// A pair of screens is two launches.  The row pass draws its spectrum as it
+// needs it (the work buffer is never loaded) and the column pass adds the
+// subharmonic modes to what it has in registers, factored by axis: per
+// level and column the three cells of each table exponent of the rows are
+// summed first, which leaves four FP64 multiply-adds per point.  Bound by
+// the arithmetic of the draws (Philox, FP64 log and sincospi), two in
+// flight per thread.
 template <typename R, class P, bool COL>
 __global__ void __launch_bounds__(P::THREADS) k_inverse(PassArgs<R> a) {
-  constexpr int N = P::N, E = P::E;
+  constexpr int N = P::N, T = P::T, E = P::E;
   using TL = Tile<P, COL>;
   using LD = TileLds<R, P, COL>;
   __shared__ cx<R> lds_mem[LD::size()];
@@ -463,11 +471,26 @@ __global__ void __launch_bounds__(P::THREADS) k_inverse(PassArgs<R> a) {
   const InstDev in = load_uniform(a.inst + (a.beam0 + tl.beam));
   if (2 * a.pair >= in.n_screens || !(in.terms & T_TURB)) return;
   const int64_t base = tl.base(a.off0);
-  const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
+  const SubBeam sb = load_uniform(static_cast<const SubBeam*>(a.aux) + (a.beam0 + tl.beam));
   const Buf<cx<R>> tw(static_cast<const cx<R>*>(a.tables) + a.tw);
   cx<R> v[E];
+  if constexpr (COL) {
+    const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
 #pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = src[tl.toff + TL::STRIDE * uint32_t(e)];
+    for (int e = 0; e < E; ++e) v[e] = src[tl.toff + TL::STRIDE * uint32_t(e)];
+  } else {
+    // through the thread's own LDS slots, so that the draws can loop
+    const int row = tl.l0 + tl.line;
+#pragma unroll 2
+    for (int e = 0; e < E; ++e) {
+      double re, im;
+      noise_sample(sb, N, row, tl.t + T * e, a.pair, &re, &im);
+      lds_mem[e * P::THREADS + int(threadIdx.x)] = {R(re), R(im)};
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = lds_mem[e * P::THREADS + int(threadIdx.x)];
+    __syncthreads();  // the transform's slots are other threads'
+  }
   cx<R> wt[tw_regs<P>()];
   if constexpr (!P::HX) load_twiddles<R, P>(wt, tl.t, tw);
   fft_line<R, P, +1>(v, tl.t, LD::make(lds_mem, tl.line), wt, tw);
@@ -476,6 +499,50 @@ __global__ void __launch_bounds__(P::THREADS) k_inverse(PassArgs<R> a) {
     R* pre = a.planes_out + in.screen_off + int64_t(2 * a.pair) * N * N + tl.l0;
     R* pim = pre + int64_t(N) * N;
     const bool has_im = 2 * a.pair + 1 < in.n_screens;
+    if (sb.sp.levels > 0) {
+      const double* region = static_cast<const double*>(a.state);
+      const double* blk = region + sb.coef_off + int64_t(kSubPair) * a.pair;
+      const double* tab = region + sb.tab_off;
+      const int col = tl.l0 + tl.line;
+      double sre[E], sim[E];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        sre[e] = -blk[128];
+        sim[e] = -blk[129];
+      }
+#pragma unroll 1
+      for (int p = 0; p < sb.sp.levels; ++p) {
+        const double xr = tab[2 * (p * N + col)], xi = tab[2 * (p * N + col) + 1];
+        const double* w = blk + 16 * p;
+        // b[iy]: the cells q = 3 iy + ix (without q = 4) over ix, with
+        // e^{i a ix} = conj(x), 1, x
+        double br[3], bi[3];
+#pragma unroll
+        for (int iy = 0; iy < 3; ++iy) {
+          const int j0 = (iy < 2) ? 3 * iy : 5;         // cell (0, iy)
+          const int j2 = (iy == 0) ? 2 : j0 + (iy == 1 ? 1 : 2);  // cell (2, iy)
+          const double lr = w[2 * j0], li = w[2 * j0 + 1];
+          const double hr = w[2 * j2], hi = w[2 * j2 + 1];
+          br[iy] = (lr + hr) * xr + (li - hi) * xi;
+          bi[iy] = (li + hi) * xr + (hr - lr) * xi;
+          if (iy != 1) {
+            br[iy] += w[2 * (j0 + 1)];
+            bi[iy] += w[2 * (j0 + 1) + 1];
+          }
+        }
+        const double sr = br[0] + br[2], si = bi[0] + bi[2];
+        const double dr = br[2] - br[0], di = bi[0] - bi[2];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int row = tl.t + T * e;
+          const double yr = tab[2 * (p * N + row)], yi = tab[2 * (p * N + row) + 1];
+          sre[e] += br[1] + sr * yr + di * yi;
+          sim[e] += bi[1] + si * yr + dr * yi;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = {R(double(v[e].re) + sre[e]), R(double(v[e].im) + sim[e])};
+    }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       pre[tl.toff + TL::STRIDE * uint32_t(e)] = v[e].re;
