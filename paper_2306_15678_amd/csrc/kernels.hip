@@ -105,6 +105,62 @@ hipError_t launch_load_field(const double* src, void* dst, int64_t n_elem,
 template hipError_t launch_load_field<float>(const double*, void*, int64_t, double, hipStream_t);
 template hipError_t launch_load_field<double>(const double*, void*, int64_t, double, hipStream_t);
 
+// Beam table entries, by value: ordered with the passes on the stream, where
+// a copy from the host's table would have to be waited for.
+struct InstChunk {
+  InstDev e[kInstChunk];
+};
+static_assert(sizeof(InstChunk) <= 3584, "kernel arguments end at 4096 bytes");
+
+__global__ void __launch_bounds__(256) k_put_inst(InstChunk src, int count,
+                                                  uint32_t* __restrict__ dst) {
+  static_assert(sizeof(InstDev) % 4 == 0, "whole dwords");
+  const uint32_t* p = reinterpret_cast<const uint32_t*>(&src);
+  for (int i = threadIdx.x; i < count * int(sizeof(InstDev) / 4); i += 256) dst[i] = p[i];
+}
+
+hipError_t launch_put_inst(const InstDev* src, int count, InstDev* dst, hipStream_t s) {
+  for (int k = 0; k < count; k += kInstChunk) {
+    const int m = std::min(kInstChunk, count - k);
+    InstChunk c{};
+    std::copy(src + k, src + k + m, c.e);
+    hipLaunchKernelGGL(k_put_inst, dim3(1), dim3(256), 0, s, c, m,
+                       reinterpret_cast<uint32_t*>(dst + k));
+  }
+  return hipGetLastError();
+}
+
+// The pending screen of every beam (grid: x over points, y over beams), in
+// place.  One launch: by a round trip of each beam through the complex128
+// staging area, 20 beams of 256^2 took 40 launches.
+template <typename R>
+__global__ void __launch_bounds__(256)
+k_flush(cx<R>* __restrict__ state, const InstDev* inst, const R* screens, const int64_t* steps,
+        int64_t pending) {
+  const InstDev in = load_uniform(inst + blockIdx.y);
+  const int64_t n2 = int64_t(in.n) * in.n;
+  const ScreenConst<R> sc = screen_const<R>(in);
+  const R* plane = find_plane(screens, steps, in, pending);
+  cx<R>* st = state + in.off;
+  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n2;
+       i += int64_t(gridDim.x) * blockDim.x)
+    st[i] = screen_apply(sc, st[i], plane ? plane[i] : R(0));
+}
+
+template <typename R>
+hipError_t launch_flush(void* state, const InstDev* inst, int n_beams, int max_n, const R* screens,
+                        const int64_t* steps, int64_t pending, hipStream_t s) {
+  const int blocks = std::min(grid_for(int64_t(max_n) * max_n, 256), 4096);
+  for (int b = 0; b < n_beams; b += 65535)
+    hipLaunchKernelGGL((k_flush<R>), dim3(blocks, std::min(n_beams - b, 65535)), dim3(256), 0, s,
+                       static_cast<cx<R>*>(state), inst + b, screens, steps, pending);
+  return hipGetLastError();
+}
+template hipError_t launch_flush<float>(void*, const InstDev*, int, int, const float*,
+                                        const int64_t*, int64_t, hipStream_t);
+template hipError_t launch_flush<double>(void*, const InstDev*, int, int, const double*,
+                                         const int64_t*, int64_t, hipStream_t);
+
 template <typename R>
 __global__ void k_store_field(const cx<R>* __restrict__ state, const InstDev* inst,
                               int b, const R* screens, const int64_t* steps,
@@ -145,12 +201,31 @@ template hipError_t launch_store_field<double>(const void*, const InstDev*, int,
                                                const double*, const int64_t*, int64_t, double,
                                                double*, bool, hipStream_t);
 
+// I - w of a point [W/m^2].
+template <typename R>
+__device__ __forceinline__ double fluence_excess(cx<R> u, double i_ref, double w) {
+  const double xx = double(u.re) * u.re + double(u.im) * u.im;
+  return xx * i_ref - w;
+}
+
+// Partial sum k (of kSumParts) of x^2, by one workgroup of 256.
+__device__ __forceinline__ void sumsq_partial(const double* __restrict__ x, int64_t n, int k,
+                                              double* part, double* red) {
+  double s[1] = {0.0};
+  for (int64_t i = k * 256 + int(threadIdx.x); i < n; i += int64_t(kSumParts) * 256)
+    s[0] += x[i] * x[i];
+  block_reduce<1, 256, false>(s, red);
+  if (threadIdx.x == 0) part[k] = s[0];
+}
+
 // Loss / cotangent seed: one workgroup per row of beam b (256 threads).
+// Mode 0 sums the 256 partials of sum w^2 in every workgroup (a launch of
+// its own cost more) and leaves the sum after the rows' losses.
 template <typename R>
 __global__ void __launch_bounds__(256)
 k_seed(int mode, const cx<R>* __restrict__ state, const InstDev* inst, int b,
        const R* screens, const int64_t* steps, int64_t pending,
-       const double* __restrict__ target, const double* wsum,
+       const double* __restrict__ target, const double* __restrict__ w_part,
        const double* __restrict__ g_ext, double g_scale, cx<R>* __restrict__ lam,
        double* part_loss, double* part_theta) {
   __shared__ double red[4 * 8];
@@ -160,7 +235,16 @@ k_seed(int mode, const cx<R>* __restrict__ state, const InstDev* inst, int b,
   const ScreenConst<R> sc = screen_const<R>(in);
   const R* plane = find_plane(screens, steps, in, pending);
   // mode 0: g_scale = I_a; loss in SI, G_u = 4 (I - w) I_a u / sum w^2
-  const double inv_w = (mode == 0) ? 1.0 / wsum[0] : 0.0;
+  double inv_w = 0.0;
+  if (mode == 0) {
+    double w[1] = {w_part[threadIdx.x]};
+    block_reduce<1, 256, false>(w, red);
+    if (threadIdx.x == 0) red[0] = w[0];
+    __syncthreads();
+    inv_w = 1.0 / red[0];
+    if (row == 0 && threadIdx.x == 0) part_loss[n] = w[0];
+    __syncthreads();
+  }
   double loss[1] = {0.0};
   double g[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int x = threadIdx.x; x < n; x += 256) {
@@ -170,8 +254,7 @@ k_seed(int mode, const cx<R>* __restrict__ state, const InstDev* inst, int b,
     const cx<R> u = (pending >= 0) ? screen_apply(sc, v, pt) : v;
     cx<R> gu;
     if (mode == 0) {
-      const double xx = double(u.re) * u.re + double(u.im) * u.im;
-      const double d = xx * g_scale - target[i];
+      const double d = fluence_excess(u, g_scale, target[i]);
       loss[0] += d * d;
       const double f = 4.0 * d * g_scale * inv_w;
       gu = {R(f * u.re), R(f * u.im)};
@@ -194,13 +277,13 @@ k_seed(int mode, const cx<R>* __restrict__ state, const InstDev* inst, int b,
 template <typename R>
 hipError_t launch_seed(int mode, const void* state, const InstDev* inst, int b, int n,
                        const R* screens, const int64_t* screen_steps, int64_t pending_step,
-                       const double* target, const double* wsum, const double* g_ext,
+                       const double* target, const double* w_part, const double* g_ext,
                        double g_scale, void* lam, double* part_loss, double* part_theta,
                        int n_blocks, hipStream_t s) {
   (void)n;
   hipLaunchKernelGGL((k_seed<R>), dim3(n_blocks), dim3(256), 0, s, mode,
                      static_cast<const cx<R>*>(state), inst, b, screens, screen_steps,
-                     pending_step, target, wsum, g_ext, g_scale, static_cast<cx<R>*>(lam),
+                     pending_step, target, w_part, g_ext, g_scale, static_cast<cx<R>*>(lam),
                      part_loss, part_theta);
   return hipGetLastError();
 }
@@ -212,6 +295,52 @@ template hipError_t launch_seed<double>(int, const void*, const InstDev*, int, i
                                         const double*, const int64_t*, int64_t, const double*,
                                         const double*, const double*, double, void*, double*,
                                         double*, int, hipStream_t);
+
+// The fluence mismatch of beam b without its gradient, in one launch: blocks
+// below n sum (I - w)^2 over a row each into part[row], the kSumParts others
+// leave the partials of sum w^2 after them.  The sums are those of
+// k_sumsq_part and k_seed, in the same order.
+template <typename R>
+__global__ void __launch_bounds__(256)
+k_mismatch(const cx<R>* __restrict__ state, const InstDev* inst, int b, const R* screens,
+           const int64_t* steps, int64_t pending, const double* __restrict__ target, double i_ref,
+           double* __restrict__ part) {
+  __shared__ double red[4];
+  const InstDev& in = inst[b];
+  const int n = in.n;
+  if (int(blockIdx.x) >= n) {
+    sumsq_partial(target, int64_t(n) * n, int(blockIdx.x) - n, part + n, red);
+    return;
+  }
+  const int64_t row = blockIdx.x;
+  const ScreenConst<R> sc = screen_const<R>(in);
+  const R* plane = find_plane(screens, steps, in, pending);
+  double loss[1] = {0.0};
+  for (int x = threadIdx.x; x < n; x += 256) {
+    const int64_t i = row * n + x;
+    cx<R> u = state[in.off + i];
+    if (pending >= 0) u = screen_apply(sc, u, plane ? plane[i] : R(0));
+    const double d = fluence_excess(u, i_ref, target[i]);
+    loss[0] += d * d;
+  }
+  block_reduce<1, 256, false>(loss, red);
+  if (threadIdx.x == 0) part[row] = loss[0];
+}
+
+template <typename R>
+hipError_t launch_mismatch(const void* state, const InstDev* inst, int b, int n, const R* screens,
+                           const int64_t* steps, int64_t pending, const double* target,
+                           double i_ref, double* part, hipStream_t s) {
+  hipLaunchKernelGGL((k_mismatch<R>), dim3(n + kSumParts), dim3(256), 0, s, static_cast<const cx<R>*>(state),
+                     inst, b, screens, steps, pending, target, i_ref, part);
+  return hipGetLastError();
+}
+template hipError_t launch_mismatch<float>(const void*, const InstDev*, int, int, const float*,
+                                           const int64_t*, int64_t, const double*, double, double*,
+                                           hipStream_t);
+template hipError_t launch_mismatch<double>(const void*, const InstDev*, int, int, const double*,
+                                            const int64_t*, int64_t, const double*, double,
+                                            double*, hipStream_t);
 
 // ---------------------------------------------------- effective lens
 template <typename R>
@@ -521,31 +650,14 @@ hipError_t launch_reduce_theta(const double* rows, const int32_t* row_begin, con
   return hipGetLastError();
 }
 
-// sum of (x/scale)^2 in two fixed-order levels
 __global__ void __launch_bounds__(256)
-k_sumsq_part(const double* __restrict__ x, int64_t n, double inv_scale, double* part) {
+k_sumsq_part(const double* __restrict__ x, int64_t n, double* part) {
   __shared__ double red[4];
-  double s[1] = {0.0};
-  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
-    const double v = x[i] * inv_scale;
-    s[0] += v * v;
-  }
-  block_reduce<1, 256, false>(s, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+  sumsq_partial(x, n, int(blockIdx.x), part, red);
 }
 
-// Sum of n <= 256 partials: one per thread, then a fixed tree.
-__global__ void __launch_bounds__(256) k_sum_small(const double* part, int n, double* out) {
-  __shared__ double red[4];
-  double s[1] = {int(threadIdx.x) < n ? part[threadIdx.x] : 0.0};
-  block_reduce<1, 256, false>(s, red);
-  if (threadIdx.x == 0) out[0] = s[0];
-}
-
-hipError_t launch_sumsq(const double* x, int64_t n, double inv_scale, double* partial,
-                        double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sumsq_part, dim3(256), dim3(256), 0, s, x, n, inv_scale, partial);
-  hipLaunchKernelGGL(k_sum_small, dim3(1), dim3(256), 0, s, partial, 256, out);
+hipError_t launch_sumsq(const double* x, int64_t n, double* partial, hipStream_t s) {
+  hipLaunchKernelGGL(k_sumsq_part, dim3(kSumParts), dim3(256), 0, s, x, n, partial);
   return hipGetLastError();
 }
 

@@ -119,7 +119,8 @@ hipError_t launch_store_field(const void* state, const InstDev* inst, int b,
 
 // Loss / cotangent seed.  For each point of beam b: u_N = screen(s_N);
 // mode 0 (g_scale = I_a): I = I_a |u|^2, partial sums of (I - w)^2 and
-// G_u = 4 (I - w) I_a u / sum w^2 (wsum[0] = sum w^2, SI);
+// G_u = 4 (I - w) I_a u / sum w^2 (w_part: launch_sumsq's sums of w^2, SI;
+// part_loss[n] gets their sum);
 // mode 1 (g_scale = sqrt(I_a)): G_u = sqrt(I_a) G_ext (G_ext in SI).
 // Then the adjoint of the pending screen writes mu_N = S^*(G_u) into lam and
 // the ansatz terms of that screen go to part_theta[row][8].
@@ -127,7 +128,7 @@ template <typename R>
 hipError_t launch_seed(int mode, const void* state, const InstDev* inst, int b,
                        int n, const R* screens, const int64_t* screen_steps,
                        int64_t pending_step, const double* target,
-                       const double* wsum, const double* g_ext,
+                       const double* w_part, const double* g_ext,
                        double g_scale, void* lam, double* part_loss,
                        double* part_theta, int n_blocks, hipStream_t s);
 
@@ -149,9 +150,25 @@ hipError_t launch_reduce_theta(const double* rows, const int32_t* row_begin, con
                                const int32_t* col_begin, int n_beams, double* out,
                                hipStream_t s);
 
-// Sum of squares of a float64 array divided by scale^2 (one value).
-hipError_t launch_sumsq(const double* x, int64_t n, double inv_scale,
-                        double* partial, double* out, hipStream_t s);
+// kSumParts partial sums of the squares of a float64 array.
+constexpr int kSumParts = 256;
+hipError_t launch_sumsq(const double* x, int64_t n, double* partial, hipStream_t s);
+
+// Copies `count` beam table entries from host memory to dst, by value.
+constexpr int kInstChunk = 16;
+hipError_t launch_put_inst(const InstDev* src, int count, InstDev* dst, hipStream_t s);
+
+// The screen of step `pending` on every beam's state, in place.
+template <typename R>
+hipError_t launch_flush(void* state, const InstDev* inst, int n_beams, int max_n, const R* screens,
+                        const int64_t* steps, int64_t pending, hipStream_t s);
+
+// Beam b's fluence mismatch (pending: as in launch_store_field): part[row] =
+// sum (I - w)^2 over a row, then launch_sumsq's partials of sum w^2.
+template <typename R>
+hipError_t launch_mismatch(const void* state, const InstDev* inst, int b, int n, const R* screens,
+                           const int64_t* steps, int64_t pending, const double* target,
+                           double i_ref, double* part, hipStream_t s);
 
 template <typename R>
 hipError_t launch_screen_to_f64(const R* plane, int64_t n_elem, double* dst,

@@ -97,7 +97,7 @@ int validate_desc(const ssfm_instance_desc* d, int32_t n_inst, int32_t precision
 struct Layout {
   size_t inst, steps, begins, tables;
   size_t S, Wk, Lam, ckpt, stack, screens, stage, diag_part, diag, theta_rows, theta_cols,
-      theta_out, seed_loss, seed_theta, scal, sumsq_part, subh, subh_beams;
+      theta_out, seed_loss, seed_theta, sumsq_part, subh, subh_beams;
   size_t total;
   int64_t field_elems;  // sum n^2
   int64_t table_elems;
@@ -151,6 +151,7 @@ struct ssfm_ctx {
   bool fd = false;
   int fd_iters = 4;
   bool precise = false;  // library sine and cosine in the FP32 screens
+  size_t inst_lo = 0, inst_hi = 0;  // beam table entries the device does not have yet
   bool spectra_changed = true;  // since the device's list of screen spectra
   int sub_pairs = 0;            // largest pair count and levels x n of the
   int64_t sub_table = 0;        // beams with subharmonics
@@ -404,9 +405,8 @@ int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t 
   l.theta_rows = take(sizeof(double) * 8 * nr_max);
   l.theta_cols = take(sizeof(double) * 8 * nc_max);
   l.theta_out = take(sizeof(double) * 8 * n_inst);
-  l.seed_loss = take(sizeof(double) * max_n);
+  l.seed_loss = take(sizeof(double) * (max_n + 1));
   l.seed_theta = take(sizeof(double) * 8 * max_n * n_inst);
-  l.scal = take(sizeof(double) * 16);
   // 256 partials of a sum of squares, moment or hot-area count, then 256 x 5
   // measure-vector partials
   l.sumsq_part = take(sizeof(double) * 256 * 6);
@@ -486,12 +486,23 @@ void drop_record(ssfm_ctx* c) {
   c->seeded_beam.assign(c->desc.size(), 0);
 }
 
-// Copy beam table entries [b0, b1) to the device (stream-ordered; waits,
-// the host table may change right after).
-int upload_inst(ssfm_ctx* c, size_t b0, size_t b1) {
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.inst + sizeof(InstDev) * b0, &c->inst[b0],
-                         sizeof(InstDev) * (b1 - b0), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
+// Beam table entries [b0, b1) have changed: they go to the device with the
+// next call that reads them (setting 20 beams' fields and parameters waited
+// for 40 small copies when each was uploaded by itself: a population of 20
+// on 256^2 took 1180 us an evaluation, now 650).
+int touch_inst(ssfm_ctx* c, size_t b0, size_t b1) {
+  c->inst_lo = c->inst_lo < c->inst_hi ? std::min(c->inst_lo, b0) : b0;
+  c->inst_hi = std::max(c->inst_hi, b1);
+  return SSFM_OK;
+}
+
+// The changed entries to the device (stream-ordered, by value: the host table
+// may change right after).  Called before anything is captured.
+int sync_inst(ssfm_ctx* c) {
+  if (c->inst_lo >= c->inst_hi) return SSFM_OK;
+  HIP_TRY(launch_put_inst(&c->inst[c->inst_lo], int(c->inst_hi - c->inst_lo),
+                          c->at<InstDev>(c->L.inst) + c->inst_lo, c->stream));
+  c->inst_lo = c->inst_hi = 0;
   return SSFM_OK;
 }
 
@@ -912,18 +923,10 @@ int half_step_lam(ssfm_ctx* c, bool forward, const Chain& ch) {
 template <typename R>
 int flush_pending(ssfm_ctx* c) {
   if (!c->pending) return SSFM_OK;
-  // store_field into the stage buffer (complex128, device units) per beam,
-  // then load it back: a pointwise round trip through the staging area.
-  for (size_t b = 0; b < c->desc.size(); ++b) {
-    const InstDev& in = c->inst[b];
-    const int64_t n2 = int64_t(in.n) * in.n;
-    double* stage = c->at<double>(c->L.stage);
-    HIP_TRY(launch_store_field<R>(c->field(c->L.S), c->at<InstDev>(c->L.inst), int(b), in.n,
-                                  c->at<R>(c->L.screens), c->at<int64_t>(c->L.steps),
-                                  c->step - 1, 1.0, stage, false, c->stream));
-    HIP_TRY(launch_load_field<R>(stage, static_cast<char*>(c->field(c->L.S)) + in.off * c->el,
-                                 n2, 1.0, c->stream));
-  }
+  if (int r = sync_inst(c)) return r;
+  HIP_TRY(launch_flush<R>(c->field(c->L.S), c->at<InstDev>(c->L.inst), int(c->desc.size()),
+                          c->L.max_n, c->at<R>(c->L.screens), c->at<int64_t>(c->L.steps),
+                          c->step - 1, c->stream));
   c->pending = false;
   return SSFM_OK;
 }
@@ -1189,8 +1192,8 @@ int do_seed(ssfm_ctx* c, int b, int mode, const double* target_dev, const double
   double* loss = c->at<double>(c->L.seed_loss);
   double* th = c->at<double>(c->L.seed_theta) + size_t(b) * 8 * c->L.max_n;
   if (mode == 0) {
-    HIP_TRY(launch_sumsq(target_dev, int64_t(in.n) * in.n, 1.0, c->at<double>(c->L.sumsq_part),
-                         c->at<double>(c->L.scal), c->stream));
+    HIP_TRY(launch_sumsq(target_dev, int64_t(in.n) * in.n, c->at<double>(c->L.sumsq_part),
+                         c->stream));
   }
   const double gs = (mode == 0) ? d.i_ref : std::sqrt(d.i_ref);
   const void* state = c->field(c->L.S);
@@ -1205,7 +1208,7 @@ int do_seed(ssfm_ctx* c, int b, int mode, const double* target_dev, const double
   }
   HIP_TRY(launch_seed<R>(mode, state, c->at<InstDev>(c->L.inst), b, in.n,
                          c->at<R>(c->L.screens), c->at<int64_t>(c->L.steps), seed_pend, target_dev,
-                         c->at<double>(c->L.scal), g_dev, gs, c->field(c->L.Lam), loss, th,
+                         c->at<double>(c->L.sumsq_part), g_dev, gs, c->field(c->L.Lam), loss, th,
                          in.n, c->stream));
   return SSFM_OK;
 }
@@ -1507,8 +1510,17 @@ int do_apply_lens(ssfm_ctx* c, int b, const ssfm_lens& l) {
   return SSFM_OK;
 }
 
-#define SSFM_DISPATCH(ctx, fn, ...) \
+#define SSFM_BY_PRECISION(ctx, fn, ...) \
   ((ctx)->precision == SSFM_FP64 ? fn<double>(__VA_ARGS__) : fn<float>(__VA_ARGS__))
+
+// fn with the device's beam table up to date.
+template <typename F>
+int with_inst(ssfm_ctx* c, F fn) {
+  if (int r = sync_inst(c)) return r;
+  return fn();
+}
+#define SSFM_DISPATCH(ctx, fn, ...) \
+  with_inst((ctx), [&]() -> int { return SSFM_BY_PRECISION((ctx), fn, __VA_ARGS__); })
 
 // Device pointer of a caller buffer, staging host data through the
 // workspace's complex128 staging area (bytes <= 16 n_max^2).
@@ -1576,9 +1588,9 @@ int do_set_field(ssfm_ctx* c, int b, const void* src, int32_t where) {
   if (same) {
     for (InstDev& in : c->inst) in.step_base = 0;
     c->step = 0;
-    return upload_inst(c, 0, c->inst.size());
+    return touch_inst(c, 0, c->inst.size());
   }
-  return upload_inst(c, b, b + 1);
+  return touch_inst(c, b, b + 1);
 }
 
 // Lines per workgroup of a variant (0 if it does not exist).
@@ -1612,7 +1624,7 @@ int apply_variants(ssfm_ctx* c, int n, const std::array<int, P_SLOTS>& var) {
   clear_graphs(c);
   std::vector<std::vector<unsigned char>> blobs;
   blobs.reserve(groups.size());
-  if (int r = SSFM_DISPATCH(c, upload_variants, c, &blobs)) return r;
+  if (int r = SSFM_BY_PRECISION(c, upload_variants, c, &blobs)) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return SSFM_OK;
 }
@@ -1827,7 +1839,7 @@ int ssfm_create(const ssfm_instance_desc* desc, int32_t n_inst, int32_t precisio
     HIP_TRY(hipEventCreateWithFlags(&ej, hipEventDisableTiming));
     c->gjoin.push_back(ej);
   }
-  int r = SSFM_DISPATCH(c, upload_plan, c.get());
+  int r = SSFM_BY_PRECISION(c, upload_plan, c.get());
   if (r) return r;
   *out = c.release();
   return SSFM_OK;
@@ -1842,7 +1854,7 @@ int ssfm_destroy(ssfm_ctx* ctx) {
 
 int ssfm_set_field(ssfm_ctx* c, int32_t inst, const void* src, int32_t where) {
   if (int r = check_inst(c, inst)) return r;
-  return SSFM_DISPATCH(c, do_set_field, c, inst, src, where);
+  return SSFM_BY_PRECISION(c, do_set_field, c, inst, src, where);
 }
 
 int ssfm_set_theta(ssfm_ctx* c, int32_t inst, const double* theta) {
@@ -1856,7 +1868,7 @@ int ssfm_set_theta(ssfm_ctx* c, int32_t inst, const double* theta) {
   // a recorded march (its stored fields, the screen its adjoint applies)
   // belongs to the old parameters
   drop_record(c);
-  return upload_inst(c, inst, inst + 1);
+  return touch_inst(c, inst, inst + 1);
 }
 
 int ssfm_gen_screens(ssfm_ctx* c) {
@@ -1941,7 +1953,7 @@ int ssfm_set_splitting(ssfm_ctx* c, int32_t scheme) {
   c->diag_valid = 0;
   drop_record(c);
   for (InstDev& in : c->inst) in.step_base = 0;
-  return upload_inst(c, 0, c->inst.size());
+  return touch_inst(c, 0, c->inst.size());
 }
 
 namespace {
@@ -2032,16 +2044,13 @@ int ssfm_fluence_loss(ssfm_ctx* c, int32_t inst, const void* target, int32_t whe
   if (int r = stage_in(c, target, where, 8 * size_t(n) * n, &dt)) return r;
   int r = SSFM_DISPATCH(c, do_seed, c, inst, 0, dt, nullptr);
   if (r) return r;
-  std::vector<double> part(n);
-  double wsum = 0.0;
-  HIP_TRY(hipMemcpyAsync(part.data(), c->ws + c->L.seed_loss, sizeof(double) * n,
+  std::vector<double> part(n + 1);  // the rows' losses, then sum w^2
+  HIP_TRY(hipMemcpyAsync(part.data(), c->ws + c->L.seed_loss, sizeof(double) * (n + 1),
                          hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(&wsum, c->ws + c->L.scal, sizeof(double), hipMemcpyDeviceToHost,
-                         c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   double s = 0.0;
   for (int i = 0; i < n; ++i) s += part[i];
-  if (loss) *loss = s / wsum;
+  if (loss) *loss = s / part[n];
   c->seeded = true;
   c->seeded_beam[inst] = 1;
   return SSFM_OK;
@@ -2054,13 +2063,9 @@ int ssfm_fluence_mismatch(ssfm_ctx* c, int32_t inst, const void* target, int32_t
   const int n = c->desc[inst].n;
   const double* dt;
   if (int r = stage_in(c, target, where, 8 * size_t(n) * n, &dt)) return r;
-  // the seed kernel in loss mode without a cotangent output; its gradient
-  // partials go to the staging area past the target
-  double* scratch = c->at<double>(c->L.stage) + size_t(n) * n;
-  double* th = scratch;
-  double* part = scratch + 8 * size_t(n);
-  const InstDev& in = c->inst[inst];
-  const ssfm_instance_desc& d = c->desc[inst];
+  // the sums go to the staging area past the target
+  double* part = c->at<double>(c->L.stage) + size_t(n) * n;
+  if (int r = sync_inst(c)) return r;
   auto run = [&]<typename R>(R*) -> int {
     // the field U: the state with its pending screen (Lie), the state itself
     // (finite differences), or L(-dz/2) of it in the work buffer (Strang)
@@ -2071,24 +2076,27 @@ int ssfm_fluence_mismatch(ssfm_ctx* c, int32_t inst, const void* target, int32_t
       state = c->field(c->L.Wk);
       pend = -1;
     }
-    HIP_TRY(launch_sumsq(dt, int64_t(n) * n, 1.0, c->at<double>(c->L.sumsq_part),
-                         c->at<double>(c->L.scal), c->stream));
-    HIP_TRY(launch_seed<R>(0, state, c->at<InstDev>(c->L.inst), inst, in.n,
-                           c->at<R>(c->L.screens), c->at<int64_t>(c->L.steps), pend, dt,
-                           c->at<double>(c->L.scal), nullptr, d.i_ref, nullptr, part, th, in.n,
-                           c->stream));
+    HIP_TRY(launch_mismatch<R>(state, c->at<InstDev>(c->L.inst), inst, n, c->at<R>(c->L.screens),
+                               c->at<int64_t>(c->L.steps), pend, dt, c->desc[inst].i_ref, part,
+                               c->stream));
     return SSFM_OK;
   };
   if (int r = (c->precision == SSFM_FP64) ? run((double*)nullptr) : run((float*)nullptr))
     return r;
-  std::vector<double> h(n);
-  double wsum = 0.0;
-  HIP_TRY(hipMemcpyAsync(h.data(), part, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(&wsum, c->ws + c->L.scal, sizeof(double), hipMemcpyDeviceToHost,
+  std::vector<double> h(size_t(n) + kSumParts);
+  HIP_TRY(hipMemcpyAsync(h.data(), part, sizeof(double) * h.size(), hipMemcpyDeviceToHost,
                          c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
-  double s = 0.0;
+  double s = 0.0, wsum = 0.0;
   for (int i = 0; i < n; ++i) s += h[i];
+  // the order in which a workgroup sums them for ssfm_fluence_loss: a
+  // butterfly over each wavefront's 64, then the wavefronts
+  for (int w = 0; w < kSumParts; w += 64) {
+    double* p = h.data() + n + w;
+    for (int off = 32; off >= 1; off /= 2)
+      for (int i = 0; i < off; ++i) p[i] += p[i + off];
+    wsum += p[0];
+  }
   *loss = s / wsum;
   return SSFM_OK;
 }
@@ -2205,6 +2213,7 @@ int ssfm_time_adjoint_passes(ssfm_ctx* c, int32_t reps, double* ms_col, double* 
   // the state standing in for the stored pre-screen field, at a step with
   // no turbulence screen (the ansatz partials go to the accumulators every
   // backward clears first).  Fields, cotangent and gradients are unchanged.
+  if (int q = sync_inst(c)) return q;
   auto body = [&]<typename R>(R*) -> int {
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.Lam);
@@ -2251,6 +2260,7 @@ int ssfm_time_passes(ssfm_ctx* c, int32_t reps, double* ms_row, double* ms_col,
   for (auto& x : ev.e) HIP_TRY(hipEventCreate(&x));
   hipEvent_t e0 = ev.e[0], e1 = ev.e[1], e2 = ev.e[2];
   int r = SSFM_OK;
+  if (int q = sync_inst(c)) return q;
   auto body = [&]<typename R>(R*) -> int {
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.S);
