@@ -25,6 +25,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace ssfm {
 
 template <typename R>
@@ -388,6 +390,7 @@ struct Plan {
   static constexpr int PA = PA_;
   static constexpr int PB = PB_;
   static constexpr bool LATE_TW = (OPT_ & 1) != 0;
+  static constexpr bool MID_TW = (OPT_ & 2) != 0;  // complex64 (see MidTable)
   static constexpr int WAVES_PER_EU = ((OPT_ >> 8) & 15) ? ((OPT_ >> 8) & 15) : 1;
   static constexpr int WAVES_PER_EU_F64 = ((OPT_ >> 12) & 7) ? ((OPT_ >> 12) & 7) : 1;
   static constexpr bool HX = (OPT_ & 0x8000) != 0;
@@ -525,17 +528,110 @@ __device__ __forceinline__ void load_twiddles(cx<R>* w, int t, const Buf<cx<R>>&
   if constexpr (!P::LATE_TW) load_twiddles_impl<R, P::N, P::T>(w, t, tw, typename P::radices{});
 }
 
+// Twiddles of late-twiddle plans with three stages, complex64: the middle
+// stage's come from a table in LDS, R0 rows of R1 - 1 entries read in pairs
+// of 16 bytes (the rows' pitch spreads them over all banks), and the last
+// stage's stay in registers from a factor's first transform to its second
+// (a half exchange has no room for them and reads them as it goes).  Read
+// from the plan's table in every stage, twiddles were 120 of a thread's 168
+// loads in a 4096-point pass and kept the compute unit's address unit busier
+// than the strided columns did (us, before and now: 4096^2 rows 100, 84.5,
+// adjoint 124, 107; columns 157, 134, adjoint 225, 215; 2048^2 columns 36,
+// 31).  complex128 tiles leave no LDS for the table (two workgroups of
+// 4096^2 rows fill it: 215 us, with the table 345).
+template <typename R, class Rad>
+struct MidTable {
+  static constexpr int PITCH = 0, SIZE = 0;
+};
+template <typename R, int R0, int R1, int R2>
+struct MidTable<R, Radices<R0, R1, R2>> {
+  static constexpr int PITCH = R1 + 2;
+  static constexpr int SIZE = R0 * PITCH;
+  const cx<R>* base;
+  static __device__ __forceinline__ void fill(cx<R>* mem, int threads, const Buf<cx<R>>& tw) {
+    // entry i: twiddle i / R0 + 1 of row i mod R0
+    for (uint32_t i = threadIdx.x; i < uint32_t(R0 * (R1 - 1)); i += uint32_t(threads))
+      mem[(i % R0) * PITCH + i / R0] = tw.get(i, 0);
+  }
+  __device__ __forceinline__ void read(cx<R>* w, int t) const {
+    const cx<R>* p = base + (unsigned(t) % unsigned(R0)) * PITCH;
+    static_assert(sizeof(R) == 4 && R1 % 2 == 0, "pairs of 16 bytes");
+#pragma unroll
+    for (int i = 0; i < R1; i += 2) {
+      const float4 q = *reinterpret_cast<const float4*>(p + i);
+      w[i] = {q.x, q.y};
+      if (i + 1 < R1 - 1) w[i + 1] = {q.z, q.w};
+    }
+  }
+};
+
+template <typename R, class P>
+constexpr bool mid_tw() {
+  return sizeof(R) == 4 && P::MID_TW;
+}
+template <typename R, class P>
+constexpr bool keep_tw() {
+  return mid_tw<R, P>() && !P::HX;
+}
+template <typename R, class P>
+constexpr int mid_table_size() {
+  return mid_tw<R, P>() ? MidTable<R, typename P::radices>::SIZE : 0;
+}
+
+// The last stage's twiddles.
+template <typename R, int N, int T, int R0, int R1, int R2>
+__device__ __forceinline__ void load_last_impl(cx<R>* w, int t, const Buf<cx<R>>& tw,
+                                               Radices<R0, R1, R2>) {
+  load_stage_twiddles<R, N, T, R0 * R1, R2, R0>(w, t, tw);
+}
+template <int N, int T, int R0, int R1, int R2>
+constexpr int last_count_impl(Radices<R0, R1, R2>) {
+  return stage_tw_sets<N, T, R0 * R1, R2>() * (R2 - 1);
+}
+
+// The twiddles of a pass as its transforms see them: all preloaded, the
+// middle table and the last stage's, or the plan's table.  keep() before a
+// factor's first transform.
+template <typename R, class P>
+struct Twiddles {
+  static constexpr int regs() {
+    if constexpr (keep_tw<R, P>())
+      return last_count_impl<P::N, P::T>(typename P::radices{});
+    else if constexpr (P::LATE_TW || P::HX)
+      return 1;
+    else
+      return TwCount<P>::value > 0 ? TwCount<P>::value : 1;
+  }
+  Buf<cx<R>> tw;
+  cx<R>* mid;  // the LDS table, after the tile
+  cx<R> w[regs()];
+  __device__ __forceinline__ Twiddles(const cx<R>* table, cx<R>* lds_table, int t)
+      : tw(table), mid(lds_table) {
+    if constexpr (mid_tw<R, P>())
+      MidTable<R, typename P::radices>::fill(mid, P::THREADS, tw);
+    else if constexpr (!P::LATE_TW && !P::HX)
+      load_twiddles<R, P>(w, t, tw);
+  }
+  __device__ __forceinline__ void keep(int t) {
+    if constexpr (keep_tw<R, P>()) {
+      asm volatile("" : "+v"(t));  // loaded here, not held from the first factor
+      load_last_impl<R, P::N, P::T>(w, t, tw, typename P::radices{});
+    }
+  }
+};
+
 // ------------------------------------------------------------- stages
 // w: the twiddles of the stage at hand, from registers (preloaded) or, with
 // LATE, requested one stage ahead, so that their latency passes behind a
 // whole butterfly and exchange (requested where they are used, the waits for
-// them were a fifth of a 4096-point pass).  tail() is called where the last
-// stage would request the next one's: it requests what follows the
-// transform.
-template <typename R, int N, int T, int DIR, int NS, int R0, bool LATE, class Lds, class Tail,
-          int RAD, int... Rest>
+// them were a fifth of a 4096-point pass); of a plan that keeps them, the
+// last stage's, the middle stage reading its own from mid.  tail() is called
+// where the last stage would request the next one's: it requests what
+// follows the transform.
+template <typename R, int N, int T, int DIR, int NS, int R0, bool LATE, class Mid, class Lds,
+          class Tail, int RAD, int... Rest>
 __device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
-                                           const Buf<cx<R>>& tw, Tail&& tail) {
+                                           const Buf<cx<R>>& tw, const Mid& mid, Tail&& tail) {
   // with late twiddles the thread index is made opaque per stage, so the
   // stage's LDS and twiddle addresses are computed where they are used
   // instead of held in registers from the kernel's start
@@ -547,14 +643,18 @@ __device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds, cons
   constexpr int SETS = stage_tw_sets<N, T, NS, RAD>();
   static_assert(E % RAD == 0, "radix must divide points per thread");
   static_assert(pow2(T), "the input slots of a thread differ by constants");
-  cx<R> wn[next_tw_regs<N, T, LATE, NS * RAD, Rest...>()];
+  constexpr bool KEEP = !std::is_same_v<Mid, int>;
+  constexpr bool MIDDLE = KEEP && !FIRST && !LAST;
+  cx<R> wn[KEEP ? 1 : next_tw_regs<N, T, LATE, NS * RAD, Rest...>()];
   if constexpr (LATE) {
     if constexpr (LAST)
       tail();
-    else
+    else if constexpr (!KEEP)
       load_stage_twiddles<R, N, T, NS * RAD, first_radix<Rest...>(), R0>(wn, t, tw);
   }
   cx<R> a[NB][RAD];
+  cx<R> wm[MIDDLE ? RAD : 1];
+  if constexpr (MIDDLE) mid.read(wm, t);
   const unsigned in0 = Lds::idx(unsigned(t));
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
@@ -572,7 +672,7 @@ __device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds, cons
   }
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    dft<RAD, DIR, (NS > 1)>(a[b], w + (SETS == 1 ? 0 : b * (RAD - 1)));
+    dft<RAD, DIR, (NS > 1)>(a[b], MIDDLE ? wm : w + (SETS == 1 ? 0 : b * (RAD - 1)));
     if constexpr (!LAST) {
       const OutSlots<Lds, RAD, NS> out(unsigned(t + T * b));  // >= 0: shifts and masks
 #pragma unroll
@@ -585,8 +685,8 @@ __device__ __forceinline__ void fft_stages(cx<R>* v, int t, const Lds& lds, cons
   if constexpr (!LAST) {
     __syncthreads();
     constexpr int used = NS > 1 ? SETS * (RAD - 1) : 0;
-    fft_stages<R, N, T, DIR, NS * RAD, R0, LATE, Lds, Tail, Rest...>(
-        v, t, lds, LATE ? wn : w + used, tw, static_cast<Tail&&>(tail));
+    fft_stages<R, N, T, DIR, NS * RAD, R0, LATE, Mid, Lds, Tail, Rest...>(
+        v, t, lds, KEEP ? w : LATE ? wn : w + used, tw, mid, static_cast<Tail&&>(tail));
   }
 }
 
@@ -630,10 +730,10 @@ __device__ __forceinline__ void hx_exchange(cx<R> (&a)[N / T / RAD][RAD],
   }
 }
 
-template <typename R, int N, int T, int DIR, int NS, int R0, class Lds, class Tail, int RA,
-          int... Rest>
+template <typename R, int N, int T, int DIR, int NS, int R0, class Mid, class Lds, class Tail,
+          int RA, int... Rest>
 __device__ __forceinline__ void hx_stages(cx<R>* v, cx<R> (&a)[N / T / RA][RA], int t,
-                                          const Lds& lds, const Buf<cx<R>>& tw,
+                                          const Lds& lds, const Buf<cx<R>>& tw, const Mid& mid,
                                           Tail&& tail) {
   constexpr bool LAST = sizeof...(Rest) == 0;
   constexpr int NB = N / T / RA;
@@ -643,10 +743,15 @@ __device__ __forceinline__ void hx_stages(cx<R>* v, cx<R> (&a)[N / T / RA][RA], 
   // one butterfly at a time, each with its own twiddles: all of a thread's
   // points are live here, and twiddles of two butterflies beside them would
   // not fit the registers of two workgroups per compute unit
-  cx<R> w[NS > 1 ? RA - 1 : 1];
+  constexpr bool MIDDLE = !std::is_same_v<Mid, int> && NS > 1 && !LAST;
+  cx<R> w[NS > 1 ? RA : 1];
+  if constexpr (MIDDLE) {
+    static_assert(SETS == 1);
+    mid.read(w, t);
+  }
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    if constexpr (NS > 1) {
+    if constexpr (NS > 1 && !MIDDLE) {
       if (b < SETS) {
         const uint32_t k = uint32_t(t + T * b) % uint32_t(NS);
 #pragma unroll
@@ -668,14 +773,14 @@ __device__ __forceinline__ void hx_stages(cx<R>* v, cx<R> (&a)[N / T / RA][RA], 
     constexpr int RB = first_radix<Rest...>();
     cx<R> nx[N / T / RB][RB];
     hx_exchange<R, N, T, RA, NS, RB>(a, nx, t, lds);
-    hx_stages<R, N, T, DIR, NS * RA, R0, Lds, Tail, Rest...>(v, nx, t, lds, tw,
-                                                             static_cast<Tail&&>(tail));
+    hx_stages<R, N, T, DIR, NS * RA, R0, Mid, Lds, Tail, Rest...>(v, nx, t, lds, tw, mid,
+                                                                  static_cast<Tail&&>(tail));
   }
 }
 
 template <typename R, class P, int DIR, class Lds, class Tail, int R0, int... Rest>
-__device__ __forceinline__ void fft_line_impl(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
-                                              const Buf<cx<R>>& tw, Tail&& tail,
+__device__ __forceinline__ void fft_line_impl(cx<R>* v, int t, const Lds& lds,
+                                              const Twiddles<R, P>& tws, Tail&& tail,
                                               Radices<R0, Rest...>) {
   if constexpr (P::HX) {
     constexpr int NB = P::E / R0;
@@ -685,30 +790,39 @@ __device__ __forceinline__ void fft_line_impl(cx<R>* v, int t, const Lds& lds, c
 #pragma unroll
       for (int r = 0; r < R0; ++r) a[b][r] = v[b + r * NB];
     }
-    hx_stages<R, P::N, P::T, DIR, 1, R0, Lds, Tail, R0, Rest...>(v, a, t, lds, tw,
-                                                                 static_cast<Tail&&>(tail));
+    if constexpr (mid_tw<R, P>()) {
+      using Mid = MidTable<R, typename P::radices>;
+      hx_stages<R, P::N, P::T, DIR, 1, R0, Mid, Lds, Tail, R0, Rest...>(
+          v, a, t, lds, tws.tw, Mid{tws.mid}, static_cast<Tail&&>(tail));
+    } else {
+      hx_stages<R, P::N, P::T, DIR, 1, R0, int, Lds, Tail, R0, Rest...>(
+          v, a, t, lds, tws.tw, 0, static_cast<Tail&&>(tail));
+    }
+  } else if constexpr (keep_tw<R, P>()) {
+    using Mid = MidTable<R, typename P::radices>;
+    fft_stages<R, P::N, P::T, DIR, 1, R0, true, Mid, Lds, Tail, R0, Rest...>(
+        v, t, lds, tws.w, tws.tw, Mid{tws.mid}, static_cast<Tail&&>(tail));
   } else {
-    fft_stages<R, P::N, P::T, DIR, 1, R0, P::LATE_TW, Lds, Tail, R0, Rest...>(
-        v, t, lds, w, tw, static_cast<Tail&&>(tail));
+    fft_stages<R, P::N, P::T, DIR, 1, R0, P::LATE_TW, int, Lds, Tail, R0, Rest...>(
+        v, t, lds, tws.w, tws.tw, 0, static_cast<Tail&&>(tail));
   }
 }
 
 // In-register FFT of one line (DIR = -1 forward, +1 inverse, unscaled),
-// with the thread's twiddles preloaded by load_twiddles<R, P> (w), or, for
-// a late-twiddle or half-exchange plan, read stage by stage from the plan's
-// stage-ordered table tw, tail() called with the last stage.  On entry and
+// with the thread's twiddles in tws; tail() is called with the last stage (a
+// plan whose twiddles come late).  On entry and
 // exit v[e] holds point t + T*e.  A full exchange leaves the LDS free (its
 // last barrier follows the last reads); a half exchange opens with the
 // barrier that guards the last reads.
 template <typename R, class P, int DIR, class Lds, class Tail>
-__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
-                                         const Buf<cx<R>>& tw, Tail&& tail) {
-  fft_line_impl<R, P, DIR>(v, t, lds, w, tw, static_cast<Tail&&>(tail), typename P::radices{});
+__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds,
+                                         const Twiddles<R, P>& tws, Tail&& tail) {
+  fft_line_impl<R, P, DIR>(v, t, lds, tws, static_cast<Tail&&>(tail), typename P::radices{});
 }
 template <typename R, class P, int DIR, class Lds>
-__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds, const cx<R>* w,
-                                         const Buf<cx<R>>& tw) {
-  fft_line<R, P, DIR>(v, t, lds, w, tw, [] {});
+__device__ __forceinline__ void fft_line(cx<R>* v, int t, const Lds& lds,
+                                         const Twiddles<R, P>& tws) {
+  fft_line<R, P, DIR>(v, t, lds, tws, [] {});
 }
 
 // Host side: the radix list of a plan.

@@ -200,11 +200,6 @@ __device__ __forceinline__ void fd_generator(const ScreenConst<R>& s, R x, R& gr
   if (tm & T_MPA) gr -= s.cM * s.inv2k1 * xk1;
 }
 
-template <class P>
-constexpr int tw_regs() {
-  return TwCount<P>::value > 0 ? TwCount<P>::value : 1;
-}
-
 // A workgroup's tile of a launch and its threads' points: thread t of a
 // line holds points t + T e, at element offset toff + STRIDE e from the
 // tile's base.
@@ -249,12 +244,15 @@ template <typename R, class P, bool COL>
 struct TileLds {
   using L = std::conditional_t<COL, LdsPointMajor<R, P::LINES, P::PA, P::PB>,
                                LdsLineMajor<R, P::N>>;
-  static constexpr int size() {
+  static constexpr int tile() {
     if constexpr (COL)
       return L::size(P::HX ? P::N / 2 : P::N);
     else
       return P::LINES * L::LINE;
   }
+  // the twiddle table of a plan that keeps them, at a 16-byte boundary
+  static constexpr int table() { return (tile() + 1) / 2 * 2; }
+  static constexpr int size() { return table() + mid_table_size<R, P>(); }
   static __device__ __forceinline__ L make(cx<R>* mem, int line) {
     if constexpr (COL)
       return L{mem + line};
@@ -279,7 +277,7 @@ __global__ void __launch_bounds__(P::THREADS)
   using TL = Tile<P, COL>;
   constexpr uint32_t STRIDE = TL::STRIDE;
   using LD = TileLds<R, P, COL>;
-  __shared__ cx<R> lds_mem[LD::size()];
+  __shared__ __align__(16) cx<R> lds_mem[LD::size()];
   const TL tl;
   if (tl.tile >= a.n_tiles) return;
   const int64_t base = tl.base(a.off0);
@@ -288,18 +286,16 @@ __global__ void __launch_bounds__(P::THREADS)
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = src.get(tl.toff, STRIDE * uint32_t(e));
   const cx<R>* tables = static_cast<const cx<R>*>(a.tables);
-  const Buf<cx<R>> tw(tables + a.tw);
   const Buf<cx<R>> prop(tables + a.prop0 + int64_t(tl.beam) * a.prop_stride);
   // plans with few points a thread keep twiddles and propagator in
   // registers for both factors; the others read them as they go
   constexpr bool LATE = P::LATE_TW || P::HX;
-  cx<R> wt[LATE ? 1 : tw_regs<P>()];
   cx<R> pr[P::HX ? 1 : E];
   if constexpr (!LATE) {
 #pragma unroll
     for (int e = 0; e < E; ++e) pr[e] = prop.get(uint32_t(tl.t), uint32_t(T * e));
-    load_twiddles<R, P>(wt, tl.t, tw);
   }
+  Twiddles<R, P> tws(tables + a.tw, lds_mem + LD::table(), tl.t);
   const auto lds = LD::make(lds_mem, tl.line);
   const InstDev* ip = a.inst + (a.beam0 + tl.beam);
   const int32_t flags = a.flags;
@@ -415,7 +411,8 @@ __global__ void __launch_bounds__(P::THREADS)
       }
       if (!(flags & PASS_OP2)) break;
     }
-    fft_line<R, P, -1>(v, tl.t, lds, wt, tw, [&] {
+    tws.keep(tl.t);
+    fft_line<R, P, -1>(v, tl.t, lds, tws, [&] {
       if constexpr (LATE && !P::HX) {
         int tp = tl.t;
         asm volatile("" : "+v"(tp));
@@ -441,7 +438,7 @@ __global__ void __launch_bounds__(P::THREADS)
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = ADJ ? cmulc(v[e], pr[e]) : cmul(v[e], pr[e]);
     }
-    fft_line<R, P, +1>(v, tl.t, lds, wt, tw);
+    fft_line<R, P, +1>(v, tl.t, lds, tws);
     if (second) break;
     second = true;
   }
@@ -465,14 +462,13 @@ __global__ void __launch_bounds__(P::THREADS) k_inverse(PassArgs<R> a) {
   constexpr int N = P::N, T = P::T, E = P::E;
   using TL = Tile<P, COL>;
   using LD = TileLds<R, P, COL>;
-  __shared__ cx<R> lds_mem[LD::size()];
+  __shared__ __align__(16) cx<R> lds_mem[LD::size()];
   const TL tl;
   if (tl.tile >= a.n_tiles) return;
   const InstDev in = load_uniform(a.inst + (a.beam0 + tl.beam));
   if (2 * a.pair >= in.n_screens || !(in.terms & T_TURB)) return;
   const int64_t base = tl.base(a.off0);
   const SubBeam sb = load_uniform(static_cast<const SubBeam*>(a.aux) + (a.beam0 + tl.beam));
-  const Buf<cx<R>> tw(static_cast<const cx<R>*>(a.tables) + a.tw);
   cx<R> v[E];
   if constexpr (COL) {
     const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
@@ -491,9 +487,9 @@ __global__ void __launch_bounds__(P::THREADS) k_inverse(PassArgs<R> a) {
     for (int e = 0; e < E; ++e) v[e] = lds_mem[e * P::THREADS + int(threadIdx.x)];
     __syncthreads();  // the transform's slots are other threads'
   }
-  cx<R> wt[tw_regs<P>()];
-  if constexpr (!P::HX) load_twiddles<R, P>(wt, tl.t, tw);
-  fft_line<R, P, +1>(v, tl.t, LD::make(lds_mem, tl.line), wt, tw);
+  Twiddles<R, P> tws(static_cast<const cx<R>*>(a.tables) + a.tw, lds_mem + LD::table(), tl.t);
+  tws.keep(tl.t);
+  fft_line<R, P, +1>(v, tl.t, LD::make(lds_mem, tl.line), tws);
   if constexpr (COL) {
     // screen pair: real part -> plane 2p, imaginary part -> plane 2p+1
     R* pre = a.planes_out + in.screen_off + int64_t(2 * a.pair) * N * N + tl.l0;
@@ -561,14 +557,13 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_row(PassArgs<R> a) {
   constexpr int T = P::T, E = P::E;
   using TL = Tile<P, false>;
   using LD = TileLds<R, P, false>;
-  __shared__ cx<R> lds_mem[LD::size()];
+  __shared__ __align__(16) cx<R> lds_mem[LD::size()];
   const TL tl;
   if (tl.tile >= a.n_tiles) return;
   const int64_t base = tl.base(a.off0);
   const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
   cx<R>* __restrict__ st = static_cast<cx<R>*>(a.state) + base;
   cx<R>* __restrict__ dst = static_cast<cx<R>*>(a.dst) + base;
-  const Buf<cx<R>> tw(static_cast<const cx<R>*>(a.tables) + a.tw);
   // v is Ubar row-transformed (the column pass applied the solve and both
   // 1/N), or U itself when the step starts
   cx<R> v[E], un[E];
@@ -576,12 +571,12 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_row(PassArgs<R> a) {
   for (int e = 0; e < E; ++e) v[e] = src[tl.toff + uint32_t(T * e)];
 #pragma unroll
   for (int e = 0; e < E; ++e) un[e] = st[tl.toff + uint32_t(T * e)];
-  cx<R> wt[tw_regs<P>()];
-  load_twiddles<R, P>(wt, tl.t, tw);
+  Twiddles<R, P> tws(static_cast<const cx<R>*>(a.tables) + a.tw, lds_mem + LD::table(), tl.t);
+  tws.keep(tl.t);
   const auto lds = LD::make(lds_mem, tl.line);
   const InstDev in = load_uniform(a.inst + (a.beam0 + tl.beam));
   const ScreenConst<R> sc = screen_const<R>(in);
-  if (a.flags & FD_SPECTRAL) fft_line<R, P, +1>(v, tl.t, lds, wt, tw);
+  if (a.flags & FD_SPECTRAL) fft_line<R, P, +1>(v, tl.t, lds, tws);
   if (a.flags & FD_FINISH) {
     // U+ = 2 Ubar - U, its power partials; it is the next step's U and
     // its first Ubar
@@ -616,7 +611,7 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_row(PassArgs<R> a) {
     gi *= R(0.5);
     v[e] = {un[e].re + (gr * v[e].re - gi * v[e].im), un[e].im + (gr * v[e].im + gi * v[e].re)};
   }
-  fft_line<R, P, -1>(v, tl.t, lds, wt, tw);
+  fft_line<R, P, -1>(v, tl.t, lds, tws);
 #pragma unroll
   for (int e = 0; e < E; ++e) dst[tl.toff + uint32_t(T * e)] = v[e];
 }
@@ -630,23 +625,22 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_col(PassArgs<R> a) {
   constexpr int N = P::N, T = P::T, E = P::E;
   using TL = Tile<P, true>;
   using LD = TileLds<R, P, true>;
-  __shared__ cx<R> lds_mem[LD::size()];
+  __shared__ __align__(16) cx<R> lds_mem[LD::size()];
   const TL tl;
   if (tl.tile >= a.n_tiles) return;
   const int64_t base = tl.base(a.off0);
   const cx<R>* __restrict__ src = static_cast<const cx<R>*>(a.src) + base;
   cx<R>* __restrict__ dst = static_cast<cx<R>*>(a.dst) + base;
   const cx<R>* tables = static_cast<const cx<R>*>(a.tables);
-  const Buf<cx<R>> tw(tables + a.tw);
   const cx<R>* __restrict__ prop = tables + a.prop0 + int64_t(tl.beam) * a.prop_stride;
   cx<R> v[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) v[e] = src[tl.toff + TL::STRIDE * uint32_t(e)];
   const R dkx = prop[tl.l0 + tl.line].re;
-  cx<R> wt[tw_regs<P>()];
-  if constexpr (!P::HX) load_twiddles<R, P>(wt, tl.t, tw);
+  Twiddles<R, P> tws(tables + a.tw, lds_mem + LD::table(), tl.t);
+  tws.keep(tl.t);
   const auto lds = LD::make(lds_mem, tl.line);
-  fft_line<R, P, -1>(v, tl.t, lds, wt, tw);
+  fft_line<R, P, -1>(v, tl.t, lds, tws);
   int tp = tl.t;
   asm volatile("" : "+v"(tp));
   const R inv_n2 = R(1) / (R(N) * R(N));
@@ -656,7 +650,7 @@ __global__ void __launch_bounds__(P::THREADS) k_fd_col(PassArgs<R> a) {
     const R den = inv_n2 / (R(1) + sm * sm);
     v[e] = cmul(v[e], cx<R>{den, -sm * den});
   }
-  fft_line<R, P, +1>(v, tl.t, lds, wt, tw);
+  fft_line<R, P, +1>(v, tl.t, lds, tws);
   uint32_t to = tl.toff;
   asm volatile("" : "+v"(to));
 #pragma unroll

@@ -1,7 +1,8 @@
 // plans.hpp -- compiled FFT tile variants of the row and column passes.
 //
 // Rows: X(N, variant, T, LINES, OPT, radices...); columns: X(N, variant,
-// T, W, A, B, OPT, radices...).  OPT: 1 = late twiddles, plus 0x100 times
+// T, W, A, B, OPT, radices...).  OPT: 1 = late twiddles, 2 =
+// the middle stage's in LDS (complex64, see MidTable), plus 0x100 times
 // the wavefronts per SIMD the compiler must leave room for, 0x8000 = column
 // exchanges through half the tile (see Plan).  T threads per line, LINES
 // lines per workgroup (rows: LINES consecutive rows; columns: W adjacent
@@ -17,7 +18,7 @@
 // E = 4 4.4, E = 8 5.0, E = 16 6.7; 256^2: E = 4 5.5, E = 8 6.0, E = 16 7.3;
 // 1024^2 rows: E = 8 11.2, E = 16 12.1).  From 2048^2 on the vector units
 // decide and the larger radices of 16 points a thread, fewest instructions,
-// win (4096^2 rows: 16 points 101 us, 8 points 105 us).
+// win (4096^2 rows: 16 points 84 us, 8 points 105 us).
 #pragma once
 
 #include "fft_core.hpp"
@@ -38,20 +39,20 @@ namespace ssfm {
   X(1024, 0, 128, 1, 0x0, 8, 8, 4, 4) \
   X(1024, 1, 256, 1, 0x0, 4, 4, 4, 4, 4) \
   X(1024, 2, 128, 1, 0x1, 8, 8, 4, 4) \
-  X(1024, 3, 64, 1, 0x1, 16, 8, 8) \
+  X(1024, 3, 64, 1, 0x3, 16, 8, 8) \
   X(2048, 0, 256, 1, 0x0, 8, 8, 8, 4) \
   X(2048, 1, 256, 1, 0x1, 8, 8, 8, 4) \
-  X(2048, 2, 128, 1, 0x401, 16, 16, 8) \
-  X(2048, 3, 128, 1, 0x1, 16, 16, 8) \
-  X(4096, 0, 256, 1, 0x401, 16, 16, 16) \
-  X(4096, 1, 256, 1, 0x1, 16, 16, 16) \
-  X(4096, 2, 256, 1, 0x301, 16, 16, 16) \
-  X(4096, 3, 256, 1, 0x201, 16, 16, 16) \
+  X(2048, 2, 128, 1, 0x403, 16, 16, 8) \
+  X(2048, 3, 128, 1, 0x3, 16, 16, 8) \
+  X(4096, 0, 256, 1, 0x403, 16, 16, 16) \
+  X(4096, 1, 256, 1, 0x3, 16, 16, 16) \
+  X(4096, 2, 256, 1, 0x303, 16, 16, 16) \
+  X(4096, 3, 256, 1, 0x203, 16, 16, 16) \
   X(4096, 4, 512, 1, 0x0, 8, 8, 8, 8) \
   X(4096, 5, 512, 1, 0x1, 8, 8, 8, 8) \
   X(4096, 6, 512, 1, 0x401, 8, 8, 8, 8) \
   X(4096, 7, 512, 1, 0x300, 8, 8, 8, 8) \
-  X(4096, 8, 256, 1, 0x501, 16, 16, 16)
+  X(4096, 8, 256, 1, 0x503, 16, 16, 16)
 
 #define SSFM_COL_PLANS(X) \
   X(128, 0, 32, 2, 16, 6, 0x0, 4, 4, 4, 2) \
@@ -74,23 +75,23 @@ namespace ssfm {
   X(1024, 1, 128, 2, 16, 2, 0x0, 8, 8, 4, 4) \
   X(1024, 2, 256, 2, 16, 6, 0x0, 4, 4, 4, 4, 4) \
   X(1024, 3, 64, 4, 8, 2, 0x0, 16, 8, 8) \
-  X(1024, 4, 64, 4, 8, 2, 0x1, 16, 8, 8) \
+  X(1024, 4, 64, 4, 8, 2, 0x3, 16, 8, 8) \
   X(1024, 5, 128, 4, 8, 4, 0x1, 8, 8, 4, 4) \
-  X(2048, 0, 128, 4, 8, 2, 0x401, 16, 16, 8) \
+  X(2048, 0, 128, 4, 8, 2, 0x403, 16, 16, 8) \
   X(2048, 1, 256, 2, 16, 2, 0x0, 8, 8, 8, 4) \
-  X(2048, 2, 128, 8, 4, 2, 0x401, 16, 16, 8) \
-  X(2048, 3, 128, 2, 16, 2, 0x401, 16, 16, 8) \
+  X(2048, 2, 128, 8, 4, 2, 0x403, 16, 16, 8) \
+  X(2048, 3, 128, 2, 16, 2, 0x403, 16, 16, 8) \
   X(2048, 4, 256, 4, 8, 4, 0x401, 8, 8, 8, 4) \
-  X(4096, 0, 256, 4, 8, 2, 0x401, 16, 16, 16) \
-  X(4096, 1, 256, 2, 16, 2, 0x401, 16, 16, 16) \
-  X(4096, 2, 256, 2, 16, 2, 0x301, 16, 16, 16) \
-  X(4096, 3, 256, 2, 16, 2, 0x1, 16, 16, 16) \
-  X(4096, 4, 128, 4, 16, 2, 0x8400, 16, 16, 16) \
-  X(4096, 5, 128, 4, 8, 2, 0x8400, 16, 16, 16) \
+  X(4096, 0, 256, 4, 8, 2, 0x403, 16, 16, 16) \
+  X(4096, 1, 256, 2, 16, 2, 0x403, 16, 16, 16) \
+  X(4096, 2, 256, 2, 16, 2, 0x303, 16, 16, 16) \
+  X(4096, 3, 256, 2, 16, 2, 0x3, 16, 16, 16) \
+  X(4096, 4, 128, 4, 16, 2, 0x8402, 16, 16, 16) \
+  X(4096, 5, 128, 4, 8, 2, 0x8402, 16, 16, 16) \
   X(4096, 6, 512, 2, 16, 2, 0x0, 8, 8, 8, 8) \
   X(4096, 7, 512, 2, 16, 2, 0x401, 8, 8, 8, 8) \
-  X(4096, 8, 128, 4, 8, 2, 0x8200, 16, 16, 16) \
-  X(4096, 9, 128, 2, 16, 2, 0x8400, 16, 16, 16) \
+  X(4096, 8, 128, 4, 8, 2, 0x8202, 16, 16, 16) \
+  X(4096, 9, 128, 2, 16, 2, 0x8402, 16, 16, 16) \
   X(4096, 10, 256, 4, 8, 4, 0x8400, 8, 8, 8, 8)
 
 // LDS of a pass workgroup against the 160 KiB a gfx950 workgroup may
@@ -101,7 +102,7 @@ constexpr size_t plan_lds_bytes(bool column) {
   const size_t tile =
       column ? size_t(LdsPointMajor<R, P::LINES, P::PA, P::PB>::size(P::HX ? P::N / 2 : P::N))
              : size_t(P::LINES) * LdsLineMajor<R, P::N>::LINE;
-  return tile * sizeof(cx<R>);
+  return ((tile + 1) / 2 * 2 + mid_table_size<R, P>()) * sizeof(cx<R>);
 }
 template <typename R, class P>
 constexpr bool plan_fits(bool column) {
