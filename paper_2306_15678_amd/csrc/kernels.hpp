@@ -38,8 +38,10 @@ constexpr bool is_col_kind(int k) {
 // adjoint), the factor of the step that begins.  PASS_RAW: the power
 // partials are those of |V|^2 without the screen's A^2; PASS_PLANE: some
 // beam of the launch has a turbulence plane at this step (else none is
-// looked for).
-enum : int32_t { PASS_OP1 = 1, PASS_SCREEN = 2, PASS_OP2 = 4, PASS_RAW = 8, PASS_PLANE = 16 };
+// looked for); PASS_SRC_KEPT: src is a recorded field (*_FWD).
+enum : int32_t {
+  PASS_OP1 = 1, PASS_SCREEN = 2, PASS_OP2 = 4, PASS_RAW = 8, PASS_PLANE = 16, PASS_SRC_KEPT = 32
+};
 // ROW_FD flags: the input is row-transformed (else it is U itself), the pass
 // finishes the step (U+ = 2 Ubar - U into the state, power partials), the
 // finished step is the last one of the launch sequence (no next RHS).
@@ -56,10 +58,10 @@ struct LaunchEv {
 template <typename R>
 struct PassArgs {
   const void* src;            // cx<R> field buffer read
-  void* dst;                  // cx<R> field buffer written
-  const void* aux;            // *_ADJ: pre-screen field V of the screen (cx<R>);
+  void* dst;                  // cx<R> field buffer written (*_FWD: or null)
+  const void* aux;            // *_ADJ: recorded pre-screen field V of the screen (cx<R>);
                               // *_INV: the screens' spectra (SubBeam per beam)
-  void* rec;                  // *_FWD: pre-screen field V written here too (or null)
+  void* rec;                  // *_FWD: pre-screen field V recorded here too (or null)
   void* state;                // ROW_FD: U of the step (read; U+ written when finishing);
                               // COL_INV: the subharmonic region (read)
   const InstDev* inst;        // beam table

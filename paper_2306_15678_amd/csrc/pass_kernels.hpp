@@ -238,6 +238,17 @@ struct Tile {
   __device__ __forceinline__ int64_t base(int64_t off0) const {
     return off0 + int64_t(beam) * N * N + in_beam();
   }
+  // recorded fields: line by line along the pass's axis, whichever it is (a
+  // field is recorded, marched on from and differentiated by passes of one
+  // axis).  Thread point e at kept_off() + T e from kept_base().
+  __device__ __forceinline__ int64_t kept_base(int64_t off0) const {
+    return off0 + int64_t(beam) * N * N + int64_t(l0) * N;
+  }
+  __device__ __forceinline__ uint32_t kept_off() const {
+    uint32_t o = uint32_t(line) * N + uint32_t(t);
+    asm volatile("" : "+v"(o));  // formed where it is used
+    return o;
+  }
 };
 
 template <typename R, class P, bool COL>
@@ -282,9 +293,17 @@ __global__ void __launch_bounds__(P::THREADS)
   if (tl.tile >= a.n_tiles) return;
   const int64_t base = tl.base(a.off0);
   const Buf<cx<R>> src(static_cast<const cx<R>*>(a.src) + base);
+  const int32_t flags = a.flags;
   cx<R> v[E];
+  if (COL && !ADJ && (flags & PASS_SRC_KEPT)) {
+    const Buf<cx<R>> kept(static_cast<const cx<R>*>(a.src) + tl.kept_base(a.off0));
+    const uint32_t ko = tl.kept_off();
 #pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = src.get(tl.toff, STRIDE * uint32_t(e));
+    for (int e = 0; e < E; ++e) v[e] = kept.get(ko, uint32_t(T * e));
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = src.get(tl.toff, STRIDE * uint32_t(e));
+  }
   const cx<R>* tables = static_cast<const cx<R>*>(a.tables);
   const Buf<cx<R>> prop(tables + a.prop0 + int64_t(tl.beam) * a.prop_stride);
   // plans with few points a thread keep twiddles and propagator in
@@ -298,7 +317,6 @@ __global__ void __launch_bounds__(P::THREADS)
   Twiddles<R, P> tws(tables + a.tw, lds_mem + LD::table(), tl.t);
   const auto lds = LD::make(lds_mem, tl.line);
   const InstDev* ip = a.inst + (a.beam0 + tl.beam);
-  const int32_t flags = a.flags;
   const int64_t part_at = int64_t(a.part0) + int64_t(tl.tile) * P::WAVES + (threadIdx.x >> 6);
 
   bool second = !(flags & PASS_OP1);
@@ -311,9 +329,10 @@ __global__ void __launch_bounds__(P::THREADS)
       asm volatile("" : "+v"(to));
       if constexpr (!ADJ) {
         if (a.rec != nullptr) {
-          const Buf<cx<R>> rec(static_cast<const cx<R>*>(a.rec) + base);
+          const Buf<cx<R>> rec(static_cast<const cx<R>*>(a.rec) + tl.kept_base(a.off0));
+          const uint32_t ko = tl.kept_off();
 #pragma unroll
-          for (int e = 0; e < E; ++e) rec.put(to, STRIDE * uint32_t(e), v[e]);
+          for (int e = 0; e < E; ++e) rec.put(ko, uint32_t(T * e), v[e]);
         }
         if ((flags & PASS_SCREEN) || a.part != nullptr) {
           const InstDev in = load_uniform(ip);
@@ -371,7 +390,8 @@ __global__ void __launch_bounds__(P::THREADS)
                                ? find_plane(a.screens, a.screen_steps, in, a.step)
                                : nullptr;
           if (plane) plane += tl.in_beam();
-          const Buf<cx<R>> svp(static_cast<const cx<R>*>(a.aux) + base);
+          const Buf<cx<R>> svp(static_cast<const cx<R>*>(a.aux) + tl.kept_base(a.off0));
+          const uint32_t ko = tl.kept_off();
           constexpr int AC = 2;  // points per batch
           static_assert(E % AC == 0, "whole batches");
           // each batch's stored field and phases are requested one batch
@@ -380,7 +400,7 @@ __global__ void __launch_bounds__(P::THREADS)
           R ph[2][AC];
           auto load_inputs = [&](int c, int k) {
 #pragma unroll
-            for (int e = 0; e < AC; ++e) sv[k][e] = svp.get(to, STRIDE * uint32_t(c + e));
+            for (int e = 0; e < AC; ++e) sv[k][e] = svp.get(ko, uint32_t(T * (c + e)));
 #pragma unroll
             for (int e = 0; e < AC; ++e) ph[k][e] = R(0);
             if (plane) {
@@ -442,6 +462,7 @@ __global__ void __launch_bounds__(P::THREADS)
     if (second) break;
     second = true;
   }
+  if (a.dst == nullptr) return;
   const Buf<cx<R>> dst(static_cast<const cx<R>*>(a.dst) + base);
   uint32_t to = tl.toff;
   asm volatile("" : "+v"(to));

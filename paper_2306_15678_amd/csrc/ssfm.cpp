@@ -640,11 +640,14 @@ bool second_axis_col(int64_t step) { return (step & 1) == 0; }
 
 // Where a march of n steps reads and writes: V_0 comes from src, the
 // half-diffracted field lives in cur (whole lines per workgroup: in place),
-// V_n goes to dst, and rec(i) (0 <= i < n), where it gives a buffer, gets
-// V_i.
+// V_n goes to dst unless that is null, and rec(i) (0 <= i <= n), where it
+// gives a buffer, gets V_i.  Recorded fields lie line by line along the axis
+// of the passes that use them, which is the first axis of their step: the
+// columns of one take contiguous stores and loads (kept: src is recorded).
 struct MarchBuffers {
   const void* src;
   void *cur, *dst;
+  bool kept;
 };
 
 // The passes that end steps i0 <= i < i1 of a march of n steps from step0
@@ -663,7 +666,7 @@ int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
     a.dst = m.cur;
     a.rec = rec(0);
     a.step = pend(0);
-    a.flags = PASS_OP2 | (a.step >= 0 ? PASS_SCREEN : 0);
+    a.flags = PASS_OP2 | (a.step >= 0 ? PASS_SCREEN : 0) | (m.kept ? PASS_SRC_KEPT : 0);
     const bool col = first_axis_col(step0);
     if (int r = run_pass<R>(c, col ? COL_FWD : ROW_FWD, a, ch, T_PROP,
                             open ? open->ev.data() : nullptr))
@@ -678,8 +681,8 @@ int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
     a.dst = last ? m.dst : m.cur;
     if (part) a.part = c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.part_stride;
     a.flags = PASS_OP1 | raw;
+    a.rec = rec(i + 1);
     if (!last) {
-      a.rec = rec(i + 1);
       a.step = pend(i + 1);
       a.flags |= PASS_SCREEN | PASS_OP2;
     }
@@ -713,7 +716,7 @@ int enqueue_propagate(ssfm_ctx* c, int64_t n, int64_t step0, bool pending0, int6
       return c->strang ? step0 + i : (i == 0 && !pending0) ? -1 : step0 + i - 1;
     };
     return enqueue_march<R>(
-        c, n, step0, i0, i1, MarchBuffers{S, S, S}, pend,
+        c, n, step0, i0, i1, MarchBuffers{S, S, S, false}, pend,
         [](int64_t) -> void* { return nullptr; }, true, ch, open, end);
   });
 }
@@ -966,7 +969,8 @@ Segments rec_segments(const ssfm_ctx* c, int64_t n) {
   return g;
 }
 
-// Where a record of n steps keeps s_i = V_i (0 <= i < n; null: not kept).
+// Where a record of n steps keeps s_i = V_i (0 <= i < n; null: not kept),
+// line by line along step i's first axis.
 void* rec_slot(ssfm_ctx* c, const Segments& g, int64_t i) {
   if (i % g.M == 0) return c->field(c->L.ckpt, i / g.M);
   const int64_t k = i / g.M;
@@ -983,9 +987,9 @@ int enqueue_record(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1
   void* S = c->field(c->L.S);
   return each_chain(c, true, [&](const Chain& ch) {
     return enqueue_march<R>(
-        c, n, step0, i0, i1, MarchBuffers{S, S, S},
+        c, n, step0, i0, i1, MarchBuffers{S, S, S, false},
         [&](int64_t i) { return rec_pending(c, step0, step0 + i); },
-        [&](int64_t i) { return rec_slot(c, g, i); }, true, ch, open, end);
+        [&](int64_t i) { return i < n ? rec_slot(c, g, i) : nullptr; }, true, ch, open, end);
   });
 }
 
@@ -1044,7 +1048,7 @@ int enqueue_backward(ssfm_ctx* c) {
     if (len < 2) return SSFM_OK;
     return enqueue_march<R>(
         c, len - 1, step0 + s0, 0, len - 1,
-        MarchBuffers{sv(k, 0), c->field(c->L.Wk), slot(k, len - 2)},
+        MarchBuffers{sv(k, 0), c->field(c->L.Wk), nullptr, true},
         [&](int64_t i) { return rec_pending(c, step0, step0 + s0 + i); },
         [&](int64_t i) { return i > 0 ? slot(k, i - 1) : nullptr; }, false, ch, nullptr,
         nullptr);
