@@ -151,6 +151,8 @@ struct ssfm_ctx {
   bool fd = false;
   int fd_iters = 4;
   bool precise = false;  // library sine and cosine in the FP32 screens
+  // radix plans whose twiddles the device holds, per size group and pass
+  std::vector<std::array<std::vector<int>, P_SLOTS>> tw_radices;
   size_t inst_lo = 0, inst_hi = 0;  // beam table entries the device does not have yet
   bool spectra_changed = true;  // since the device's list of screen spectra
   int sub_pairs = 0;            // largest pair count and levels x n of the
@@ -1300,25 +1302,36 @@ int do_gen_screens(ssfm_ctx* c) {
   });
 }
 
-// Upload the twiddle tables of every group's plans and the first partials
-// of every beam (they follow the variants in use); *blob holds the host copy
-// until the caller synchronises.
+// Upload the twiddle tables of every group's plans, where the device does
+// not hold them yet (most variants of a size share a radix plan, and tuning
+// goes through all of them), and the first partials of every beam (they
+// follow the variants in use); *blobs holds the host copies until the caller
+// synchronises.
 template <typename R>
 int upload_variants(ssfm_ctx* c, std::vector<std::vector<unsigned char>>* blobs) {
   const bool fp64 = c->precision == SSFM_FP64;
   std::vector<double> tmp;
-  for (const Group& g : c->groups) {
-    std::vector<unsigned char> blob;
+  c->tw_radices.resize(c->groups.size());
+  for (size_t gi = 0; gi < c->groups.size(); ++gi) {
+    const Group& g = c->groups[gi];
     for (int s = 0; s < P_SLOTS; ++s) {
-      PlanInfo pi;
+      PlanInfo pi{};
       if (!plan_info(s & 1, g.n, g.variant(s), fp64, &pi))
         return fail(SSFM_EUNSUPPORTED, "no kernel plan for n=%d", g.n);
+      std::vector<int> radices;
+      for (const int* r = pi.radices; *r; ++r) radices.push_back(*r);
+      std::vector<int>& held = c->tw_radices[gi][s];
+      if (held == radices) continue;
       stage_twiddles(g.n, pi.radices, &tmp);
+      std::vector<unsigned char> blob;
       append_table<R>(&blob, tmp);
+      blobs->push_back(std::move(blob));
+      held.clear();  // unknown should the copy fail
+      HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + (g.tw + int64_t(s) * g.n) * c->el,
+                             blobs->back().data(), blobs->back().size(), hipMemcpyHostToDevice,
+                             c->stream));
+      held = radices;
     }
-    blobs->push_back(std::move(blob));
-    HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + g.tw * c->el, blobs->back().data(),
-                           blobs->back().size(), hipMemcpyHostToDevice, c->stream));
   }
   HIP_TRY(hipMemcpyAsync(c->ws + c->L.begins, c->begins.data(),
                          sizeof(int32_t) * c->begins.size(), hipMemcpyHostToDevice, c->stream));
@@ -1335,7 +1348,7 @@ int upload_plan(ssfm_ctx* c) {
   c->screen_steps.clear();
   int64_t foff = 0, soff = 0;
   std::vector<std::vector<unsigned char>> blobs;
-  blobs.reserve(2 * c->groups.size());
+  blobs.reserve((P_SLOTS + 1) * c->groups.size());
   if (int r = upload_variants<R>(c, &blobs)) return r;
   for (const Group& g : c->groups) {
     // the group's beams: T_COUNT tables each
@@ -1627,7 +1640,7 @@ int apply_variants(ssfm_ctx* c, int n, const std::array<int, P_SLOTS>& var) {
   c->L = L2;
   clear_graphs(c);
   std::vector<std::vector<unsigned char>> blobs;
-  blobs.reserve(groups.size());
+  blobs.reserve(P_SLOTS * groups.size());
   if (int r = SSFM_BY_PRECISION(c, upload_variants, c, &blobs)) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return SSFM_OK;
