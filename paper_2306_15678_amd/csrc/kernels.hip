@@ -35,7 +35,7 @@ int plan_default(bool column, int n, bool fp64) {
   static constexpr Default kDefaults[] = {{128, 0, 0, 0, 0},  {256, 0, 0, 1, 3},
                                           {512, 0, 0, 0, 0},  {768, 0, 0, 0, 0},
                                           {1024, 0, 1, 2, 5}, {2048, 0, 0, 1, 3},
-                                          {4096, 3, 0, 3, 1}};
+                                          {4096, 3, 0, 3, 0}};
   for (const Default& d : kDefaults)
     if (d.n == n) return column ? (fp64 ? d.col_f64 : d.col) : (fp64 ? d.row_f64 : d.row);
   return 0;
@@ -105,30 +105,35 @@ hipError_t launch_load_field(const double* src, void* dst, int64_t n_elem,
 template hipError_t launch_load_field<float>(const double*, void*, int64_t, double, hipStream_t);
 template hipError_t launch_load_field<double>(const double*, void*, int64_t, double, hipStream_t);
 
-// Beam table entries, by value: ordered with the passes on the stream, where
-// a copy from the host's table would have to be waited for.
-struct InstChunk {
-  InstDev e[kInstChunk];
+// Host records to device memory, by value: ordered with the passes on the
+// stream, where a copy from the host's memory would have to be waited for.
+template <typename T>
+struct Chunk {
+  static constexpr int N = int(3584 / sizeof(T));  // kernel arguments end at 4096 bytes
+  T e[N];
 };
-static_assert(sizeof(InstChunk) <= 3584, "kernel arguments end at 4096 bytes");
 
-__global__ void __launch_bounds__(256) k_put_inst(InstChunk src, int count,
-                                                  uint32_t* __restrict__ dst) {
-  static_assert(sizeof(InstDev) % 4 == 0, "whole dwords");
+template <typename T>
+__global__ void __launch_bounds__(256) k_put(Chunk<T> src, int count, uint32_t* __restrict__ dst) {
+  static_assert(sizeof(T) % 4 == 0, "whole dwords");
   const uint32_t* p = reinterpret_cast<const uint32_t*>(&src);
-  for (int i = threadIdx.x; i < count * int(sizeof(InstDev) / 4); i += 256) dst[i] = p[i];
+  for (int i = threadIdx.x; i < count * int(sizeof(T) / 4); i += 256) dst[i] = p[i];
 }
 
-hipError_t launch_put_inst(const InstDev* src, int count, InstDev* dst, hipStream_t s) {
-  for (int k = 0; k < count; k += kInstChunk) {
-    const int m = std::min(kInstChunk, count - k);
-    InstChunk c{};
+template <typename T>
+hipError_t launch_put(const T* src, int count, T* dst, hipStream_t s) {
+  constexpr int N = Chunk<T>::N;
+  for (int k = 0; k < count; k += N) {
+    const int m = std::min(N, count - k);
+    Chunk<T> c{};
     std::copy(src + k, src + k + m, c.e);
-    hipLaunchKernelGGL(k_put_inst, dim3(1), dim3(256), 0, s, c, m,
+    hipLaunchKernelGGL((k_put<T>), dim3(1), dim3(256), 0, s, c, m,
                        reinterpret_cast<uint32_t*>(dst + k));
   }
   return hipGetLastError();
 }
+template hipError_t launch_put<InstDev>(const InstDev*, int, InstDev*, hipStream_t);
+template hipError_t launch_put<SubBeam>(const SubBeam*, int, SubBeam*, hipStream_t);
 
 // The pending screen of every beam (grid: x over points, y over beams), in
 // place.  One launch: by a round trip of each beam through the complex128

@@ -156,9 +156,10 @@ hipError_t launch_reduce_theta(const double* rows, const int32_t* row_begin, con
 constexpr int kSumParts = 256;
 hipError_t launch_sumsq(const double* x, int64_t n, double* partial, hipStream_t s);
 
-// Copies `count` beam table entries from host memory to dst, by value.
-constexpr int kInstChunk = 16;
-hipError_t launch_put_inst(const InstDev* src, int count, InstDev* dst, hipStream_t s);
+// Copies `count` records (beam table entries, screen spectra) from host
+// memory to dst, by value.
+template <typename T>
+hipError_t launch_put(const T* src, int count, T* dst, hipStream_t s);
 
 // The screen of step `pending` on every beam's state, in place.
 template <typename R>

@@ -82,8 +82,8 @@ namespace ssfm {
   X(2048, 2, 128, 8, 4, 2, 0x403, 16, 16, 8) \
   X(2048, 3, 128, 2, 16, 2, 0x403, 16, 16, 8) \
   X(2048, 4, 256, 4, 8, 4, 0x401, 8, 8, 8, 4) \
-  X(4096, 0, 256, 4, 8, 2, 0x403, 16, 16, 16) \
-  X(4096, 1, 256, 2, 16, 2, 0x403, 16, 16, 16) \
+  X(4096, 0, 256, 2, 16, 2, 0x403, 16, 16, 16) \
+  X(4096, 1, 256, 4, 8, 2, 0x403, 16, 16, 16) \
   X(4096, 2, 256, 2, 16, 2, 0x303, 16, 16, 16) \
   X(4096, 3, 256, 2, 16, 2, 0x3, 16, 16, 16) \
   X(4096, 4, 128, 4, 16, 2, 0x8402, 16, 16, 16) \

@@ -154,9 +154,6 @@ struct ssfm_ctx {
   // radix plans whose twiddles the device holds, per size group and pass
   std::vector<std::array<std::vector<int>, P_SLOTS>> tw_radices;
   size_t inst_lo = 0, inst_hi = 0;  // beam table entries the device does not have yet
-  bool spectra_changed = true;  // since the device's list of screen spectra
-  int sub_pairs = 0;            // largest pair count and levels x n of the
-  int64_t sub_table = 0;        // beams with subharmonics
   struct Spectrum {
     int kind = SSFM_SPECTRUM_KOLMOGOROV;
     double tau = 0.0, kappa_h = 0.0;
@@ -488,22 +485,26 @@ void drop_record(ssfm_ctx* c) {
   c->seeded_beam.assign(c->desc.size(), 0);
 }
 
+int sync_inst(ssfm_ctx* c);
+
 // Beam table entries [b0, b1) have changed: they go to the device with the
 // next call that reads them (setting 20 beams' fields and parameters waited
 // for 40 small copies when each was uploaded by itself: a population of 20
-// on 256^2 took 1180 us an evaluation, now 650).
+// on 256^2 took 1180 us an evaluation, now 650).  Without the library's own
+// graphs they go at once: a caller's capture of the march must read the
+// table and not hold a copy of it.
 int touch_inst(ssfm_ctx* c, size_t b0, size_t b1) {
   c->inst_lo = c->inst_lo < c->inst_hi ? std::min(c->inst_lo, b0) : b0;
   c->inst_hi = std::max(c->inst_hi, b1);
-  return SSFM_OK;
+  return c->use_graphs ? SSFM_OK : sync_inst(c);
 }
 
 // The changed entries to the device (stream-ordered, by value: the host table
 // may change right after).  Called before anything is captured.
 int sync_inst(ssfm_ctx* c) {
   if (c->inst_lo >= c->inst_hi) return SSFM_OK;
-  HIP_TRY(launch_put_inst(&c->inst[c->inst_lo], int(c->inst_hi - c->inst_lo),
-                          c->at<InstDev>(c->L.inst) + c->inst_lo, c->stream));
+  HIP_TRY(launch_put<InstDev>(&c->inst[c->inst_lo], int(c->inst_hi - c->inst_lo),
+                              c->at<InstDev>(c->L.inst) + c->inst_lo, c->stream));
   c->inst_lo = c->inst_hi = 0;
   return SSFM_OK;
 }
@@ -1220,13 +1221,13 @@ int do_seed(ssfm_ctx* c, int b, int mode, const double* target_dev, const double
 }
 
 
-// The list of the beams' screen spectra, uploaded when they have changed.
-// The subharmonic region is laid out over every turbulent beam in order.
-int upload_spectra(ssfm_ctx* c) {
-  if (!c->spectra_changed) return SSFM_OK;
+// The list of the beams' screen spectra to the device; the largest pair
+// count and levels x n of the beams with subharmonics.  The subharmonic
+// region is laid out over every turbulent beam in order.
+int upload_spectra(ssfm_ctx* c, int* sub_pairs, int64_t* sub_table) {
   std::vector<SubBeam> list(c->desc.size(), SubBeam{});
-  c->sub_pairs = 0;
-  c->sub_table = 0;
+  *sub_pairs = 0;
+  *sub_table = 0;
   int64_t region_off = 0;
   for (size_t b = 0; b < c->desc.size(); ++b) {
     const ssfm_instance_desc& d = c->desc[b];
@@ -1256,13 +1257,11 @@ int upload_spectra(ssfm_ctx* c) {
     region_off += subharmonic_region_doubles(d.n, e.pairs);
     if (sp.subharmonics == 0 || (!step && !(d.cn2 > 0))) continue;
     e.sp.levels = sp.subharmonics;
-    c->sub_pairs = std::max(c->sub_pairs, e.pairs);
-    c->sub_table = std::max<int64_t>(c->sub_table, int64_t(sp.subharmonics) * d.n);
+    *sub_pairs = std::max(*sub_pairs, e.pairs);
+    *sub_table = std::max<int64_t>(*sub_table, int64_t(sp.subharmonics) * d.n);
   }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.subh_beams, list.data(), sizeof(SubBeam) * list.size(),
-                         hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));  // the list goes out of scope
-  c->spectra_changed = false;
+  HIP_TRY(launch_put<SubBeam>(list.data(), int(list.size()), c->at<SubBeam>(c->L.subh_beams),
+                              c->stream));
   return SSFM_OK;
 }
 
@@ -1277,10 +1276,12 @@ int upload_spectra(ssfm_ctx* c) {
 // the same chains 703 us, now 540, of which 350 are the 28 read-outs.
 template <typename R>
 int do_gen_screens(ssfm_ctx* c) {
-  if (int r = upload_spectra(c)) return r;
+  int sub_pairs = 0;
+  int64_t sub_table = 0;
+  if (int r = upload_spectra(c, &sub_pairs, &sub_table)) return r;
   const SubBeam* spectra = c->at<SubBeam>(c->L.subh_beams);
-  if (c->sub_pairs > 0)
-    HIP_TRY(launch_subharmonic_setup(spectra, int(c->desc.size()), c->sub_pairs, c->sub_table,
+  if (sub_pairs > 0)
+    HIP_TRY(launch_subharmonic_setup(spectra, int(c->desc.size()), sub_pairs, sub_table,
                                      c->at<double>(c->L.subh), c->stream));
   return each_chain(c, true, [&](const Chain& ch) -> int {
     int pairs = 0;
@@ -2190,7 +2191,7 @@ int ssfm_set_precise_math(ssfm_ctx* c, int32_t enable) {
 int ssfm_use_graphs(ssfm_ctx* c, int32_t enable) {
   if (int r = check_ctx(c)) return r;
   c->use_graphs = enable != 0;
-  return SSFM_OK;
+  return sync_inst(c);
 }
 
 int ssfm_plan_variants(int32_t n, int32_t precision, int32_t* n_row, int32_t* n_col) {
@@ -2323,7 +2324,6 @@ int ssfm_set_screen_spectrum(ssfm_ctx* c, int32_t inst, int32_t kind, double tau
   sp.kind = kind;
   sp.tau = tau;
   sp.kappa_h = kappa_h;
-  c->spectra_changed = true;
   return SSFM_OK;
 }
 
@@ -2333,7 +2333,6 @@ int ssfm_set_subharmonics(ssfm_ctx* c, int32_t inst, int32_t levels) {
     return fail(SSFM_EINVAL, "subharmonic levels must be in [0, %d], got %d",
                 kMaxSubharmonicLevels, levels);
   c->spectrum[inst].subharmonics = levels;
-  c->spectra_changed = true;
   return SSFM_OK;
 }
 

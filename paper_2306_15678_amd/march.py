@@ -58,7 +58,7 @@ def _ptr_where(x, dtype_np, dtype_t):
 
 
 class Propagator:
-    """A batch of beams marching in lock-step on one GPU."""
+    """A batch of beams marched by the same number of steps on one GPU."""
 
     def __init__(self, descs: Sequence[L.InstanceDesc], precision: int = 32,
                  max_steps: int = 0, ckpt_every: int = 1,

@@ -30,7 +30,7 @@ import sys
 
 # The sources the row and column pass kernels are compiled from.
 PASS_SOURCES = ("fft_core.hpp", "plans.hpp", "screen.hpp", "internal.hpp", "kernels.hpp",
-                "pass_kernels.hpp", "pass_row_f32.hip", "pass_row_f64.hip",
+                "pass_kernels.hpp", "noise.hpp", "subharmonics.hpp", "pass_row_f32.hip", "pass_row_f64.hip",
                 "pass_col_f32.hip", "pass_col_f64.hip",
                 "pass_col_hx_f32.hip")
 
