@@ -20,7 +20,7 @@
 // traffic at the junction.  Twiddles come from a table in stage order
 // computed in FP64 on the host and rounded once; a thread with few points
 // loads the ones it needs once and keeps them in registers, one with many
-// loads them stage by stage.
+// loads them stage by stage or takes part of them from LDS.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -374,10 +374,12 @@ constexpr int first_radix() {
 // N points per line, T threads per line, LINES lines per workgroup; column
 // tiles pad their LDS by B slots every A points (see LdsPointMajor).  OPT:
 // bit 0 set loads each stage's twiddles just before that stage (fewer live
-// registers) instead of all of them before the first; bits 8-11 give the
+// registers) instead of all of them before the first; bit 1 has the middle
+// stage's in LDS and the last stage's in registers (three stages, complex64;
+// see MidTable); bits 8-11 give the
 // wavefronts per SIMD the compiler must leave room for in the complex64
 // kernels (0: no target), bits 12-14 the same for the complex128 ones; bit
-// 15 makes a column pass exchange through half its tile (fft_line_hx),
+// 15 makes a column pass exchange through half its tile (hx_stages),
 // complex64 only.
 template <int N_, int T_, int LINES_, class Rad, int PA_ = 32, int PB_ = 0, int OPT_ = 0>
 struct Plan {

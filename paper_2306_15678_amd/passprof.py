@@ -30,9 +30,9 @@ import sys
 
 # The sources the row and column pass kernels are compiled from.
 PASS_SOURCES = ("fft_core.hpp", "plans.hpp", "screen.hpp", "internal.hpp", "kernels.hpp",
-                "pass_kernels.hpp", "noise.hpp", "subharmonics.hpp", "pass_row_f32.hip", "pass_row_f64.hip",
-                "pass_col_f32.hip", "pass_col_f64.hip",
-                "pass_col_hx_f32.hip")
+                "subharmonics.hpp", "noise.hpp", "pass_kernels.hpp",
+                "pass_row_f32.hip", "pass_row_f64.hip", "pass_col_f32.hip",
+                "pass_col_f64.hip", "pass_col_hx_f32.hip")
 
 
 FD_ITERS = 4  # fixed-point iterations per finite-difference step
@@ -54,7 +54,7 @@ def kernel_kind(name: str):
     """'row_fwd' / 'col_fwd' / 'col_adj' / 'row_adj' for a march pass
     kernel's name (its last three template arguments: column pass, adjoint,
     library sine), 'copy' for the calibration copy, None otherwise."""
-    base = name.split("<")[0].split("::")[-1].strip()
+    base = name.split("(")[0].split("<")[0].split("::")[-1].strip()
     if base == "k_block_mean":
         return "copy"
     if base == "k_march":
