@@ -19,7 +19,7 @@ struct InstDev {
   double cK;           // k0 n2 I_a dz
   double cM;           // (K-1) beta_K I_a^(K-1) dz
   double inv2k1;       // 1 / (2 (K-1))
-  double x_weak;       // x up to which x^(K-1) and cM x^(K-1) vanish beside 1
+  double x_weak;       // x up to which x^(K-1) and cM x^(K-1) vanish beside 1 (-1: none)
   double theta[8];     // ansatz parameters
   // the same rounded to float: complex64 kernels read them by scalar loads
   // and need no conversions (which would sit in vector registers)

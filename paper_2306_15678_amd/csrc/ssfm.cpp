@@ -1392,13 +1392,16 @@ int upload_plan(ssfm_ctx* c) {
       in.cK = k0 * d.n2 * d.i_ref * d.dz;
       in.cM = (d.terms & SSFM_MPA) ? (in.K - 1) * d.beta_k * std::pow(d.i_ref, in.K - 1) * d.dz : 0.0;
       in.inv2k1 = 1.0 / (2.0 * (in.K - 1));
-      // x^(K-1) max(1, cM) <= 2^-26 (2^-55 in double): below half an ulp of
-      // 1 with room for the powers' rounding
-      const double weak = 1.0 / std::max(1.0, in.cM);
-      in.x_weak = 0.999 * std::pow(0x1p-55 * weak, 1.0 / (in.K - 1));
-      in.x_weak_f = float(0.999 * std::pow(0x1p-26 * weak, 1.0 / (in.K - 1)));
       in.cK_f = float(in.cK);
       in.cM_f = float(in.cM);
+      // x^(K-1) max(1, |cM|) <= 2^-26 (2^-55 in double): below half an ulp of
+      // 1, on either side of it, with room for the powers' rounding.  A
+      // coefficient that is not finite leaves nothing weak.
+      const auto weak_level = [&](double half_ulp) {
+        return 0.999 * std::pow(half_ulp / std::max(1.0, std::fabs(in.cM)), 1.0 / (in.K - 1));
+      };
+      in.x_weak = std::isfinite(in.cM) ? weak_level(0x1p-55) : -1.0;
+      in.x_weak_f = std::isfinite(in.cM_f) ? float(weak_level(0x1p-26)) : -1.0f;
       in.inv2k1_f = float(in.inv2k1);
       for (int p = 0; p < 8; ++p) in.theta[p] = in.theta_f[p] = 0.0;
     }
