@@ -81,7 +81,8 @@ template hipError_t launch_pass<double>(int, int, int, const PassArgs<double>&, 
 // ----------------------------------------------------- pointwise kernels
 template <typename R>
 __global__ void k_load_field(const double* __restrict__ src, cx<R>* __restrict__ dst,
-                             int64_t n_elem, double scale) {
+                             int64_t n_elem, double scale, InstDev entry, InstDev* slot) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *slot = entry;
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n_elem;
        i += int64_t(gridDim.x) * blockDim.x) {
     dst[i] = {R(src[2 * i] * scale), R(src[2 * i + 1] * scale)};
@@ -96,14 +97,16 @@ static int grid_for(int64_t n_elem, int threads) {
 }
 
 template <typename R>
-hipError_t launch_load_field(const double* src, void* dst, int64_t n_elem,
-                             double scale, hipStream_t s) {
+hipError_t launch_load_field(const double* src, void* dst, int64_t n_elem, double scale,
+                             const InstDev& entry, InstDev* slot, hipStream_t s) {
   hipLaunchKernelGGL((k_load_field<R>), dim3(grid_for(n_elem, 256)), dim3(256), 0, s,
-                     src, static_cast<cx<R>*>(dst), n_elem, scale);
+                     src, static_cast<cx<R>*>(dst), n_elem, scale, entry, slot);
   return hipGetLastError();
 }
-template hipError_t launch_load_field<float>(const double*, void*, int64_t, double, hipStream_t);
-template hipError_t launch_load_field<double>(const double*, void*, int64_t, double, hipStream_t);
+template hipError_t launch_load_field<float>(const double*, void*, int64_t, double, const InstDev&,
+                                             InstDev*, hipStream_t);
+template hipError_t launch_load_field<double>(const double*, void*, int64_t, double,
+                                              const InstDev&, InstDev*, hipStream_t);
 
 // Host records to device memory, by value: ordered with the passes on the
 // stream, where a copy from the host's memory would have to be waited for.

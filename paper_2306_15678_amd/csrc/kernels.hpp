@@ -105,10 +105,12 @@ hipError_t launch_pass(int kind, int n, int variant, const PassArgs<R>& a, hipSt
 
 // Pointwise helpers -------------------------------------------------------
 
-// dst (cx<R> device state, beam b at off) = src (complex128 SI) * scale
+// dst (cx<R> device state, beam b at off) = src (complex128 SI) * scale; the
+// beam's entry goes to its slot of the beam table with it (a launch of its
+// own for each: 12 beams of 256^2 took 703 us an evaluation, so 678)
 template <typename R>
-hipError_t launch_load_field(const double* src, void* dst, int64_t n_elem,
-                             double scale, hipStream_t s);
+hipError_t launch_load_field(const double* src, void* dst, int64_t n_elem, double scale,
+                             const InstDev& entry, InstDev* slot, hipStream_t s);
 
 // dst (complex128 SI) = sqrt(I_a) * [pending screen](state); optionally
 // intensity only (float64 I = I_a |u|^2).

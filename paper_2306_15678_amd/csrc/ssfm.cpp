@@ -153,7 +153,6 @@ struct ssfm_ctx {
   bool precise = false;  // library sine and cosine in the FP32 screens
   // radix plans whose twiddles the device holds, per size group and pass
   std::vector<std::array<std::vector<int>, P_SLOTS>> tw_radices;
-  size_t inst_lo = 0, inst_hi = 0;  // beam table entries the device does not have yet
   struct Spectrum {
     int kind = SSFM_SPECTRUM_KOLMOGOROV;
     double tau = 0.0, kappa_h = 0.0;
@@ -485,27 +484,26 @@ void drop_record(ssfm_ctx* c) {
   c->seeded_beam.assign(c->desc.size(), 0);
 }
 
-int sync_inst(ssfm_ctx* c);
-
-// Beam table entries [b0, b1) have changed: they go to the device with the
-// next call that reads them (setting 20 beams' fields and parameters waited
-// for 40 small copies when each was uploaded by itself: a population of 20
-// on 256^2 took 1180 us an evaluation, now 650).  Without the library's own
-// graphs they go at once: a caller's capture of the march must read the
-// table and not hold a copy of it.
-int touch_inst(ssfm_ctx* c, size_t b0, size_t b1) {
-  c->inst_lo = c->inst_lo < c->inst_hi ? std::min(c->inst_lo, b0) : b0;
-  c->inst_hi = std::max(c->inst_hi, b1);
-  return c->use_graphs ? SSFM_OK : sync_inst(c);
+// Fields and parameters are set outside captures: the host's counts and its
+// copy of the beam table change with the device's, at the call.
+int not_captured(ssfm_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+  if (st != hipStreamCaptureStatusNone)
+    return fail(SSFM_EHIP, "fields and parameters cannot be set while the stream is captured");
+  return SSFM_OK;
 }
 
-// The changed entries to the device (stream-ordered, by value: the host table
-// may change right after).  Called before anything is captured.
-int sync_inst(ssfm_ctx* c) {
-  if (c->inst_lo >= c->inst_hi) return SSFM_OK;
-  HIP_TRY(launch_put<InstDev>(&c->inst[c->inst_lo], int(c->inst_hi - c->inst_lo),
-                              c->at<InstDev>(c->L.inst) + c->inst_lo, c->stream));
-  c->inst_lo = c->inst_hi = 0;
+// Beam table entries [b0, b1) to the device, now and in order on the stream:
+// whatever is launched or captured after this reads them from the table, and
+// a captured read keeps no copy of its own.  By value: the host table may
+// change right after, and nothing waits (12 beams of 256^2, fields and
+// parameters set, marched, compared: 1300 us with a copy and a wait for each
+// change, now 680).
+int upload_inst(ssfm_ctx* c, size_t b0, size_t b1) {
+  if (int r = not_captured(c)) return r;
+  HIP_TRY(launch_put<InstDev>(&c->inst[b0], int(b1 - b0), c->at<InstDev>(c->L.inst) + b0,
+                              c->stream));
   return SSFM_OK;
 }
 
@@ -929,7 +927,6 @@ int half_step_lam(ssfm_ctx* c, bool forward, const Chain& ch) {
 template <typename R>
 int flush_pending(ssfm_ctx* c) {
   if (!c->pending) return SSFM_OK;
-  if (int r = sync_inst(c)) return r;
   HIP_TRY(launch_flush<R>(c->field(c->L.S), c->at<InstDev>(c->L.inst), int(c->desc.size()),
                           c->L.max_n, c->at<R>(c->L.screens), c->at<int64_t>(c->L.steps),
                           c->step - 1, c->stream));
@@ -1531,17 +1528,8 @@ int do_apply_lens(ssfm_ctx* c, int b, const ssfm_lens& l) {
   return SSFM_OK;
 }
 
-#define SSFM_BY_PRECISION(ctx, fn, ...) \
-  ((ctx)->precision == SSFM_FP64 ? fn<double>(__VA_ARGS__) : fn<float>(__VA_ARGS__))
-
-// fn with the device's beam table up to date.
-template <typename F>
-int with_inst(ssfm_ctx* c, F fn) {
-  if (int r = sync_inst(c)) return r;
-  return fn();
-}
 #define SSFM_DISPATCH(ctx, fn, ...) \
-  with_inst((ctx), [&]() -> int { return SSFM_BY_PRECISION((ctx), fn, __VA_ARGS__); })
+  ((ctx)->precision == SSFM_FP64 ? fn<double>(__VA_ARGS__) : fn<float>(__VA_ARGS__))
 
 // Device pointer of a caller buffer, staging host data through the
 // workspace's complex128 staging area (bytes <= 16 n_max^2).
@@ -1579,6 +1567,7 @@ int store_out(ssfm_ctx* c, int b, const void* state, int64_t pending, double sca
 
 template <typename R>
 int do_set_field(ssfm_ctx* c, int b, const void* src, int32_t where) {
+  if (int r = not_captured(c)) return r;
   if (c->step > 0 || c->pending) {
     // keep the other beams exact: apply their pending screen first
     if (int r = flush_pending<R>(c)) return r;
@@ -1586,16 +1575,6 @@ int do_set_field(ssfm_ctx* c, int b, const void* src, int32_t where) {
   const int n = c->desc[b].n;
   const double* dsrc;
   if (int r = stage_in(c, src, where, 16 * size_t(n) * n, &dsrc)) return r;
-  HIP_TRY(launch_load_field<R>(dsrc, static_cast<char*>(c->field(c->L.S)) + c->inst[b].off * c->el,
-                               int64_t(n) * n, 1.0 / std::sqrt(c->desc[b].i_ref), c->stream));
-  if (c->strang) {
-    // the state of a Strang march is V = L(dz/2) U: half a step for beam b
-    if (int r = half_steps<R>(c, true)) return r;
-    const size_t off = size_t(c->inst[b].off) * c->el;
-    HIP_TRY(launch_copy<R>(static_cast<char*>(c->field(c->L.Wk)) + off,
-                           static_cast<char*>(c->field(c->L.S)) + off, int64_t(n) * n,
-                           c->stream));
-  }
   // beam b starts its own step count (its screen schedule) here; the other
   // beams keep theirs.  Once every beam has been set at the same step, the
   // context count restarts at 0 (so marches from fresh fields reuse their
@@ -1609,9 +1588,21 @@ int do_set_field(ssfm_ctx* c, int b, const void* src, int32_t where) {
   if (same) {
     for (InstDev& in : c->inst) in.step_base = 0;
     c->step = 0;
-    return touch_inst(c, 0, c->inst.size());
+    if (c->inst.size() > 1)
+      if (int r = upload_inst(c, 0, c->inst.size())) return r;
   }
-  return touch_inst(c, b, b + 1);
+  HIP_TRY(launch_load_field<R>(dsrc, static_cast<char*>(c->field(c->L.S)) + c->inst[b].off * c->el,
+                               int64_t(n) * n, 1.0 / std::sqrt(c->desc[b].i_ref), c->inst[b],
+                               c->at<InstDev>(c->L.inst) + b, c->stream));
+  if (c->strang) {
+    // the state of a Strang march is V = L(dz/2) U: half a step for beam b
+    if (int r = half_steps<R>(c, true)) return r;
+    const size_t off = size_t(c->inst[b].off) * c->el;
+    HIP_TRY(launch_copy<R>(static_cast<char*>(c->field(c->L.Wk)) + off,
+                           static_cast<char*>(c->field(c->L.S)) + off, int64_t(n) * n,
+                           c->stream));
+  }
+  return SSFM_OK;
 }
 
 // Lines per workgroup of a variant (0 if it does not exist).
@@ -1645,7 +1636,7 @@ int apply_variants(ssfm_ctx* c, int n, const std::array<int, P_SLOTS>& var) {
   clear_graphs(c);
   std::vector<std::vector<unsigned char>> blobs;
   blobs.reserve(P_SLOTS * groups.size());
-  if (int r = SSFM_BY_PRECISION(c, upload_variants, c, &blobs)) return r;
+  if (int r = SSFM_DISPATCH(c, upload_variants, c, &blobs)) return r;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return SSFM_OK;
 }
@@ -1860,7 +1851,7 @@ int ssfm_create(const ssfm_instance_desc* desc, int32_t n_inst, int32_t precisio
     HIP_TRY(hipEventCreateWithFlags(&ej, hipEventDisableTiming));
     c->gjoin.push_back(ej);
   }
-  int r = SSFM_BY_PRECISION(c, upload_plan, c.get());
+  int r = SSFM_DISPATCH(c, upload_plan, c.get());
   if (r) return r;
   *out = c.release();
   return SSFM_OK;
@@ -1875,7 +1866,7 @@ int ssfm_destroy(ssfm_ctx* ctx) {
 
 int ssfm_set_field(ssfm_ctx* c, int32_t inst, const void* src, int32_t where) {
   if (int r = check_inst(c, inst)) return r;
-  return SSFM_BY_PRECISION(c, do_set_field, c, inst, src, where);
+  return SSFM_DISPATCH(c, do_set_field, c, inst, src, where);
 }
 
 int ssfm_set_theta(ssfm_ctx* c, int32_t inst, const double* theta) {
@@ -1889,7 +1880,7 @@ int ssfm_set_theta(ssfm_ctx* c, int32_t inst, const double* theta) {
   // a recorded march (its stored fields, the screen its adjoint applies)
   // belongs to the old parameters
   drop_record(c);
-  return touch_inst(c, inst, inst + 1);
+  return upload_inst(c, inst, inst + 1);
 }
 
 int ssfm_gen_screens(ssfm_ctx* c) {
@@ -1974,7 +1965,7 @@ int ssfm_set_splitting(ssfm_ctx* c, int32_t scheme) {
   c->diag_valid = 0;
   drop_record(c);
   for (InstDev& in : c->inst) in.step_base = 0;
-  return touch_inst(c, 0, c->inst.size());
+  return upload_inst(c, 0, c->inst.size());
 }
 
 namespace {
@@ -2086,7 +2077,6 @@ int ssfm_fluence_mismatch(ssfm_ctx* c, int32_t inst, const void* target, int32_t
   if (int r = stage_in(c, target, where, 8 * size_t(n) * n, &dt)) return r;
   // the sums go to the staging area past the target
   double* part = c->at<double>(c->L.stage) + size_t(n) * n;
-  if (int r = sync_inst(c)) return r;
   auto run = [&]<typename R>(R*) -> int {
     // the field U: the state with its pending screen (Lie), the state itself
     // (finite differences), or L(-dz/2) of it in the work buffer (Strang)
@@ -2194,7 +2184,7 @@ int ssfm_set_precise_math(ssfm_ctx* c, int32_t enable) {
 int ssfm_use_graphs(ssfm_ctx* c, int32_t enable) {
   if (int r = check_ctx(c)) return r;
   c->use_graphs = enable != 0;
-  return sync_inst(c);
+  return SSFM_OK;
 }
 
 int ssfm_plan_variants(int32_t n, int32_t precision, int32_t* n_row, int32_t* n_col) {
@@ -2234,7 +2224,6 @@ int ssfm_time_adjoint_passes(ssfm_ctx* c, int32_t reps, double* ms_col, double* 
   // the state standing in for the stored pre-screen field, at a step with
   // no turbulence screen (the ansatz partials go to the accumulators every
   // backward clears first).  Fields, cotangent and gradients are unchanged.
-  if (int q = sync_inst(c)) return q;
   auto body = [&]<typename R>(R*) -> int {
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.Lam);
@@ -2281,7 +2270,6 @@ int ssfm_time_passes(ssfm_ctx* c, int32_t reps, double* ms_row, double* ms_col,
   for (auto& x : ev.e) HIP_TRY(hipEventCreate(&x));
   hipEvent_t e0 = ev.e[0], e1 = ev.e[1], e2 = ev.e[2];
   int r = SSFM_OK;
-  if (int q = sync_inst(c)) return q;
   auto body = [&]<typename R>(R*) -> int {
     PassArgs<R> a = base_args<R>(c);
     a.src = c->field(c->L.S);
