@@ -346,33 +346,32 @@ __global__ void __launch_bounds__(P::THREADS)
           double s = 0.0, m = 0.0;
 #pragma unroll
           for (int c = 0; c < E; c += SB) {
-            R x[SB], a2[SB];
-            if (flags & PASS_SCREEN) {
-              R ph[SB], am[SB];
+            R x[SB], ph[SB];
 #pragma unroll
-              for (int e = 0; e < SB; ++e) ph[e] = R(0);
-              if (plane) {
+            for (int e = 0; e < SB; ++e) ph[e] = R(0);
+            if (plane) {
 #pragma unroll
-                for (int e = 0; e < SB; ++e) ph[e] = plane[to + STRIDE * uint32_t(c + e)];
-              }
-              screen_apply_n<R, SB, PRECISE>(sc, v + c, ph, x, am);
-#pragma unroll
-              for (int e = 0; e < SB; ++e) a2[e] = am[e] * am[e];
-            } else {
-#pragma unroll
-              for (int e = 0; e < SB; ++e) x[e] = v[c + e].re * v[c + e].re + v[c + e].im * v[c + e].im;
-              if (!(flags & PASS_RAW)) screen_amp2_n<R, SB>(sc, x, a2);
+              for (int e = 0; e < SB; ++e) ph[e] = plane[to + STRIDE * uint32_t(c + e)];
             }
-            if (flags & PASS_RAW) {
+#pragma unroll
+            for (int e = 0; e < SB; ++e) x[e] = v[c + e].re * v[c + e].re + v[c + e].im * v[c + e].im;
+            const ScreenTerms<R, SB> st(sc, x);
+            if (a.part != nullptr) {
+              // x A^2 with the A^2 of its own exponential whether or not the
+              // screen is applied here: the trace of a march cut anywhere is
+              // the same (the square of the screen's A rounds differently)
+              R a2[SB];
 #pragma unroll
               for (int e = 0; e < SB; ++e) a2[e] = R(1);
-            }
+              if (!(flags & PASS_RAW)) st.amp2(sc, a2);
 #pragma unroll
-            for (int e = 0; e < SB; ++e) {
-              const double xa = double(x[e]) * double(a2[e]);
-              s += xa;
-              m = fmax(m, xa);
+              for (int e = 0; e < SB; ++e) {
+                const double xa = double(x[e]) * double(a2[e]);
+                s += xa;
+                m = fmax(m, xa);
+              }
             }
+            if (flags & PASS_SCREEN) st.template apply<PRECISE>(sc, v + c, ph);
           }
           if (a.part != nullptr) {
             wave_sum_max(s, m);

@@ -107,25 +107,6 @@ __device__ __forceinline__ void screen_eval(const ScreenConst<R>& s, R x,
   }
 }
 
-// A^2 at x (for the power diagnostics: |E V|^2 = x A^2).
-template <typename R>
-__device__ __forceinline__ R screen_amp2(const ScreenConst<R>& s, R x) {
-  const unsigned tm = s.terms;
-  R l2 = R(0);  // log2 of A^2
-  if (tm & T_MPA) {
-    const R xk1 = ipow(x, s.K - 1);
-    l2 -= fast_log2(R(1) + s.cM * xk1) * (R(2) * s.inv2k1);
-  }
-  if (tm & T_ANSATZ) {
-    const R x2 = x * x, x3 = x2 * x, x4 = x2 * x2;
-    const R im = (s.th[4] * x + s.th[5] * x2 + s.th[6] * x3 + s.th[7] * x4) *
-                 rcp(R(1) + x4);
-    l2 -= R(2) * s.cK * im * R(1.44269504088896340736);
-  }
-  if (l2 == R(0)) return R(1);
-  return fast_exp2(l2);
-}
-
 // u <- u E(|u|^2) exp(i phi_t)
 template <typename R>
 __device__ __forceinline__ cx<R> screen_apply(const ScreenConst<R>& s, cx<R> u,
@@ -265,104 +246,85 @@ __device__ __forceinline__ void ipow_n(const R* x, int m, R* out) {
   }
 }
 
-// ln A and Phi (without turbulence) at C points; strong: strong_n of them.
+// The screen's terms at C points: lq = log2(1 + cM x^(K-1)), im = Im f, phi =
+// Phi without turbulence.  absorbs: whether any of them has A != 1.
 template <typename R, int C>
-__device__ __forceinline__ void screen_eval_n(const ScreenConst<R>& s, const R* x, bool strong,
-                                              R* log_a, R* phi) {
-  const unsigned tm = s.terms;
+struct ScreenTerms {
+  R lq[C], im[C], phi[C];
+  bool absorbs;
+  __device__ __forceinline__ ScreenTerms(const ScreenConst<R>& s, const R* x) {
+    const unsigned tm = s.terms;
 #pragma unroll
-  for (int e = 0; e < C; ++e) {
-    log_a[e] = R(0);
-    phi[e] = R(0);
-  }
-  if (tm & T_KERR) {
+    for (int e = 0; e < C; ++e) lq[e] = im[e] = phi[e] = R(0);
+    if (tm & T_KERR) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) phi[e] += s.cK * x[e];
-  }
-  if (strong) {
-    R xk1[C];
-    ipow_n<R, C>(x, s.K - 1, xk1);
-    if (tm & T_PLASMA) {
-#pragma unroll
-      for (int e = 0; e < C; ++e) phi[e] -= s.cK * x[e] * (R(1) - rcp(R(1) + xk1[e]));
+      for (int e = 0; e < C; ++e) phi[e] += s.cK * x[e];
     }
-    if (tm & T_MPA) {
+    const bool strong = strong_n<R, C>(s, x);
+    if (strong) {
+      R xk1[C];
+      ipow_n<R, C>(x, s.K - 1, xk1);
+      if (tm & T_PLASMA) {
 #pragma unroll
-      for (int e = 0; e < C; ++e)
-        log_a[e] -= fast_log2(R(1) + s.cM * xk1[e]) * (R(0.69314718055994530942) * s.inv2k1);
-    }
-  }
-  if (tm & T_ANSATZ) {
+        for (int e = 0; e < C; ++e) phi[e] -= s.cK * x[e] * (R(1) - rcp(R(1) + xk1[e]));
+      }
+      if (tm & T_MPA) {
 #pragma unroll
-    for (int e = 0; e < C; ++e) {
-      const R xe = x[e], x2 = xe * xe, x3 = x2 * xe, x4 = x2 * x2;
-      const R inv = rcp(R(1) + x4);
-      const R re = (s.th[0] * xe + s.th[1] * x2 + s.th[2] * x3 + s.th[3] * x4) * inv;
-      const R im = (s.th[4] * xe + s.th[5] * x2 + s.th[6] * x3 + s.th[7] * x4) * inv;
-      phi[e] += s.cK * re;
-      log_a[e] -= s.cK * im;
+        for (int e = 0; e < C; ++e) lq[e] = fast_log2(R(1) + s.cM * xk1[e]);
+      }
     }
+    if (tm & T_ANSATZ) {
+#pragma unroll
+      for (int e = 0; e < C; ++e) {
+        const R xe = x[e], x2 = xe * xe, x3 = x2 * xe, x4 = x2 * x2;
+        const R inv = rcp(R(1) + x4);
+        const R re = (s.th[0] * xe + s.th[1] * x2 + s.th[2] * x3 + s.th[3] * x4) * inv;
+        im[e] = (s.th[4] * xe + s.th[5] * x2 + s.th[6] * x3 + s.th[7] * x4) * inv;
+        phi[e] += s.cK * re;
+      }
+    }
+    absorbs = (strong && (tm & T_MPA)) || (tm & T_ANSATZ);
   }
-}
 
-// A^2 at C points.
-template <typename R, int C>
-__device__ __forceinline__ void screen_amp2_n(const ScreenConst<R>& s, const R* x, R* out) {
-  const unsigned tm = s.terms;
-  R l2[C];
-#pragma unroll
-  for (int e = 0; e < C; ++e) l2[e] = R(0);
-  const bool absorb = (tm & T_MPA) && strong_n<R, C>(s, x);
-  if (absorb) {
-    R xk1[C];
-    ipow_n<R, C>(x, s.K - 1, xk1);
-#pragma unroll
-    for (int e = 0; e < C; ++e)
-      l2[e] -= fast_log2(R(1) + s.cM * xk1[e]) * (R(2) * s.inv2k1);
-  }
-  if (tm & T_ANSATZ) {
-#pragma unroll
-    for (int e = 0; e < C; ++e) {
-      const R xe = x[e], x2 = xe * xe, x3 = x2 * xe, x4 = x2 * x2;
-      const R im = (s.th[4] * xe + s.th[5] * x2 + s.th[6] * x3 + s.th[7] * x4) *
-                   rcp(R(1) + x4);
-      l2[e] -= R(2) * s.cK * im * R(1.44269504088896340736);
-    }
-  }
-  if (absorb || (tm & T_ANSATZ)) {
-#pragma unroll
-    for (int e = 0; e < C; ++e) out[e] = (l2[e] == R(0)) ? R(1) : fast_exp2(l2[e]);
-  } else {
+  // A^2
+  __device__ __forceinline__ void amp2(const ScreenConst<R>& s, R* out) const {
 #pragma unroll
     for (int e = 0; e < C; ++e) out[e] = R(1);
+    if (absorbs) {
+#pragma unroll
+      for (int e = 0; e < C; ++e) {
+        R l2 = R(0);
+        l2 -= lq[e] * (R(2) * s.inv2k1);
+        l2 -= R(2) * s.cK * im[e] * R(1.44269504088896340736);
+        if (l2 != R(0)) out[e] = fast_exp2(l2);
+      }
+    }
   }
-}
 
-// u <- u E(|u|^2) exp(i phi_t) at C points; x: |u|^2 and a: A at them.
-template <typename R, int C, bool PRECISE>
-__device__ __forceinline__ void screen_apply_n(const ScreenConst<R>& s, cx<R>* u,
-                                               const R* phi_t, R* x, R* a) {
-  R log_a[C], phi[C];
-#pragma unroll
-  for (int e = 0; e < C; ++e) x[e] = u[e].re * u[e].re + u[e].im * u[e].im;
-  const bool strong = strong_n<R, C>(s, x);
-  screen_eval_n<R, C>(s, x, strong, log_a, phi);
-  if ((strong && (s.terms & T_MPA)) || (s.terms & T_ANSATZ)) {
-#pragma unroll
-    for (int e = 0; e < C; ++e)
-      a[e] = (log_a[e] == R(0)) ? R(1) : fast_exp2(log_a[e] * R(1.44269504088896340736));
-  } else {
+  // u <- u E(|u|^2) exp(i phi_t)
+  template <bool PRECISE>
+  __device__ __forceinline__ void apply(const ScreenConst<R>& s, cx<R>* u, const R* phi_t) const {
+    R a[C];
 #pragma unroll
     for (int e = 0; e < C; ++e) a[e] = R(1);
+    if (absorbs) {
+#pragma unroll
+      for (int e = 0; e < C; ++e) {
+        R log_a = R(0);
+        log_a -= lq[e] * (R(0.69314718055994530942) * s.inv2k1);
+        log_a -= s.cK * im[e];
+        if (log_a != R(0)) a[e] = fast_exp2(log_a * R(1.44269504088896340736));
+      }
+    }
+    R sn[C], cs[C];
+#pragma unroll
+    for (int e = 0; e < C; ++e) sin_cos(phi[e] + phi_t[e], &sn[e], &cs[e], PRECISE);
+#pragma unroll
+    for (int e = 0; e < C; ++e)
+      u[e] = {a[e] * (u[e].re * cs[e] - u[e].im * sn[e]),
+              a[e] * (u[e].re * sn[e] + u[e].im * cs[e])};
   }
-  R sn[C], cs[C];
-#pragma unroll
-  for (int e = 0; e < C; ++e) sin_cos(phi[e] + phi_t[e], &sn[e], &cs[e], PRECISE);
-#pragma unroll
-  for (int e = 0; e < C; ++e)
-    u[e] = {a[e] * (u[e].re * cs[e] - u[e].im * sn[e]),
-            a[e] * (u[e].re * sn[e] + u[e].im * cs[e])};
-}
+};
 
 // Adjoint of the screen at C points (see screen_adjoint): lam holds the
 // cotangents of the screened values and is overwritten with those of V;
