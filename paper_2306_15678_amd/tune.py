@@ -5,11 +5,15 @@ For every grid size present in a ``Propagator`` it times each compiled
 variant of the forward row pass and of the forward column pass with the
 library's HIP-event timing hook (``ssfm_time_passes``: launches on the
 context's stream), keeps the fastest of each and selects them.  Results are
-cached in a JSON file keyed by device name, grid size and precision
-(``SSFM_TUNE_CACHE``, default ``~/.cache/ssfm_tune.json``).
+cached in a JSON file keyed by device name, grid size, precision and build of
+the library (``SSFM_TUNE_CACHE``, default ``~/.cache/ssfm_tune.json``): a
+variant is an index into that build's tiles, which another build may not have
+or have for other tiles.
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
 from typing import Dict
@@ -25,9 +29,15 @@ def _cache_path() -> str:
                           os.path.join(os.path.expanduser("~"), ".cache", "ssfm_tune.json"))
 
 
+@functools.lru_cache(maxsize=None)
+def _build() -> str:
+    with open(L.LIB_PATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def _key(n: int, precision: int) -> str:
     name = torch.cuda.get_device_name(0) if torch.cuda.is_available() else "none"
-    return f"{name}|n={n}|fp{precision}"
+    return f"{name}|n={n}|fp{precision}|{_build()}"
 
 
 def load_cache() -> Dict:

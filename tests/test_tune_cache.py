@@ -1,0 +1,74 @@
+"""The tuner's cache file: what it keeps belongs to one build of the library,
+whose tile variants its indices name."""
+import json
+
+import pytest
+
+from paper_2306_15678_amd import _lib as L
+from paper_2306_15678_amd import tune as tuner
+from paper_2306_15678_amd.march import make_desc
+
+N = 1024
+
+
+class _Context:
+    """A context as the tuner sees it: two variants of each pass, the second
+    one the faster."""
+
+    precision = 32
+
+    def __init__(self, max_steps=0):
+        self.descs = [make_desc(N, 0.06, 0.1, wavelength=8e-7, n2=3.2e-23, terms=1)]
+        self.max_steps = max_steps
+        self.plan, self.adjoint, self.timed = (0, 0), (-1, -1), 0
+
+    def _known(self, *variants):
+        if any(not -1 <= v < 2 for v in variants):
+            raise L.SsfmError(L.EINVAL, "select", "variant out of range")
+
+    def select_plan(self, n, row, col):
+        self._known(row, col)
+        self.plan = (row, col)
+
+    def select_adjoint_plan(self, n, row, col):
+        self._known(row, col)
+        self.adjoint = (row, col)
+
+    def time_passes(self, reps):
+        self.timed += 1
+        return 2.0 - self.plan[0], 2.0 - self.plan[1], 0.0, 0.0
+
+    def time_adjoint_passes(self, reps):
+        self.timed += 1
+        return 2.0 - self.adjoint[1], 2.0 - self.adjoint[0]
+
+
+@pytest.fixture
+def cache(tmp_path, monkeypatch):
+    path = tmp_path / "tune.json"
+    monkeypatch.setenv("SSFM_TUNE_CACHE", str(path))
+    monkeypatch.setattr(tuner, "plan_variants", lambda n, precision: (2, 2))
+    return path
+
+
+@pytest.mark.parametrize("row,col", [(6, 6), (0, 0)])
+def test_entries_of_other_builds_are_not_used(cache, row, col):
+    """Variants saved by another build (whose indices this one may not have,
+    or have for other tiles) are measured anew."""
+    name = "none" if not tuner.torch.cuda.is_available() else tuner.torch.cuda.get_device_name(0)
+    old = {f"{name}|n={N}|fp32": {"row": row, "col": col, "row_adj": row, "col_adj": col}}
+    cache.write_text(json.dumps(old))
+    p = _Context(max_steps=4)
+    best = tuner.tune(p)[N]
+    assert p.timed > 0
+    assert (best["row"], best["col"], best["row_adj"], best["col_adj"]) == (1, 1, 1, 1)
+    assert p.plan == (1, 1) and p.adjoint == (1, 1)
+
+
+def test_entries_of_this_build_are_used(cache):
+    first, second = _Context(max_steps=4), _Context(max_steps=4)
+    best = tuner.tune(first)[N]
+    again = tuner.tune(second)[N]
+    assert second.timed == 0 and second.plan == (1, 1) and second.adjoint == (1, 1)
+    assert {k: best[k] for k in ("row", "col", "row_adj", "col_adj")} == \
+        {k: again[k] for k in ("row", "col", "row_adj", "col_adj")}
