@@ -651,17 +651,17 @@ struct MarchBuffers {
   bool kept;
 };
 
-// The passes that end steps i0 <= i < i1 of a march of n steps from step0
-// (for i0 = 0 also the pass that opens it).  pend(i): step whose screen acts
-// before step i diffracts (-1: none).  part: whether to reduce the power and
-// peak of each step.  open, end: timing events of the opening and of the
-// (single) ending pass.
+// The passes that end steps i0 <= i < i1 of a march of n steps from step0 (for
+// i0 = 0 also, with opens, the pass that opens it).  pend(i): step whose
+// screen acts before step i diffracts (-1: none).  part: whether to reduce
+// the power and peak of each step.  open, end: timing events of the opening
+// and of the (single) ending pass.
 template <typename R, typename Pend, typename Rec>
-int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
+int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1, bool opens,
                   const MarchBuffers& m, Pend pend, Rec rec, bool part, const Chain& ch,
                   const ssfm_ctx::PassSample* open, const ssfm_ctx::PassSample* end) {
   const int32_t raw = c->strang ? PASS_RAW : 0;  // Strang: |U|^2 = |V|^2 summed as it is
-  if (i0 == 0) {
+  if (i0 == 0 && opens) {
     PassArgs<R> a = base_args<R>(c);
     a.src = m.src;
     a.dst = m.cur;
@@ -703,6 +703,19 @@ int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
   return SSFM_OK;
 }
 
+// Runs enqueue(chain, i0, i1, opens) for the passes that end steps i0 <= i <
+// i1, as chains.  Before a sampled pass (end) the chains are joined also
+// after the opening pass: the pass starts in all size groups together, so
+// that its span over them is its own.
+template <typename F>
+int march_chains(ssfm_ctx* c, int64_t i0, int64_t i1, const ssfm_ctx::PassSample* end, F enqueue) {
+  const bool apart = end && i0 == 0;
+  if (apart)
+    if (int r = each_chain(c, true, [&](const Chain& ch) { return enqueue(ch, 0, 0, true); }))
+      return r;
+  return each_chain(c, true, [&](const Chain& ch) { return enqueue(ch, i0, i1, !apart); });
+}
+
 // Steps i0 <= i < i1 of an n-step plain forward march from step0 (pending0:
 // the state holds V with the screen of step0 - 1 still to apply), in place
 // on the state.  Lie: the screen of the previous step acts before step i;
@@ -711,13 +724,13 @@ template <typename R>
 int enqueue_propagate(ssfm_ctx* c, int64_t n, int64_t step0, bool pending0, int64_t i0,
                       int64_t i1, const ssfm_ctx::PassSample* open,
                       const ssfm_ctx::PassSample* end) {
-  return each_chain(c, true, [&](const Chain& ch) {
+  return march_chains(c, i0, i1, end, [&](const Chain& ch, int64_t k0, int64_t k1, bool opens) {
     void* S = c->field(c->L.S);
     auto pend = [&](int64_t i) {
       return c->strang ? step0 + i : (i == 0 && !pending0) ? -1 : step0 + i - 1;
     };
     return enqueue_march<R>(
-        c, n, step0, i0, i1, MarchBuffers{S, S, S, false}, pend,
+        c, n, step0, k0, k1, opens, MarchBuffers{S, S, S, false}, pend,
         [](int64_t) -> void* { return nullptr; }, true, ch, open, end);
   });
 }
@@ -985,9 +998,9 @@ int enqueue_record(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1
                    const ssfm_ctx::PassSample* open, const ssfm_ctx::PassSample* end) {
   const Segments g = rec_segments(c, n);
   void* S = c->field(c->L.S);
-  return each_chain(c, true, [&](const Chain& ch) {
+  return march_chains(c, i0, i1, end, [&](const Chain& ch, int64_t k0, int64_t k1, bool opens) {
     return enqueue_march<R>(
-        c, n, step0, i0, i1, MarchBuffers{S, S, S, false},
+        c, n, step0, k0, k1, opens, MarchBuffers{S, S, S, false},
         [&](int64_t i) { return rec_pending(c, step0, step0 + i); },
         [&](int64_t i) { return i < n ? rec_slot(c, g, i) : nullptr; }, true, ch, open, end);
   });
@@ -1047,7 +1060,7 @@ int enqueue_backward(ssfm_ctx* c) {
     const int64_t len = std::min<int64_t>(M, n - s0);
     if (len < 2) return SSFM_OK;
     return enqueue_march<R>(
-        c, len - 1, step0 + s0, 0, len - 1,
+        c, len - 1, step0 + s0, 0, len - 1, true,
         MarchBuffers{sv(k, 0), c->field(c->L.Wk), nullptr, true},
         [&](int64_t i) { return rec_pending(c, step0, step0 + s0 + i); },
         [&](int64_t i) { return i > 0 ? slot(k, i - 1) : nullptr; }, false, ch, nullptr,
@@ -1098,25 +1111,26 @@ int enqueue_backward(ssfm_ctx* c) {
   auto open = [&](const Chain& ch) -> int {
     if (c->strang)
       if (int r = half_step_lam<R>(c, true, ch)) return r;
-    if (g.recomputed(n_seg - 1))
-      if (int r = recompute(n_seg - 1, ch)) return r;
+    return g.recomputed(n_seg - 1) ? recompute(n_seg - 1, ch) : SSFM_OK;
+  };
+  auto first = [&](const Chain& ch) -> int {
     return (every > 0 && n == 1) ? timed_adj_pass(n, nullptr, ch)
                                  : adj_pass(n, nullptr, ch, nullptr);
   };
+  // adjoint step i of segment k
+  auto pass = [&](int64_t k, int64_t i, const Chain& ch) -> int {
+    const int64_t s = k * M + i, len = std::min<int64_t>(M, n - k * M);
+    // sampled steps of the first segment, and the pass after each (along
+    // the other axis)
+    const bool sampled = every > 0 && k == 0 && s % every == every / 2;
+    const bool after = every > 0 && k == 0 && i < len - 1 && (s + 1) % every == every / 2;
+    if (sampled && ch.g0 == 0) ++c->n_adj_samples;
+    return (sampled || after) ? timed_adj_pass(s, sv(k, i), ch)
+                              : adj_pass(s, sv(k, i), ch, nullptr);
+  };
   auto segment = [&](int64_t k, const Chain& ch) -> int {
-    const int64_t s0 = k * M;
-    const int64_t len = std::min<int64_t>(M, n - s0);
-    for (int64_t i = len - 1; i >= 0; --i) {
-      const int64_t s = s0 + i;
-      // sampled steps of the first segment, and the pass after each (along
-      // the other axis)
-      const bool sampled = every > 0 && k == 0 && s % every == every / 2;
-      const bool after = every > 0 && k == 0 && i < len - 1 && (s + 1) % every == every / 2;
-      if (sampled && ch.g0 == 0) ++c->n_adj_samples;
-      if (int r = (sampled || after) ? timed_adj_pass(s, sv(k, i), ch)
-                                     : adj_pass(s, sv(k, i), ch, nullptr))
-        return r;
-    }
+    for (int64_t i = std::min<int64_t>(M, n - k * M) - 1; i >= 0; --i)
+      if (int r = pass(k, i, ch)) return r;
     return SSFM_OK;
   };
   // Strang: V_0 = L(dz/2) U_0, so dL/dU_0 = L(-dz/2) dL/dV_0
@@ -1124,9 +1138,11 @@ int enqueue_backward(ssfm_ctx* c) {
     return c->strang ? half_step_lam<R>(c, false, ch) : SSFM_OK;
   };
   const bool overlap = c->overlap_recompute && g.first_kept > 0 && n_seg > 1;
-  if (!overlap) {
-    const int r = each_chain(c, true, [&](const Chain& ch) -> int {
+  auto chains = [&](auto body) { return each_chain(c, true, body); };
+  if (!overlap && every == 0) {
+    const int r = chains([&](const Chain& ch) -> int {
       if (int q = open(ch)) return q;
+      if (int q = first(ch)) return q;
       for (int64_t k = n_seg - 1; k >= 0; --k) {
         if (int q = segment(k, ch)) return q;
         if (k >= 1 && g.recomputed(k - 1))
@@ -1136,19 +1152,37 @@ int enqueue_backward(ssfm_ctx* c) {
     });
     if (r) return r;
   } else {
-    if (int r = each_chain(c, true, open)) return r;
+    // joined around the overlapped recompute, and around every pass of a
+    // sampled segment: a sampled pass starts in all size groups together,
+    // so that its span over them is its own
+    const bool apart = every > 0;
+    if (apart)
+      if (int r = chains(open)) return r;
+    if (int r = chains([&](const Chain& ch) -> int {
+          if (!apart)
+            if (int q = open(ch)) return q;
+          return first(ch);
+        }))
+      return r;
     for (int64_t k = n_seg - 1; k >= 0; --k) {
       const bool rec_prev = k >= 1 && g.recomputed(k - 1);
-      if (rec_prev) {
+      if (rec_prev && overlap) {
         HIP_TRY(hipEventRecord(c->ev_fork, c->stream));
         HIP_TRY(hipStreamWaitEvent(c->aux, c->ev_fork, 0));
         if (int r = recompute(k - 1, whole(c, c->aux))) return r;
         HIP_TRY(hipEventRecord(c->ev_join, c->aux));
       }
-      if (int r = each_chain(c, true, [&](const Chain& ch) { return segment(k, ch); })) return r;
-      if (rec_prev) HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_join, 0));
+      if (every > 0 && k == 0) {
+        for (int64_t i = std::min<int64_t>(M, n) - 1; i >= 0; --i)
+          if (int r = chains([&](const Chain& ch) { return pass(0, i, ch); })) return r;
+      } else {
+        if (int r = chains([&](const Chain& ch) { return segment(k, ch); })) return r;
+      }
+      if (rec_prev && overlap) HIP_TRY(hipStreamWaitEvent(c->stream, c->ev_join, 0));
+      if (rec_prev && !overlap)
+        if (int r = chains([&](const Chain& ch) { return recompute(k - 1, ch); })) return r;
     }
-    if (int r = each_chain(c, true, close)) return r;
+    if (int r = chains(close)) return r;
   }
   const int32_t* begins = c->at<int32_t>(c->L.begins);
   const size_t nb = c->desc.size() + 1;
@@ -2516,8 +2550,8 @@ int ssfm_set_pass_timing(ssfm_ctx* c, int32_t every) {
 
 namespace {
 // Mean span of the sampled row passes and column passes: for each sample the
-// earliest start to the latest stop over its size groups (group 0 launches
-// first; the others run concurrently).
+// earliest start to the latest stop over its size groups, which a sampled
+// pass starts together and runs side by side.
 int mean_spans(ssfm_ctx* c, const std::vector<ssfm_ctx::PassSample>& samples, double* row,
                double* col) {
   double acc[2] = {0.0, 0.0};
