@@ -179,10 +179,11 @@ struct ssfm_ctx {
   bool overlap_recompute = false;
   std::vector<char> seeded_beam;  // per beam: cotangent set since the record
   bool use_graphs = true;
-  std::map<std::tuple<int, int64_t, int64_t, int64_t, int64_t>, hipGraphExec_t> graphs;
-  // step_base of every beam when the graphs were captured (they hold which
-  // of their passes meet a turbulence screen)
-  std::vector<int64_t> graph_bases;
+  // captured marches by (kind, a, b, i0, i1) and the steps at which the
+  // turbulent beams' fields were set: the passes hold whether a turbulence
+  // screen acts on them
+  using GraphKey = std::tuple<int, int64_t, int64_t, int64_t, int64_t, std::vector<int64_t>>;
+  std::map<GraphKey, hipGraphExec_t> graphs;
   // Sampled pass timing (0: off): with timing_every = m, the pass that ends
   // step s of a forward march, s % m == m / 2, runs outside the step
   // graphs, launched with start/stop events on its own dispatch, and so
@@ -777,16 +778,10 @@ int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1, const Chain& 
 template <typename F>
 int maybe_graph(ssfm_ctx* c, int kind, int64_t a, int64_t b, int64_t i0, int64_t i1, F body) {
   if (!c->use_graphs) return body();
-  // captured passes hold whether a turbulence screen acts on them, which
-  // depends on the step at which each beam's field was set
   std::vector<int64_t> bases;
-  for (const InstDev& in : c->inst) bases.push_back(in.step_base);
-  if (bases != c->graph_bases) {
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    clear_graphs(c);
-    c->graph_bases = bases;
-  }
-  auto key = std::make_tuple(kind, a, b, i0, i1);
+  for (const InstDev& in : c->inst)
+    if ((in.terms & SSFM_TURB) && in.n_screens > 0) bases.push_back(in.step_base);
+  const ssfm_ctx::GraphKey key(kind, a, b, i0, i1, std::move(bases));
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
     // graphs are specific to their first step; a caller marching in many

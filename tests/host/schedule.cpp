@@ -359,6 +359,25 @@ void samples() {
           check_samples({ROW_ADJ, COL_ADJ}, every / 2 < ckpt);
         }
 }
+
+// Beams set at different steps in a repeating pattern: the marches of the
+// second time round are those captured the first time, and marches whose
+// turbulence screens fall on other passes have graphs of their own.
+void graphs() {
+  for (uint32_t turbulence : {0u, uint32_t(SSFM_TURB)}) {
+    W.graphs = 0;
+    Context x({beam(128, SSFM_KERR | turbulence, 3), beam(256, SSFM_KERR | turbulence, 3)}, 4, 4);
+    for (int turn = 0; turn < 3; ++turn)
+      for (int again : {0, 1}) {
+        x.set(0);
+        x.set(1);
+        EXPECT(ssfm_propagate(x.c, 4) == SSFM_OK);
+        x.set(again);
+        EXPECT(ssfm_propagate(x.c, 4) == SSFM_OK);
+      }
+    EXPECT(W.graphs == (turbulence ? 3 : 2));
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -366,6 +385,7 @@ int main(int argc, char** argv) {
   const std::pair<const char*, void (*)()> checks[] = {
       {"captured", captured},
       {"samples", samples},
+      {"graphs", graphs},
   };
   for (const auto& c : checks)
     if (only.empty() || only == c.first) {

@@ -6,6 +6,8 @@ import numpy as np
 import pytest
 
 import workloads as W
+from oracle import march as M
+from oracle import turbulence as T
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +42,37 @@ def test_power_trace_does_not_depend_on_the_cuts(n, precision, terms):
         p.close()
     for a, b in zip(*out):
         assert np.array_equal(a, b), np.argwhere(a != b)[:8]
+
+
+@pytest.mark.parametrize("graphs", [True, False])
+def test_beams_set_at_different_steps_after_a_captured_march(graphs):
+    """Two turbulent beams of different sizes: both march 4 steps, one is set
+    anew, both march 4 more, twice over.  Each beam meets its screens by its
+    own step count, in the marches captured first and in those replayed.
+    Against the oracle (FP64, 1e-11)."""
+    base = {i.n: i for i in W.config3()}
+    # screens after own steps 0, 2, 3, 5
+    insts = [dataclasses.replace(base[n], n=m, n_steps=8, cn2=1e-11, n_screens=4,
+                                 screen_dz=1.75 * base[n].dz) for n, m in ((256, 256), (512, 128))]
+    assert list(insts[0].screen_steps()) == [0, 2, 3, 5]
+    screens = [T.instance_screens(i) for i in insts]
+    fields = [W.initial_field(i) for i in insts]
+    eight, four = ([M.march(u, i, n_steps=k, screens=s).field
+                    for u, i, s in zip(fields, insts, screens)] for k in (8, 4))
+    p = _prop(insts, 64)
+    p.use_graphs(graphs)
+    p.gen_screens()
+    for turn in range(2):
+        for b in range(2):
+            p.set_field(b, fields[b])
+        p.propagate(4)
+        p.set_field(turn, fields[turn])
+        p.propagate(4)
+        for b in range(2):
+            want = four[b] if b == turn else eight[b]
+            err = M.rel_l2(p.field(b), want)
+            assert err < 1e-11, (turn, b, err)
+    p.close()
 
 
 def test_captured_read_out_sees_later_parameters():
