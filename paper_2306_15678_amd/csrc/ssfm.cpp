@@ -522,12 +522,15 @@ PassArgs<R> base_args(ssfm_ctx* c) {
 }
 
 // Whether a beam of the group has a turbulence screen after context step
-// `step`, so that the passes of the other steps do not look for one.
+// `step`, so that the passes of the other steps do not look for one.  Without
+// the library's own graphs any turbulent beam counts: a caller may capture
+// these passes and replay them after setting fields at other steps.
 bool group_has_plane(const ssfm_ctx* c, const Group& g, int64_t step) {
   if (step < 0) return false;
   for (int b = g.beam0; b < g.beam0 + g.count; ++b) {
     const InstDev& in = c->inst[b];
     if (!(in.terms & SSFM_TURB) || in.n_screens <= 0) continue;
+    if (!c->use_graphs) return true;
     const auto first = c->screen_steps.begin() + in.steps_off;
     if (std::binary_search(first, first + in.n_screens, step - in.step_base)) return true;
   }

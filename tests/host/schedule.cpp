@@ -378,6 +378,20 @@ void graphs() {
     EXPECT(W.graphs == (turbulence ? 3 : 2));
   }
 }
+
+// Passes launched outside the library's own graphs, which a caller may
+// capture and replay after setting fields at other steps, look for their
+// turbulence screens on the device.
+void planes() {
+  Context x({beam(128, SSFM_KERR | SSFM_TURB, 1), beam(256, SSFM_KERR, 0)}, 0, 1);
+  EXPECT(ssfm_use_graphs(x.c, 0) == SSFM_OK);
+  x.set(0);
+  x.set(1);
+  W.passes.clear();
+  EXPECT(ssfm_propagate(x.c, 6) == SSFM_OK);
+  for (const Pass& p : W.passes)
+    EXPECT(bool(p.flags & PASS_PLANE) == (p.n == 128 && (p.flags & PASS_SCREEN)));
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -386,6 +400,7 @@ int main(int argc, char** argv) {
       {"captured", captured},
       {"samples", samples},
       {"graphs", graphs},
+      {"planes", planes},
   };
   for (const auto& c : checks)
     if (only.empty() || only == c.first) {
