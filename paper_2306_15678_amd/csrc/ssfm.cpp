@@ -96,13 +96,20 @@ int validate_desc(const ssfm_instance_desc* d, int32_t n_inst, int32_t precision
 // Device-side layout of everything a context keeps in the workspace.
 struct Layout {
   size_t inst, steps, begins, tables;
-  size_t S, Wk, Lam, ckpt, stack, screens, stage, diag_part, diag, theta_rows, theta_cols,
-      theta_out, seed_loss, seed_theta, sumsq_part, subh, subh_beams;
+  // theta_rows, theta_cols: theta accumulators of the adjoint passes; the
+  // region at theta_rows also takes the power partials of finite-difference
+  // marches (fd_chunk steps of them) and of timed passes.  Those of the other
+  // marches, which leave the work buffer alone, go there.  One for each
+  // wavefront, sized for any variant, the partials would be up to a fifth of
+  // a batch's workspace in regions of their own.
+  size_t S, Wk, Lam, ckpt, stack, screens, stage, diag, theta_rows, theta_cols, theta_out,
+      seed_loss, seed_theta, sumsq_part, subh, subh_beams;
   size_t total;
   int64_t field_elems;  // sum n^2
   int64_t table_elems;
   int64_t part_stride;  // power partials of one step (room for any variant, either axis)
   int64_t theta_row_parts, theta_col_parts;  // theta accumulators of the adjoint passes
+  int fd_chunk;
   int64_t n_ckpt, n_stack, diag_cap, screen_elems, n_steps_total;
   // regions of n_stack segment slots: recompute banks (0, 1 or 2) and
   // segments kept whole by the forward record
@@ -398,11 +405,19 @@ int plan_layout(const ssfm_instance_desc* d, int n_inst, int precision, int64_t 
   l.stack = take(el * fe * l.n_stack * (l.n_banks + l.n_kept));
   l.screens = take(rel * se);
   l.stage = take(16 * size_t(max_n) * max_n);
-  // power partials of the pass that ends a step
-  l.diag_part = take(sizeof(double) * 2 * kDiagChunk * l.part_stride);
   l.diag = take(sizeof(double) * 2 * l.diag_cap * n_inst);
-  l.theta_rows = take(sizeof(double) * 8 * nr_max);
-  l.theta_cols = take(sizeof(double) * 8 * nc_max);
+  // the accumulators live within one backward: in the staging area where they
+  // fit it (all but large batches)
+  const size_t theta_bytes = sizeof(double) * 8 * size_t(nr_max + nc_max);
+  const size_t stage_bytes = 16 * size_t(max_n) * max_n;
+  l.theta_rows = theta_bytes <= stage_bytes ? l.stage : take(theta_bytes);
+  l.theta_cols = l.theta_rows + sizeof(double) * 8 * nr_max;
+  const size_t step_bytes = sizeof(double) * 2 * size_t(l.part_stride);
+  l.fd_chunk = int(std::min<size_t>(kDiagChunk, std::max(theta_bytes, stage_bytes) / step_bytes));
+  // a line of n points is at most n / 256 wavefronts, so that kDiagChunk steps
+  // of partials take no more than half of a complex64 field
+  if (l.fd_chunk < 1 || kDiagChunk * step_bytes > el * size_t(fe))
+    return fail(SSFM_EUNSUPPORTED, "the work buffer cannot hold the power partials");
   l.theta_out = take(sizeof(double) * 8 * n_inst);
   l.seed_loss = take(sizeof(double) * (max_n + 1));
   l.seed_theta = take(sizeof(double) * 8 * max_n * n_inst);
@@ -598,13 +613,18 @@ int run_pass(ssfm_ctx* c, int kind, PassArgs<R> a, const Chain& ch, int table = 
   return SSFM_OK;
 }
 
+// Power partials of a chunk's step `slot` (see Layout).
+double* power_parts(ssfm_ctx* c, int slot) {
+  return c->at<double>(c->fd ? c->L.theta_rows : c->L.Wk) + size_t(slot) * 2 * c->L.part_stride;
+}
+
 // Power and peak of `steps` steps from context step `step0`, for the beams of
 // a chain.
 int finalize_diag(ssfm_ctx* c, const int32_t* begin_even, const int32_t* begin_odd, int steps,
                   int64_t step0, const Chain& ch) {
   const int b0 = c->groups[ch.g0].beam0;
   const Group& last = c->groups[ch.g1 - 1];
-  HIP_TRY(launch_diag_finalize(c->at<double>(c->L.diag_part), c->L.part_stride, begin_even,
+  HIP_TRY(launch_diag_finalize(power_parts(c, 0), c->L.part_stride, begin_even,
                                begin_odd, b0, last.beam0 + last.count - b0, steps,
                                c->at<double>(c->L.diag), step0, c->L.diag_cap, ch.st));
   return SSFM_OK;
@@ -684,7 +704,7 @@ int enqueue_march(ssfm_ctx* c, int64_t n, int64_t step0, int64_t i0, int64_t i1,
     PassArgs<R> a = base_args<R>(c);
     a.src = m.cur;
     a.dst = last ? m.dst : m.cur;
-    if (part) a.part = c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.part_stride;
+    if (part) a.part = power_parts(c, slot);
     a.flags = PASS_OP1 | raw;
     a.rec = rec(i + 1);
     if (!last) {
@@ -759,16 +779,15 @@ int enqueue_fd(ssfm_ctx* c, int64_t step0, int64_t i0, int64_t i1, const Chain& 
   a.src = c->field(c->L.Wk);
   int64_t chunk_start = step0 + i0;
   for (int64_t i = i0; i < i1; ++i) {
-    const int slot = int((i - i0) % kDiagChunk);
+    const int slot = int((i - i0) % c->L.fd_chunk);
     for (int k = 1; k <= c->fd_iters; ++k) {
       if (int r = run_pass<R>(c, COL_FD, col, ch, T_FD)) return r;
       const bool fin = (k == c->fd_iters);
       a.flags = FD_SPECTRAL | (fin ? FD_FINISH : 0) | ((fin && i == i1 - 1) ? FD_LAST : 0);
-      a.part = fin ? c->at<double>(c->L.diag_part) + size_t(slot) * 2 * c->L.part_stride
-                   : nullptr;
+      a.part = fin ? power_parts(c, slot) : nullptr;
       if (int r = run_pass<R>(c, ROW_FD, a, ch)) return r;
     }
-    if (slot == kDiagChunk - 1 || i == i1 - 1) {
+    if (slot == c->L.fd_chunk - 1 || i == i1 - 1) {
       const int32_t* rows = c->at<int32_t>(c->L.begins) + P_ROW * (c->desc.size() + 1);
       if (int r = finalize_diag(c, rows, rows, slot + 1, chunk_start, ch)) return r;
       chunk_start = step0 + i + 1;
@@ -2308,7 +2327,7 @@ int ssfm_time_passes(ssfm_ctx* c, int32_t reps, double* ms_row, double* ms_col,
     a.dst = c->field(c->L.Wk);
     a.step = int64_t(1) << 60;  // a step with no turbulence screen
     a.flags = PASS_OP1 | PASS_SCREEN | PASS_OP2;
-    a.part = c->at<double>(c->L.diag_part);
+    a.part = c->at<double>(c->L.theta_rows);
     PassArgs<R> b = a;
     b.src = c->field(c->L.Wk);
     HIP_TRY(hipEventRecord(e0, c->stream));

@@ -142,9 +142,9 @@ int plan_default(bool, int, bool) { return 0; }
 int plan_count(bool, int) { return 2; }
 bool plan_info(bool, int n, int v, bool, PlanInfo* o) {
   *o = PlanInfo{};
-  o->threads = 256;
+  o->threads = 64;
   o->lines = v + 1;
-  o->waves = 4;
+  o->waves = 1;
   o->t = 64;
   o->radices[0] = n;
   return v >= 0 && v < 2;
