@@ -16,7 +16,7 @@ import functools
 import hashlib
 import json
 import os
-from typing import Dict
+from typing import Callable, Dict, List, Tuple
 
 import torch
 
@@ -58,37 +58,43 @@ def save_cache(d: Dict) -> None:
         pass
 
 
-def _select(prop: Propagator, n: int, row: int, col: int) -> bool:
-    """Select a variant pair; False if this precision does not build it."""
+def _accepted(select: Callable[[int, int], None], row: int, col: int, refusals) -> bool:
+    """Select a variant pair; False if the library refuses it."""
     try:
-        prop.select_plan(n, row, col)
+        select(row, col)
     except L.SsfmError as e:
-        if e.status != L.EUNSUPPORTED:
+        if e.status not in refusals:
             raise
         return False
     return True
 
 
+def _times(select: Callable[[int, int], None], measure: Callable[[], Tuple[float, float]],
+           n_row: int, n_col: int, base: int, refusals) -> Tuple[List, List]:
+    """(time, variant) of every row and every column variant that the library
+    accepts.  One measurement times a row and a column pass, which do not
+    depend on each other: row variant v beside column variant v, or beside
+    `base` where that pair is refused or there is no such column."""
+    rows, cols = [], []
+    for v in range(max(n_row, n_col)):
+        if v < min(n_row, n_col) and _accepted(select, v, v, refusals):
+            ms_row, ms_col = measure()
+            rows.append((ms_row, v))
+            cols.append((ms_col, v))
+            continue
+        if v < n_row and _accepted(select, v, base, refusals):
+            rows.append((measure()[0], v))
+        if v < n_col and _accepted(select, base, v, refusals):
+            cols.append((measure()[1], v))
+    return rows, cols
+
+
 def _tune_adjoint(prop: Propagator, n: int, n_row: int, n_col: int, reps: int) -> Dict:
     """Adjoint-pass variants for size n among those with the forward
     variants' tiling (the library refuses the others)."""
-    rows, cols = [], []
-    for v in range(n_row):
-        try:
-            prop.select_adjoint_plan(n, v, -1)
-        except L.SsfmError as e:
-            if e.status not in (L.EINVAL, L.EUNSUPPORTED):
-                raise
-            continue
-        rows.append((prop.time_adjoint_passes(reps)[1], v))
-    for v in range(n_col):
-        try:
-            prop.select_adjoint_plan(n, -1, v)
-        except L.SsfmError as e:
-            if e.status not in (L.EINVAL, L.EUNSUPPORTED):
-                raise
-            continue
-        cols.append((prop.time_adjoint_passes(reps)[0], v))
+    rows, cols = _times(lambda r, c: prop.select_adjoint_plan(n, r, c),
+                        lambda: prop.time_adjoint_passes(reps)[::-1], n_row, n_col, -1,
+                        (L.EINVAL, L.EUNSUPPORTED))
     br, bc = min(rows)[1], min(cols)[1]
     prop.select_adjoint_plan(n, br, bc)
     return {"row_adj": br, "col_adj": bc, "ms_row_adj": min(rows)[0], "ms_col_adj": min(cols)[0],
@@ -113,20 +119,11 @@ def tune(prop: Propagator, reps: int = 50, use_cache: bool = True,
             out[n] = best
             continue
         n_row, n_col = plan_variants(n, prop.precision)
-        rows, cols = [], []
-        # rows vary with the column variant fixed, then the other way round;
         # a variant whose tile does not fit a workgroup at this precision is
         # not built for it (EUNSUPPORTED) and is skipped
-        for v in range(n_row):
-            if not _select(prop, n, v, 0):
-                continue
-            ms_row, _, _, _ = prop.time_passes(reps)
-            rows.append((ms_row, v))
-        for v in range(n_col):
-            if not _select(prop, n, 0, v):
-                continue
-            _, ms_col, _, _ = prop.time_passes(reps)
-            cols.append((ms_col, v))
+        rows, cols = _times(lambda r, c: prop.select_plan(n, r, c),
+                            lambda: prop.time_passes(reps)[:2], n_row, n_col, 0,
+                            (L.EUNSUPPORTED,))
         br, bc = min(rows)[1], min(cols)[1]
         prop.select_plan(n, br, bc)
         best = {"row": br, "col": bc, "ms_row": min(rows)[0], "ms_col": min(cols)[0],

@@ -1,5 +1,5 @@
-"""The tuner's cache file: what it keeps belongs to one build of the library,
-whose tile variants its indices name."""
+"""The tuner on a stand-in for a context: what it measures, and its cache file,
+whose entries belong to one build of the library."""
 import json
 
 import pytest
@@ -72,3 +72,44 @@ def test_entries_of_this_build_are_used(cache):
     assert second.timed == 0 and second.plan == (1, 1) and second.adjoint == (1, 1)
     assert {k: best[k] for k in ("row", "col", "row_adj", "col_adj")} == \
         {k: again[k] for k in ("row", "col", "row_adj", "col_adj")}
+
+
+class _Uneven(_Context):
+    """Three row and five column variants; rows 1 and columns 2 are not built,
+    and the adjoint takes even variants only."""
+
+    def _known(self, *variants):
+        pass
+
+    def select_plan(self, n, row, col):
+        if row == 1 or col == 2:
+            raise L.SsfmError(L.EUNSUPPORTED, "select", "not built")
+        super().select_plan(n, row, col)
+
+    def select_adjoint_plan(self, n, row, col):
+        if row % 2 == 1 and row > 0 or col % 2 == 1 and col > 0:
+            raise L.SsfmError(L.EINVAL, "select", "other lines per workgroup")
+        super().select_adjoint_plan(n, row, col)
+
+    def time_passes(self, reps):
+        self.timed += 1
+        return 10.0 + self.plan[0], 20.0 - self.plan[1], 0.0, 0.0
+
+    def time_adjoint_passes(self, reps):
+        self.timed += 1
+        return 40.0 + self.adjoint[1], 30.0 - self.adjoint[0]
+
+
+def test_every_accepted_variant_is_timed_as_itself(cache, monkeypatch):
+    """A row and a column variant share a measurement where both are accepted;
+    where one is refused, the other is timed beside the base variant."""
+    monkeypatch.setattr(tuner, "plan_variants", lambda n, precision: (3, 5))
+    p = _Uneven(max_steps=4)
+    best = tuner.tune(p, use_cache=False)[N]
+    assert best["rows_ms"] == [10.0, 12.0]                      # rows 0, 2
+    assert best["cols_ms"] == [20.0, 19.0, 17.0, 16.0]          # columns 0, 1, 3, 4
+    assert (best["row"], best["col"]) == (0, 4)
+    assert best["rows_adj_ms"] == {0: 30.0, 2: 28.0}
+    assert best["cols_adj_ms"] == {0: 40.0, 2: 42.0, 4: 44.0}
+    assert (best["row_adj"], best["col_adj"]) == (2, 0)
+    assert p.timed == 5 + 3 and p.plan == (0, 4) and p.adjoint == (2, 0)
