@@ -154,7 +154,9 @@ int ssfm_destroy(ssfm_ctx* ctx);
  * ownership.  The instance's own step count, which places its turbulence
  * screens, restarts at 0; the other instances keep their fields (with any
  * pending screen applied) and their step counts.  Drops a recorded march
- * and its cotangents.  SSFM_EINVAL for inst out of range or src NULL. */
+ * and its cotangents.  SSFM_EINVAL for inst out of range or src NULL;
+ * SSFM_EHIP while the stream is captured (the host's step counts change
+ * with the device's). */
 int ssfm_set_field(ssfm_ctx* ctx, int32_t inst, const void* src, int32_t where);
 
 /* Ansatz parameters theta[8] of instance inst, the sparse-grid stand-in for
@@ -163,7 +165,8 @@ int ssfm_set_field(ssfm_ctx* ctx, int32_t inst, const void* src, int32_t where);
  * f_theta(x) = [sum_p theta_p x^p + i sum_p theta_{4+p} x^p] / (1 + x^4),
  * x = I / I_a, applied as exp(i k0 n2 I_a dz f_theta) every step.  theta:
  * host double[8], copied.  Drops a recorded march (its stored fields were
- * made with the old theta).  SSFM_EINVAL for a non-finite entry. */
+ * made with the old theta).  SSFM_EINVAL for a non-finite entry; SSFM_EHIP
+ * while the stream is captured. */
 int ssfm_set_theta(ssfm_ctx* ctx, int32_t inst, const double* theta);
 
 /* Generate every instance's turbulence phase screens eps_t on the device
@@ -400,8 +403,9 @@ int ssfm_hot_areas(ssfm_ctx* ctx, const double* w, int32_t n, double threshold,
  * must not call hipMalloc, e.g. tight serving loops or harnesses that forbid
  * it) and have no context: the same count, with the labels and the result
  * in a fixed device array inside the library (16 MiB + 4 KiB per GPU, held
- * until the process ends) instead of a workspace.  w: n x n FP64 device array [W/m^2], row-major; n <= 2048 (larger grids:
- * ssfm_hot_areas with a context), else SSFM_EINVAL; stream: hipStream_t or
+ * until the process ends) instead of a workspace.  w: n x n FP64 device
+ * array [W/m^2], row-major; n <= 2048 (larger grids: ssfm_hot_areas with a
+ * context), else SSFM_EINVAL; stream: hipStream_t or
  * NULL.  Calls no hipMalloc or hipFree.  All calls on one GPU share that
  * array: calls that overlap on one GPU (other threads or streams) race and
  * must be serialised by the caller.  Synchronises stream; *count on the
@@ -476,10 +480,12 @@ int ssfm_select_plan(ssfm_ctx* ctx, int32_t n, int32_t row_variant, int32_t col_
 /* Variants of the adjoint row and column passes for grid size n, chosen
  * apart from the forward ones (their registers and best tiles differ); -1
  * follows the forward variant (the default).  A variant must have the lines
- * per workgroup of the forward variant in use (the tuner picks tiles per size),
- * else SSFM_EINVAL; one not built at the context's precision returns
- * SSFM_EUNSUPPORTED.  A later ssfm_select_plan whose lines differ resets the
- * adjoint choice to -1.  Drops the context's captured graphs. */
+ * per workgroup of the forward variant in use, else SSFM_EINVAL: a rule of
+ * this call since passes shared lists of their work, kept so that what it
+ * refuses does not change; no kernel depends on it.  One not built at the
+ * context's precision returns SSFM_EUNSUPPORTED.  A later ssfm_select_plan
+ * whose lines differ resets the adjoint choice to -1.  Drops the context's
+ * captured graphs. */
 int ssfm_select_adjoint_plan(ssfm_ctx* ctx, int32_t n, int32_t row_variant,
                              int32_t col_variant);
 
@@ -487,8 +493,8 @@ int ssfm_select_adjoint_plan(ssfm_ctx* ctx, int32_t n, int32_t row_variant,
  * column pass and of the adjoint row pass over all instances (with their
  * selected variants), timed with HIP events on the context's stream; mean
  * milliseconds per launch.  The passes read the cotangent buffer and the
- * state and write the work buffer and the theta accumulators (which every
- * backward clears first): fields, cotangents and gradients are unchanged.
+ * state and write the work buffer and the theta accumulators in the staging
+ * area (which every backward clears first): fields, cotangents and gradients are unchanged.
  * SSFM_ESTATE unless the context was created with max_steps > 0. */
 int ssfm_time_adjoint_passes(ssfm_ctx* ctx, int32_t reps, double* ms_col, double* ms_row);
 
@@ -499,8 +505,8 @@ int ssfm_time_adjoint_passes(ssfm_ctx* ctx, int32_t reps, double* ms_col, double
  * step of the march is one such pass, along rows and columns in turn).
  * Writes the mean milliseconds per launch and the bytes each launch moves
  * (algorithmic: read + write of the field).  The passes read the state and
- * write the work buffer only, so the fields and the march position are
- * unchanged. */
+ * write the work buffer and the staging area only, so the fields and the
+ * march position are unchanged. */
 int ssfm_time_passes(ssfm_ctx* ctx, int32_t reps, double* ms_row,
                      double* ms_col, double* bytes_row, double* bytes_col);
 

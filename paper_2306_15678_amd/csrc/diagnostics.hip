@@ -29,9 +29,10 @@
 #include "kernels.hpp"
 
 // Device scratch of the allocation-free hot-area count: labels of an n x n
-// grid with n <= kStaticMaxN and the result.  One copy per GPU, held until the process ends; host code never
-// uses this name as an address (it stands for a host-side shadow): the
-// device address comes from hipGetSymbolAddress in static_scratch().
+// grid with n <= kStaticMaxN and the result.  One copy per GPU, held until
+// the process ends; host code never uses this name as an address (it stands
+// for a host-side shadow): the device address comes from hipGetSymbolAddress
+// in static_scratch().
 static __device__ __align__(256) unsigned char scratch[ssfm::kStaticScratchBytes];
 
 namespace ssfm {

@@ -62,10 +62,12 @@ __device__ __forceinline__ ScreenConst<R> screen_const(const InstDev& in) {
   return s;
 }
 
-// Uniform reads of the tables no kernel writes (beam table, screen step
-// lists) through the constant address space: scalar loads, counted apart
-// from the vector loads, so waiting for them never waits for the field
-// loads in flight.
+// Uniform reads of the beam table, the screen step lists and the spectra
+// through the constant address space: scalar loads, counted apart from the
+// vector loads, so waiting for them never waits for the field loads in
+// flight.  No kernel that may run at the same time writes these tables: the
+// launches that do (k_put, k_load_field) are on the context's stream, and
+// the chains of the size groups fork from it after them and join it again.
 template <typename T>
 using const_as4 = const __attribute__((address_space(4))) T;
 template <typename T>

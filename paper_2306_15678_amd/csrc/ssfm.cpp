@@ -9,10 +9,11 @@
 //            axis alternates from step to step (see pass_kernels.hpp)
 //   adjoint  the same passes in reverse
 //
-// All beams of a context march in lock-step; beams of equal grid size are
-// neighbours in every table and buffer and share one launch per pass, so a
-// batch of uneven beams costs one launch per distinct size per pass
-// (captured once into a HIP graph and replayed).
+// All beams of a context march by the same number of steps; beams of equal
+// grid size are neighbours in every table and buffer and share one launch
+// per pass, so a batch of uneven beams costs one launch per distinct size
+// per pass.  The sizes march as independent chains, forked and joined once
+// per call (captured once into a HIP graph and replayed).
 #include "../../include/ssfm.h"
 
 #include <hip/hip_runtime.h>
@@ -2046,9 +2047,6 @@ int ssfm_set_fd_iterations(ssfm_ctx* c, int32_t iterations) {
   c->fd_iters = iterations;
   return SSFM_OK;
 }
-
-namespace {
-}  // namespace
 
 int ssfm_get_diag(ssfm_ctx* c, int32_t inst, double* power, double* peak, int64_t n) {
   if (int r = check_inst(c, inst)) return r;
