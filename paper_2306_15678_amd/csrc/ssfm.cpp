@@ -1638,9 +1638,10 @@ int do_set_field(ssfm_ctx* c, int b, const void* src, int32_t where) {
   bool same = true;
   for (const InstDev& in : c->inst) same = same && (in.step_base == c->step);
   if (same) {
+    const bool restart = c->step != 0;
     for (InstDev& in : c->inst) in.step_base = 0;
     c->step = 0;
-    if (c->inst.size() > 1)
+    if (restart && c->inst.size() > 1)
       if (int r = upload_inst(c, 0, c->inst.size())) return r;
   }
   HIP_TRY(launch_load_field<R>(dsrc, static_cast<char*>(c->field(c->L.S)) + c->inst[b].off * c->el,

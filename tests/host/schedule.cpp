@@ -51,6 +51,7 @@ struct World {
   Clock host;
   std::vector<Pass> passes;
   int graphs = 0;                       // instantiated
+  int puts = 0;                         // uploads of table entries by themselves
   hipStream_t captured = nullptr;       // a stream that its caller captures
   intptr_t next = 0x1000;
 } W;
@@ -226,6 +227,7 @@ STUB(float)
 STUB(double)
 template <typename T>
 hipError_t launch_put(const T* src, int count, T* dst, hipStream_t s) {
+  ++W.puts;
   std::copy(src, src + count, dst);
   return one(s);
 }
@@ -392,6 +394,19 @@ void planes() {
   for (const Pass& p : W.passes)
     EXPECT(bool(p.flags & PASS_PLANE) == (p.n == 128 && (p.flags & PASS_SCREEN)));
 }
+
+// Setting fields again before any step changes no start step: each call loads
+// its field with its own entry and nothing else.
+void entries() {
+  Context x(std::vector<ssfm_instance_desc>(64, beam(128, SSFM_KERR, 0)), 0, 1);
+  for (int i = 0; i < 64; ++i) x.set(i);
+  W.puts = 0;
+  for (int i = 0; i < 64; ++i) x.set(i);
+  EXPECT(W.puts == 0);
+  EXPECT(ssfm_propagate(x.c, 2) == SSFM_OK);
+  for (int i = 0; i < 64; ++i) x.set(i);
+  EXPECT(W.puts == 1);  // the restart of the step count, with the last beam
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -401,6 +416,7 @@ int main(int argc, char** argv) {
       {"samples", samples},
       {"graphs", graphs},
       {"planes", planes},
+      {"entries", entries},
   };
   for (const auto& c : checks)
     if (only.empty() || only == c.first) {
