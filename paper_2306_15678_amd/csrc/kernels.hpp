@@ -37,7 +37,7 @@ constexpr bool is_col_kind(int k) {
 // they act: the diffraction factor of the step that ends, the screen (its
 // adjoint), the factor of the step that begins.  PASS_RAW: the power
 // partials are those of |V|^2 without the screen's A^2; PASS_PLANE: some
-// beam of the launch has a turbulence plane at this step (else none is
+// beam of the launch may have a turbulence plane at this step (else none is
 // looked for); PASS_SRC_KEPT: src is a recorded field (*_FWD).
 enum : int32_t {
   PASS_OP1 = 1, PASS_SCREEN = 2, PASS_OP2 = 4, PASS_RAW = 8, PASS_PLANE = 16, PASS_SRC_KEPT = 32
