@@ -1352,13 +1352,14 @@ int do_gen_screens(ssfm_ctx* c) {
   });
 }
 
-// Upload the twiddle tables of every group's plans, where the device does
-// not hold them yet (most variants of a size share a radix plan, and tuning
-// goes through all of them), and the first partials of every beam (they
-// follow the variants in use); *blobs holds the host copies until the caller
-// synchronises.
-template <typename R>
-int upload_variants(ssfm_ctx* c, std::vector<std::vector<unsigned char>>* blobs) {
+// Host twiddle tables by radix plan (whose product is the size): most passes
+// of a size share one.
+using TwiddleTables = std::map<std::vector<int>, std::vector<unsigned char>>;
+
+// write(g, s, table) for every group and pass whose stage-ordered twiddles the
+// device does not hold yet (tuning goes through all variants of a size).
+template <typename R, typename Write>
+int each_new_twiddles(ssfm_ctx* c, TwiddleTables* tables, Write write) {
   const bool fp64 = c->precision == SSFM_FP64;
   std::vector<double> tmp;
   c->tw_radices.resize(c->groups.size());
@@ -1372,34 +1373,59 @@ int upload_variants(ssfm_ctx* c, std::vector<std::vector<unsigned char>>* blobs)
       for (const int* r = pi.radices; *r; ++r) radices.push_back(*r);
       std::vector<int>& held = c->tw_radices[gi][s];
       if (held == radices) continue;
-      stage_twiddles(g.n, pi.radices, &tmp);
-      std::vector<unsigned char> blob;
-      append_table<R>(&blob, tmp);
-      blobs->push_back(std::move(blob));
-      held.clear();  // unknown should the copy fail
-      HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + (g.tw + int64_t(s) * g.n) * c->el,
-                             blobs->back().data(), blobs->back().size(), hipMemcpyHostToDevice,
-                             c->stream));
+      std::vector<unsigned char>& table = (*tables)[radices];
+      if (table.empty()) {
+        stage_twiddles(g.n, pi.radices, &tmp);
+        append_table<R>(&table, tmp);
+      }
+      held.clear();  // unknown should the write fail
+      if (int r = write(g, s, table)) return r;
       held = radices;
     }
   }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.begins, c->begins.data(),
-                         sizeof(int32_t) * c->begins.size(), hipMemcpyHostToDevice, c->stream));
   return SSFM_OK;
 }
 
-// Upload host tables and beam constants.
+// The twiddles of newly selected variants and the first partials of every
+// beam (they follow the variants in use) to the device.
+template <typename R>
+int upload_variants(ssfm_ctx* c) {
+  auto copy = [&](const Group& g, int s, const std::vector<unsigned char>& table) -> int {
+    HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + (g.tw + int64_t(s) * g.n) * c->el, table.data(),
+                           table.size(), hipMemcpyHostToDevice, c->stream));
+    return SSFM_OK;
+  };
+  TwiddleTables tables;
+  if (int r = each_new_twiddles<R>(c, &tables, copy)) return r;
+  HIP_TRY(hipMemcpyAsync(c->ws + c->L.begins, c->begins.data(),
+                         sizeof(int32_t) * c->begins.size(), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  return SSFM_OK;
+}
+
+// Host tables and beam constants to the device: the regions from the beam
+// table to the end of the tables as one image (by a copy per table, and a
+// twiddle table computed for each pass, creating a context of four sizes took
+// 608 us, so 396; one of 4096^2 633, 421).
 template <typename R>
 int upload_plan(ssfm_ctx* c) {
   const int n_inst = int(c->desc.size());
   std::vector<double> tmp;
+  std::vector<unsigned char> image(c->L.tables + size_t(c->L.table_elems) * c->el - c->L.inst);
+  auto place = [&](size_t at, const void* src, size_t bytes) {
+    std::memcpy(image.data() + (at - c->L.inst), src, bytes);
+  };
   c->inst.assign(n_inst, InstDev{});
   if (c->spectrum.size() != size_t(n_inst)) c->spectrum.assign(n_inst, ssfm_ctx::Spectrum{});
   c->screen_steps.clear();
   int64_t foff = 0, soff = 0;
-  std::vector<std::vector<unsigned char>> blobs;
-  blobs.reserve((P_SLOTS + 1) * c->groups.size());
-  if (int r = upload_variants<R>(c, &blobs)) return r;
+  auto place_twiddles = [&](const Group& g, int s, const std::vector<unsigned char>& table) {
+    place(c->L.tables + (g.tw + int64_t(s) * g.n) * c->el, table.data(), table.size());
+    return SSFM_OK;
+  };
+  TwiddleTables twiddles;
+  if (int r = each_new_twiddles<R>(c, &twiddles, place_twiddles)) return r;
+  place(c->L.begins, c->begins.data(), sizeof(int32_t) * c->begins.size());
   for (const Group& g : c->groups) {
     // the group's beams: T_COUNT tables each
     std::vector<unsigned char> blob;
@@ -1454,16 +1480,13 @@ int upload_plan(ssfm_ctx* c) {
       in.inv2k1_f = float(in.inv2k1);
       for (int p = 0; p < 8; ++p) in.theta[p] = in.theta_f[p] = 0.0;
     }
-    blobs.push_back(std::move(blob));
-    HIP_TRY(hipMemcpyAsync(c->ws + c->L.tables + g.prop * c->el, blobs.back().data(),
-                           blobs.back().size(), hipMemcpyHostToDevice, c->stream));
+    place(c->L.tables + g.prop * c->el, blob.data(), blob.size());
   }
-  HIP_TRY(hipMemcpyAsync(c->ws + c->L.inst, c->inst.data(), sizeof(InstDev) * n_inst,
-                         hipMemcpyHostToDevice, c->stream));
+  place(c->L.inst, c->inst.data(), sizeof(InstDev) * n_inst);
   if (!c->screen_steps.empty())
-    HIP_TRY(hipMemcpyAsync(c->ws + c->L.steps, c->screen_steps.data(),
-                           sizeof(int64_t) * c->screen_steps.size(), hipMemcpyHostToDevice,
-                           c->stream));
+    place(c->L.steps, c->screen_steps.data(), sizeof(int64_t) * c->screen_steps.size());
+  HIP_TRY(hipMemcpyAsync(c->ws + c->L.inst, image.data(), image.size(), hipMemcpyHostToDevice,
+                         c->stream));
   HIP_TRY(hipMemsetAsync(c->field(c->L.S), 0, c->el * c->L.field_elems, c->stream));
   HIP_TRY(hipMemsetAsync(c->ws + c->L.diag, 0, sizeof(double) * 2 * c->L.diag_cap * n_inst,
                          c->stream));
@@ -1687,10 +1710,7 @@ int apply_variants(ssfm_ctx* c, int n, const std::array<int, P_SLOTS>& var) {
   c->begins = begins;
   c->L = L2;
   clear_graphs(c);
-  std::vector<std::vector<unsigned char>> blobs;
-  blobs.reserve(P_SLOTS * groups.size());
-  if (int r = SSFM_DISPATCH(c, upload_variants, c, &blobs)) return r;
-  HIP_TRY(hipStreamSynchronize(c->stream));
+  if (int r = SSFM_DISPATCH(c, upload_variants, c)) return r;
   return SSFM_OK;
 }
 

@@ -51,6 +51,7 @@ struct World {
   Clock host;
   std::vector<Pass> passes;
   int graphs = 0;                       // instantiated
+  int copies = 0;                       // hipMemcpyAsync
   int puts = 0;                         // uploads of table entries by themselves
   hipStream_t captured = nullptr;       // a stream that its caller captures
   intptr_t next = 0x1000;
@@ -107,6 +108,7 @@ const char* hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
   launched(st);
+  ++W.copies;
   std::memcpy(d, s, n);
   return hipSuccess;
 }
@@ -407,6 +409,15 @@ void entries() {
   for (int i = 0; i < 64; ++i) x.set(i);
   EXPECT(W.puts == 1);  // the restart of the step count, with the last beam
 }
+
+// A context's tables reach the device in one copy, whatever its sizes.
+void create() {
+  Context one({beam(128, SSFM_KERR, 0)}, 0, 1);
+  EXPECT(W.copies == 1);
+  W.copies = 0;
+  Context four({beam(512, SSFM_TURB, 2), beam(128, 0, 0), beam(256, 0, 0), beam(128, 0, 0)}, 4, 2);
+  EXPECT(W.copies == 1);
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -417,6 +428,7 @@ int main(int argc, char** argv) {
       {"graphs", graphs},
       {"planes", planes},
       {"entries", entries},
+      {"create", create},
   };
   for (const auto& c : checks)
     if (only.empty() || only == c.first) {

@@ -34,7 +34,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["captured", "samples", "graphs", "planes", "entries"])
+@pytest.mark.parametrize("check", ["captured", "samples", "graphs", "planes", "entries", "create"])
 def test_schedule(driver, check):
     r = subprocess.run([driver, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "all checks passed" in r.stdout, r.stdout + r.stderr
