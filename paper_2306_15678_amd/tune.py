@@ -89,11 +89,11 @@ def _times(select: Callable[[int, int], None], measure: Callable[[], Tuple[float
     return rows, cols
 
 
-def _tune_adjoint(prop: Propagator, n: int, n_row: int, n_col: int, reps: int) -> Dict:
+def _tune_adjoint(prop: Propagator, n: int, n_row: int, n_col: int, launches: int) -> Dict:
     """Adjoint-pass variants for size n among those with the forward
     variants' tiling (the library refuses the others)."""
     rows, cols = _times(lambda r, c: prop.select_adjoint_plan(n, r, c),
-                        lambda: prop.time_adjoint_passes(reps)[::-1], n_row, n_col, -1,
+                        lambda: prop.time_adjoint_passes(launches)[::-1], n_row, n_col, -1,
                         (L.EINVAL, L.EUNSUPPORTED))
     br, bc = min(rows)[1], min(cols)[1]
     prop.select_adjoint_plan(n, br, bc)
@@ -105,8 +105,11 @@ def tune(prop: Propagator, reps: int = 50, use_cache: bool = True,
          verbose: bool = False) -> Dict[int, Dict]:
     """Select the fastest row and column variants for each grid size of
     ``prop`` (and, for a context that can record, the fastest adjoint-pass
-    variants with the same tiling) and return the timings.  The timing
-    launches write the work buffer only; the fields are unchanged."""
+    variants with the same tiling) and return the timings.  reps: diffraction
+    factors timed of each variant and axis; a launch holds two, so half as
+    many launches.  The timing launches write the work buffer and the staging
+    area only; the fields are unchanged."""
+    launches = max(1, (reps + 1) // 2)
     cache = load_cache() if use_cache else {}
     out = {}
     for n in sorted({d.n for d in prop.descs}):
@@ -122,14 +125,14 @@ def tune(prop: Propagator, reps: int = 50, use_cache: bool = True,
         # a variant whose tile does not fit a workgroup at this precision is
         # not built for it (EUNSUPPORTED) and is skipped
         rows, cols = _times(lambda r, c: prop.select_plan(n, r, c),
-                            lambda: prop.time_passes(reps)[:2], n_row, n_col, 0,
+                            lambda: prop.time_passes(launches)[:2], n_row, n_col, 0,
                             (L.EUNSUPPORTED,))
         br, bc = min(rows)[1], min(cols)[1]
         prop.select_plan(n, br, bc)
         best = {"row": br, "col": bc, "ms_row": min(rows)[0], "ms_col": min(cols)[0],
                 "rows_ms": [r[0] for r in rows], "cols_ms": [c[0] for c in cols]}
         if prop.max_steps > 0:
-            best.update(_tune_adjoint(prop, n, n_row, n_col, reps))
+            best.update(_tune_adjoint(prop, n, n_row, n_col, launches))
         if verbose:
             print(f"tune n={n} fp{prop.precision}: rows(us)="
                   f"{[round(r[0] * 1e3, 2) for r in rows]} cols(us)="

@@ -21,6 +21,7 @@ class _Context:
         self.descs = [make_desc(N, 0.06, 0.1, wavelength=8e-7, n2=3.2e-23, terms=1)]
         self.max_steps = max_steps
         self.plan, self.adjoint, self.timed = (0, 0), (-1, -1), 0
+        self.launches = set()
 
     def _known(self, *variants):
         if any(not -1 <= v < 2 for v in variants):
@@ -36,10 +37,12 @@ class _Context:
 
     def time_passes(self, reps):
         self.timed += 1
+        self.launches.add(reps)
         return 2.0 - self.plan[0], 2.0 - self.plan[1], 0.0, 0.0
 
     def time_adjoint_passes(self, reps):
         self.timed += 1
+        self.launches.add(reps)
         return 2.0 - self.adjoint[1], 2.0 - self.adjoint[0]
 
 
@@ -93,10 +96,12 @@ class _Uneven(_Context):
 
     def time_passes(self, reps):
         self.timed += 1
+        self.launches.add(reps)
         return 10.0 + self.plan[0], 20.0 - self.plan[1], 0.0, 0.0
 
     def time_adjoint_passes(self, reps):
         self.timed += 1
+        self.launches.add(reps)
         return 40.0 + self.adjoint[1], 30.0 - self.adjoint[0]
 
 
@@ -113,3 +118,10 @@ def test_every_accepted_variant_is_timed_as_itself(cache, monkeypatch):
     assert best["cols_adj_ms"] == {0: 40.0, 2: 42.0, 4: 44.0}
     assert (best["row_adj"], best["col_adj"]) == (2, 0)
     assert p.timed == 5 + 3 and p.plan == (0, 4) and p.adjoint == (2, 0)
+
+
+@pytest.mark.parametrize("reps,launches", [(50, 25), (11, 6), (1, 1)])
+def test_a_launch_times_two_factors(cache, reps, launches):
+    p = _Context(max_steps=4)
+    tuner.tune(p, reps=reps, use_cache=False)
+    assert p.launches == {launches}
