@@ -16,7 +16,7 @@ CSRC = os.path.join(ROOT, "paper_2306_15678_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def driver(tmp_path_factory):
+def program(tmp_path_factory):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("needs hipcc")
@@ -35,6 +35,6 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["captured", "samples", "graphs", "planes", "entries", "create"])
-def test_schedule(driver, check):
-    r = subprocess.run([driver, check], capture_output=True, text=True, timeout=300)
+def test_schedule(program, check):
+    r = subprocess.run([program, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and "all checks passed" in r.stdout, r.stdout + r.stderr

@@ -1,5 +1,5 @@
 """The tuner on a stand-in for a context: what it measures, and its cache file,
-whose entries belong to one build of the library."""
+whose entries belong to one library file."""
 import json
 
 import pytest
@@ -55,8 +55,8 @@ def cache(tmp_path, monkeypatch):
 
 
 @pytest.mark.parametrize("row,col", [(6, 6), (0, 0)])
-def test_entries_of_other_builds_are_not_used(cache, row, col):
-    """Variants saved by another build (whose indices this one may not have,
+def test_entries_of_other_libraries_are_not_used(cache, row, col):
+    """Variants saved with another library (whose indices this one may not have,
     or have for other tiles) are measured anew."""
     name = "none" if not tuner.torch.cuda.is_available() else tuner.torch.cuda.get_device_name(0)
     old = {f"{name}|n={N}|fp32": {"row": row, "col": col, "row_adj": row, "col_adj": col}}
@@ -68,7 +68,7 @@ def test_entries_of_other_builds_are_not_used(cache, row, col):
     assert p.plan == (1, 1) and p.adjoint == (1, 1)
 
 
-def test_entries_of_this_build_are_used(cache):
+def test_entries_of_the_same_library_are_used(cache):
     first, second = _Context(max_steps=4), _Context(max_steps=4)
     best = tuner.tune(first)[N]
     again = tuner.tune(second)[N]
