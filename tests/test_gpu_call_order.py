@@ -104,3 +104,41 @@ def test_captured_read_out_sees_later_parameters():
         assert np.array_equal(out.cpu().numpy(), want[name]), name
         assert np.array_equal(p.intensity(0), want[name]), name
     p.close()
+
+
+def test_captured_march_reads_what_is_set_later():
+    """A caller's own graph of a march of two sizes and its read-outs, the
+    library's graphs off: its replays march the fields and parameters set by
+    then, bit for bit as the same calls made one by one."""
+    import torch
+    insts = [dataclasses.replace(W.config4_sparse(), n=n, sigma=0.02) for n in (128, 256)]
+    fields = [[torch.from_numpy(W.initial_field(i) * a).cuda() for i in insts] for a in (1.0, 0.9)]
+    thetas = [np.array(W.THETA0) + W.random_theta(k, 0.3) for k in (1, 2)]
+
+    def set_all(p, k):
+        for b in range(2):
+            p.set_field(b, fields[k][b])
+            p.set_theta(b, thetas[k])
+
+    stream = torch.cuda.Stream()
+    p, q = _prop(insts, 32, stream=stream), _prop(insts, 32)
+    want = []
+    for k in range(2):
+        set_all(q, k)
+        q.propagate(5)
+        want.append([q.intensity(b) for b in range(2)])
+    p.use_graphs(False)
+    set_all(p, 0)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        p.propagate(5)
+        out = [p.intensity(b, device=True) for b in range(2)]
+    for k in (0, 1, 0, 1):
+        set_all(p, k)
+        with torch.cuda.stream(stream):
+            graph.replay()
+        p.synchronize()
+        for b in range(2):
+            assert np.array_equal(out[b].cpu().numpy(), want[k][b]), (k, b)
+    p.close()
+    q.close()
